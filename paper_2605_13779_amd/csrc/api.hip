@@ -104,25 +104,45 @@ __global__ void meta_set_kernel(int32_t *rank, float *scale, int64_t *catalog, i
 }
 
 // token -> slot through the catalog ids the slots hold: the lowest ready slot whose id matches, else -1.
-// One workgroup per 256 tokens; the id table (<= a few KB) is staged in LDS in pieces.
-__global__ __launch_bounds__(256)
-void slot_lookup_kernel(const int64_t *token_id, int T, const int64_t *catalog, const int32_t *rank, int n_slots,
-                        int32_t *token_slot)
+// A workgroup takes kLookupTokens tokens and its threads divide the slots: a thread reads kLookupFlight
+// slots' ids and ranks together (neighbouring lanes, neighbouring slots) and compares them with the tokens'
+// ids from LDS (all lanes read one address); the rare hit goes through an LDS minimum.  What bounds the
+// launch is the round trip of those reads -- one for up to 1024 slots -- so few tokens per workgroup, many
+// workgroups.  (A thread per token walking all slots in LDS, the form before, is a chain of n_slots
+// dependent steps: 96 us for 512 tokens over 1024 slots.)
+constexpr int kLookupTokens = 4, kLookupFlight = 4, kLookupThreads = 256;
+__global__ __launch_bounds__(kLookupThreads)
+void slot_lookup_kernel(const int64_t *__restrict__ token_id, int T, const int64_t *__restrict__ catalog,
+                        const int32_t *__restrict__ rank, int n_slots, int32_t *__restrict__ token_slot)
 {
-    __shared__ int64_t ids[1024];
-    const int t = (int)(blockIdx.x * 256 + threadIdx.x);
-    const int64_t want = t < T ? token_id[t] : -1;
-    int found = -1;
-    for (int base = 0; base < n_slots; base += 1024) {
-        const int n = min(1024, n_slots - base);
-        __syncthreads();
-        for (int k = (int)threadIdx.x; k < n; k += 256) ids[k] = rank[base + k] > 0 ? catalog[base + k] : -1;
-        __syncthreads();
-        if (want >= 0 && found < 0)
-            for (int k = 0; k < n; ++k)
-                if (ids[k] == want) { found = base + k; break; }
+    __shared__ int64_t want[kLookupTokens];
+    __shared__ int best[kLookupTokens];
+    const int tid = (int)threadIdx.x, t0 = (int)blockIdx.x * kLookupTokens;
+    if (tid < kLookupTokens) {
+        want[tid] = t0 + tid < T ? token_id[t0 + tid] : -1;
+        best[tid] = n_slots;
     }
-    if (t < T) token_slot[t] = found;
+    bool synced = false;
+    for (int base = 0; base < n_slots; base += kLookupFlight * kLookupThreads) {
+        int64_t id[kLookupFlight];
+#pragma unroll
+        for (int q = 0; q < kLookupFlight; ++q) {
+            const int s = base + q * kLookupThreads + tid, sc = s < n_slots ? s : 0;
+            const int64_t c = catalog[sc];
+            id[q] = s < n_slots && rank[sc] > 0 ? c : -1;
+        }
+        if (!synced) { __syncthreads(); synced = true; }
+#pragma unroll
+        for (int t = 0; t < kLookupTokens; ++t) {
+            const int64_t w = want[t];
+            if (w < 0) continue;
+#pragma unroll
+            for (int q = 0; q < kLookupFlight; ++q)
+                if (id[q] == w) atomicMin(&best[t], base + q * kLookupThreads + tid);
+        }
+    }
+    __syncthreads();
+    if (tid < kLookupTokens && t0 + tid < T) token_slot[t0 + tid] = best[tid] < n_slots ? best[tid] : -1;
 }
 
 __global__ void meta_clear_kernel(int32_t *rank, float *scale, int64_t *catalog, int n)
@@ -743,7 +763,7 @@ int32_t lora_slot_lookup(mlora_site *s, const int64_t *token_catalog_id, int32_t
     if (!token_catalog_id || !token_slot) return MLORA_E_INVALID;
     DeviceGuard g(s->d.device);
     if (!g.good) return MLORA_E_HIP;
-    slot_lookup_kernel<<<dim3((unsigned)((T + 255) / 256)), dim3(256), 0, (hipStream_t)stream>>>(
+    slot_lookup_kernel<<<dim3((unsigned)((T + kLookupTokens - 1) / kLookupTokens)), dim3(kLookupThreads), 0, (hipStream_t)stream>>>(
         token_catalog_id, T, s->catalog, s->rank, s->d.n_slots, token_slot);
     return ok(hipGetLastError()) ? MLORA_OK : MLORA_E_HIP;
 }

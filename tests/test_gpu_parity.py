@@ -1408,6 +1408,28 @@ def test_device_side_catalog_id_lookup(M, oracle):
     P.check_untouched(P.host_bits(y), c.y0, want < 0, "by catalog id")
 
 
+@pytest.mark.parametrize("T,S", [(1, 1), (3, 5), (5, 255), (513, 1024), (6, 1025), (64, 3000)])
+def test_lookup_sizes_and_duplicate_ids(M, T, S):
+    """Around the lookup kernel's tiles (4 tokens per workgroup, 1024 slots per flight); an id held by
+    several slots maps to the lowest ready one.  Whole numbers: exact."""
+    site = M.Site(8, 8, 1, S)
+    r = np.random.default_rng(T * 10007 + S)
+    ids = r.integers(0, max(2, S // 2), size=S)        # duplicates
+    ready = r.random(S) < 0.8
+    raw = site.bufs[2]                                 # rank int32[S] | scale fp32[S] | catalog int64[S]
+    raw[:4 * S].view(torch.int32).copy_(torch.from_numpy(ready.astype(np.int32)))
+    raw[8 * S:16 * S].view(torch.int64).copy_(torch.from_numpy(ids.astype(np.int64)))
+    tok = r.integers(-1, max(2, S // 2) + 2, size=T).astype(np.int64)
+    host = {}
+    for k in range(S):
+        if ready[k]:
+            host.setdefault(int(ids[k]), k)
+    want = np.array([host.get(int(v), -1) if v >= 0 else -1 for v in tok], dtype=np.int32)
+    out = torch.full((T,), -7, dtype=torch.int32, device="cuda")
+    M.lora_slot_lookup(site, torch.from_numpy(tok).cuda(), out)
+    assert np.array_equal(out.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("seed", [1, 2, 3])
 def test_random_shapes_against_oracle(M, oracle, seed):
     """Shapes nobody picked by hand: seeded draws of rank (powers of two and not), per-slot true ranks
