@@ -41,6 +41,10 @@ struct PlanView {
     int32_t *tok_ticket;  // [max_items]
     int32_t *tok_tmp;     // [max_items]
     int32_t *tok_sorted;  // [max_items]
+    // Large batches (see plan_big_count_kernel): per range of kBigRange items and key the range's count, then
+    // the count of the ranges in front of it; one more row of totals.  Null in plans that never need them.
+    int32_t *big;         // [ranges + 1][n_keys]
+    int32_t *tok_big;     // the same for the tokens
 };
 // The view the planner kernels take for the token-level grouping (no chunk records).
 __host__ __device__ inline PlanView plan_token_view(const PlanView &v)
@@ -48,6 +52,7 @@ __host__ __device__ inline PlanView plan_token_view(const PlanView &v)
     PlanView t{};
     t.hdr = v.tok_hdr; t.count = v.tok_count; t.group_off = v.tok_off; t.chunk_base = nullptr;
     t.key_of = v.tok_key_of; t.ticket = v.tok_ticket; t.tmp = v.tok_tmp; t.sorted = v.tok_sorted; t.chunks = nullptr;
+    t.big = v.tok_big;
     return t;
 }
 

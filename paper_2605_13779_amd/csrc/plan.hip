@@ -7,10 +7,25 @@
 
 namespace mlora {
 
+constexpr int kOneRange = 256;     // one-launch route index build: pairs owned by a workgroup
+constexpr int kOneKeys = 4096;     // ... largest key space (LDS: three int32 tables of this size)
+constexpr int kOnePairs = 32768;   // ... largest batch (each workgroup walks all of it)
+constexpr int kOneThreads = 1024;
+constexpr int kBigRange = 1024;    // three-launch form: items owned by a workgroup
+constexpr int kBigKeys = 16384;    // ... largest key space (LDS: two int32 tables of this size)
+
+// Words of ONE count table of the three-launch form (0: such a plan never takes it).
+static int64_t plan_big_words(int64_t M, int64_t NK)
+{
+    if ((M <= kOnePairs && NK <= kOneKeys) || NK > kBigKeys) return 0;
+    return ((M + kBigRange - 1) / kBigRange + 1) * NK;
+}
+
 size_t plan_words(int64_t M, int64_t NK)
 {
     return 8 + 3 * (NK + 1) + 4 * M + kRec * max_chunks(M, NK) + 64      // the grouping of the items and its chunk records
-         + 8 + 2 * (NK + 1) + 4 * M;                                       // the grouping of the tokens (route plans)
+         + 8 + 2 * (NK + 1) + 4 * M                                        // the grouping of the tokens (route plans)
+         + 2 * plan_big_words(M, NK);
 }
 
 PlanView plan_view(void *base, int64_t M, int64_t NK)
@@ -32,7 +47,10 @@ PlanView plan_view(void *base, int64_t M, int64_t NK)
     v.tok_key_of = p;     p += M;
     v.tok_ticket = p;     p += M;
     v.tok_tmp = p;        p += M;
-    v.tok_sorted = p;
+    v.tok_sorted = p;     p += M;
+    const int64_t bw = plan_big_words(M, NK);
+    v.big = bw ? p : nullptr;
+    v.tok_big = bw ? p + bw : nullptr;
     return v;
 }
 
@@ -213,11 +231,6 @@ void plan_fix_kernel(PlanView pv, int P, int32_t *__restrict__ out_sorted, int r
 // (P * 4 bytes from L2 each), which is what replaces the three dependent launches and the global
 // atomics of the pipeline above; the result is the unique stable counting sort either way.
 // ---------------------------------------------------------------------------------------------
-constexpr int kOneRange = 256;     // pairs owned by a workgroup
-constexpr int kOneKeys = 4096;     // largest key space (LDS: three int32 tables of this size)
-constexpr int kOnePairs = 32768;   // largest batch (each workgroup walks all of it)
-constexpr int kOneThreads = 1024;
-
 // k_magic = ceil(2^32 / K) (0 for K = 1): p / K is then the high word of p * k_magic, exact while
 // p * K < 2^32.  A wave instruction takes four cycles on the 16-lane SIMDs, every workgroup walks
 // all pairs, and the general division is some forty instructions per pair.
@@ -399,6 +412,167 @@ void plan_route_one_kernel(PlanView pv, const int32_t *__restrict__ topk, const 
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Large batches (more than kOnePairs items, or more than kOneKeys keys, up to kBigKeys): three launches,
+// no global atomics, every step parallel over the batch.
+//   count   a workgroup owns kBigRange consecutive items: each one's rank among the range's earlier items
+//           of its key (-> ticket), and the range's count of every key (-> a row of the count table).
+//           Inside a wave the rank comes from comparing with the wave's 64 keys; the sixteen waves then
+//           take turns adding their counts to the LDS table, which keeps the order stable.
+//   scan    per key, an exclusive prefix over the ranges, in place; the totals go to the last row.
+//   place   every workgroup scans the totals of all keys (group starts, chunk numbers) and puts its items
+//           at  group start + items of the key in earlier ranges + ticket.
+// The tokens of a route plan are grouped by slot in further workgroups of the same launches.
+// (The pipeline above in its place -- hist with one global atomic per item, one workgroup that scans all
+// keys, scatter, and a rank by counting over the whole group, pairs and tokens one after the other, eight
+// launches -- took 75 us for 64000 pairs on 4096 keys: groups of several hundred tokens alone 26 us.)
+// ---------------------------------------------------------------------------------------------
+struct BigSide {                   // one grouping: the pairs, or the tokens
+    PlanView pv;
+    const int32_t *topk;
+    int32_t P, E, NK, blocks;      // items, experts, keys, ranges
+    uint32_t k_magic;
+};
+
+__global__ __launch_bounds__(kBigRange)
+void plan_big_count_kernel(const BigSide pairs, const BigSide toks, const int32_t *__restrict__ token_slot, int n_slots,
+                           const int32_t *__restrict__ ready_rank)
+{
+    __shared__ uint16_t cnt[kBigKeys];
+    __shared__ __attribute__((aligned(16))) int32_t lkey[kBigRange];
+    const bool is_tok = (int)blockIdx.x >= pairs.blocks;
+    const BigSide &d = is_tok ? toks : pairs;
+    const int block = (int)blockIdx.x - (is_tok ? pairs.blocks : 0);
+    const int tid = (int)threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int p = block * kBigRange + tid;
+    const int key = p < d.P ? route_key(d.topk, token_slot, ready_rank, p, d.k_magic, d.E, n_slots) : -1;
+    for (int k = tid; k < d.NK; k += kBigRange) cnt[k] = 0;
+    lkey[tid] = key;                             // (read back by the same wave only: LDS serves a wave in order)
+    int rank = 0, same = 0;
+    const int32_t *mine = lkey + 64 * w;
+#pragma unroll 4
+    for (int j = 0; j < 64; j += 4) {
+        const int4 v = *(const int4 *)(mine + j);
+        same += (v.x == key) + (v.y == key) + (v.z == key) + (v.w == key);
+        rank += (v.x == key && j < lane) + (v.y == key && j + 1 < lane) + (v.z == key && j + 2 < lane) + (v.w == key && j + 3 < lane);
+    }
+    __syncthreads();
+    int base = 0;
+    for (int v = 0; v < kBigRange / 64; ++v) {
+        if (v == w && key >= 0) {
+            base = cnt[key];
+            if (rank == 0) cnt[key] = (uint16_t)(base + same);
+        }
+        __syncthreads();
+    }
+    if (p < d.P) {
+        d.pv.key_of[p] = key;
+        d.pv.ticket[p] = base + rank;
+    }
+    int32_t *row = d.pv.big + (int64_t)block * d.NK;
+    for (int k = tid; k < d.NK; k += kBigRange) row[k] = cnt[k];
+}
+
+// A workgroup takes 64 keys; its sixteen waves divide the ranges, each keeps its part in registers.
+constexpr int kScanSeg = 8;        // ranges per wave and pass
+__global__ __launch_bounds__(1024)
+void plan_big_scan_kernel(const BigSide pairs, const BigSide toks, int pair_blocks)
+{
+    __shared__ int32_t seg[16][64];
+    const bool is_tok = (int)blockIdx.x >= pair_blocks;
+    const BigSide &d = is_tok ? toks : pairs;
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+    const int k = ((int)blockIdx.x - (is_tok ? pair_blocks : 0)) * 64 + lane;
+    const bool on = k < d.NK;
+    int32_t *col = d.pv.big + (on ? k : 0);
+    int run = 0;                                 // items of the key in the passes before
+    for (int b0 = 0; b0 < d.blocks; b0 += 16 * kScanSeg) {
+        const int lo = b0 + w * kScanSeg;
+        int c[kScanSeg], sum = 0;
+#pragma unroll
+        for (int i = 0; i < kScanSeg; ++i) c[i] = lo + i < d.blocks ? col[(int64_t)(lo + i) * d.NK] : 0;
+#pragma unroll
+        for (int i = 0; i < kScanSeg; ++i) sum += c[i];
+        seg[w][lane] = sum;
+        __syncthreads();
+        int before = run, all = 0;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { const int s = seg[v][lane]; before += v < w ? s : 0; all += s; }
+        run += all;
+#pragma unroll
+        for (int i = 0; i < kScanSeg; ++i) {
+            if (on && lo + i < d.blocks) col[(int64_t)(lo + i) * d.NK] = before;
+            before += c[i];
+        }
+        __syncthreads();
+    }
+    if (on && w == 0) col[(int64_t)d.blocks * d.NK] = run;
+}
+
+__global__ __launch_bounds__(kBigRange)
+void plan_big_place_kernel(const BigSide pairs, const BigSide toks, int32_t *__restrict__ out_sorted,
+                           int32_t *__restrict__ out_group_off, int rec_bound)
+{
+    __shared__ int32_t goff[kBigKeys + 1];
+    __shared__ int32_t cbase[kBigKeys + 1];
+    __shared__ __attribute__((aligned(16))) int32_t wave_tot[16];
+    const bool is_tok = (int)blockIdx.x >= pairs.blocks;
+    const BigSide &d = is_tok ? toks : pairs;
+    const PlanView &pv = d.pv;
+    const int block = (int)blockIdx.x - (is_tok ? pairs.blocks : 0);
+    const int tid = (int)threadIdx.x, NK = d.NK;
+    const bool records = !is_tok;
+    const int j = block * kBigRange + tid;
+    // this item's own words travel while the totals are scanned
+    const int key = j < d.P ? pv.key_of[j] : -1, ticket = j < d.P ? pv.ticket[j] : 0;
+    const int earlier = key >= 0 ? pv.big[(int64_t)block * NK + key] : 0;
+    const int32_t *total = pv.big + (int64_t)d.blocks * NK;
+    const int per = (NK + kBigRange - 1) / kBigRange;           // <= 16 keys per thread
+    const int lo = min(NK, tid * per), hi = min(NK, lo + per);
+    constexpr int kPer = kBigKeys / kBigRange;
+    int cnt[kPer], items = 0, chunks = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) cnt[u] = lo + u < hi ? total[lo + u] : 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) { items += cnt[u]; chunks += (cnt[u] + kChunk - 1) / kChunk; }
+    const int inc_i = block_scan<false>(items, tid, 16, wave_tot), inc_c = block_scan<false>(chunks, tid, 16, wave_tot);
+    int run_i = inc_i - items, run_c = inc_c - chunks;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (lo + u < hi) {
+            goff[lo + u] = run_i; cbase[lo + u] = run_c;
+            run_i += cnt[u];
+            run_c += (cnt[u] + kChunk - 1) / kChunk;
+        }
+    }
+    if (tid == kBigRange - 1) { goff[NK] = inc_i; cbase[NK] = inc_c; }
+    __syncthreads();
+    const int n_rows = goff[NK], n_chunks = cbase[NK];
+    // group offsets: each workgroup writes a share
+    for (int k = block * kBigRange + tid; k <= NK; k += d.blocks * kBigRange) {
+        pv.group_off[k] = goff[k];
+        if (records) {
+            pv.chunk_base[k] = cbase[k];
+            if (out_group_off) out_group_off[k] = goff[k];
+        }
+    }
+    if (block == 0 && tid == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
+    if (j >= d.P) return;
+    if (records && j >= n_chunks && j < rec_bound) pv.chunks[(int64_t)j * kRec + 1] = 0;      // empty record past the live chunks
+    if (j >= n_rows) {
+        pv.sorted[j] = -1;
+        if (records && out_sorted) out_sorted[j] = -1;
+    }
+    if (key < 0) return;
+    const int r = earlier + ticket, off = goff[key], n = goff[key + 1] - off;
+    pv.sorted[off + r] = j;
+    if (!records) return;
+    if (out_sorted) out_sorted[off + r] = j;
+    int32_t *rec = pv.chunks + (int64_t)(cbase[key] + r / kChunk) * kRec;
+    rec[4 + (r % kChunk)] = j;
+    if (r % kChunk == 0) { rec[0] = key; rec[1] = min(kChunk, n - r); rec[2] = off + r; rec[3] = 0; }
+}
+
 bool plan_route_in_one_launch(int64_t P, int64_t NK)
 {
     return P <= kOnePairs && NK <= kOneKeys && !tuning(kPlanPipeline);
@@ -410,11 +584,22 @@ hipError_t launch_plan_general(const PlanView &pv, const int32_t *topk, const in
 {
     const int P = T * K, NK = n_slots * E;
     const bool route = topk != nullptr;            // a route plan also groups the tokens by slot
+    const uint32_t magic = K > 1 ? (uint32_t)((0x100000000ull + (uint64_t)K - 1) / (uint64_t)K) : 0u;
     if (plan_route_in_one_launch(P, NK)) {
         const int pair_blocks = (P + kOneRange - 1) / kOneRange, tok_blocks = route ? (T + kOneRange - 1) / kOneRange : 0;
         plan_route_one_kernel<<<dim3((unsigned)(pair_blocks + tok_blocks)), dim3(kOneThreads), 0, st>>>(
-            pv, topk, token_slot, P, K, K > 1 ? (uint32_t)((0x100000000ull + (uint64_t)K - 1) / (uint64_t)K) : 0u, E, n_slots,
+            pv, topk, token_slot, P, K, magic, E, n_slots,
             ready_rank, out_sorted, out_group_off, (int)max_chunks(P, NK), pair_blocks, T);
+        return hipGetLastError();
+    }
+    if (pv.big && NK <= kBigKeys && (int64_t)P * K < ((int64_t)1 << 32) && !tuning(kPlanPipeline)) {     // (the bound: k_magic)
+        const BigSide pairs{pv, topk, P, E, NK, (P + kBigRange - 1) / kBigRange, magic};
+        BigSide toks{plan_token_view(pv), nullptr, T, 1, n_slots, route ? (T + kBigRange - 1) / kBigRange : 0, 0u};
+        const unsigned nb = (unsigned)(pairs.blocks + toks.blocks);
+        const int pair_scans = (NK + 63) / 64, tok_scans = route ? (n_slots + 63) / 64 : 0;
+        plan_big_count_kernel<<<dim3(nb), dim3(kBigRange), 0, st>>>(pairs, toks, token_slot, n_slots, ready_rank);
+        plan_big_scan_kernel<<<dim3((unsigned)(pair_scans + tok_scans)), dim3(1024), 0, st>>>(pairs, toks, pair_scans);
+        plan_big_place_kernel<<<dim3(nb), dim3(kBigRange), 0, st>>>(pairs, toks, out_sorted, out_group_off, (int)max_chunks(P, NK));
         return hipGetLastError();
     }
     const unsigned nb = (unsigned)((P + 255) / 256);

@@ -1046,6 +1046,15 @@ def test_route_index_build_paths_agree(M, oracle, T, K, E, S):
     assert np.all(outs[0][1][outs[0][0]:, 1] == 0)
 
 
+@pytest.mark.parametrize("T,K,E,S", [(1, 1, 4097, 1), (1023, 1, 128, 33), (1025, 2, 256, 64), (130, 8, 512, 32), (33, 1, 331, 50),
+                                     (8200, 4, 16, 3), (70000, 2, 8, 3), (140000, 1, 3, 3)])
+def test_route_index_build_of_large_batches(M, oracle, T, K, E, S):
+    """The three-launch form (more than 32768 pairs or 4096 keys): edges of its 1024-item ranges, of a scan
+    workgroup's 64 keys and of a scan pass (128 ranges), its smallest and largest key space (16384) and one
+    beyond it (16550, the pipeline again); against the oracle and the pipeline, bit for bit."""
+    test_route_index_build_paths_agree(M, oracle, T, K, E, S)
+
+
 def run_moe_down(M, site, c, y0_bits):
     x, y = P.dev_bf16(c.x), P.dev_bf16(y0_bits)
     topk, ts = torch.from_numpy(c.topk).cuda(), torch.from_numpy(c.token_slot).cuda()
