@@ -46,6 +46,12 @@ struct RowsCfg {
     // works on 16 independent 4x4 blocks, lane l = (block l/4, column l%4), so lane l's result
     // column is its own output and its four accumulator registers are the chunk's four rows.
     static constexpr bool MX = (RP == 8 || RP == 16) && kChunk == 4;
+    // The shrink of ranks 4 and above runs on the matrix cores as well, on operands exactly as whole-line
+    // loads leave them (see shrink_units) -- in the 8-wave kernels: the 4-wave ones stream at the memory
+    // system's rate with the vector form (packed MoE), and its few registers are what lets five of their
+    // workgroups share a CU.
+    static constexpr bool SX = RP >= 4 && NW == 8 && kChunk == 4;
+    static constexpr int JQ = SX ? JPW / 4 : 1;          // groups of four A rows per wave
     // Every row of x (and y) of a chunk is loaded whatever its count: fewer, emptier loads lost time in
     // the 8-wave decode kernels of rank 8 / 16 and won it everywhere else (load issue is what they save).
     static constexpr bool ALLROWS = MX && NW == 8;
@@ -286,11 +292,47 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
             for (int jj = 0; jj < C::JPW; ++jj) a_row_off[jj] = (uint32_t)min(a_j0 + jj, a_last) * a_row_bytes;
         }
         const uint4 *xp[kChunk];
+        if constexpr (!C::SX) {
 #pragma unroll
-        for (int c = 0; c < kChunk; ++c) xp[c] = (const uint4 *)(a.x + (int64_t)(row[c] / a.top_k) * a.ldx);
-        uint4 av[C::JPW], xv[kChunk];
+            for (int c = 0; c < kChunk; ++c) xp[c] = (const uint4 *)(a.x + (int64_t)(row[c] / a.top_k) * a.ldx);
+        }
+        uint4 av[C::JPW], xv[kChunk];                             // (SX: av[q * 4 + b], xv[b] -- four rows each, unit block b)
+        // SX: this lane's row (of four A rows, and of the chunk's four rows) and its place in a block of 16 units
+        const int lr = (lane >> 2) & 3, lu = (lane >> 4) * 4 + (lane & 3);
+        uint32_t sx_off[C::JQ];
+        const char *sx_x = nullptr;
+        if constexpr (C::SX) {
+            int a_last = C::JPW - 1;
+            if constexpr (!XCH) {
+                // (rank-bounded reads, as below for the other ranks)
+                if (a.rank_bound) a_last = min(max(__builtin_amdgcn_readfirstlane(a.meta.rank[slot]), 1), RP) - 1 - jg * C::JPW;
+            }
+#pragma unroll
+            for (int q = 0; q < C::JQ; ++q) sx_off[q] = (uint32_t)((XCH ? 0 : jg * C::JPW) + min(4 * q + lr, a_last)) * a_row_bytes;      // (XCH: Ag starts at the wave's rows)
+            const int xr = lr == 0 ? row[0] : (lr == 1 ? row[1] : (lr == 2 ? row[2] : row[3]));
+            sx_x = (const char *)(a.x + (int64_t)(xr / a.top_k) * a.ldx);
+        }
         auto load_flight = [&](int f, int ul, int uh, auto first_c) {  // first_c: the item's first flight (row items have its x already)
             constexpr bool early = RI && decltype(first_c)::value != 0;
+            if constexpr (C::SX) {
+                // Block b of 16 units: one load covers 256 contiguous bytes of each of four rows, neighbouring
+                // lanes on neighbouring pieces.  Blocks past the range are not fetched.
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int ub = f + ks * 64 + b * 16;
+                    if (__builtin_amdgcn_readfirstlane(ub) >= uh) {
+#pragma unroll
+                        for (int q = 0; q < C::JQ; ++q) av[q * 4 + b] = make_uint4(0, 0, 0, 0);
+                        xv[b] = make_uint4(0, 0, 0, 0);
+                        continue;
+                    }
+                    const uint32_t u16 = (uint32_t)(ub + lu < uh ? ub + lu : ul) * 16u;
+#pragma unroll
+                    for (int q = 0; q < C::JQ; ++q) av[q * 4 + b] = *(const uint4 *)(Ag + (size_t)sx_off[q] + u16);
+                    xv[b] = *(const uint4 *)(sx_x + u16);
+                }
+                return;
+            }
             const int u = f + ks * 64 + lane;
             const uint32_t ub = (uint32_t)(u < uh ? u : ul) * 16u;
             // The waves past the end of the range issue nothing (a k-slice of an exchange item is often
@@ -327,10 +369,33 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
         };
         // Shrink over the units [ul, uh) of d_in.  Returns, in thread c * RP + j, the sum for row c
         // of the chunk and adapter row j (other threads: 0).
+        // SX: on v_mfma_f32_16x16x32_bf16 with operands as loaded.  Lane l holds 8 values of row (l/4)%4 at piece
+        // l%4 of the lane group l/16; to the instruction that is operand row (or column) l%16 = (row, piece) at
+        // contraction group l/16.  Products of A row a, piece c with x row t, piece c' are only meant where c = c',
+        // a quarter of what the instruction computes -- which the matrix cores have to spare (a load of 1 KB
+        // is 16 of their cycles), and in return no operand is shuffled or staged and the sum over d_in needs
+        // no lane-to-lane steps: it ends in accumulator l%4 of lane l (A row l/16, x row (l/4)%4), to be added
+        // over the four lanes of a quad once per item.  (With packed dot products on the vector ALU and a
+        // transposing sum over the 64 lanes per flight the shrink's arithmetic was 6 us of the c2 layer step.)
         auto shrink_units = [&](int ul, int uh, bool then_tiles) -> float {
             bool first = true;
+            f32x4_t sacc[C::JQ];
+#pragma unroll
+            for (int q = 0; q < C::JQ; ++q) sacc[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             for (int f = ul; f < uh; f += C::FLU) {
                 if (f > ul) load_flight(f, ul, uh, IntC<0>{});
+                if constexpr (C::SX) {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        const bool in = f + ks * 64 + b * 16 + lu < uh;
+                        const uint4 xz = in ? xv[b] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+                        for (int q = 0; q < C::JQ; ++q)
+                            sacc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[q * 4 + b]),
+                                                                              __builtin_bit_cast(bf16x8_t, xz), sacc[q], 0, 0, 0);
+                    }
+                    continue;
+                }
                 const bool in = f + ks * 64 + lane < uh;
 #pragma unroll
                 for (int c0 = 0; c0 < kChunk; c0 += C::CS) {
@@ -354,6 +419,16 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
                     }
                 }
                 first = false;
+            }
+            if constexpr (C::SX) {
+#pragma unroll
+                for (int q = 0; q < C::JQ; ++q) {
+                    const int c4 = lane & 3;
+                    float v = c4 == 0 ? sacc[q][0] : (c4 == 1 ? sacc[q][1] : (c4 == 2 ? sacc[q][2] : sacc[q][3]));
+                    v += lane_xor<1>(v);
+                    v += lane_xor<2>(v);
+                    if (c4 == q) part[ks][lr][jg * C::JPW + 4 * q + (lane >> 4)] = v;
+                }
             }
             if (then_tiles) {
                 if constexpr (C::MX) load_tile(out0, IntC<0>{}, IntC<1>{});            // (see kTilesBehindShrink)
