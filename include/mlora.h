@@ -253,9 +253,10 @@ int32_t lora_apply_decode_noalloc(mlora_site *site, const void *x, int64_t ldx, 
 
 /* Segmented prefill: rows [seg_off[k], seg_off[k+1]) all use slot seg_slot[k] (a request's
  * prompt is one contiguous run).  seg_off (int32[S+1]) and seg_slot (int32[S]) are HOST arrays;
- * they are validated here (MLORA_E_SEGMENTS / MLORA_E_SLOT) and copied to the device.  Sites
- * with r_pad == 64 and d_in a multiple of 16 run the MFMA kernel; others run the
- * vector kernel over runs of MLORA_CHUNK rows. */
+ * they are validated here (MLORA_E_SEGMENTS / MLORA_E_SLOT) and travel in the kernel arguments (long
+ * tables are copied to the device).  Everything runs on the matrix cores: wide rank-64 sites with d_in a
+ * multiple of 16 as a shrink and an expand half with d_in and d_out cut over workgroups, others in tiles
+ * of up to 48 rows. */
 int32_t lora_apply_segmented(mlora_site *site, const void *x, int64_t ldx, void *y, int64_t ldy,
                              const int32_t *seg_off, const int32_t *seg_slot, int32_t S,
                              int32_t T, void *stream);
@@ -308,7 +309,7 @@ int32_t mlora_resident_stats(mlora_resident *r, int64_t *out /* [MLORA_RESIDENT_
 /* Switches read where a launch is shaped (0 = automatic / default).  Host-side, process-wide; meant for
  * sweeps and for tests that force a path.  Names: rows_poll_limit, rows_rank_bound, rows_items_target,
  * rows_mode, rows_waves, rows_chunk_run (decode / MoE launches); plan_general, plan_separate, plan_pipeline (planners);
- * seg_expand_groups, seg_table_copy, seg_shrink_wgs, seg_no_mfma, seg_overlap (batches of the rank-64
+ * seg_expand_groups, seg_table_copy, seg_shrink_wgs, seg_tiles, seg_overlap (batches of the rank-64
  * prefill in flight on a second stream), seg_fused (-1: that prefill as two launches instead of one);
  * upload_piece_kb.
  * MLORA_E_INVALID for any other name. */

@@ -62,7 +62,7 @@ constexpr int32_t kSegHpBlocks = (int32_t)((kSegXchBytes - kXchBytes - kSegCount
 std::atomic<int32_t> g_knob[kKnobCount];
 const char *const kKnobName[kKnobCount] = {
     "rows_poll_limit", "rows_rank_bound", "rows_items_target", "rows_mode", "rows_waves", "plan_general",
-    "plan_separate", "plan_pipeline", "seg_expand_groups", "seg_table_copy", "seg_shrink_wgs", "seg_no_mfma", "seg_overlap",
+    "plan_separate", "plan_pipeline", "seg_expand_groups", "seg_table_copy", "seg_shrink_wgs", "seg_tiles", "seg_overlap",
     "upload_piece_kb", "seg_fused", "rows_chunk_run"};
 
 // Host-side record of a slot's rank (the kernels read the device table; this only tells the launch
@@ -465,6 +465,71 @@ int32_t segmented_mfma(mlora_site *s, const void *x, int64_t ldx, void *y, int64
         } else if (!ok(launch_seg_shrink(a, st)) || !ok(launch_seg_expand(a, st))) return MLORA_E_HIP;
     }
     return MLORA_OK;
+}
+
+int32_t cu_count(int32_t device)
+{
+    static std::atomic<int32_t> cus{0};                // (the GPUs of a host are alike)
+    int32_t n = cus.load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (!ok(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device)) || n < 1) n = 256;
+        cus.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
+// Prefill through the tile kernel: one launch, a table of the segments (in the kernel arguments when it fits).
+int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy,
+                        const int32_t *seg_off, const int32_t *seg_slot, int32_t S, hipStream_t st)
+{
+    TileArgs a{};
+    a.x = (const uint16_t *)x; a.ldx = ldx; a.y = (uint16_t *)y; a.ldy = ldy;
+    a.a_tab = s->a_tab; a.b_tab = s->b_tab; a.rank = s->rank; a.scale = s->scale;
+    a.d_in = s->d.d_in; a.d_out = s->d.d_out; a.n_experts = 1;
+    // Rows per tile: the fewest that cut the batch into one round of tiles (one per CU), or two, three, ...
+    // rounds when a round's tiles would be too large.  A round takes as long as its tiles, so a few
+    // tiles more than CUs cost a whole second one: 8192 rows in 16 runs, 2560 -> 2560 at rank 16, take 33.2
+    // us in tiles of 32 rows (264 of them), 25.6 us in 34 (256), 30.0 us in 17 (512), 36 us in 11.
+    int32_t longest = 0, live = 0;
+    for (int32_t k = 0; k < S; ++k) {
+        const int32_t rows = seg_off[k + 1] - seg_off[k];
+        if (seg_slot[k] < 0 || rows == 0) continue;
+        ++live;
+        longest = std::max(longest, rows);
+    }
+    if (live == 0) return MLORA_OK;
+    auto count = [&](int32_t q) {
+        int64_t n = 0;
+        for (int32_t k = 0; k < S; ++k)
+            if (seg_slot[k] >= 0) n += (seg_off[k + 1] - seg_off[k] + q - 1) / q;
+        return n;
+    };
+    const int32_t cus = cu_count(s->d.device), q_max = tile_max_rows();
+    const int64_t rounds = (count(q_max) + cus - 1) / cus;
+    int32_t lo = 1, hi = std::min(q_max, longest);
+    while (lo < hi) {                                  // count() falls with q
+        const int32_t q = (lo + hi) / 2;
+        if (count(q) <= rounds * cus) hi = q; else lo = q + 1;
+    }
+    a.tile_rows = lo;
+    std::vector<int32_t> tab;
+    tab.reserve((size_t)live * 4);
+    int64_t tiles = 0;
+    for (int32_t k = 0; k < S; ++k) {
+        const int32_t rows = seg_off[k + 1] - seg_off[k];
+        if (seg_slot[k] < 0 || rows == 0) continue;
+        tab.push_back((int32_t)tiles); tab.push_back(seg_off[k]); tab.push_back(rows); tab.push_back(seg_slot[k]);
+        tiles += (rows + a.tile_rows - 1) / a.tile_rows;
+    }
+    a.n_segs = live;
+    a.n_tiles = (int32_t)tiles;
+    if (tab.size() > (size_t)kTileInline || tuning(kSegTableCopy)) {
+        if (tab.size() > (size_t)s->seg_cap * 3) return MLORA_E_UNSUPPORTED;
+        int32_t rc = stage_table(s, tab, st);
+        if (rc) return rc;
+        a.segs = s->seg_dev;
+    }
+    return ok(launch_tile_seg(a, s->r_pad, (const uint32_t *)tab.data(), st)) ? MLORA_OK : MLORA_E_HIP;
 }
 
 }  // namespace
@@ -1185,35 +1250,15 @@ int32_t lora_apply_segmented(mlora_site *s, const void *x, int64_t ldx, void *y,
     if (!g.good) return MLORA_E_HIP;
     hipStream_t st = (hipStream_t)stream;
 
-    const bool mfma = s->r_pad == 64 && (s->d.d_in & 15) == 0 && s->xch && !tuning(kSegNoMfma);
-    if (mfma) return segmented_mfma(s, x, ldx, y, ldy, seg_off, seg_slot, S, st);
-    std::vector<int32_t> tab;
-    for (int32_t k = 0; k < S; ++k) {
-        if (seg_slot[k] < 0) continue;
-        for (int32_t r0 = seg_off[k]; r0 < seg_off[k + 1]; r0 += kChunk) {
-            const int32_t n = seg_off[k + 1] - r0 < kChunk ? seg_off[k + 1] - r0 : kChunk;
-            tab.push_back(seg_slot[k]); tab.push_back(n); tab.push_back(r0); tab.push_back(0);
-            for (int32_t c = 0; c < kChunk; ++c) tab.push_back(r0 + (c < n ? c : n - 1));
-        }
-    }
-    const int64_t n_units = (int64_t)(tab.size() / kRec);
-    if (n_units == 0) return MLORA_OK;
-    // the records go to the site's device area in batches that fit it (one copy + one launch each; the
-    // stream orders a batch's copy behind the launch that read the batch before it)
-    const int64_t per_batch = (int64_t)s->seg_cap * 3 / kRec - 1;
-    if (per_batch < 1) return MLORA_E_UNSUPPORTED;
-    std::vector<int32_t> piece;
-    for (int64_t u0 = 0; u0 < n_units; u0 += per_batch) {
-        const int64_t n = n_units - u0 < per_batch ? n_units - u0 : per_batch;
-        if (n < n_units) piece.assign(tab.begin() + u0 * kRec, tab.begin() + (u0 + n) * kRec);
-        rc = stage_table(s, n < n_units ? piece : tab, st);
-        if (rc) return rc;
-        RowsArgs a = rows_args(s, x, ldx, y, ldy);
-        a.chunks = s->seg_dev;
-        a.grid_chunks = (int32_t)n;
-        if (!ok(launch_rows(a, st))) return MLORA_E_HIP;
-    }
-    return MLORA_OK;
+    // Rank 64: the tile kernel pulls the adapter's A and B (128 bytes per input and output) through a CU once
+    // per tile of a few dozen rows, which the shrink / expand pair avoids by cutting d_in and d_out over
+    // workgroups, at the price of handing h over.  The line lies where the adapter gets small: at 1024 -> 1024 the
+    // tiles take half the pair's time (2048 rows: 11.5 against 19.4 us), at 2560 -> 2560 about the same
+    // (25.9 / 25.7), at 7168 -> 7168 more (57.6 / 43.8).  "seg_tiles" = 1 / -1: always / never.
+    const int tiles = tuning(kSegTiles);
+    const bool pair = s->r_pad == 64 && (s->d.d_in & 15) == 0 && s->xch && tiles <= 0 && (tiles < 0 || s->d.d_in + s->d.d_out > 4096);
+    return pair ? segmented_mfma(s, x, ldx, y, ldy, seg_off, seg_slot, S, st)
+                : segmented_tiles(s, x, ldx, y, ldy, seg_off, seg_slot, S, st);
 }
 
 int32_t moe_lora_apply_packed(mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy,

@@ -117,6 +117,23 @@ hipError_t launch_rows_multi_plan(const RowsArgs *sites, int n, const PlanView &
                                   int n_slots, const int32_t *ready_rank, hipStream_t st);
 hipError_t launch_rows_multi(const RowsArgs *sites, int n, hipStream_t st);
 
+// tile.hip: matrix-core apply over tiles of up to 32 rows of one adapter
+constexpr int kTileInline = 840;  // words of the segment table inside the kernel arguments (four per segment)
+struct TileArgs {
+    const uint16_t *x; int64_t ldx;
+    uint16_t *y;       int64_t ldy;
+    const uint16_t *a_tab; const uint16_t *b_tab;
+    const int32_t *rank; const float *scale;
+    int32_t d_in, d_out;
+    int32_t n_experts;       // >= 1: key / n_experts = slot
+    int32_t tile_rows;       // rows per tile, at most tile_max_rows()
+    int32_t n_tiles;
+    const int32_t *segs;     // device copy of the segment table, or null: it travels in the kernel arguments
+    int32_t n_segs;
+};
+int tile_max_rows();
+hipError_t launch_tile_seg(const TileArgs &a, int r_pad, const uint32_t *inl, hipStream_t st);
+
 // moe_down.hip: second launch of the MoE down projection (expand + routing-weight combine on the matrix cores)
 struct MoeDownArgs {
     uint16_t *y; int64_t ldy;
@@ -191,7 +208,7 @@ int seg_expand_capacity();
 // tests set them; the launch code reads each knob it needs once per call.
 enum Knob {
     kRowsPollLimit, kRowsRankBound, kRowsItemsTarget, kRowsMode, kRowsWaves, kPlanGeneral, kPlanSeparate,
-    kPlanPipeline, kSegExpandGroups, kSegTableCopy, kSegShrinkWgs, kSegNoMfma, kSegOverlap, kUploadPieceKb, kSegFused,
+    kPlanPipeline, kSegExpandGroups, kSegTableCopy, kSegShrinkWgs, kSegTiles, kSegOverlap, kUploadPieceKb, kSegFused,
     kRowsChunkRun, kKnobCount
 };
 int tuning(Knob k);             // api.hip
@@ -206,6 +223,17 @@ namespace mlora {
 
 // a compile-time integer as a function argument (static loops over register arrays)
 template <int I> struct IntC { static constexpr int value = I; };
+
+// Calls f(IntC<0>{}) ... f(IntC<N - 1>{}): a loop whose index is a compile-time constant inside the body
+// (register arrays stay in registers).
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(IntC<I>{});
+        static_for<N, I + 1>(f);
+    }
+}
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;

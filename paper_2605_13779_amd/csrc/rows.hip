@@ -58,17 +58,6 @@ struct RowsCfg {
     static_assert(JG * KS == NW && EU >= 1, "wave layout");
 };
 
-// Calls f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N - 1>): a loop whose
-// index is a compile-time constant inside the body (register arrays stay in registers).
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(IntC<I>{});
-        static_for<N, I + 1>(f);
-    }
-}
-
 template <int OPL> struct YVec;
 template <> struct YVec<1> { typedef uint16_t T; };
 template <> struct YVec<2> { typedef uint32_t T; };

@@ -795,6 +795,57 @@ def test_segmented_small_rank_beyond_one_table(M, oracle):
     check_dense(M, oracle, c, lambda y0: run_seg(M, site, c, y0))
 
 
+@pytest.mark.parametrize("rows", [1, 8, 9, 17, 25, 33, 41, 48, 49])
+@pytest.mark.parametrize("r,d_in,d_out", [(16, 136, 72), (64, 1000, 584), (6, 64, 8), (32, 520, 1032)])
+def test_segmented_tiles(M, oracle, rows, r, d_in, d_out):
+    """The tile kernel at every tile height (a multiple of 8 up to 48 rows; one row more is two tiles): 260 runs, so
+    that the runs' own lengths are the tiles; d_in with a partial shrink step and fewer steps than
+    waves, d_out with fewer blocks than waves and a ragged last one; true ranks below the padded one, an
+    empty slot, rows without adapter, and a table that fits the kernel arguments or is copied (211
+    runs do not fit)."""
+    n = 260 if rows < 9 else 12
+    if n == 12:                                        # tall tiles need few runs: a long one fills the other CUs
+        lens = [rows] * n + [256 * rows - 13 * rows]
+    else:
+        lens = [rows] * n
+    seg_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    seg_slot = (np.arange(len(lens)) % 5 - 1).astype(np.int32)
+    c = W.seg_case("tiles", 4700 + rows + r, int(seg_off[-1]), len(lens), d_in, d_out, 4, r, 2.0 * r, ranks=[r, max(1, r - 3), 0, r],
+                   seg_off=seg_off, seg_slot=seg_slot, std_a=0.05, std_b=0.05)
+    site = dense_site(M, c)
+    sel = np.sort(np.random.default_rng(rows).permutation(c.T)[:200])
+    M.set_tuning("seg_tiles", 1)
+    try:
+        check_dense(M, oracle, c, lambda y0: run_seg(M, site, c, y0), rows=sel)
+        a = run_seg(M, site, c, c.y0)
+        M.set_tuning("seg_table_copy", 1)
+        assert np.array_equal(run_seg(M, site, c, c.y0), a)
+    finally:
+        M.set_tuning("seg_table_copy", 0)
+        M.set_tuning("seg_tiles", 0)
+
+
+@pytest.mark.parametrize("which", ["small", "batches", "in_flight", "one_launch", "graph", "random"])
+def test_rank_64_shrink_and_expand_halves_on_narrow_sites(M, oracle, which):
+    """Narrow rank-64 sites take the tile kernel by themselves; the two halves still have to be right there."""
+    M.set_tuning("seg_tiles", -1)
+    try:
+        if which == "small":
+            test_segmented_small(M, oracle, 64, 208, 328)
+        elif which == "batches":
+            test_segmented_many_tiles_in_batches(M, oracle)
+        elif which == "in_flight":
+            test_segmented_batches_in_flight(M, oracle, 2)
+        elif which == "one_launch":
+            test_segmented_in_one_launch(M, oracle)
+        elif which == "graph":
+            test_prefill_graph_replay_keeps_results_right(M, oracle)
+        else:
+            test_prefill_random_segment_structures(M, oracle, 1)
+    finally:
+        M.set_tuning("seg_tiles", 0)
+
+
 def test_segmented_rejects_bad_offsets(M):
     site = M.Site(64, 64, 64, 2)
     x = torch.zeros((10, 64), dtype=torch.bfloat16, device="cuda")
