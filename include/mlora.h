@@ -241,7 +241,7 @@ int32_t lora_apply_decode(mlora_site *site, const void *x, int64_t ldx, void *y,
  * arguments, same result bit for bit; it allocates nothing (no hipMalloc / hipFree, no allocating
  * library call).  What lora_apply_decode keeps in the site's scratch buffer -- the batch plan, the
  * control block and the exchange words of launches whose workgroups trade partial sums -- lives in a
- * device array inside the library: 1,147,904 bytes per GPU the library runs on, held until the process ends
+ * device array inside the library: 1,164,288 bytes per GPU the library runs on, held until the process ends
  * and set up by the first call on that GPU (a few small fill launches on `stream`, waited for once;
  * make that first call outside any graph capture).
  * Limits: T <= 1024 rows and a site of at most 1024 slots, else MLORA_E_UNSUPPORTED (nothing is
@@ -308,7 +308,7 @@ int32_t mlora_resident_stats(mlora_resident *r, int64_t *out /* [MLORA_RESIDENT_
 
 /* Switches read where a launch is shaped (0 = automatic / default).  Host-side, process-wide; meant for
  * sweeps and for tests that force a path.  Names: rows_poll_limit, rows_rank_bound, rows_items_target,
- * rows_mode, rows_waves, rows_chunk_run (decode / MoE launches); plan_general, plan_separate, plan_pipeline (planners);
+ * rows_mode, rows_waves, rows_chunk_run (launches over chunks), tile_rows, tile_parts (launches over tiles); plan_general, plan_separate, plan_pipeline (planners);
  * seg_expand_groups, seg_table_copy, seg_shrink_wgs, seg_tiles, seg_overlap (batches of the rank-64
  * prefill in flight on a second stream), seg_fused (-1: that prefill as two launches instead of one);
  * upload_piece_kb.

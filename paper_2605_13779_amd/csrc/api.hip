@@ -16,6 +16,7 @@ struct mlora_plan {
     PlanView pv;
     // what the last planning call put in it (host-side knowledge only)
     int32_t items, top_k, n_experts, n_slots, grid_chunks;
+    int32_t tile_rows;          // height of the tiles the plan also holds (0: none)
     bool moe;
 };
 
@@ -63,7 +64,7 @@ std::atomic<int32_t> g_knob[kKnobCount];
 const char *const kKnobName[kKnobCount] = {
     "rows_poll_limit", "rows_rank_bound", "rows_items_target", "rows_mode", "rows_waves", "plan_general",
     "plan_separate", "plan_pipeline", "seg_expand_groups", "seg_table_copy", "seg_shrink_wgs", "seg_tiles", "seg_overlap",
-    "upload_piece_kb", "seg_fused", "rows_chunk_run"};
+    "upload_piece_kb", "seg_fused", "rows_chunk_run", "tile_rows", "tile_parts"};
 
 // Host-side record of a slot's rank (the kernels read the device table; this only tells the launch
 // code whether any slot is padded, i.e. whether rank-bounded reads of A can save traffic).
@@ -210,20 +211,86 @@ void init_plan(mlora_plan *p, int32_t max_items, int32_t n_keys, int32_t device,
 {
     p->max_items = max_items; p->n_keys = n_keys; p->device = device;
     p->pv = plan_view(base, max_items, n_keys);
-    p->items = 0; p->top_k = 1; p->n_experts = 1; p->n_slots = 0; p->grid_chunks = 0; p->moe = false;
+    p->items = 0; p->top_k = 1; p->n_experts = 1; p->n_slots = 0; p->grid_chunks = 0; p->tile_rows = 0; p->moe = false;
+}
+
+int32_t cu_count(int32_t device)
+{
+    static std::atomic<int32_t> cus{0};                // (the GPUs of a host are alike)
+    int32_t n = cus.load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (!ok(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device)) || n < 1) n = 256;
+        cus.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
+// Height of the tiles a dense plan holds beside its chunk records (0: none): low tiles while there are CUs for
+// all of them (a tile's time falls with its rows), tall ones beyond (fewer times an adapter is fetched).
+int32_t dense_tile_rows(const PlanView &pv, int32_t T, int32_t n_slots)
+{
+    const int t = tuning(kTileRows);
+    if (t < 0 || ((T > kDensePrivItems || tuning(kPlanGeneral)) && !plan_can_tile(pv, T, n_slots))) return 0;
+    if (t > 0) return t;
+    return max_tiles(T, n_slots, 8) <= 128 ? 8 : 16;
+}
+
+// Whether a dense site's apply of such a batch runs in tiles (else in chunks of four rows).
+bool takes_tiles(const mlora_site *s, int32_t tile_rows)
+{
+    if (tile_rows <= 0 || s->r_pad < 4 || s->d.n_experts > 0) return false;
+    return !(tuning(kRowsMode) || tuning(kRowsWaves) || tuning(kRowsItemsTarget));   // shapes of the chunk launches asked for
+}
+
+// Launch arguments of one of n_sites sites that share a launch.
+TileArgs tile_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy, const PlanView &pv,
+                   uint64_t *xch, uint32_t *ctrl, int32_t T, int32_t n_slots, int32_t tile_rows, int32_t n_sites)
+{
+    TileArgs a{};
+    a.x = (const uint16_t *)x; a.ldx = ldx; a.y = (uint16_t *)y; a.ldy = ldy;
+    a.a_tab = s->a_tab; a.b_tab = s->b_tab; a.rank = s->rank; a.scale = s->scale;
+    a.d_in = s->d.d_in; a.d_out = s->d.d_out; a.r_pad = s->r_pad; a.n_experts = 1; a.top_k = 1;
+    a.tile_rows = tile_rows;
+    a.n_tiles = (int32_t)max_tiles(T, n_slots, tile_rows);
+    a.tiles = pv.tiles; a.sorted = pv.sorted;
+    const int32_t n_blk = (s->d.d_out + 63) / 64, n_steps = (s->d.d_in + 63) / 64;
+    // Parts per tile: as many as leave a CU for every workgroup (the bound on the tiles is about a quarter
+    // above what a batch has).  A part sums all of d_in again unless the adapter's A is long: then the
+    // parts divide d_in and trade sums, about a microsecond, what a CU needs for 40 KB.
+    const bool trade = xch && s->r_pad * s->d.d_in >= 65536;
+    const int32_t live = trade ? a.n_tiles : std::max(1, (int32_t)((int64_t)a.n_tiles * 17 / 20));
+    int32_t parts = tuning(kTileParts) > 0 ? tuning(kTileParts) : cu_count(s->d.device) / (live * n_sites);
+    const int32_t words = (tile_rows + 7) / 8 * 8 * std::max(s->r_pad, 8);
+    if (trade) parts = std::min({parts, 16, n_steps, (int32_t)(kXchBytes / 8 / ((int64_t)a.n_tiles * words))});
+    else parts = std::min(parts, n_blk / 8);
+    parts = std::max(1, std::min(parts, n_blk));
+    a.part_blocks = (n_blk + parts - 1) / parts;
+    a.parts = (n_blk + a.part_blocks - 1) / a.part_blocks;
+    if (trade && a.parts > 1) {
+        a.xch = xch; a.ctrl = ctrl;
+        const int pl = tuning(kRowsPollLimit);
+        a.poll_limit = pl < 0 ? 0 : (pl > 0 ? pl : 4096);
+    }
+    return a;
+}
+
+void plan_is_dense(mlora_plan *plan, int32_t T, int32_t n_slots)
+{
+    plan->items = T; plan->top_k = 1; plan->n_experts = 1; plan->n_slots = n_slots; plan->moe = false;
+    plan->grid_chunks = (int32_t)max_chunks(T, n_slots);
+    plan->tile_rows = dense_tile_rows(plan->pv, T, n_slots);
 }
 
 int32_t plan_decode_impl(mlora_plan *plan, const int32_t *token_slot, int32_t T, int32_t n_slots,
                          const int32_t *ready_rank, hipStream_t st)
 {
     if (T > plan->max_items || n_slots > plan->n_keys) return MLORA_E_UNSUPPORTED;
-    plan->items = T; plan->top_k = 1; plan->n_experts = 1; plan->n_slots = n_slots; plan->moe = false;
-    plan->grid_chunks = (int32_t)max_chunks(T, n_slots);
+    plan_is_dense(plan, T, n_slots);
     hipError_t e;
     if (T <= kDensePrivItems && !tuning(kPlanGeneral))
-        e = launch_plan_dense_small(plan->pv, token_slot, T, n_slots, ready_rank, st);
+        e = launch_plan_dense_small(plan->pv, token_slot, T, n_slots, ready_rank, plan->tile_rows, st);
     else
-        e = launch_plan_general(plan->pv, nullptr, token_slot, T, 1, 1, n_slots, ready_rank, nullptr, nullptr, st);
+        e = launch_plan_general(plan->pv, nullptr, token_slot, T, 1, 1, n_slots, ready_rank, nullptr, nullptr, plan->tile_rows, st);
     return ok(e) ? MLORA_OK : MLORA_E_HIP;
 }
 
@@ -234,8 +301,9 @@ int32_t plan_route_impl(mlora_plan *plan, const int32_t *topk, const int32_t *to
     const int64_t P = (int64_t)T * K, NK = (int64_t)n_slots * E;
     if (P > plan->max_items || NK > plan->n_keys) return MLORA_E_UNSUPPORTED;
     plan->items = (int32_t)P; plan->top_k = K; plan->n_experts = E; plan->n_slots = n_slots; plan->moe = true;
+    plan->tile_rows = 0;
     plan->grid_chunks = (int32_t)max_chunks(P, NK);
-    hipError_t e = launch_plan_general(plan->pv, topk, token_slot, T, K, E, n_slots, ready_rank, out_sorted, out_off, st);
+    hipError_t e = launch_plan_general(plan->pv, topk, token_slot, T, K, E, n_slots, ready_rank, out_sorted, out_off, plan->tile_rows, st);
     return ok(e) ? MLORA_OK : MLORA_E_HIP;
 }
 
@@ -243,6 +311,10 @@ int32_t apply_planned_impl(mlora_site *s, const mlora_plan *plan, const void *x,
                            void *y, int64_t ldy, hipStream_t st)
 {
     if (plan->items == 0) return MLORA_OK;
+    if (!plan->moe && takes_tiles(s, plan->tile_rows)) {
+        const TileArgs t = tile_args(s, x, ldx, y, ldy, plan->pv, s->xch, s->ctrl, plan->items, plan->n_slots, plan->tile_rows, 1);
+        return ok(launch_tile_multi(&t, 1, st)) ? MLORA_OK : MLORA_E_HIP;
+    }
     RowsArgs a = rows_args(s, x, ldx, y, ldy);
     a.chunks = plan->pv.chunks;
     a.top_k = plan->top_k;
@@ -467,17 +539,6 @@ int32_t segmented_mfma(mlora_site *s, const void *x, int64_t ldx, void *y, int64
     return MLORA_OK;
 }
 
-int32_t cu_count(int32_t device)
-{
-    static std::atomic<int32_t> cus{0};                // (the GPUs of a host are alike)
-    int32_t n = cus.load(std::memory_order_relaxed);
-    if (n == 0) {
-        if (!ok(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device)) || n < 1) n = 256;
-        cus.store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
-
 // Prefill through the tile kernel: one launch, a table of the segments (in the kernel arguments when it fits).
 int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy,
                         const int32_t *seg_off, const int32_t *seg_slot, int32_t S, hipStream_t st)
@@ -485,7 +546,7 @@ int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int6
     TileArgs a{};
     a.x = (const uint16_t *)x; a.ldx = ldx; a.y = (uint16_t *)y; a.ldy = ldy;
     a.a_tab = s->a_tab; a.b_tab = s->b_tab; a.rank = s->rank; a.scale = s->scale;
-    a.d_in = s->d.d_in; a.d_out = s->d.d_out; a.n_experts = 1;
+    a.d_in = s->d.d_in; a.d_out = s->d.d_out; a.r_pad = s->r_pad; a.n_experts = 1;
     // Rows per tile: the fewest that cut the batch into one round of tiles (one per CU), or two, three, ...
     // rounds when a round's tiles would be too large.  A round takes as long as its tiles, so a few
     // tiles more than CUs cost a whole second one: 8192 rows in 16 runs, 2560 -> 2560 at rank 16, take 33.2
@@ -529,7 +590,7 @@ int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int6
         if (rc) return rc;
         a.segs = s->seg_dev;
     }
-    return ok(launch_tile_seg(a, s->r_pad, (const uint32_t *)tab.data(), st)) ? MLORA_OK : MLORA_E_HIP;
+    return ok(launch_tile_seg(a, (const uint32_t *)tab.data(), st)) ? MLORA_OK : MLORA_E_HIP;
 }
 
 }  // namespace
@@ -894,6 +955,14 @@ int32_t lora_apply_decode_planned(mlora_site *s, const mlora_plan *plan, const v
     return apply_planned_impl(s, plan, x, ldx, y, ldy, (hipStream_t)stream);
 }
 
+// How many of the leading sites share a launch of tiles (sites of one rank; 0: the first takes none).
+static int32_t tile_group(mlora_site *const *sites, int32_t n_sites, int32_t tile_rows)
+{
+    int32_t n = 0;
+    while (n < n_sites && n < kMaxMulti && takes_tiles(sites[n], tile_rows) && sites[n]->r_pad == sites[0]->r_pad) ++n;
+    return n;
+}
+
 // Neighbouring sites that can share a launch are grouped; the others get a launch of their own.
 static int32_t apply_multi_impl(mlora_site *const *sites, int32_t n_sites, const mlora_plan *plan,
                                 const void *const *xs, const int64_t *ldxs, void *const *ys, const int64_t *ldys,
@@ -901,6 +970,14 @@ static int32_t apply_multi_impl(mlora_site *const *sites, int32_t n_sites, const
 {
     int32_t k = 0;
     while (k < n_sites) {
+        if (const int32_t n = tile_group(sites + k, n_sites - k, plan->moe ? 0 : plan->tile_rows)) {
+            TileArgs grp[kMaxMulti];
+            for (int32_t i = 0; i < n; ++i)
+                grp[i] = tile_args(sites[k + i], xs[k + i], ldxs[k + i], ys[k + i], ldys[k + i], plan->pv, sites[k + i]->xch, sites[k + i]->ctrl, plan->items, plan->n_slots, plan->tile_rows, n);
+            if (!ok(launch_tile_multi(grp, n, st))) return MLORA_E_HIP;
+            k += n;
+            continue;
+        }
         RowsArgs grp[kMaxMulti];
         int32_t n = 0, nw = 0;
         while (k + n < n_sites && n < kMaxMulti) {
@@ -908,6 +985,7 @@ static int32_t apply_multi_impl(mlora_site *const *sites, int32_t n_sites, const
             a.chunks = plan->pv.chunks; a.top_k = plan->top_k; a.grid_chunks = plan->grid_chunks;
             const int w = rows_group_waves(a);
             if (w == 0 || (n > 0 && (a.r_pad != grp[0].r_pad || w != nw))) break;
+            if (!plan->moe && takes_tiles(sites[k + n], plan->tile_rows)) break;
             nw = w;
             grp[n++] = a;
         }
@@ -971,7 +1049,17 @@ int32_t lora_plan_apply_decode_multi(mlora_site *const *sites, int32_t n_sites, 
     if (T <= rows_local_plan_rows() && n_slots <= rows_local_plan_slots() && max_chunks(T, n_slots) <= rows_local_plan_rows() &&
         !tuning(kPlanGeneral) &&
         !tuning(kPlanSeparate)) {
+        const int32_t q = dense_tile_rows(plan->pv, T, n_slots);
+        if (const int32_t nt = tile_group(sites, n_sites, q)) {
+            TileArgs tg[kMaxMulti];
+            for (int32_t i = 0; i < nt; ++i) tg[i] = tile_args(sites[i], xs[i], ldxs[i], ys[i], ldys[i], plan->pv, sites[i]->xch, sites[i]->ctrl, T, n_slots, q, nt);
+            plan_is_dense(plan, T, n_slots);
+            if (!ok(launch_tile_multi_plan(tg, nt, plan->pv, token_slot, T, n_slots, ready_rank, st))) return MLORA_E_HIP;
+            if (nt == n_sites) return MLORA_OK;
+            return apply_multi_impl(sites + nt, n_sites - nt, plan, xs + nt, ldxs + nt, ys + nt, ldys + nt, st);
+        }
         while (n < n_sites && n < kMaxMulti) {
+            if (n > 0 && takes_tiles(sites[n], q)) break;
             RowsArgs a = rows_args(sites[n], xs[n], ldxs[n], ys[n], ldys[n]);
             a.chunks = plan->pv.chunks; a.top_k = 1; a.grid_chunks = (int32_t)max_chunks(T, n_slots);
             if (rows_group_waves(a) != 8 || (n > 0 && a.r_pad != grp[0].r_pad)) {
@@ -987,9 +1075,8 @@ int32_t lora_plan_apply_decode_multi(mlora_site *const *sites, int32_t n_sites, 
         if (rc) return rc;
         return apply_multi_impl(sites, n_sites, plan, xs, ldxs, ys, ldys, st);
     }
-    plan->items = T; plan->top_k = 1; plan->n_experts = 1; plan->n_slots = n_slots; plan->moe = false;
-    plan->grid_chunks = (int32_t)max_chunks(T, n_slots);
-    if (!ok(launch_rows_multi_plan(grp, n, plan->pv, token_slot, T, n_slots, ready_rank, st))) return MLORA_E_HIP;
+    plan_is_dense(plan, T, n_slots);
+    if (!ok(launch_rows_multi_plan(grp, n, plan->pv, token_slot, T, n_slots, ready_rank, plan->tile_rows, st))) return MLORA_E_HIP;
     if (n == n_sites) return MLORA_OK;
     return apply_multi_impl(sites + n, n_sites - n, plan, xs + n, ldxs + n, ys + n, ldys + n, st);
 }
@@ -1129,17 +1216,28 @@ static int32_t apply_decode_impl(mlora_site *s, const void *x, int64_t ldx, void
         // same bits; see lora_plan_apply_decode_multi)
         if (n <= rows_local_plan_rows() && s->d.n_slots <= rows_local_plan_slots() &&
             max_chunks(n, s->d.n_slots) <= rows_local_plan_rows() && !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
+            const int32_t q = dense_tile_rows(plan->pv, n, s->d.n_slots);
+            if (takes_tiles(s, q)) {
+                const TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, q, 1);
+                plan_is_dense(plan, n, s->d.n_slots);
+                if (!ok(launch_tile_multi_plan(&t, 1, plan->pv, token_slot + t0, n, s->d.n_slots, s->rank, st))) return MLORA_E_HIP;
+                continue;
+            }
             RowsArgs a = args(xs, ys);
             a.chunks = plan->pv.chunks; a.top_k = 1; a.grid_chunks = (int32_t)max_chunks(n, s->d.n_slots);
             if (rows_plans_alone(a)) {
-                plan->items = n; plan->top_k = 1; plan->n_experts = 1; plan->n_slots = s->d.n_slots; plan->moe = false;
-                plan->grid_chunks = a.grid_chunks;
-                if (!ok(launch_rows_multi_plan(&a, 1, plan->pv, token_slot + t0, n, s->d.n_slots, s->rank, st))) return MLORA_E_HIP;
+                plan_is_dense(plan, n, s->d.n_slots);
+                if (!ok(launch_rows_multi_plan(&a, 1, plan->pv, token_slot + t0, n, s->d.n_slots, s->rank, plan->tile_rows, st))) return MLORA_E_HIP;
                 continue;
             }
         }
         int32_t rc = plan_decode_impl(plan, token_slot + t0, n, s->d.n_slots, s->rank, st);
         if (rc) return rc;
+        if (takes_tiles(s, plan->tile_rows)) {
+            const TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, plan->tile_rows, 1);
+            if (!ok(launch_tile_multi(&t, 1, st))) return MLORA_E_HIP;
+            continue;
+        }
         RowsArgs a = args(xs, ys);
         a.chunks = plan->pv.chunks; a.top_k = plan->top_k; a.grid_chunks = plan->grid_chunks;
         if (!ok(launch_rows(a, st))) return MLORA_E_HIP;
@@ -1173,7 +1271,7 @@ int32_t lora_apply_decode(mlora_site *s, const void *x, int64_t ldx, void *y, in
 // in a file-scope device array of fixed size, one copy per GPU, held until the process ends.
 constexpr int32_t kNoAllocRows = 1024;             // largest batch (rows) and slot count the array is sized for
 constexpr int32_t kNoAllocSlots = 1024;
-constexpr size_t kNoAllocPlanBytes = 98304;        // >= plan_words(kNoAllocRows, kNoAllocSlots) * 4, checked at set-up
+constexpr size_t kNoAllocPlanBytes = 114688;       // >= plan_words(kNoAllocRows, kNoAllocSlots) * 4, checked at set-up
 constexpr size_t kNoAllocBytes = kNoAllocPlanBytes + kCtrlBytes + kXchBytes;      // 1.1 MB
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 

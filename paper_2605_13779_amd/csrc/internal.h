@@ -30,6 +30,9 @@ struct PlanView {
     int32_t *tmp;         // [max_items]
     int32_t *sorted;      // [max_items]
     int32_t *chunks;      // [kRec * max_chunks]
+    // Dense plans also cut every group into tiles of up to the plan's tile height (>= kChunk rows): 4 ints per tile
+    // {key, count, first position in `sorted`, 0}; records past the live tiles have count 0.
+    int32_t *tiles;       // [4 * max_chunks]
     // Route plans also group the batch's TOKENS by slot (the MoE down projection sums a token's pairs
     // into one output row and works per slot): tok_hdr[1] = usable tokens, tok_off = exclusive prefix
     // of the slots' token counts, tok_sorted = tokens grouped by slot, ascending inside a slot; the
@@ -66,11 +69,13 @@ inline int64_t max_chunks(int64_t items, int64_t n_keys)
 }
 
 // plan.hip
+int64_t max_tiles(int64_t items, int64_t n_keys, int tile_rows);
 hipError_t launch_plan_dense_small(const PlanView &pv, const int32_t *token_slot, int T, int n_slots,
-                                   const int32_t *ready_rank, hipStream_t st);
+                                   const int32_t *ready_rank, int tile_rows, hipStream_t st);
 hipError_t launch_plan_general(const PlanView &pv, const int32_t *topk, const int32_t *token_slot,
                                int T, int K, int E, int n_slots, const int32_t *ready_rank,
-                               int32_t *out_sorted, int32_t *out_group_off, hipStream_t st);
+                               int32_t *out_sorted, int32_t *out_group_off, int tile_rows, hipStream_t st);
+bool plan_can_tile(const PlanView &pv, int64_t P, int64_t NK);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
 
 // rows.hip: vector-ALU apply over plan chunks (decode, MoE, small-rank segmented)
@@ -114,25 +119,39 @@ bool rows_plans_alone(const RowsArgs &a);
 int rows_local_plan_rows();
 int rows_local_plan_slots();
 hipError_t launch_rows_multi_plan(const RowsArgs *sites, int n, const PlanView &pv, const int32_t *token_slot, int T,
-                                  int n_slots, const int32_t *ready_rank, hipStream_t st);
+                                  int n_slots, const int32_t *ready_rank, int tile_rows, hipStream_t st);
 hipError_t launch_rows_multi(const RowsArgs *sites, int n, hipStream_t st);
 
-// tile.hip: matrix-core apply over tiles of up to 32 rows of one adapter
+// tile.hip: matrix-core apply over tiles of rows of one adapter
 constexpr int kTileInline = 840;  // words of the segment table inside the kernel arguments (four per segment)
 struct TileArgs {
     const uint16_t *x; int64_t ldx;
     uint16_t *y;       int64_t ldy;
     const uint16_t *a_tab; const uint16_t *b_tab;
     const int32_t *rank; const float *scale;
-    int32_t d_in, d_out;
+    int32_t d_in, d_out, r_pad;
     int32_t n_experts;       // >= 1: key / n_experts = slot
     int32_t tile_rows;       // rows per tile, at most tile_max_rows()
-    int32_t n_tiles;
+    int32_t n_tiles;         // segments: tiles; plans: upper bound on them
+    // segments
     const int32_t *segs;     // device copy of the segment table, or null: it travels in the kernel arguments
     int32_t n_segs;
+    // plans
+    const int32_t *tiles;    // records (see PlanView)
+    const int32_t *sorted;
+    int32_t top_k;           // x row = item / top_k
+    int32_t parts;           // workgroups per tile: part p expands blocks [p * part_blocks, ...) of 64 outputs
+    int32_t part_blocks;
+    // parts that also divide d_in trade their partial sums (see the exchange below); null: every part sums alone
+    uint64_t *xch;           // [n_tiles][parts][tile height rounded up to 8][padded rank] words
+    uint32_t *ctrl;          // [0] launch tag, [1] error flag, [8..72) sign-ins
+    int32_t poll_limit;
 };
 int tile_max_rows();
-hipError_t launch_tile_seg(const TileArgs &a, int r_pad, const uint32_t *inl, hipStream_t st);
+hipError_t launch_tile_seg(const TileArgs &a, const uint32_t *inl, hipStream_t st);
+hipError_t launch_tile_multi(const TileArgs *sites, int n, hipStream_t st);
+hipError_t launch_tile_multi_plan(const TileArgs *sites, int n, const PlanView &pv, const int32_t *token_slot, int T,
+                                  int n_slots, const int32_t *ready_rank, hipStream_t st);
 
 // moe_down.hip: second launch of the MoE down projection (expand + routing-weight combine on the matrix cores)
 struct MoeDownArgs {
@@ -209,7 +228,7 @@ int seg_expand_capacity();
 enum Knob {
     kRowsPollLimit, kRowsRankBound, kRowsItemsTarget, kRowsMode, kRowsWaves, kPlanGeneral, kPlanSeparate,
     kPlanPipeline, kSegExpandGroups, kSegTableCopy, kSegShrinkWgs, kSegTiles, kSegOverlap, kUploadPieceKb, kSegFused,
-    kRowsChunkRun, kKnobCount
+    kRowsChunkRun, kTileRows, kTileParts, kKnobCount
 };
 int tuning(Knob k);             // api.hip
 #ifdef MLORA_PROF

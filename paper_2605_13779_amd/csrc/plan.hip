@@ -21,9 +21,16 @@ static int64_t plan_big_words(int64_t M, int64_t NK)
     return ((M + kBigRange - 1) / kBigRange + 1) * NK;
 }
 
+// sum over groups of ceil(n_g / tile_rows), at most
+int64_t max_tiles(int64_t items, int64_t n_keys, int tile_rows)
+{
+    const int64_t touched = n_keys < items ? n_keys : items;
+    return (items + (tile_rows - 1) * touched) / tile_rows;
+}
+
 size_t plan_words(int64_t M, int64_t NK)
 {
-    return 8 + 3 * (NK + 1) + 4 * M + kRec * max_chunks(M, NK) + 64      // the grouping of the items and its chunk records
+    return 8 + 3 * (NK + 1) + 4 * M + (kRec + 4) * max_chunks(M, NK) + 64 + 4    // the grouping of the items, its chunk and tile records
          + 8 + 2 * (NK + 1) + 4 * M                                        // the grouping of the tokens (route plans)
          + 2 * plan_big_words(M, NK);
 }
@@ -51,6 +58,8 @@ PlanView plan_view(void *base, int64_t M, int64_t NK)
     const int64_t bw = plan_big_words(M, NK);
     v.big = bw ? p : nullptr;
     v.tok_big = bw ? p + bw : nullptr;
+    p += 2 * bw;
+    v.tiles = (int32_t *)(((uintptr_t)p + 15) & ~(uintptr_t)15);
     return v;
 }
 
@@ -68,21 +77,94 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Small dense batches (up to kSortMax rows): one workgroup, one key (slot, row) per thread, sorted
+// Small dense batches (up to kSortMax rows) over up to kSmallSlots slots: one workgroup, one row per thread.
+// A row's place is (rows of smaller slots) + (earlier rows of its slot); the second term comes from comparing
+// with the wave's 64 slots (four at a time, all lanes one LDS address) and from the waves adding their
+// counts to an LDS table in turn, the first from a scan over the slots.  All of it is barriers and LDS
+// latency, and there are about as many of the former as the batch has waves.  (The sorting network below,
+// which larger slot tables take, has fifty exchange steps: 8.9 against 7.9 us for 1001 rows over 64 slots.)
+// ---------------------------------------------------------------------------------------------
+constexpr int kSmallSlots = 4096;
+__global__ __launch_bounds__(kSortMax)
+void plan_dense_count_kernel(PlanView pv, const int32_t *__restrict__ token_slot, int T, int n_slots,
+                             const int32_t *__restrict__ ready_rank, int rec_bound, int tile_rows, int tile_bound)
+{
+    __shared__ int32_t cnt[kSmallSlots];           // rows of the slot
+    __shared__ int32_t off[kSmallSlots];           // rows of smaller slots
+    __shared__ int32_t base2[kSmallSlots];         // chunks | tiles << 16 of smaller slots
+    __shared__ __attribute__((aligned(16))) int32_t lkey[kSortMax];
+    __shared__ __attribute__((aligned(16))) int32_t wave_tot[16];
+    __shared__ int32_t s_tot[2];
+    const int i = (int)threadIdx.x, N = (int)blockDim.x, lane = i & 63, w = i >> 6;
+    int s = -1;
+    if (i < T) {
+        const int v = token_slot[i];
+        if (v >= 0 && v < n_slots && !(ready_rank && ready_rank[v] <= 0)) s = v;
+    }
+    for (int k = i; k < n_slots; k += N) cnt[k] = 0;
+    lkey[i] = s;                                   // (read back by the same wave only: LDS serves a wave in order)
+    int rank = 0, same = 0;
+    const int32_t *mine = lkey + 64 * w;
+#pragma unroll 4
+    for (int j = 0; j < 64; j += 4) {
+        const int4 v = *(const int4 *)(mine + j);
+        same += (v.x == s) + (v.y == s) + (v.z == s) + (v.w == s);
+        rank += (v.x == s && j < lane) + (v.y == s && j + 1 < lane) + (v.z == s && j + 2 < lane) + (v.w == s && j + 3 < lane);
+    }
+    __syncthreads();
+    const bool first = rank == 0;
+    for (int v = 0; v < (N >> 6); ++v) {
+        if (v == w && s >= 0) {
+            const int before = cnt[s];
+            rank += before;
+            if (first) cnt[s] = before + same;
+        }
+        __syncthreads();
+    }
+    const int per = (n_slots + N - 1) / N, k_lo = min(n_slots, i * per), k_hi = min(n_slots, k_lo + per);
+    int size = 0, recs = 0;
+    auto recs_of = [&](int c) { return (c + kChunk - 1) / kChunk + (tile_rows > 0 ? (c + tile_rows - 1) / tile_rows << 16 : 0); };
+    for (int k = k_lo; k < k_hi; ++k) { size += cnt[k]; recs += recs_of(cnt[k]); }
+    const int inc_s = block_scan<false>(size, i, N >> 6, wave_tot), inc_r = block_scan<false>(recs, i, N >> 6, wave_tot);
+    int run_s = inc_s - size, run_r = inc_r - recs;
+    for (int k = k_lo; k < k_hi; ++k) {
+        off[k] = run_s; base2[k] = run_r;
+        run_s += cnt[k]; run_r += recs_of(cnt[k]);
+    }
+    if (i == N - 1) { s_tot[0] = inc_s; s_tot[1] = inc_r; }
+    __syncthreads();
+    const int n_rows = s_tot[0], n_chunks = s_tot[1] & 0xffff, n_tiles = s_tot[1] >> 16;
+    if (s >= 0) {
+        const int pos = off[s] + rank, n = cnt[s], b = base2[s];
+        pv.sorted[pos] = i;
+        int32_t *rec = pv.chunks + (int64_t)((b & 0xffff) + rank / kChunk) * kRec;
+        rec[4 + (rank % kChunk)] = i;
+        if (rank % kChunk == 0) { rec[0] = s; rec[1] = min(kChunk, n - rank); rec[2] = pos; rec[3] = 0; }
+        if (tile_rows > 0 && rank % tile_rows == 0)
+            ((int4 *)pv.tiles)[(b >> 16) + rank / tile_rows] = make_int4(s, min(tile_rows, n - rank), pos, 0);
+    }
+    if (i == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
+    // records past the live ones are marked empty (count 0): the apply kernels read only records
+    for (int d = n_chunks + i; d < rec_bound; d += N) pv.chunks[(int64_t)d * kRec + 1] = 0;
+    for (int d = n_tiles + i; d < tile_bound; d += N) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same for any number of slots: one workgroup, one key (slot, row) per thread, sorted
 // with a bitonic network -- keys are distinct, so the result is the stable sort by slot.  Exchanges
 // at distance < 64 stay inside a wave (DPP / swizzle), only the few longer ones go through LDS.
 // Group starts and chunk numbers then come from two scans, and the chunk records are written.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024)
 void plan_dense_small_kernel(PlanView pv, const int32_t *__restrict__ token_slot, int T, int n_slots,
-                             const int32_t *__restrict__ ready_rank, int rec_bound, int N)
+                             const int32_t *__restrict__ ready_rank, int rec_bound, int tile_rows, int tile_bound, int N)
 {
-    __shared__ uint2 xch[kSortMax];              // long-distance exchanges, then sorted slots / chunk starts
+    __shared__ uint2 xch[kSortMax + 2];          // long-distance exchanges, then sorted slots / chunk and tile starts
     __shared__ __attribute__((aligned(16))) int32_t wave_tot[16];
-    __shared__ int32_t s_rows, s_chunks;
+    __shared__ int32_t s_rows, s_chunks, s_tiles;
     const int i = threadIdx.x;                   // blockDim.x == N, a power of two in [64, 1024]
     const uint32_t kNone = 0xffffffffu;
-    if (i == 0) { s_rows = 0; s_chunks = 0; }
+    if (i == 0) { s_rows = 0; s_chunks = 0; s_tiles = 0; }
     uint32_t ks = kNone, kt = (uint32_t)i;
     if (i < T) {
         const int s = token_slot[i];
@@ -102,14 +184,21 @@ void plan_dense_small_kernel(PlanView pv, const int32_t *__restrict__ token_slot
     const int gs = block_scan<true>(start ? i : 0, i, N >> 6, wave_tot);
     const int r = i - gs;
     const bool cstart = live && (r % kChunk) == 0;
-    const int c = block_scan<false>(cstart ? 1 : 0, i, N >> 6, wave_tot) - 1;     // chunk of this row
-    if (live && i == n_rows - 1) s_chunks = c + 1;
+    const bool tstart = live && tile_rows > 0 && (r % tile_rows) == 0;
+    const int both = block_scan<false>((cstart ? 1 : 0) | (tstart ? 0x10000 : 0), i, N >> 6, wave_tot);
+    const int c = (both & 0xffff) - 1, tl = (both >> 16) - 1;                       // chunk and tile of this row
+    if (live && i == n_rows - 1) { s_chunks = c + 1; s_tiles = tl + 1; }
     int32_t *cs = (int32_t *)xch;                // chunk c starts at sorted position cs[c]
+    int32_t *tls = cs + kSortMax + 1;            // tile t at tls[t] (at most kSortMax - 1 of them: tiles have room for kChunk rows)
     __syncthreads();
-    const int n_chunks = s_chunks;
+    const int n_chunks = s_chunks, n_tiles = s_tiles;
     if (cstart) cs[c] = i;
-    if (i == 0) cs[n_chunks] = n_rows;
+    if (tstart) tls[tl] = i;
+    if (i == 0) { cs[n_chunks] = n_rows; tls[n_tiles] = n_rows; }
     __syncthreads();
+    if (tstart) ((int4 *)pv.tiles)[tl] = make_int4((int)ks, tls[tl + 1] - i, i, 0);
+    if (tile_rows > 0)
+        for (int d = n_tiles + i; d < tile_bound; d += N) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
     if (live) {
         pv.sorted[i] = (int32_t)kt;
         int32_t *rec = pv.chunks + (int64_t)c * kRec;
@@ -122,13 +211,20 @@ void plan_dense_small_kernel(PlanView pv, const int32_t *__restrict__ token_slot
 }
 
 hipError_t launch_plan_dense_small(const PlanView &pv, const int32_t *token_slot, int T, int n_slots,
-                                   const int32_t *ready_rank, hipStream_t st)
+                                   const int32_t *ready_rank, int tile_rows, hipStream_t st)
 {
     int N = 64;
     while (N < T) N <<= 1;
     if (N > kSortMax) return hipErrorInvalidValue;
+    if (n_slots <= kSmallSlots) {
+        plan_dense_count_kernel<<<dim3(1), dim3((unsigned)(T + 63) / 64 * 64), 0, st>>>(
+            pv, token_slot, T, n_slots, ready_rank, (int)max_chunks(T, n_slots), tile_rows,
+            tile_rows > 0 ? (int)max_tiles(T, n_slots, tile_rows) : 0);
+        return hipGetLastError();
+    }
     plan_dense_small_kernel<<<dim3(1), dim3(N), 0, st>>>(pv, token_slot, T, n_slots, ready_rank,
-                                                         (int)max_chunks(T, n_slots), N);
+                                                         (int)max_chunks(T, n_slots), tile_rows,
+                                                         tile_rows > 0 ? (int)max_tiles(T, n_slots, tile_rows) : 0, N);
     return hipGetLastError();
 }
 
@@ -246,8 +342,10 @@ __device__ __forceinline__ int route_key(const int32_t *__restrict__ topk, const
 __device__ __forceinline__
 void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, const int32_t *__restrict__ token_slot,
                          int P, int K, uint32_t k_magic, int E, int n_slots, const int32_t *__restrict__ ready_rank,
-                         int32_t *__restrict__ out_sorted, int32_t *__restrict__ out_group_off, int rec_bound, const int block)
+                         int32_t *__restrict__ out_sorted, int32_t *__restrict__ out_group_off, int rec_bound, const int block,
+                         const int tile_rows, const int tile_bound)
 {
+    __shared__ int32_t tbase[kOneKeys + 1];      // first tile of each group
     __shared__ int32_t goff[kOneKeys + 1];       // exclusive group starts
     __shared__ uint32_t cnt2[kOneKeys];          // per key: pairs in the batch (low half) | pairs in front of this range (high half)
     __shared__ int32_t cbase[kOneKeys + 1];      // first chunk of each group
@@ -360,8 +458,20 @@ void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, c
         }
     }
     if (tid == kOneThreads - 1) { goff[NK] = inc_i; cbase[NK] = inc_c; }
+    const bool tiled = records && tile_rows > 0;
+    if (tiled) {                                 // (uniform)
+        int tiles = 0;
+#pragma unroll
+        for (int u = 0; u < kOneKeys / kOneThreads; ++u) tiles += (cnt[u] + tile_rows - 1) / tile_rows;
+        const int inc_t = block_scan<false>(tiles, tid, 16, wave_tot);
+        int run_t = inc_t - tiles;
+#pragma unroll
+        for (int u = 0; u < kOneKeys / kOneThreads; ++u)
+            if (lo + u < hi) { tbase[lo + u] = run_t; run_t += (cnt[u] + tile_rows - 1) / tile_rows; }
+        if (tid == kOneThreads - 1) tbase[NK] = inc_t;
+    }
     __syncthreads();
-    const int n_rows = goff[NK], n_chunks = cbase[NK];
+    const int n_rows = goff[NK], n_chunks = cbase[NK], n_tiles = tiled ? tbase[NK] : 0;
     if (block == 0) {
         for (int k = tid; k <= NK; k += kOneThreads) {
             pv.group_off[k] = goff[k];
@@ -374,6 +484,7 @@ void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, c
         const int j = p0 + tid;                  // this range also owns positions / records [p0, p0 + kOneRange)
         if (j < P) {
             if (records && j >= n_chunks && j < rec_bound) pv.chunks[(int64_t)j * kRec + 1] = 0;   // empty record past the live chunks
+            if (tiled && j >= n_tiles && j < tile_bound) ((int4 *)pv.tiles)[j] = make_int4(0, 0, 0, 0);
             if (j >= n_rows) {
                 pv.sorted[j] = -1;
                 if (out_sorted) out_sorted[j] = -1;
@@ -390,6 +501,7 @@ void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, c
                     rec[4 + (r % kChunk)] = j;
                     if (r % kChunk == 0) { rec[0] = key; rec[1] = min(kChunk, n - r); rec[2] = off + r; rec[3] = 0; }
                 }
+                if (tiled && r % tile_rows == 0) ((int4 *)pv.tiles)[tbase[key] + r / tile_rows] = make_int4(key, min(tile_rows, n - r), off + r, 0);
             }
         }
     }
@@ -401,14 +513,14 @@ __global__ __launch_bounds__(kOneThreads)
 void plan_route_one_kernel(PlanView pv, const int32_t *__restrict__ topk, const int32_t *__restrict__ token_slot,
                            int P, int K, uint32_t k_magic, int E, int n_slots, const int32_t *__restrict__ ready_rank,
                            int32_t *__restrict__ out_sorted, int32_t *__restrict__ out_group_off, int rec_bound,
-                           int pair_blocks, int T)
+                           int pair_blocks, int T, int tile_rows, int tile_bound)
 {
     const int b = (int)blockIdx.x;
     if (b < pair_blocks) {
-        plan_route_one_body(pv, topk, token_slot, P, K, k_magic, E, n_slots, ready_rank, out_sorted, out_group_off, rec_bound, b);
+        plan_route_one_body(pv, topk, token_slot, P, K, k_magic, E, n_slots, ready_rank, out_sorted, out_group_off, rec_bound, b, tile_rows, tile_bound);
     } else {
         const PlanView tv = plan_token_view(pv);
-        plan_route_one_body(tv, nullptr, token_slot, T, 1, 0u, 1, n_slots, ready_rank, nullptr, nullptr, 0, b - pair_blocks);
+        plan_route_one_body(tv, nullptr, token_slot, T, 1, 0u, 1, n_slots, ready_rank, nullptr, nullptr, 0, b - pair_blocks, 0, 0);
     }
 }
 
@@ -509,12 +621,16 @@ void plan_big_scan_kernel(const BigSide pairs, const BigSide toks, int pair_bloc
     if (on && w == 0) col[(int64_t)d.blocks * d.NK] = run;
 }
 
+// TILED: tile records too, for half as many keys (a third LDS table).
+template <bool TILED>
 __global__ __launch_bounds__(kBigRange)
 void plan_big_place_kernel(const BigSide pairs, const BigSide toks, int32_t *__restrict__ out_sorted,
-                           int32_t *__restrict__ out_group_off, int rec_bound)
+                           int32_t *__restrict__ out_group_off, int rec_bound, int tile_rows, int tile_bound)
 {
-    __shared__ int32_t goff[kBigKeys + 1];
-    __shared__ int32_t cbase[kBigKeys + 1];
+    constexpr int kKeys = TILED ? kBigKeys / 2 : kBigKeys;
+    __shared__ int32_t goff[kKeys + 1];
+    __shared__ int32_t cbase[kKeys + 1];
+    __shared__ int32_t tbase[TILED ? kKeys + 1 : 1];
     __shared__ __attribute__((aligned(16))) int32_t wave_tot[16];
     const bool is_tok = (int)blockIdx.x >= pairs.blocks;
     const BigSide &d = is_tok ? toks : pairs;
@@ -529,7 +645,7 @@ void plan_big_place_kernel(const BigSide pairs, const BigSide toks, int32_t *__r
     const int32_t *total = pv.big + (int64_t)d.blocks * NK;
     const int per = (NK + kBigRange - 1) / kBigRange;           // <= 16 keys per thread
     const int lo = min(NK, tid * per), hi = min(NK, lo + per);
-    constexpr int kPer = kBigKeys / kBigRange;
+    constexpr int kPer = kKeys / kBigRange;
     int cnt[kPer], items = 0, chunks = 0;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) cnt[u] = lo + u < hi ? total[lo + u] : 0;
@@ -546,8 +662,19 @@ void plan_big_place_kernel(const BigSide pairs, const BigSide toks, int32_t *__r
         }
     }
     if (tid == kBigRange - 1) { goff[NK] = inc_i; cbase[NK] = inc_c; }
+    if constexpr (TILED) {
+        int tiles = 0;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) tiles += (cnt[u] + tile_rows - 1) / tile_rows;
+        const int inc_t = block_scan<false>(tiles, tid, 16, wave_tot);
+        int run_t = inc_t - tiles;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            if (lo + u < hi) { tbase[lo + u] = run_t; run_t += (cnt[u] + tile_rows - 1) / tile_rows; }
+        if (tid == kBigRange - 1) tbase[NK] = inc_t;
+    }
     __syncthreads();
-    const int n_rows = goff[NK], n_chunks = cbase[NK];
+    const int n_rows = goff[NK], n_chunks = cbase[NK], n_tiles = TILED ? tbase[NK] : 0;
     // group offsets: each workgroup writes a share
     for (int k = block * kBigRange + tid; k <= NK; k += d.blocks * kBigRange) {
         pv.group_off[k] = goff[k];
@@ -559,6 +686,7 @@ void plan_big_place_kernel(const BigSide pairs, const BigSide toks, int32_t *__r
     if (block == 0 && tid == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
     if (j >= d.P) return;
     if (records && j >= n_chunks && j < rec_bound) pv.chunks[(int64_t)j * kRec + 1] = 0;      // empty record past the live chunks
+    if (TILED && records && j >= n_tiles && j < tile_bound) ((int4 *)pv.tiles)[j] = make_int4(0, 0, 0, 0);
     if (j >= n_rows) {
         pv.sorted[j] = -1;
         if (records && out_sorted) out_sorted[j] = -1;
@@ -571,6 +699,14 @@ void plan_big_place_kernel(const BigSide pairs, const BigSide toks, int32_t *__r
     int32_t *rec = pv.chunks + (int64_t)(cbase[key] + r / kChunk) * kRec;
     rec[4 + (r % kChunk)] = j;
     if (r % kChunk == 0) { rec[0] = key; rec[1] = min(kChunk, n - r); rec[2] = off + r; rec[3] = 0; }
+    if (TILED && r % tile_rows == 0) ((int4 *)pv.tiles)[tbase[key] + r / tile_rows] = make_int4(key, min(tile_rows, n - r), off + r, 0);
+}
+
+// Whether a plan of this size can hold tile records (the pipeline writes none).
+bool plan_can_tile(const PlanView &pv, int64_t P, int64_t NK)
+{
+    if (tuning(kPlanPipeline)) return false;
+    return (P <= kOnePairs && NK <= kOneKeys) || (pv.big && NK <= kBigKeys / 2 && P < (1 << 24));
 }
 
 bool plan_route_in_one_launch(int64_t P, int64_t NK)
@@ -580,16 +716,17 @@ bool plan_route_in_one_launch(int64_t P, int64_t NK)
 
 hipError_t launch_plan_general(const PlanView &pv, const int32_t *topk, const int32_t *token_slot,
                                int T, int K, int E, int n_slots, const int32_t *ready_rank,
-                               int32_t *out_sorted, int32_t *out_group_off, hipStream_t st)
+                               int32_t *out_sorted, int32_t *out_group_off, int tile_rows, hipStream_t st)
 {
     const int P = T * K, NK = n_slots * E;
+    const int tile_bound = tile_rows > 0 ? (int)max_tiles(P, NK, tile_rows) : 0;
     const bool route = topk != nullptr;            // a route plan also groups the tokens by slot
     const uint32_t magic = K > 1 ? (uint32_t)((0x100000000ull + (uint64_t)K - 1) / (uint64_t)K) : 0u;
     if (plan_route_in_one_launch(P, NK)) {
         const int pair_blocks = (P + kOneRange - 1) / kOneRange, tok_blocks = route ? (T + kOneRange - 1) / kOneRange : 0;
         plan_route_one_kernel<<<dim3((unsigned)(pair_blocks + tok_blocks)), dim3(kOneThreads), 0, st>>>(
             pv, topk, token_slot, P, K, magic, E, n_slots,
-            ready_rank, out_sorted, out_group_off, (int)max_chunks(P, NK), pair_blocks, T);
+            ready_rank, out_sorted, out_group_off, (int)max_chunks(P, NK), pair_blocks, T, tile_rows, tile_bound);
         return hipGetLastError();
     }
     if (pv.big && NK <= kBigKeys && (int64_t)P * K < ((int64_t)1 << 32) && !tuning(kPlanPipeline)) {     // (the bound: k_magic)
@@ -599,7 +736,10 @@ hipError_t launch_plan_general(const PlanView &pv, const int32_t *topk, const in
         const int pair_scans = (NK + 63) / 64, tok_scans = route ? (n_slots + 63) / 64 : 0;
         plan_big_count_kernel<<<dim3(nb), dim3(kBigRange), 0, st>>>(pairs, toks, token_slot, n_slots, ready_rank);
         plan_big_scan_kernel<<<dim3((unsigned)(pair_scans + tok_scans)), dim3(1024), 0, st>>>(pairs, toks, pair_scans);
-        plan_big_place_kernel<<<dim3(nb), dim3(kBigRange), 0, st>>>(pairs, toks, out_sorted, out_group_off, (int)max_chunks(P, NK));
+        if (tile_rows > 0)
+            plan_big_place_kernel<true><<<dim3(nb), dim3(kBigRange), 0, st>>>(pairs, toks, out_sorted, out_group_off, (int)max_chunks(P, NK), tile_rows, tile_bound);
+        else
+            plan_big_place_kernel<false><<<dim3(nb), dim3(kBigRange), 0, st>>>(pairs, toks, out_sorted, out_group_off, (int)max_chunks(P, NK), 0, 0);
         return hipGetLastError();
     }
     const unsigned nb = (unsigned)((P + 255) / 256);

@@ -122,13 +122,15 @@ struct PlanLocalLds {
     int32_t prt[256];                      // the upper half's counts for each row (same << 16 | earlier)
     int32_t off[kLocalPlanSlots + 1];      // rows of smaller slots
     int32_t cbase[kLocalPlanSlots + 1];    // chunks of smaller slots
+    int32_t tbase[kLocalPlanSlots + 1];    // tiles of smaller slots
     __attribute__((aligned(16))) int32_t wave_tot[16];
 };
 
 __device__ __forceinline__ void plan_dense_local(const int32_t *__restrict__ token_slot, int T, int n_slots,
                                                  const int32_t *__restrict__ ready_rank, int rec_bound,
                                                  int i, int nthreads, PlanLocalLds &L,
-                                                 int32_t *lrec, bool write_pv, const PlanView &pv)
+                                                 int32_t *lrec, bool write_pv, const PlanView &pv,
+                                                 int tile_rows, int tile_bound, int4 *ltile = nullptr, int32_t *lsorted = nullptr)
 {
     const int lane = i & 63, w = i >> 6, nw = nthreads >> 6;
     constexpr int kRowWaves = 4;
@@ -171,36 +173,53 @@ __device__ __forceinline__ void plan_dense_local(const int32_t *__restrict__ tok
     }
     if (s >= 0 && rank == 0) L.cntw[w][s] = same;
     __syncthreads();
-    // per slot: size and chunks, a run of slots per thread; one scan carries both sums (each total is
-    // at most 256)
+    // per slot: size, chunks and tiles, a run of slots per thread; one scan carries the three sums (each total
+    // is at most 256; a slot has no more tiles than chunks)
     const int per = (n_slots + nthreads - 1) / nthreads;
     const int k_lo = min(n_slots, i * per), k_hi = min(n_slots, k_lo + per);
-    int size = 0, chunks = 0;
+    auto tiles_of = [&](int c) { int n = 0; if (tile_rows > 0) for (int r = 0; r < c; r += tile_rows) ++n; return n; };
+    int size = 0, chunks = 0, tiles = 0;
     for (int k = k_lo; k < k_hi; ++k) {
         int c = 0;
         for (int v = 0; v < kRowWaves; ++v) c += L.cntw[v][k];
         size += c;
         chunks += (c + kChunk - 1) / kChunk;
+        tiles += tiles_of(c);
     }
-    const int inc = block_scan<false>(chunks << 16 | size, i, nw, L.wave_tot);
-    int run_s = (inc & 0xffff) - size, run_c = (inc >> 16) - chunks;
+    const int inc = block_scan<false>(tiles << 20 | chunks << 10 | size, i, nw, L.wave_tot);
+    int run_s = (inc & 0x3ff) - size, run_c = (inc >> 10 & 0x3ff) - chunks, run_t = (inc >> 20) - tiles;
     for (int k = k_lo; k < k_hi; ++k) {
         int c = 0;
         for (int v = 0; v < kRowWaves; ++v) c += L.cntw[v][k];
-        L.off[k] = run_s; L.cbase[k] = run_c;
+        L.off[k] = run_s; L.cbase[k] = run_c; L.tbase[k] = run_t;
         run_s += c;
         run_c += (c + kChunk - 1) / kChunk;
+        run_t += tiles_of(c);
     }
-    if (i == nthreads - 1) { L.off[kLocalPlanSlots] = inc & 0xffff; L.cbase[kLocalPlanSlots] = inc >> 16; }
+    if (i == nthreads - 1) {
+        L.off[kLocalPlanSlots] = inc & 0x3ff; L.cbase[kLocalPlanSlots] = inc >> 10 & 0x3ff; L.tbase[kLocalPlanSlots] = inc >> 20;
+    }
     __syncthreads();
-    const int n_rows = L.off[kLocalPlanSlots], n_chunks = L.cbase[kLocalPlanSlots];
+    const int n_rows = L.off[kLocalPlanSlots], n_chunks = L.cbase[kLocalPlanSlots], n_tiles = L.tbase[kLocalPlanSlots];
     if (s >= 0) {
         int n = 0;
         for (int k = 0; k < kRowWaves; ++k) { const int c = L.cntw[k][s]; n += c; rank += k < w ? c : 0; }
         const int pos = L.off[s] + rank, c = L.cbase[s] + rank / kChunk;
-        int32_t *rec = lrec + c * kRec;
-        rec[4 + (rank % kChunk)] = i;
-        if (rank % kChunk == 0) { rec[0] = s; rec[1] = min(kChunk, n - rank); rec[2] = pos; rec[3] = 0; }
+        if (lrec) {
+            int32_t *rec = lrec + c * kRec;
+            rec[4 + (rank % kChunk)] = i;
+            if (rank % kChunk == 0) { rec[0] = s; rec[1] = min(kChunk, n - rank); rec[2] = pos; rec[3] = 0; }
+        }
+        if (lsorted) lsorted[pos] = i;
+        if (tile_rows > 0) {
+            int t = 0, r0 = 0;                     // this row's tile of the slot, and the tile's first row
+            while (r0 + tile_rows <= rank) { r0 += tile_rows; ++t; }
+            if (r0 == rank) {
+                const int4 v = make_int4(s, min(tile_rows, n - rank), pos, 0);
+                if (ltile) ltile[L.tbase[s] + t] = v;
+                if (write_pv) ((int4 *)pv.tiles)[L.tbase[s] + t] = v;
+            }
+        }
         if (write_pv) {
             pv.sorted[pos] = i;
             int32_t *g = pv.chunks + (int64_t)c * kRec;
@@ -210,8 +229,12 @@ __device__ __forceinline__ void plan_dense_local(const int32_t *__restrict__ tok
     }
     if (write_pv && i == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
     for (int d = n_chunks + i; d < rec_bound; d += nthreads) {
-        lrec[d * kRec + 1] = 0;
+        if (lrec) lrec[d * kRec + 1] = 0;
         if (write_pv) pv.chunks[(int64_t)d * kRec + 1] = 0;
+    }
+    for (int d = n_tiles + i; d < tile_bound; d += nthreads) {
+        if (ltile) ltile[d] = make_int4(0, 0, 0, 0);
+        if (write_pv) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
     }
     __syncthreads();
 }

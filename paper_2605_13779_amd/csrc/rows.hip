@@ -669,7 +669,7 @@ constexpr int kLocalPlanRows = 256;   // more rows mean more distinct slots per 
 struct PlanLocalArgs {
     const int32_t *token_slot;
     const int32_t *ready_rank;
-    int32_t T, n_slots, rec_bound;
+    int32_t T, n_slots, rec_bound, tile_rows, tile_bound;
     PlanView pv;
 };
 
@@ -681,7 +681,7 @@ void rows_multi_plan_kernel(const MultiArgs m, const PlanLocalArgs pl)
     __shared__ __attribute__((aligned(16))) int32_t p_rec[kLocalPlanRows * kRec];
     const int b = (int)blockIdx.x;
     plan_dense_local(pl.token_slot, pl.T, pl.n_slots, pl.ready_rank, pl.rec_bound, (int)threadIdx.x, NW * 64,
-                     p_lds, p_rec, b == 0, pl.pv);
+                     p_lds, p_rec, b == 0, pl.pv, pl.tile_rows, pl.tile_bound);
     int s = 0;
 #pragma unroll
     for (int k = 1; k < kMaxMulti; ++k) s += (k < m.n && b >= m.first[k]) ? 1 : 0;
@@ -904,7 +904,7 @@ int rows_local_plan_rows() { return kLocalPlanRows; }
 int rows_local_plan_slots() { return kLocalPlanSlots; }
 
 hipError_t launch_rows_multi_plan(const RowsArgs *sites, int n, const PlanView &pv, const int32_t *token_slot, int T,
-                                  int n_slots, const int32_t *ready_rank, hipStream_t st)
+                                  int n_slots, const int32_t *ready_rank, int tile_rows, hipStream_t st)
 {
     if (n < 1 || n > kMaxMulti || T < 1 || T > kLocalPlanRows || n_slots > kLocalPlanSlots) return hipErrorInvalidValue;
     if (n == 1) {
@@ -917,6 +917,8 @@ hipError_t launch_rows_multi_plan(const RowsArgs *sites, int n, const PlanView &
     pl.token_slot = token_slot; pl.ready_rank = ready_rank; pl.T = T; pl.n_slots = n_slots;
     pl.rec_bound = (int)max_chunks(T, n_slots);
     if (pl.rec_bound > kLocalPlanRows) return hipErrorInvalidValue;
+    pl.tile_rows = tile_rows;
+    pl.tile_bound = tile_rows > 0 ? (int)max_tiles(T, n_slots, tile_rows) : 0;
     pl.pv = pv;
     switch (sites[0].r_pad) {
         case 1:  return launch_multi_rp<1, 8>(sites, n, st, &pl);
