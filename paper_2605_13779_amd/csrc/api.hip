@@ -50,9 +50,8 @@ namespace {
 constexpr int32_t kDensePrivItems = 1024;      // rows per private dense plan (one-workgroup planner)
 constexpr int32_t kMoePrivItems = 131072;      // pairs per private MoE plan
 constexpr int32_t kSegCap = 65536;             // segment tiles / chunks per call
-constexpr int32_t kXchChunks = 256;            // chunks per launch whose parts may trade partial sums
 constexpr size_t kCtrlBytes = 1024;
-constexpr size_t kXchBytes = (size_t)kXchChunks * 128 * kChunk * 8;   // <= 128 values per row of a chunk
+constexpr size_t kXchBytes = (size_t)1 << 20;          // words that the parts of a launch's tiles trade their partial sums through
 constexpr size_t kSegXchBytes = (size_t)24 << 20;   // rank-64 sites: exchange words, then the prefill's partial shrink results
 // behind the exchange words: tile counters (16 KB), then per tile 16 KB of h (bf16 head + tail), then the
 // fp32 partials of the k-slices
@@ -199,7 +198,6 @@ RowsArgs rows_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int
     a.meta.rank = s->rank; a.meta.scale = s->scale;
     a.d_in = s->d.d_in; a.d_out = s->d.d_out; a.r_pad = s->r_pad;
     a.n_experts = s->E; a.top_k = 1;
-    a.xch = s->xch; a.ctrl = s->ctrl; a.xch_chunks = s->xch ? kXchChunks : 0;   // a rank-64 site's larger area holds these too
     a.rank_bound = s->n_short > 0 ? 1 : 0;      // the launch code keeps it only where it pays
 #ifdef MLORA_PROF
     a.prof = debug_prof();
@@ -269,7 +267,7 @@ TileArgs tile_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int
     if (trade && a.parts > 1) {
         a.xch = xch; a.ctrl = ctrl;
         const int pl = tuning(kRowsPollLimit);
-        a.poll_limit = pl < 0 ? 0 : (pl > 0 ? pl : 4096);
+        a.poll_limit = pl < 0 ? 0 : (pl > 0 ? pl : kPollLimit);
     }
     return a;
 }
@@ -1194,11 +1192,7 @@ struct DecodeScratch {
 static int32_t apply_decode_impl(mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy,
                                  const int32_t *token_slot, int32_t T, hipStream_t st, const DecodeScratch &sc)
 {
-    auto args = [&](const void *xp, void *yp) {
-        RowsArgs a = rows_args(s, xp, ldx, yp, ldy);
-        a.xch = sc.xch; a.ctrl = sc.ctrl; a.xch_chunks = sc.xch ? kXchChunks : 0;
-        return a;
-    };
+    auto args = [&](const void *xp, void *yp) { return rows_args(s, xp, ldx, yp, ldy); };
     if (s->r_pad <= 2 && !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
         // Tiny adapters (the compact rank-1 catalog of Section 4): rows are applied one by one, without
         // a plan -- grouping would save at most two adapter rows per row, a planner launch costs more.

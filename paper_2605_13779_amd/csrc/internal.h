@@ -89,16 +89,9 @@ struct RowsArgs {
     int32_t n_experts;       // >= 1: key / n_experts = slot
     int32_t top_k;           // x row = item / top_k
     int32_t grid_chunks;     // upper bound on the number of chunks
-    // exchange area of the site (null on sites that only run fused launches)
-    uint64_t *xch;           // [xch_chunks][<= 128 values][kChunk] words
-    uint32_t *ctrl;          // [0] launch tag, [1] error flag, [8..72) sign-ins
-    int32_t xch_chunks;
     // filled in by the launcher
-    int32_t mode;            // 0 nothing crosses workgroups; 2 parts that trade k-slices
-    int32_t ksplit, kslice_units;
     int32_t tile_par;        // parts a chunk is cut into (one item each; 1 = one item per chunk): part p expands
-    int32_t out_per_part;    // outputs [p * out_per_part, ...) and, in mode 2, shrinks k-slice p
-    int32_t poll_limit;      // polls of an exchange word before a reader takes the item on its own
+    int32_t out_per_part;    // outputs [p * out_per_part, ...)
     int32_t rank_bound;      // 1: read the slot's rank first and fetch only that many rows of A
     // ungrouped launch (ranks 1 and 2 only): item i is row i with slot row_slot[i]; `chunks` is not read
     const int32_t *row_slot;
@@ -270,9 +263,10 @@ typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 // error flag raised when a bounded wait gives up.
 constexpr int kSpinLimit = 1 << 18;
 constexpr uint32_t kTagPoison = 0xffffffffu;   // exchange switched off after a bounded wait gave up (see tag_advance)
-// Polls of an exchange word before a reader computes the value itself (a partner can start late).
-// The two ways of getting the value add the same terms in a different order, so an output can differ
-// by one rounding step between them; both are within the tolerance of the result.
+// Polls of an exchange word before a reader computes the value itself (a partner can start late): about
+// 100 us, far longer than any launch here lasts.  The two ways of getting the value add the same terms in a
+// different order, so an output can differ by one rounding step between them; both are within the
+// tolerance of the result.
 constexpr int kPollLimit = 4096;
 
 __device__ __forceinline__ void xch_put(uint64_t *p, float v, uint32_t tag)

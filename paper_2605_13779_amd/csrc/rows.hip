@@ -8,18 +8,9 @@
 // run to the padded rank; big launches over tables with padded slots skip the reads of those rows of A.
 //
 // These launches last microseconds, so what matters is how few dependent memory round trips a
-// workgroup makes: every work item issues its loads in one flight.  Two shapes of launch:
-//   one item per chunk   shrink, then expand, h stays in LDS (MoE sites, rank-1 sites, and dense
-//                        launches that have enough chunks to fill the GPU).
-//   chunk parts          a dense launch with fewer chunks than the GPU has CUs cuts every chunk
-//                        into parts.  Part p shrinks k-slice p of d_in and expands its own range of
-//                        outputs; the parts trade their partial h (fp32, a few hundred bytes)
-//                        through a small L2-resident exchange buffer, while the B rows and y
-//                        values of the expand are already on their way.  No adapter byte is read
-//                        twice and a big d_in or d_out spreads over many CUs.  Each word of the
-//                        exchange carries value and launch tag in one 64-bit store, so no fences
-//                        are needed; a part whose partners have not published after a bounded
-//                        number of polls takes its item again on its own, with the whole shrink.
+// workgroup makes: every work item issues its loads in one flight.  An item is a chunk (shrink, then
+// expand, h stays in LDS), or, where a dense launch has fewer chunks than the GPU has room for, a part
+// of a chunk's outputs (each part redoes the shrink).
 #include "plan_device.h"
 #include "wave_ops.h"
 
@@ -84,20 +75,17 @@ __device__ __forceinline__ void y_pack(const float *f, uint4 &r)
 }
 
 // Work of workgroup `wg` out of `n_wg` on one site (one launch may cover several sites).
-// XCH: the kernel can pass partial shrink results between workgroups (a.mode 2).
 // RI: the launch has no plan; item i is row i and its slot is a.row_slot[i] (rank 1 and 2 only).
 // RUN: one item per chunk -- 1 << RUN consecutive chunks go to one XCD (3 everywhere; one instantiation
 // with longer runs exists for measurements, see rows_multi_kernel).
-template <int RP, int NW, bool XCH, bool RI = false, int RUN = 3>
+template <int RP, int NW, bool RI = false, int RUN = 3>
 __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const int n_wg, const int32_t *lrec = nullptr)
 {
-    static_assert(!RI || (!XCH && RP <= 2), "row items: small ranks, nothing traded");
+    static_assert(!RI || RP <= 2, "row items: small ranks");
     using C = RowsCfg<RP, NW>;
     typedef typename YVec<C::OPL>::T yvec_t;
     __shared__ __attribute__((aligned(16))) float hs[kChunk][RP];
     __shared__ float part[C::KS][kChunk][RP];
-    __shared__ uint32_t s_tag;
-    __shared__ uint32_t s_missing;
 
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     const int jg = w % C::JG, ks = w / C::JG;
@@ -109,26 +97,10 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
 #endif
     if (prof && tid == 0) { prof[0] = wall_clock64(); prof[7] = 0; }
 
-    const bool use_x = XCH && a.mode != 0;                   // this site's items exchange partial results
-    // Items are numbered over the upper bound of chunks, so an item's chunk record can be fetched
-    // together with the live chunk count (and the launch tag) in one round trip.
     constexpr int kRunMask = (8 << RUN) - 1;                   // chunks per XCD run times 8 XCDs, minus one
     const int n_items = a.tile_par > 1 ? ((a.grid_chunks + 7) & ~7) * a.tile_par : ((a.grid_chunks + kRunMask) & ~kRunMask);
 
-    // Launches that exchange carry a tag that must differ from launch to launch, also when a
-    // captured graph replays the same kernel arguments, so it lives in device memory: every
-    // workgroup reads it, then signs in (fire-and-forget add on one of 64 counters); the last
-    // workgroup of the grid, when its own items are done, sees all sign-ins and advances the tag
-    // for the next launch.  Nobody waits for an atomic's return value on the way in.
-    uint32_t tag = 0;
-    if (XCH && tid == 0) {
-        s_missing = 0;
-        if (use_x) tag = tag_read(a.ctrl);
-    }
     bool first_item = true;
-    // An item is taken a second time only after a bounded wait for another workgroup's partial sums
-    // has given up: it then runs on its own, with the whole shrink.
-    bool solo_next = false;
 
     for (int item = wg; item < n_items; item += n_wg) {
         // Per-item copies of the thread's coordinates: what is derived from them (LDS addresses, lane
@@ -139,19 +111,17 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
         const int tid = tid_item, w = tid >> 6, lane = tid & 63;
         const int jg = w % C::JG, ks = w / C::JG;
         // ---- which chunk, which part of it ----
-        int chunk, kslice = 0, out0 = 0, out1 = a.d_out;
+        int chunk, out0 = 0, out1 = a.d_out;
         // The first launch of the MoE down projection only shrinks (a.h_out); it comes here for padded ranks
         // above 16 only, so the kernels of the smaller ranks do not carry that mode.
-        constexpr bool HMODE = RP >= 32 && !XCH && !RI;
+        constexpr bool HMODE = RP >= 32 && !RI;
         const bool h_only = HMODE && a.h_out != nullptr;
-        bool do_shrink = true, do_expand = !h_only;
-        int part_i = 0;
+        bool do_expand = !h_only;
         if (a.tile_par > 1) {
             // workgroups are dealt round-robin to the 8 XCDs: keep the parts of one chunk (they share
-            // the chunk's rows of x and its exchange words) on one XCD and its L2, and deal the chunks
-            // over the XCDs
+            // the chunk's rows of x and the adapter's A) on one XCD and its L2, and deal the chunks over the XCDs
             const int idx = item >> 3, grp8 = idx / a.tile_par;
-            part_i = idx - grp8 * a.tile_par;
+            const int part_i = idx - grp8 * a.tile_par;
             chunk = grp8 * 8 + (item & 7);
             out0 = part_i * a.out_per_part; out1 = min(a.d_out, out0 + a.out_per_part);
             do_expand = out0 < out1 && !h_only;
@@ -190,21 +160,7 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
         row[0] = __builtin_amdgcn_readfirstlane(r1.x); row[1] = __builtin_amdgcn_readfirstlane(r1.y);
         row[2] = __builtin_amdgcn_readfirstlane(r1.z); row[3] = __builtin_amdgcn_readfirstlane(r1.w);
         if (prof && tid == 0 && first_item) prof[5] = wall_clock64();      // the chunk record has arrived
-        if (XCH && first_item) {
-            if (tid == 0) {
-                s_tag = tag;
-                if (use_x) tag_sign_in(a.ctrl, wg, tag);
-            }
-            __syncthreads();
-            tag = s_tag;
-        }
-        if (prof && tid == 0 && first_item) prof[6] = wall_clock64();      // ... and the launch tag
         if (cnt <= 0) { first_item = false; continue; }            // record past the live chunks of this batch
-        // An item runs on its own (whole shrink, nothing published or awaited) when its bounded wait
-        // has just given up, or when an earlier launch's give-up has switched the exchange off.
-        const bool solo = solo_next || (XCH && tag == kTagPoison);
-        solo_next = false;
-        if (a.tile_par > 1 && use_x && !solo) { kslice = part_i; do_shrink = part_i < a.ksplit; }   // else every part does the whole shrink
 #pragma unroll
         for (int c = 1; c < kChunk; ++c) row[c] = c < cnt ? row[c] : row[0];
         static_assert(kChunk == 4 && kRec == 8, "record layout: two 16-byte loads");
@@ -219,7 +175,6 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
         int rank;                  // (requested behind the shrink's operands, which are wanted first)
         float scale;
 
-        const bool xitem = use_x && !solo;
         // ---- one flight: every load of this item is issued here ----
         const uint16_t *Bg = a.b_tab + (int64_t)key * a.d_out * RP;
         // MoE down projection, first launch: no expand here; the chunk's scaled h, times the row's
@@ -265,11 +220,7 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
         const uint32_t a_row_bytes = (uint32_t)a.d_in * 2u;
         const char *Ag = (const char *)(a.a_tab + (int64_t)key * RP * a.d_in);
         uint32_t a_row_off[C::JPW];
-        if constexpr (XCH) {
-            Ag += (int64_t)(jg * C::JPW) * a_row_bytes;
-#pragma unroll
-            for (int jj = 0; jj < C::JPW; ++jj) a_row_off[jj] = (uint32_t)jj * a_row_bytes;
-        } else {
+        if constexpr (!C::SX) {
             // Rank-bounded reads (slots of different true rank in one padded table): rows of A past
             // the slot's rank are not fetched.  The wave that would have read them reads the slot's
             // last real row again (a cache hit, every load is still issued), and what it computes
@@ -291,13 +242,10 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
         uint32_t sx_off[C::JQ];
         const char *sx_x = nullptr;
         if constexpr (C::SX) {
-            int a_last = C::JPW - 1;
-            if constexpr (!XCH) {
-                // (rank-bounded reads, as below for the other ranks)
-                if (a.rank_bound) a_last = min(max(__builtin_amdgcn_readfirstlane(a.meta.rank[slot]), 1), RP) - 1 - jg * C::JPW;
-            }
+            int a_last = C::JPW - 1;               // (rank-bounded reads, as above for the other ranks)
+            if (a.rank_bound) a_last = min(max(__builtin_amdgcn_readfirstlane(a.meta.rank[slot]), 1), RP) - 1 - jg * C::JPW;
 #pragma unroll
-            for (int q = 0; q < C::JQ; ++q) sx_off[q] = (uint32_t)((XCH ? 0 : jg * C::JPW) + min(4 * q + lr, a_last)) * a_row_bytes;      // (XCH: Ag starts at the wave's rows)
+            for (int q = 0; q < C::JQ; ++q) sx_off[q] = (uint32_t)(jg * C::JPW + min(4 * q + lr, a_last)) * a_row_bytes;
             const int xr = lr == 0 ? row[0] : (lr == 1 ? row[1] : (lr == 2 ? row[2] : row[3]));
             sx_x = (const char *)(a.x + (int64_t)(xr / a.top_k) * a.ldx);
         }
@@ -324,12 +272,10 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
             }
             const int u = f + ks * 64 + lane;
             const uint32_t ub = (uint32_t)(u < uh ? u : ul) * 16u;
-            // The waves past the end of the range issue nothing (a k-slice of an exchange item is often
-            // one wave wide, and the last flight of a long shrink is partial).  A CU accepts one 64-lane
-            // 16-byte load per 16 cycles whatever the lanes fetch, and clamped loads took more of that
-            // than the item's real bytes.  (Not in the 4-wave kernels: their ranges fill the workgroup,
-            // and the branch alone measured slower there.)
-            if constexpr (XCH || NW == 8) {
+            // The waves past the end of the range issue nothing (the last flight of a long shrink is partial).
+            // A CU accepts one 64-lane 16-byte load per 16 cycles whatever the lanes fetch.  (Not in the 4-wave
+            // kernels: their ranges fill the workgroup, and the branch alone measured slower there.)
+            if constexpr (NW == 8) {
                 if (__builtin_amdgcn_readfirstlane(f + ks * 64) >= uh) {
 #pragma unroll
                     for (int jj = 0; jj < C::JPW; ++jj) av[jj] = make_uint4(0, 0, 0, 0);
@@ -432,8 +378,7 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
             __syncthreads();                                      // part may be written again
             return s;
         };
-        const int u_lo = solo ? 0 : kslice * a.kslice_units, u_hi = solo ? U : min(U, u_lo + a.kslice_units);
-        if (do_shrink) load_flight(u_lo, u_lo, u_hi, IntC<1>{});
+        load_flight(0, 0, U, IntC<1>{});
         rank = a.meta.rank[slot + lane_zero];
         scale = a.meta.scale[slot + lane_zero];
         // The first expand tile travels with the shrink operands -- except in the kernels of ranks 8 and
@@ -443,76 +388,26 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
         // partial sums have been reduced (and traded) (c2 layer step 65.05 -> 64.0 us; packed MoE gate+up
         // 97.9 -> 97.3 us).
         constexpr bool kTilesBehindShrink = C::MX;
-        if (do_expand && !(kTilesBehindShrink && do_shrink)) {
-            load_tile(out0, IntC<0>{}, IntC<1>{});
-            if (!do_shrink) load_more_tiles();
-        }
-        if (prof && tid == 0 && first_item) { prof[1] = wall_clock64(); prof[7] = cnt + 100 * (do_shrink ? 1 : 0) + 1000 * (do_expand ? 1 : 0); }
+        if (do_expand && !kTilesBehindShrink) load_tile(out0, IntC<0>{}, IntC<1>{});
+        if (prof && tid == 0 && first_item) { prof[1] = wall_clock64(); prof[7] = cnt + 1000 * (do_expand ? 1 : 0); }
 
         // ---- shrink over this item's range of d_in ----
-        float own = 0.f;
-        if (do_shrink) own = shrink_units(u_lo, u_hi, do_expand);
+        const float own = shrink_units(0, U, do_expand);
         if (prof && tid == 0 && first_item) prof[2] = wall_clock64();
         const int hc = tid / RP, hj = tid % RP;                   // this thread's element of h (tid < kChunk * RP)
         const bool h_thread = tid < kChunk * RP && hc < cnt;
-        if (!xitem) {
-            if (tid < kChunk * RP) hs[hc][hj] = own * scale;
-            if constexpr (HMODE) if (h_only) {
-                // weighted, scaled h of row hc as a bf16 head (truncated) and tail (rounded) in one word:
-                // 16 bits of it reach the matrix cores of the second launch; rows of an empty slot are skipped there too
-                if (h_thread && rank > 0) {
-                    const float f = own * scale * (hc == 0 ? wrow[0] : (hc == 1 ? wrow[1] : (hc == 2 ? wrow[2] : wrow[3])));
-                    const int hrow = hc == 0 ? row[0] : (hc == 1 ? row[1] : (hc == 2 ? row[2] : row[3]));
-                    const uint32_t hi = __float_as_uint(f) & 0xffff0000u;
-                    a.h_out[(int64_t)hrow * RP + hj] = (hi >> 16) | (f2bf(f - __uint_as_float(hi)) << 16);
-                }
-            }
-            __syncthreads();
-        } else {
-            uint64_t *xw = a.xch + ((int64_t)(chunk * a.ksplit) * kChunk + hc) * RP + hj;   // + k * kChunk * RP: slice k
-            if (do_shrink && h_thread) xch_put(xw + (int64_t)kslice * kChunk * RP, own, tag);
-            if (do_expand) {
-                // ---- the partial sums of every k-slice, added in slice order ----
-                // The workgroups that produce them belong to this launch and publish before they wait
-                // for anything, so they arrive within microseconds when those workgroups are running.
-                // Should one not be running yet (more live items than the GPU holds at once), the
-                // bounded wait ends and this workgroup starts the item again on its own.
-                float s = 0.f;
-                bool gave_up = false;
-                if (h_thread) {
-                    for (int k0 = 0; k0 < a.ksplit; k0 += 4) {    // four words in flight at a time
-                        uint64_t wv[4];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            if (k0 + k < a.ksplit) wv[k] = xch_get(xw + (int64_t)(k0 + k) * kChunk * RP);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            if (k0 + k < a.ksplit) {
-                                if (do_shrink && k0 + k == kslice) { s += own; continue; }
-                                int spins = 0;
-                                while ((uint32_t)(wv[k] >> 32) != tag) {
-                                    if (++spins > a.poll_limit) { gave_up = true; break; }
-                                    __builtin_amdgcn_s_sleep(1);
-                                    wv[k] = xch_get(xw + (int64_t)(k0 + k) * kChunk * RP);
-                                }
-                                s += __uint_as_float((uint32_t)wv[k]);
-                            }
-                        }
-                    }
-                    if (gave_up) atomicOr(&s_missing, 1u);
-                }
-                __syncthreads();
-                if (s_missing) {                                  // rare
-                    __syncthreads();
-                    if (tid == 0) s_missing = 0;                  // next use is behind the shrink's barriers
-                    solo_next = true; first_item = false;
-                    item -= n_wg;
-                    continue;
-                }
-                if (tid < kChunk * RP) hs[hc][hj] = s * scale;
-                __syncthreads();
+        if (tid < kChunk * RP) hs[hc][hj] = own * scale;
+        if constexpr (HMODE) if (h_only) {
+            // weighted, scaled h of row hc as a bf16 head (truncated) and tail (rounded) in one word:
+            // 16 bits of it reach the matrix cores of the second launch; rows of an empty slot are skipped there too
+            if (h_thread && rank > 0) {
+                const float f = own * scale * (hc == 0 ? wrow[0] : (hc == 1 ? wrow[1] : (hc == 2 ? wrow[2] : wrow[3])));
+                const int hrow = hc == 0 ? row[0] : (hc == 1 ? row[1] : (hc == 2 ? row[2] : row[3]));
+                const uint32_t hi = __float_as_uint(f) & 0xffff0000u;
+                a.h_out[(int64_t)hrow * RP + hj] = (hi >> 16) | (f2bf(f - __uint_as_float(hi)) << 16);
             }
         }
+        __syncthreads();
         if (prof && tid == 0 && first_item) prof[3] = wall_clock64();
 
         // ---- expand + in-place add ----
@@ -607,30 +502,20 @@ __device__ __forceinline__ void rows_body(const RowsArgs &a, const int wg, const
         if (prof && tid == 0 && first_item) prof[4] = wall_clock64();
         first_item = false;
     }
-
-    // ---- tag bookkeeping ----
-    if (use_x) {
-        if (first_item && tid == 0) tag_sign_in(a.ctrl, wg, tag);   // a workgroup without items still signs in
-        if (wg == n_wg - 1 && w == 0) {
-            if (!first_item) tag = s_tag;
-            else tag = __shfl(tag, 0, 64);
-            if (tag != kTagPoison) tag_advance(a.ctrl, n_wg, tag, lane);
-        }
-    }
 }
 
 // Waves per SIMD the kernels are compiled for (the register budget follows): 4 for the 8-wave kernels
-// of ranks up to 16, and 5 for the 4-wave rank-8 kernel without exchange -- the packed MoE launches,
+// of ranks up to 16, and 5 for the 4-wave rank-8 kernel -- the packed MoE launches,
 // which stream at the memory system's rate and gained 3.6 % from the fifth workgroup per CU (94
 // registers, no spills; compiled for 6 it spills and takes 40 % longer).
-template <int RP, int NW, bool XCH>
-constexpr int rows_waves_per_simd() { return (NW >= 8 && RP <= 16) ? 4 : ((NW == 4 && RP == 8 && !XCH) ? 5 : 1); }
+template <int RP, int NW>
+constexpr int rows_waves_per_simd() { return (NW >= 8 && RP <= 16) ? 4 : ((NW == 4 && RP == 8) ? 5 : 1); }
 
-template <int RP, int NW, bool XCH>
-__global__ __launch_bounds__(NW * 64, (rows_waves_per_simd<RP, NW, XCH>()))
+template <int RP, int NW>
+__global__ __launch_bounds__(NW * 64, (rows_waves_per_simd<RP, NW>()))
 void rows_kernel(const RowsArgs a)
 {
-    rows_body<RP, NW, XCH>(a, (int)blockIdx.x, (int)gridDim.x);
+    rows_body<RP, NW>(a, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // The launch without a plan: item i is row i (rank 1 and 2).
@@ -638,7 +523,7 @@ template <int RP, int NW>
 __global__ __launch_bounds__(NW * 64, NW >= 8 ? 4 : 1)
 void rows_items_kernel(const RowsArgs a)
 {
-    rows_body<RP, NW, false, true>(a, (int)blockIdx.x, (int)gridDim.x);
+    rows_body<RP, NW, true>(a, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // Several sites that share a batch plan in one launch (q/k/v of one layer, or gate/up): site s owns
@@ -649,15 +534,15 @@ struct MultiArgs {
     RowsArgs site[kMaxMulti];
 };
 
-template <int RP, int NW, bool XCH, int RUN = 3>
-__global__ __launch_bounds__(NW * 64, (rows_waves_per_simd<RP, NW, XCH>()))
+template <int RP, int NW, int RUN = 3>
+__global__ __launch_bounds__(NW * 64, (rows_waves_per_simd<RP, NW>()))
 void rows_multi_kernel(const MultiArgs m)
 {
     const int b = (int)blockIdx.x;
     int s = 0;
 #pragma unroll
     for (int k = 1; k < kMaxMulti; ++k) s += (k < m.n && b >= m.first[k]) ? 1 : 0;
-    rows_body<RP, NW, XCH, false, RUN>(m.site[s], b - m.first[s], m.first[s + 1] - m.first[s]);
+    rows_body<RP, NW, false, RUN>(m.site[s], b - m.first[s], m.first[s + 1] - m.first[s]);
 }
 
 // The first launch of a decode step can plan for itself: every workgroup sorts the batch's
@@ -673,8 +558,8 @@ struct PlanLocalArgs {
     PlanView pv;
 };
 
-template <int RP, int NW, bool XCH>
-__global__ __launch_bounds__(NW * 64, (rows_waves_per_simd<RP, NW, XCH>()))
+template <int RP, int NW>
+__global__ __launch_bounds__(NW * 64, (rows_waves_per_simd<RP, NW>()))
 void rows_multi_plan_kernel(const MultiArgs m, const PlanLocalArgs pl)
 {
     __shared__ PlanLocalLds p_lds;
@@ -685,17 +570,17 @@ void rows_multi_plan_kernel(const MultiArgs m, const PlanLocalArgs pl)
     int s = 0;
 #pragma unroll
     for (int k = 1; k < kMaxMulti; ++k) s += (k < m.n && b >= m.first[k]) ? 1 : 0;
-    rows_body<RP, NW, XCH>(m.site[s], b - m.first[s], m.first[s + 1] - m.first[s], p_rec);
+    rows_body<RP, NW>(m.site[s], b - m.first[s], m.first[s + 1] - m.first[s], p_rec);
 }
 
-template <int RP, int NW, bool XCH>
+template <int RP, int NW>
 static int rows_capacity()
 {
     static int cap = 0;
     if (cap == 0) {
         int per_cu = 0, cus = 0, dev = 0;
         if (hipGetDevice(&dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rows_kernel<RP, NW, XCH>, NW * 64, 0) != hipSuccess) return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rows_kernel<RP, NW>, NW * 64, 0) != hipSuccess) return 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
         cap = per_cu * cus;
     }
@@ -709,41 +594,17 @@ static double chunk_bytes(const RowsArgs &a)
     return 2.0 * a.d_in * (a.r_pad + kChunk) + (double)a.d_out * (2.0 * a.r_pad + 4.0 * kChunk);
 }
 
-static bool can_exchange(const RowsArgs &a)
-{
-    return a.xch && a.ctrl && a.n_experts == 1 && a.grid_chunks <= a.xch_chunks;
-}
-
 // Cuts a chunk of a dense site into `parts` items.  A CU pulls only so many bytes per microsecond,
 // so a launch with fewer chunks than the GPU has CUs spreads each chunk over several workgroups:
-// part p expands outputs [p * out_per_part, ...) and, where the site has an exchange area, shrinks
-// k-slice p of d_in and trades the partial sums with the other parts of its chunk (no adapter byte
-// is read twice); without an exchange area every part redoes the whole shrink.
-static void set_parts(RowsArgs &a, int parts, bool exchange)
+// part p expands outputs [p * out_per_part, ...); every part redoes the whole shrink.
+static void set_parts(RowsArgs &a, int parts)
 {
-    const int U = a.d_in >> 3;
     const int groups = (a.d_out + 63) / 64;
-    if (exchange) {
-        if (parts > 8) parts = 8;
-        if (parts * a.r_pad > 128) parts = 128 / a.r_pad;
-    }
     if (parts > groups) parts = groups;
     if (parts < 1 || a.n_experts != 1 || a.h_out) parts = 1;       // (a launch that only shrinks has no outputs to divide)
     const int gpp = (groups + parts - 1) / parts;
     a.out_per_part = gpp * 64;
     a.tile_par = (groups + gpp - 1) / gpp;
-    a.mode = 0; a.ksplit = 1; a.kslice_units = U;
-    // "rows_poll_limit" (testing): a negative value makes every reader give up at once, so that each
-    // item runs the path that does not depend on other workgroups
-    const int pl = tuning(kRowsPollLimit);
-    a.poll_limit = pl < 0 ? 0 : (pl > 0 ? pl : kPollLimit);
-    if (exchange && a.tile_par > 1) {
-        int ku = (U + a.tile_par - 1) / a.tile_par;
-        ku = (ku + 63) & ~63;
-        a.mode = 2;
-        a.kslice_units = ku;
-        a.ksplit = (U + ku - 1) / ku;
-    }
 }
 
 static int fused_grid(const RowsArgs &a, int run_log2 = 3)
@@ -759,7 +620,7 @@ static int use_rank_bound(const RowsArgs &a, int cap)
 {
     const int t = tuning(kRowsRankBound);
     if (t) return t > 0 ? 1 : 0;
-    return a.rank_bound && a.mode != 2 && (int64_t)a.grid_chunks * 2 >= cap;
+    return a.rank_bound && (int64_t)a.grid_chunks * 2 >= cap;
 }
 
 static int items_target(int cap)
@@ -773,17 +634,15 @@ static int items_target(int cap)
 template <int RP, int NW>
 static hipError_t launch_rp(RowsArgs a, hipStream_t st)
 {
-    const int mode = tuning(kRowsMode);     // 0 auto, 1 parts that redo the shrink, 3 one item per chunk
-    const int cap = rows_capacity<RP, NW, true>();
+    const int mode = tuning(kRowsMode);     // 0 auto, 1 parts, 3 one item per chunk
+    const int cap = rows_capacity<RP, NW>();
     if (cap <= 0) return hipErrorUnknown;
-    const bool exchange = can_exchange(a) && mode == 0 && !a.row_slot;
-    set_parts(a, mode == 3 ? 1 : items_target(cap) / a.grid_chunks, exchange);
+    set_parts(a, mode == 3 ? 1 : items_target(cap) / a.grid_chunks);
     a.rank_bound = use_rank_bound(a, cap);
     if (a.row_slot) {
         if constexpr (RP <= 2) rows_items_kernel<RP, NW><<<dim3((unsigned)fused_grid(a)), dim3(NW * 64), 0, st>>>(a);
         else return hipErrorInvalidValue;
-    } else if (a.mode == 2) rows_kernel<RP, NW, true><<<dim3((unsigned)fused_grid(a)), dim3(NW * 64), 0, st>>>(a);
-    else rows_kernel<RP, NW, false><<<dim3((unsigned)fused_grid(a)), dim3(NW * 64), 0, st>>>(a);
+    } else rows_kernel<RP, NW><<<dim3((unsigned)fused_grid(a)), dim3(NW * 64), 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -802,23 +661,20 @@ static hipError_t launch_nw(const RowsArgs &a, hipStream_t st)
 template <int RP, int NW>
 static hipError_t launch_multi_rp(const RowsArgs *sites, int n, hipStream_t st, const PlanLocalArgs *pl = nullptr)
 {
-    const int cap = rows_capacity<RP, NW, true>();
+    const int cap = rows_capacity<RP, NW>();
     if (cap <= 0) return hipErrorUnknown;
     MultiArgs m;
     m.n = n;
     m.first[0] = 0;
     // every item of the launch should move about the same number of bytes
     double total = 0.0;
-    bool exchange = tuning(kRowsMode) == 0;
-    for (int k = 0; k < n; ++k) { total += chunk_bytes(sites[k]); exchange = exchange && can_exchange(sites[k]); }
+    for (int k = 0; k < n; ++k) total += chunk_bytes(sites[k]);
     const double per_item = total * sites[0].grid_chunks / items_target(cap);
-    bool any_x = false;
     for (int k = 0; k < n; ++k) {
         m.site[k] = sites[k];
         // (one site alone gets the parts its own launch would get, so that the results are the same bits)
-        set_parts(m.site[k], n == 1 ? items_target(cap) / sites[0].grid_chunks : (int)(chunk_bytes(sites[k]) / per_item + 0.5), exchange);
+        set_parts(m.site[k], n == 1 ? items_target(cap) / sites[0].grid_chunks : (int)(chunk_bytes(sites[k]) / per_item + 0.5));
         m.site[k].rank_bound = use_rank_bound(m.site[k], cap);
-        any_x = any_x || m.site[k].mode == 2;
         m.first[k + 1] = m.first[k] + fused_grid(m.site[k]);
     }
     // "rows_chunk_run" = 256 (measurements; the rank-8 four-wave launch without parts, i.e. the packed MoE
@@ -827,7 +683,7 @@ static hipError_t launch_multi_rp(const RowsArgs *sites, int n, hipStream_t st, 
     constexpr int kLongRun = 8;
     bool long_run = false;
     if constexpr (RP == 8 && NW == 4) {
-        if (!any_x && !pl && tuning(kRowsChunkRun) == (1 << kLongRun)) {
+        if (!pl && tuning(kRowsChunkRun) == (1 << kLongRun)) {
             long_run = true;
             for (int k = 0; k < n; ++k) long_run = long_run && m.site[k].tile_par == 1;
             if (long_run)
@@ -837,20 +693,18 @@ static hipError_t launch_multi_rp(const RowsArgs *sites, int n, hipStream_t st, 
     for (int k = n; k < kMaxMulti; ++k) { m.site[k] = m.site[0]; m.first[k + 1] = m.first[n]; }
     if constexpr (NW == 8) {
         if (pl) {
-            if (any_x) rows_multi_plan_kernel<RP, NW, true><<<dim3((unsigned)m.first[n]), dim3(NW * 64), 0, st>>>(m, *pl);
-            else rows_multi_plan_kernel<RP, NW, false><<<dim3((unsigned)m.first[n]), dim3(NW * 64), 0, st>>>(m, *pl);
+            rows_multi_plan_kernel<RP, NW><<<dim3((unsigned)m.first[n]), dim3(NW * 64), 0, st>>>(m, *pl);
             return hipGetLastError();
         }
     }
     if (pl) return hipErrorInvalidValue;
     if constexpr (RP == 8 && NW == 4) {
         if (long_run) {
-            rows_multi_kernel<RP, NW, false, kLongRun><<<dim3((unsigned)m.first[n]), dim3(NW * 64), 0, st>>>(m);
+            rows_multi_kernel<RP, NW, kLongRun><<<dim3((unsigned)m.first[n]), dim3(NW * 64), 0, st>>>(m);
             return hipGetLastError();
         }
     }
-    if (any_x) rows_multi_kernel<RP, NW, true><<<dim3((unsigned)m.first[n]), dim3(NW * 64), 0, st>>>(m);
-    else rows_multi_kernel<RP, NW, false><<<dim3((unsigned)m.first[n]), dim3(NW * 64), 0, st>>>(m);
+    rows_multi_kernel<RP, NW><<<dim3((unsigned)m.first[n]), dim3(NW * 64), 0, st>>>(m);
     return hipGetLastError();
 }
 

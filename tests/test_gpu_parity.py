@@ -471,6 +471,82 @@ def test_tiny_rank_rows_without_a_plan(M, oracle, r):
     check_dense(M, oracle, c, lambda y0: run_decode(M, site, c, y0), rows=rows)
 
 
+@pytest.mark.parametrize("q", [8, 16])
+@pytest.mark.parametrize("r,d_in,d_out", [(4, 136, 72), (12, 72, 584), (16, 4160, 264), (32, 2056, 1096), (64, 1032, 520), (8, 9728, 64)])
+def test_decode_tiles(M, oracle, r, d_in, d_out, q):
+    """Decode in tiles: slots with 1, q - 1, q, q + 1 and 2 q rows, rows without adapter, an empty slot, true ranks
+    below the padded one; d_in with a partial step, fewer steps than waves, and long enough for parts that
+    divide it and trade sums; d_out with fewer blocks than waves and a ragged last one.  One part per tile, the
+    launch's own choice, many parts, and parts whose partners never answer: all to the oracle, the first two
+    in the same bits where nothing is traded."""
+    slots = np.concatenate([np.full(n, k) for k, n in enumerate([1, q - 1, q, q + 1, 2 * q, 3])] + [np.full(4, -1)]).astype(np.int32)
+    slots = W.rng(r + q).permutation(slots).astype(np.int32)
+    c = W.dense_case("tiles", 3500 + r + q, len(slots), d_in, d_out, 6, r, 2.0 * r, ranks=[r, max(1, r - 3), r, r, r, 0],
+                     token_slot=slots, std_a=0.05, std_b=0.05)
+    site = dense_site(M, c)
+    outs = []
+    for knobs in ({"tile_parts": 1}, {}, {"tile_parts": 5}, {"tile_parts": 3, "rows_poll_limit": -1}):
+        for name, v in {"tile_rows": q, **knobs}.items():
+            M.set_tuning(name, v)
+        try:
+            check_dense(M, oracle, c, lambda y0: run_decode(M, site, c, y0))
+            check_dense(M, oracle, c, lambda y0: run_decode(M, site, c, y0, planned=True))
+            outs.append(run_decode(M, site, c, c.y0))
+        finally:
+            for name in ("tile_rows", "tile_parts", "rows_poll_limit"):
+                M.set_tuning(name, 0)
+    if max(8, 1 << (r - 1).bit_length()) * d_in < 65536:           # nothing is traded: parts do not change the sums
+        assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+    site.check()
+
+
+def _plan_tiles(plan, max_items, n_keys):
+    """The tile records of a plan buffer (behind everything else, 16-byte aligned)."""
+    chunks = (max_items + 3 * min(n_keys, max_items)) // 4
+    big = 2 * (-(-max_items // 1024) + 1) * n_keys if (max_items > 32768 or n_keys > 4096) and n_keys <= 16384 else 0
+    off = 8 + 3 * (n_keys + 1) + 4 * max_items + 8 * chunks + 64 + 8 + 2 * (n_keys + 1) + 4 * max_items + big
+    return plan.buf.view(torch.int32)[-(-off // 4) * 4:][:4 * chunks].cpu().numpy().reshape(-1, 4)
+
+
+@pytest.mark.parametrize("T,S,q", [(1, 1, 8), (64, 3, 8), (65, 64, 8), (256, 64, 8), (257, 64, 16), (1000, 7, 8), (1024, 4096, 8), (1024, 4097, 16),
+                                   (1025, 64, 16), (4000, 300, 8), (33000, 20, 16), (2000, 5000, 8)])
+def test_plan_tile_records(M, T, S, q):
+    """The planners (inside a launch, counting, sorting, one launch for large batches, three launches) leave the
+    same grouping and tiles: {slot, rows, first position} for every run of up to q rows of a slot, then zeros."""
+    slots = W.rng(7 * T + S).integers(-1, S, size=T).astype(np.int32)
+    if T > 60:
+        slots[10:40] = min(2, S - 1)                   # a crowded slot
+    ts = torch.from_numpy(slots).cuda()
+    order = np.concatenate([np.nonzero(slots == s)[0] for s in np.unique(slots[slots >= 0])]) if (slots >= 0).any() else np.zeros(0, int)
+    want, pos = [], 0
+    for s in np.unique(slots[slots >= 0]):
+        n = int((slots == s).sum())
+        want += [(s, min(q, n - r), pos + r) for r in range(0, n, q)]
+        pos += n
+    bound = (T + (q - 1) * min(S, T)) // q
+    assert len(want) <= bound
+    plan = M.Plan(T, S)
+    site = M.Site(64, 64, 16, S)
+    x, y = (torch.zeros((T, 64), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    M.set_tuning("tile_rows", q)
+    try:
+        for fused in ((False, True) if T <= 256 and S <= 1024 else (False,)):
+            plan.buf.fill_(0x5A)
+            plan.buf[:4 * (8 + 3 * (S + 1))].zero_()
+            if fused:
+                M.lora_plan_apply_decode_multi([site], plan, ts, S, [x], [y])
+            else:
+                M.lora_plan_decode(plan, ts, S)
+            torch.cuda.synchronize()
+            hdr, srt, _ = _plan_words(plan, T, S)
+            assert int(hdr[1]) == len(order) and np.array_equal(srt[:len(order)], order)
+            rec = _plan_tiles(plan, T, S)[:bound]
+            assert np.array_equal(rec[:len(want), :3], np.array(want, dtype=np.int32).reshape(-1, 3))
+            assert np.all(rec[len(want):, 1] == 0)
+    finally:
+        M.set_tuning("tile_rows", 0)
+
+
 def test_graph_replay_keeps_results_right(M, oracle):
     """A captured graph replays the same kernel arguments; the launches that exchange partial
     results between workgroups must still tell one replay from the next.  Inputs change between
