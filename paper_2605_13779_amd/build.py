@@ -6,7 +6,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmlora.so")
-SOURCES = ["api.hip", "plan.hip", "rows.hip", "tile.hip", "seg_mfma.hip", "moe_down.hip", "resident.hip"]
+SOURCES = ["api.hip", "plan.hip", "rows.hip", "tile_seg.hip", "tile_multi.hip", "tile_moe.hip", "seg_mfma.hip", "moe_down.hip", "resident.hip"]
 # packed-fp32 VALU forms are switched off for all device code: hipcc forms them by itself from plain
 # float code and some of those forms have given wrong results on this hardware
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
@@ -21,7 +21,7 @@ def _compile(src: str) -> str:
 
 
 def build(verbose: bool = False) -> str:
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=6) as ex:
         objs = list(ex.map(_compile, SOURCES))
     subprocess.run(["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB, *objs], check=True)
     if verbose:
@@ -46,7 +46,7 @@ def build_sanitized(outdir: str) -> str:
         obj = os.path.join(outdir, src.replace(".hip", ".o"))
         subprocess.run(["hipcc", *flags, "-c", os.path.join(CSRC, src), "-o", obj], check=True, stderr=subprocess.PIPE)
         return obj
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=6) as ex:
         objs = list(ex.map(one, SOURCES))
     lib = os.path.join(outdir, "libmlora_san.so")
     subprocess.run(["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-fsanitize=address", "-fsanitize=undefined",

@@ -133,6 +133,7 @@ struct TileArgs {
     const int32_t *tiles;    // records (see PlanView)
     const int32_t *sorted;
     int32_t top_k;           // x row = item / top_k
+    int32_t one_tile;        // most groups are one tile
     int32_t parts;           // workgroups per tile: part p expands blocks [p * part_blocks, ...) of 64 outputs
     int32_t part_blocks;
     // parts that also divide d_in trade their partial sums (see the exchange below); null: every part sums alone
@@ -142,6 +143,7 @@ struct TileArgs {
 };
 int tile_max_rows();
 hipError_t launch_tile_seg(const TileArgs &a, const uint32_t *inl, hipStream_t st);
+hipError_t launch_tile_moe(const TileArgs *sites, int n, hipStream_t st);
 hipError_t launch_tile_multi(const TileArgs *sites, int n, hipStream_t st);
 hipError_t launch_tile_multi_plan(const TileArgs *sites, int n, const PlanView &pv, const int32_t *token_slot, int T,
                                   int n_slots, const int32_t *ready_rank, hipStream_t st);
@@ -221,7 +223,7 @@ int seg_expand_capacity();
 enum Knob {
     kRowsPollLimit, kRowsRankBound, kRowsItemsTarget, kRowsMode, kRowsWaves, kPlanGeneral, kPlanSeparate,
     kPlanPipeline, kSegExpandGroups, kSegTableCopy, kSegShrinkWgs, kSegTiles, kSegOverlap, kUploadPieceKb, kSegFused,
-    kRowsChunkRun, kTileRows, kTileParts, kKnobCount
+    kRowsChunkRun, kTileRows, kTileParts, kTileMoeRows, kKnobCount
 };
 int tuning(Knob k);             // api.hip
 #ifdef MLORA_PROF

@@ -1,0 +1,98 @@
+// Prefill in tiles (see tile_body.h): the batch's segments, cut into tiles of up to 48 rows.
+#include "tile_body.h"
+
+namespace mlora {
+
+// The tile's segment: segs holds, per segment, its first tile, first row, rows and slot.
+template <int TM>
+__device__ __forceinline__ bool tile_from_segments(const TileArgs &a, const uint32_t *segs, int tile, int lane, TileRows<TM> &t)
+{
+    int first = 0, row0 = 0, rows = 0, slot = -1;
+    for (int s0 = 0; s0 < a.n_segs; s0 += 64) {
+        const int si = s0 + lane;
+        int4 v = make_int4(0x7fffffff, 0, 0, 0);
+        if (si < a.n_segs) v = ((const int4 *)segs)[si];
+        const uint64_t hit = __ballot(v.x <= tile);          // segments in tile order: the last one that starts at or before it
+        if (hit) {
+            const int l = 63 - __builtin_clzll(hit);
+            first = __shfl(v.x, l, 64); row0 = __shfl(v.y, l, 64); rows = __shfl(v.z, l, 64); slot = __shfl(v.w, l, 64);
+        }
+        if (hit != ~0ull) break;
+    }
+    first = __builtin_amdgcn_readfirstlane(first); row0 = __builtin_amdgcn_readfirstlane(row0);
+    rows = __builtin_amdgcn_readfirstlane(rows);
+    t.key = __builtin_amdgcn_readfirstlane(slot);
+    const int r0 = (tile - first) * a.tile_rows;
+    t.cnt = min(a.tile_rows, rows - r0);
+    if (t.cnt <= 0) return false;
+#pragma unroll
+    for (int g = 0; g < TM / 8; ++g) {
+        t.xrow[g] = row0 + r0 + min(8 * g + ((lane >> 1) & 7), t.cnt - 1);
+        t.yrow[g] = row0 + r0 + min(8 * g + (lane >> 3), t.cnt - 1);
+    }
+    return true;
+}
+
+struct TileSegInline { uint32_t w[kTileInline]; };
+
+template <int RP, int NW, int TM, int CP = 0>
+__global__ __launch_bounds__(NW * 64, 2)
+void tile_seg_kernel(const TileArgs a, const TileSegInline inl)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char lds[TileCfg<RP, NW, TM>::LDS];
+    // an XCD gets a contiguous range of tiles (workgroups are dealt round-robin): neighbours share an adapter, in its L2
+    const int n8 = (int)gridDim.x >> 3, tile = ((int)blockIdx.x & 7) * n8 + ((int)blockIdx.x >> 3);
+    if (tile >= a.n_tiles) return;
+    TileRows<TM> t;
+    if (!tile_from_segments<TM>(a, a.segs ? (const uint32_t *)a.segs : inl.w, tile, (int)threadIdx.x & 63, t)) return;
+    tile_body<RP, NW, TM, false, 1, CP>(a, a, t, lds, 0, (a.d_out + 63) >> 6);
+}
+
+template <int RP>
+static hipError_t launch_tile_seg_rp(const TileArgs &a, const uint32_t *inl, hipStream_t st)
+{
+    TileSegInline table;
+    if (!a.segs) for (int i = 0; i < 4 * a.n_segs; ++i) table.w[i] = inl[i];
+    const dim3 grid((unsigned)((a.n_tiles + 7) / 8 * 8)), block(512);
+    // (8192 rows, 2560 -> 9728 at rank 16: 81.1 -> 73.7 us with y streamed; 2560 -> 2560: 25.7 -> 26.6)
+    const bool stream = (int64_t)a.n_tiles * a.tile_rows * a.d_out * 2 >= (96 << 20);
+    if constexpr (RP >= 8) if (stream) switch ((a.tile_rows + 7) / 8) {
+        case 1: break;
+        case 2: tile_seg_kernel<RP, 8, 16, kStreamY><<<grid, block, 0, st>>>(a, table); return hipGetLastError();
+        case 3: tile_seg_kernel<RP, 8, 24, kStreamY><<<grid, block, 0, st>>>(a, table); return hipGetLastError();
+        case 4: tile_seg_kernel<RP, 8, 32, kStreamY><<<grid, block, 0, st>>>(a, table); return hipGetLastError();
+        case 5: tile_seg_kernel<RP, 8, 40, kStreamY><<<grid, block, 0, st>>>(a, table); return hipGetLastError();
+        case 6: tile_seg_kernel<RP, 8, 48, kStreamY><<<grid, block, 0, st>>>(a, table); return hipGetLastError();
+        default: return hipErrorInvalidValue;
+    }
+    switch ((a.tile_rows + 7) / 8) {
+        case 1: tile_seg_kernel<RP, 8, 8><<<grid, block, 0, st>>>(a, table); break;
+        case 2: tile_seg_kernel<RP, 8, 16><<<grid, block, 0, st>>>(a, table); break;
+        case 3: tile_seg_kernel<RP, 8, 24><<<grid, block, 0, st>>>(a, table); break;
+        case 4: tile_seg_kernel<RP, 8, 32><<<grid, block, 0, st>>>(a, table); break;
+        case 5: tile_seg_kernel<RP, 8, 40><<<grid, block, 0, st>>>(a, table); break;
+        case 6: tile_seg_kernel<RP, 8, 48><<<grid, block, 0, st>>>(a, table); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+int tile_max_rows() { return 48; }
+
+hipError_t launch_tile_seg(const TileArgs &a, const uint32_t *inl, hipStream_t st)
+{
+    if (a.n_tiles <= 0) return hipSuccess;
+    if (a.tile_rows < 1 || a.tile_rows > tile_max_rows() || (!a.segs && 4 * a.n_segs > kTileInline)) return hipErrorInvalidValue;
+    switch (a.r_pad) {
+        case 1:  return launch_tile_seg_rp<1>(a, inl, st);
+        case 2:  return launch_tile_seg_rp<2>(a, inl, st);
+        case 4:  return launch_tile_seg_rp<4>(a, inl, st);
+        case 8:  return launch_tile_seg_rp<8>(a, inl, st);
+        case 16: return launch_tile_seg_rp<16>(a, inl, st);
+        case 32: return launch_tile_seg_rp<32>(a, inl, st);
+        case 64: return launch_tile_seg_rp<64>(a, inl, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace mlora
