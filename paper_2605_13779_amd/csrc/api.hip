@@ -605,24 +605,36 @@ int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int6
         if (count(q) <= rounds * cus) hi = q; else lo = q + 1;
     }
     a.tile_rows = lo;
+    // A table that the site's device area does not hold goes there in pieces, one copy + one launch each (the
+    // stream orders a piece's copy behind the launch that read the piece before it).
+    const size_t piece = (size_t)s->seg_cap * 3 / 4 * 4;
     std::vector<int32_t> tab;
-    tab.reserve((size_t)live * 4);
+    tab.reserve(std::min((size_t)live * 4, piece));
     int64_t tiles = 0;
+    auto flush = [&]() -> int32_t {
+        if (tab.empty()) return MLORA_OK;
+        a.n_segs = (int32_t)(tab.size() / 4);
+        a.n_tiles = (int32_t)tiles;
+        a.segs = nullptr;
+        if (tab.size() > (size_t)kTileInline || tuning(kSegTableCopy)) {
+            const int32_t rc = stage_table(s, tab, st);
+            if (rc) return rc;
+            a.segs = s->seg_dev;
+        }
+        const hipError_t e = launch_tile_seg(a, (const uint32_t *)tab.data(), st);
+        tab.clear();
+        tiles = 0;
+        return ok(e) ? MLORA_OK : MLORA_E_HIP;
+    };
     for (int32_t k = 0; k < S; ++k) {
         const int32_t rows = seg_off[k + 1] - seg_off[k];
         if (seg_slot[k] < 0 || rows == 0) continue;
+        if (tab.size() == piece)
+            if (const int32_t rc = flush()) return rc;
         tab.push_back((int32_t)tiles); tab.push_back(seg_off[k]); tab.push_back(rows); tab.push_back(seg_slot[k]);
         tiles += (rows + a.tile_rows - 1) / a.tile_rows;
     }
-    a.n_segs = live;
-    a.n_tiles = (int32_t)tiles;
-    if (tab.size() > (size_t)kTileInline || tuning(kSegTableCopy)) {
-        if (tab.size() > (size_t)s->seg_cap * 3) return MLORA_E_UNSUPPORTED;
-        int32_t rc = stage_table(s, tab, st);
-        if (rc) return rc;
-        a.segs = s->seg_dev;
-    }
-    return ok(launch_tile_seg(a, (const uint32_t *)tab.data(), st)) ? MLORA_OK : MLORA_E_HIP;
+    return flush();
 }
 
 }  // namespace

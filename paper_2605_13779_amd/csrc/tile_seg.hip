@@ -3,21 +3,25 @@
 
 namespace mlora {
 
-// The tile's segment: segs holds, per segment, its first tile, first row, rows and slot.
+// The tile's segment: segs holds, per segment, its first tile, first row, rows and slot, in tile order.  The wave
+// looks for the last segment that starts at or before the tile, 64 of them at equal distances at a time: one
+// round trip for up to 64 segments, two for 4096 (walking the table takes one for every 64 of them).
 template <int TM>
 __device__ __forceinline__ bool tile_from_segments(const TileArgs &a, const uint32_t *segs, int tile, int lane, TileRows<TM> &t)
 {
     int first = 0, row0 = 0, rows = 0, slot = -1;
-    for (int s0 = 0; s0 < a.n_segs; s0 += 64) {
-        const int si = s0 + lane;
+    for (int lo = 0, len = a.n_segs;;) {
+        const int step = (len + 63) >> 6, at = lane * step;
         int4 v = make_int4(0x7fffffff, 0, 0, 0);
-        if (si < a.n_segs) v = ((const int4 *)segs)[si];
-        const uint64_t hit = __ballot(v.x <= tile);          // segments in tile order: the last one that starts at or before it
-        if (hit) {
-            const int l = 63 - __builtin_clzll(hit);
+        if (at < len) v = ((const int4 *)segs)[lo + at];
+        const uint64_t hit = __ballot(v.x <= tile);          // (lane 0 always: segment lo starts at or before the tile)
+        const int l = hit ? 63 - __builtin_clzll(hit) : 0;
+        if (step <= 1) {
             first = __shfl(v.x, l, 64); row0 = __shfl(v.y, l, 64); rows = __shfl(v.z, l, 64); slot = __shfl(v.w, l, 64);
+            break;
         }
-        if (hit != ~0ull) break;
+        lo += l * step;
+        len = min(step, len - l * step);
     }
     first = __builtin_amdgcn_readfirstlane(first); row0 = __builtin_amdgcn_readfirstlane(row0);
     rows = __builtin_amdgcn_readfirstlane(rows);

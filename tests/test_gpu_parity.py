@@ -901,6 +901,21 @@ def test_segmented_tiles(M, oracle, rows, r, d_in, d_out):
         M.set_tuning("seg_tiles", 0)
 
 
+@pytest.mark.parametrize("n", [80, 82, 5120, 5122, 62000])
+def test_segmented_many_short_runs(M, oracle, n):
+    """Runs of one to three rows, four in five with an adapter: 64 and 65 segments (one look at the table or two),
+    4096 and some more (two or three), and more than the site's device area holds (49152), which go in pieces."""
+    lens = np.random.default_rng(n).integers(1, 4, size=n)
+    seg_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    seg_slot = (np.arange(n) % 5 - 1).astype(np.int32)
+    c = W.seg_case("runs", 5300 + n, int(seg_off[-1]), n, 64, 72, 4, 8, 16.0, ranks=[8, 5, 0, 8],
+                   seg_off=seg_off, seg_slot=seg_slot, std_a=0.05, std_b=0.05)
+    site = dense_site(M, c)
+    last = np.arange(max(0, c.T - 100), c.T)
+    sel = np.unique(np.concatenate([np.random.default_rng(1).permutation(c.T)[:400], np.arange(min(100, c.T)), last]))
+    check_dense(M, oracle, c, lambda y0: run_seg(M, site, c, y0), rows=sel)
+
+
 @pytest.mark.parametrize("which", ["small", "batches", "in_flight", "one_launch", "graph", "random"])
 def test_rank_64_shrink_and_expand_halves_on_narrow_sites(M, oracle, which):
     """Narrow rank-64 sites take the tile kernel by themselves; the two halves still have to be right there."""
