@@ -264,7 +264,8 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, const TileArgs &b2,
         s = j % C::RPE < RP ? s * (j < C::RPE ? scale[0] : scale[NS - 1]) : 0.f;
         const uint32_t hi = f2bf(s);
         hs_hi[m * C::H_LD + j] = (uint16_t)hi;
-        hs_lo[m * C::H_LD + j] = (uint16_t)f2bf(s - __uint_as_float(hi << 16));
+        // (an infinite head has no tail: inf - inf would turn the row's infinities into NaN)
+        hs_lo[m * C::H_LD + j] = (hi & 0x7f80u) != 0x7f80u ? (uint16_t)f2bf(s - __uint_as_float(hi << 16)) : (uint16_t)0;
     };
     shrink();
     first_fetch();

@@ -937,6 +937,33 @@ def test_rank_64_shrink_and_expand_halves_on_narrow_sites(M, oracle, which):
         M.set_tuning("seg_tiles", 0)
 
 
+@pytest.mark.parametrize("path", ["decode", "segmented"])
+@pytest.mark.parametrize("r", [4, 8, 16, 32, 64])
+def test_an_infinite_activation_stays_infinite(M, r, path):
+    """All of A and B positive: an infinite x makes every h of its row and so the whole row +inf, never NaN (h is
+    split into head and tail, and inf - inf is none); the rows beside it are what they are without it."""
+    T, d_in, d_out = 21, 200, 136
+    site = M.Site(d_in, d_out, r, 2)
+    g = torch.Generator().manual_seed(r)
+    for s in range(2):
+        A, B = (torch.rand(sh, generator=g).add_(0.1).to(torch.bfloat16).cuda() for sh in ((r, d_in), (d_out, r)))
+        M.lora_slots_upload(site, s, s, A, B, r, 2.0 * r)
+    x = torch.rand((T, d_in), generator=g).to(torch.bfloat16).cuda()
+
+    def run(x):
+        y = torch.ones((T, d_out), dtype=torch.bfloat16, device="cuda")
+        if path == "decode":
+            M.lora_apply_decode(site, x, y, torch.zeros(T, dtype=torch.int32, device="cuda"))
+        else:
+            M.lora_apply_segmented(site, x, y, np.array([0, T], dtype=np.int32), np.zeros(1, dtype=np.int32))
+        return y
+    want = run(x)
+    assert bool(torch.isfinite(want).all())
+    x[5, 37] = float("inf")
+    want[5] = float("inf")
+    assert torch.equal(run(x), want)
+
+
 def test_segmented_rejects_bad_offsets(M):
     site = M.Site(64, 64, 64, 2)
     x = torch.zeros((10, 64), dtype=torch.bfloat16, device="cuda")
