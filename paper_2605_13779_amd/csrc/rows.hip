@@ -1,5 +1,5 @@
-// LoRA apply over plan chunks: decode (gather by slot index), packed MoE pairs and small-rank
-// segments.  Vector ALU, with the expand of padded ranks 8 and 16 on 4x4x4 matrix-core blocks.  A chunk is up to MLORA_CHUNK rows that share one adapter (and expert):
+// LoRA apply over plan chunks: decode at ranks 1 and 2, packed MoE pairs that are few per (slot, expert) or wider than
+// rank 16, batches whose plan holds no tiles (the tile kernels take the rest).  A chunk is up to MLORA_CHUNK rows that share one adapter (and expert):
 //   shrink  h[c][j] = sum_i x[row_c, i] * A[j, i]   -- wavefront reduction, packed-bf16 dot2,
 //                                                      fp32 accumulate
 //   scale   h *= alpha / r

@@ -1,4 +1,8 @@
 // Dense decode in tiles (see tile_body.h): one or several sites that share a batch plan.
+// Bound by the chain launch -> plan -> first loads -> (trade) -> expand, one or two tiles per CU.  Measured
+// against the chunk launches of rows.hip: 93 rows at rank 64, 7168 -> 7168, 40.8 -> 14.5 us (33 MB); the seven
+// projections of a 2560-wide layer at rank 16, 256 rows 58.6 -> 53.4 us (123 MB), 1001 rows 130.5 -> 93.4 us
+// (261 MB).
 #include "tile_body.h"
 
 namespace mlora {
