@@ -170,6 +170,8 @@ struct MoeDownArgs {
     int32_t d_in;
     const int32_t *chunks;            // the plan's chunk records (kRec ints: key, count, -, -, the chunk's pairs)
     int32_t chunk_bound;              // records to look at (those past the live chunks have count 0)
+    const int32_t *tiles;             // the plan's tile records (4 ints: key, count, first place in `sorted`, -), or null
+    int32_t tile_rows, n_tiles;       // their height (<= 16) and how many to look at (those past the live ones have count 0)
 };
 bool moe_down_shrinks_by_wave(int r_pad);
 hipError_t launch_moe_down_shrink(const MoeDownArgs &a, hipStream_t st);

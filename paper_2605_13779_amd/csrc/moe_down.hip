@@ -388,6 +388,106 @@ void moe_down_shrink_kernel(const MoeDownArgs a)
     }
 }
 
+// The same where the plan holds tiles of 8 or 16 pairs (several pairs per (slot, expert)): one wave per tile, the sums
+// on the matrix cores with operands as whole-line loads leave them (lane l: 16 bytes of row (l/2)%8 at piece
+// 2*(l/16) + l%2; only products of pieces of equal parity are meant, see tile_body.h).  Bound by what a CU pulls
+// through its L1, and a chunk of four pairs pulls the adapter's A once per four
+// rows of x.  Expert layer of 8000 tokens (16 pairs per group, rank 8, 768 -> 2048) 296.9 -> 293.0 us, this launch 32.4 us for 150 MB;
+// of 2048 tokens (4 per group) 158.7 -> 157.6 us, 17.6 us for 75 MB.
+template <int RP, int TG>
+__global__ __launch_bounds__(256)
+void moe_down_shrink_tile_kernel(const MoeDownArgs a)
+{
+    constexpr int RG = RP <= 8 ? 1 : 2;            // groups of eight adapter rows
+    constexpr int DP = RG + TG <= 3 ? 6 : 4;       // steps of 64 inputs in flight
+    const int lane = (int)threadIdx.x & 63;
+    const int tile = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + ((int)threadIdx.x >> 6));
+    if (tile >= a.n_tiles) return;
+    const int4 r = ((const int4 *)a.tiles)[tile];
+    const int key = __builtin_amdgcn_readfirstlane(r.x), cnt = __builtin_amdgcn_readfirstlane(r.y);
+    if (cnt <= 0) return;                                                 // past the live tiles
+    const int32_t *pairs = a.sorted + __builtin_amdgcn_readfirstlane(r.z);
+    const int lr = (lane >> 1) & 7, kq = lane >> 4, lu = kq * 2 + (lane & 1);
+    const int s = key / a.E, U = a.d_in >> 3, n = (U + 7) >> 3;
+    int p[TG];
+#pragma unroll
+    for (int g = 0; g < TG; ++g) p[g] = pairs[min(8 * g + lr, cnt - 1)];
+    const char *Ag = (const char *)(a.a_tab + (int64_t)key * RP * a.d_in);
+    uint32_t a_off[RG];
+#pragma unroll
+    for (int j = 0; j < RG; ++j) a_off[j] = (uint32_t)min(j * 8 + lr, RP - 1) * ((uint32_t)a.d_in * 2u);
+    uint4 av[DP][RG], xv[DP][TG];
+    const char *xp[TG];
+    auto load_a = [&](int i, auto slot_c) __attribute__((always_inline)) {
+        constexpr int d = decltype(slot_c)::value;
+        const uint32_t u16 = (uint32_t)min(i * 8 + lu, U - 1) * 16u;
+#pragma unroll
+        for (int j = 0; j < RG; ++j) av[d][j] = *(const uint4 *)(Ag + (size_t)(a_off[j] + u16));
+    };
+    auto load_x = [&](int i, auto slot_c) __attribute__((always_inline)) {
+        constexpr int d = decltype(slot_c)::value;
+        const uint32_t u16 = (uint32_t)min(i * 8 + lu, U - 1) * 16u;
+#pragma unroll
+        for (int g = 0; g < TG; ++g) xv[d][g] = *(const uint4 *)(xp[g] + u16);
+    };
+    f32x4_t acc[RG][TG];
+#pragma unroll
+    for (int j = 0; j < RG; ++j)
+#pragma unroll
+        for (int g = 0; g < TG; ++g) acc[j][g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto consume = [&](int i, auto slot_c) __attribute__((always_inline)) {
+        constexpr int d = decltype(slot_c)::value;
+        const bool in = i * 8 + lu < U;
+#pragma unroll
+        for (int g = 0; g < TG; ++g) {
+            const uint4 xz = in ? xv[d][g] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < RG; ++j)
+                acc[j][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[d][j]), __builtin_bit_cast(bf16x8_t, xz), acc[j][g], 0, 0, 0);
+        }
+    };
+    // (A does not depend on the pair ids, which are still on their way)
+    static_for<DP>([&](auto d) { if (d.value < n) load_a(d.value, d); });
+#pragma unroll
+    for (int g = 0; g < TG; ++g) xp[g] = (const char *)(a.x + (int64_t)p[g] * a.ldx);
+    static_for<DP>([&](auto d) { if (d.value < n) load_x(d.value, d); });
+    float w[TG];
+#pragma unroll
+    for (int g = 0; g < TG; ++g) w[g] = a.pair_w[p[g]];
+    const int r_s = a.rank[s];
+    const float scale = a.scale[s];
+    int i = 0;
+    for (; i + 2 * DP <= n; i += DP)
+        static_for<DP>([&](auto d) { consume(i + d.value, d); load_a(i + DP + d.value, d); load_x(i + DP + d.value, d); });
+    static_for<DP>([&](auto d) {
+        if (i + d.value < n) consume(i + d.value, d);
+        if (i + DP + d.value < n) { load_a(i + DP + d.value, d); load_x(i + DP + d.value, d); }
+    });
+    static_for<DP>([&](auto d) { if (i + DP + d.value < n) consume(i + DP + d.value, d); });
+    if (r_s <= 0) return;                                                 // the slot holds no adapter at this site
+    const bool odd = lane & 1;
+#pragma unroll
+    for (int j = 0; j < RG; ++j)
+#pragma unroll
+        for (int g = 0; g < TG; ++g) {
+            float v0 = odd ? acc[j][g][1] : acc[j][g][0], v1 = odd ? acc[j][g][3] : acc[j][g][2];
+            v0 += lane_xor<1>(v0);
+            v1 += lane_xor<1>(v1);
+            const int row = j * 8 + lu;                                   // (2 * kq + parity: even lanes keep the first)
+            const float f = (odd ? v1 : v0) * scale * w[g];
+            const uint32_t hi = __float_as_uint(f) & 0xffff0000u;         // head truncated, tail rounded
+            if (row < RP && 8 * g + lr < cnt) a.h[(int64_t)p[g] * RP + row] = (hi >> 16) | (f2bf(f - __uint_as_float(hi)) << 16);
+        }
+}
+
+template <int RP>
+static void launch_moe_down_shrink_tile(const MoeDownArgs &a, hipStream_t st)
+{
+    const dim3 grid((unsigned)((a.n_tiles + 3) / 4)), block(256);
+    if (a.tile_rows <= 8) moe_down_shrink_tile_kernel<RP, 1><<<grid, block, 0, st>>>(a);
+    else moe_down_shrink_tile_kernel<RP, 2><<<grid, block, 0, st>>>(a);
+}
+
 bool moe_down_shrinks_by_wave(int r_pad) { return r_pad <= 16; }
 
 hipError_t launch_moe_down_shrink(const MoeDownArgs &a, hipStream_t st)
@@ -395,6 +495,14 @@ hipError_t launch_moe_down_shrink(const MoeDownArgs &a, hipStream_t st)
     const int64_t groups = (int64_t)a.n_slots * a.E;
     if (groups <= 0 || a.T <= 0) return hipSuccess;
     if (!a.chunks || a.chunk_bound <= 0) return hipErrorInvalidValue;
+    if (a.tiles && a.n_tiles > 0 && a.tile_rows <= 16) {
+        switch (a.r_pad) {
+            case 2:  launch_moe_down_shrink_tile<2>(a, st); return hipGetLastError();
+            case 4:  launch_moe_down_shrink_tile<4>(a, st); return hipGetLastError();
+            case 8:  launch_moe_down_shrink_tile<8>(a, st); return hipGetLastError();
+            case 16: launch_moe_down_shrink_tile<16>(a, st); return hipGetLastError();
+        }
+    }
     // 64 records per round of the eight XCDs (two workgroups of four waves each per XCD)
     const dim3 grid((unsigned)(((int64_t)a.chunk_bound + 63) / 64 * 16)), block(256);
     switch (a.r_pad) {

@@ -1275,6 +1275,22 @@ def test_moe_down_small(M, oracle, T, K, E, S, r):
     check_moe_down(M, oracle, c, site)
 
 
+@pytest.mark.parametrize("q", [4, 8, 13, 16])
+@pytest.mark.parametrize("r,d_in", [(2, 8), (4, 72), (8, 392), (8, 512), (16, 264), (16, 2056)])
+def test_moe_down_shrink_in_tiles(M, oracle, r, d_in, q):
+    """The shrink per tile of pairs: heights at the edges of its 8 rows, groups from none to several tiles, d_in of
+    one piece, of part of a step, of fewer and of more steps than are in flight; tolerances are the oracle's."""
+    T, K, E, S = 120, 2, 4, 3
+    c = W.moe_down_case(f"down_tile_{r}_{d_in}_{q}", 5400 + 16 * q + r + d_in, T, K, E, d_in, 72, S, r, 2.0 * r,
+                        std_a=0.05, std_b=0.05)
+    site = moe_site(M, c)
+    M.set_tuning("tile_moe_rows", q)
+    try:
+        check_moe_down(M, oracle, c, site)
+    finally:
+        M.set_tuning("tile_moe_rows", 0)
+
+
 def test_moe_down_pairs_the_plan_left_out(M, oracle):
     """Pairs that the route plan drops must add nothing: expert ids outside [0, E) (masked or padded
     routing tables), and tokens whose slot was not ready at the site the plan was built against
