@@ -340,15 +340,18 @@ __device__ __forceinline__ void st_stream(void *p, const uint4 &v)
 // ends any prefetch of the next tile.  Issued this way, a store only makes a later wait a little
 // longer while it is unacknowledged: the hardware counter still includes it.  The data registers
 // are read when the instruction issues; they may be reused right away.
+// (A store of more than 64 bits still reads its data registers when the next instructions issue: a vector instruction
+// that writes one of them needs two wait states in between.  The compiler inserts them behind its own stores, not
+// behind inline assembly, so they are part of it.)
 __device__ __forceinline__ void st_quiet(void *p, const uint4 &v)
 {
     u32x4_t t = {v.x, v.y, v.z, v.w};
-    asm volatile("global_store_dwordx4 %0, %1, off" : : "v"(p), "v"(t) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" : : "v"(p), "v"(t) : "memory");
 }
 __device__ __forceinline__ void st_quiet_stream(void *p, const uint4 &v)
 {
     u32x4_t t = {v.x, v.y, v.z, v.w};
-    asm volatile("global_store_dwordx4 %0, %1, off nt" : : "v"(p), "v"(t) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" : : "v"(p), "v"(t) : "memory");
 }
 __device__ __forceinline__ void st_quiet(void *p, uint2 v)
 {
