@@ -323,7 +323,7 @@ int32_t mlora_resident_stats(mlora_resident *r, int64_t *out /* [MLORA_RESIDENT_
  * seg_expand_groups, seg_table_copy, seg_shrink_wgs, seg_tiles (1 / -1: rank-64 prefill always / never in
  * tiles; seg_no_mfma, 0 or 1, is an earlier name of it), seg_overlap (batches of the rank-64
  * prefill in flight on a second stream), seg_fused (-1: that prefill as two launches instead of one);
- * upload_piece_kb.
+ * upload_piece_kb; moe_down_form (down projection: 1 token by token up to rank 16, -1 in two launches).
  * MLORA_E_INVALID for any other name and for a tile height outside its range. */
 int32_t mlora_set_tuning(const char *name, int32_t value);
 

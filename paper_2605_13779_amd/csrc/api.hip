@@ -63,7 +63,7 @@ std::atomic<int32_t> g_knob[kKnobCount];
 const char *const kKnobName[kKnobCount] = {
     "rows_poll_limit", "rows_rank_bound", "rows_items_target", "rows_mode", "rows_waves", "plan_general",
     "plan_separate", "plan_pipeline", "seg_expand_groups", "seg_table_copy", "seg_shrink_wgs", "seg_tiles", "seg_overlap",
-    "upload_piece_kb", "seg_fused", "rows_chunk_run", "tile_rows", "tile_parts", "tile_moe_rows"};
+    "upload_piece_kb", "seg_fused", "rows_chunk_run", "tile_rows", "tile_parts", "tile_moe_rows", "moe_down_form"};
 
 // Host-side record of a slot's rank (the kernels read the device table; this only tells the launch
 // code whether any slot is padded, i.e. whether rank-bounded reads of A can save traffic).
@@ -1301,6 +1301,9 @@ int32_t moe_lora_apply_down(mlora_site *s, const mlora_plan *plan, const void *x
         d.tiles = plan->pv.tiles; d.tile_rows = plan->tile_rows;
         d.n_tiles = (int32_t)max_tiles(plan->items, (int64_t)plan->n_slots * plan->n_experts, plan->tile_rows);
     }
+    const int32_t cus = cu_count(s->d.device);
+    if (moe_down_takes_tokens(T, plan->top_k, s->E, plan->n_slots, s->r_pad, s->d.d_in, s->d.d_out, cus))
+        return ok(launch_moe_down_token(d, cus, st)) ? MLORA_OK : MLORA_E_HIP;
     // first launch: per chunk of a (slot, expert) group, h = w * (alpha / r) * A x for the chunk's pairs
     if (moe_down_shrinks_by_wave(s->r_pad)) {
         if (!ok(launch_moe_down_shrink(d, st))) return MLORA_E_HIP;

@@ -176,6 +176,8 @@ struct MoeDownArgs {
     int32_t tile_rows, n_tiles;       // their height (<= 16) and how many to look at (those past the live ones have count 0)
 };
 bool moe_down_shrinks_by_wave(int r_pad);
+bool moe_down_takes_tokens(int T, int K, int E, int n_slots, int r_pad, int d_in, int d_out, int cus);
+hipError_t launch_moe_down_token(const MoeDownArgs &a, int cus, hipStream_t st);
 hipError_t launch_moe_down_shrink(const MoeDownArgs &a, hipStream_t st);
 hipError_t launch_moe_down(const MoeDownArgs &a, hipStream_t st);
 int moe_down_tile_rows(int r_pad, int K, int E);   // 0: this shape does not fit
@@ -227,7 +229,7 @@ int seg_expand_capacity();
 enum Knob {
     kRowsPollLimit, kRowsRankBound, kRowsItemsTarget, kRowsMode, kRowsWaves, kPlanGeneral, kPlanSeparate,
     kPlanPipeline, kSegExpandGroups, kSegTableCopy, kSegShrinkWgs, kSegTiles, kSegOverlap, kUploadPieceKb, kSegFused,
-    kRowsChunkRun, kTileRows, kTileParts, kTileMoeRows, kKnobCount
+    kRowsChunkRun, kTileRows, kTileParts, kTileMoeRows, kMoeDownForm, kKnobCount
 };
 int tuning(Knob k);             // api.hip
 #ifdef MLORA_PROF

@@ -1,4 +1,5 @@
-// MoE down projection: shrink per chunk of a (slot, expert) group, then expand + routing-weight combine
+// MoE down projection with the routing-weight combine: token by token in one launch where the batch has few pairs per
+// adapter (moe_down_token_kernel), else a shrink per chunk or tile of a (slot, expert) group and an expand + combine
 // on the matrix cores.
 //
 // Per-expert LoRA tensors sit on the expert down projection too (Sections 3.4 and 4.4): pair
@@ -31,7 +32,9 @@
 // vector or the zeros -- so that after the prologue the waves run without a barrier until the
 // epilogue.  Ranks below 8 are padded to 8 in the contraction (zeros in both operands; the loads
 // fetch the real ranks only).
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 #include "plan_device.h"
 #include "wave_ops.h"
 
@@ -486,6 +489,186 @@ static void launch_moe_down_shrink_tile(const MoeDownArgs &a, hipStream_t st)
     const dim3 grid((unsigned)((a.n_tiles + 3) / 4)), block(256);
     if (a.tile_rows <= 8) moe_down_shrink_tile_kernel<RP, 1><<<grid, block, 0, st>>>(a);
     else moe_down_shrink_tile_kernel<RP, 2><<<grid, block, 0, st>>>(a);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Both halves in one launch, token by token, for batches with few pairs per adapter (decode steps; see
+// moe_down_takes_tokens).  A workgroup owns one token and a range of outputs: its waves take the token's pairs,
+// h = w * (alpha / r) * A x per pair (dot products, one transposing reduction over the wave) meets in LDS, and a
+// thread per output adds the K deltas in fp32, in order of k.  Of the plan it needs the pairs' keys only.  It is bound
+// by one chain, launch -> keys -> rows of A, x and the first B -> sums -> outputs, where the two launches pay two
+// and a dense form whose tiles hold a token or two each.  Parts of a token sum its A again; they sit on one XCD and
+// find it in L2.  Expert layers of 128 experts x 32 slots, rank 8, 768 -> 2048, top-8, the down call: 48 tokens
+// (17 MB of adapters) 17.9 -> 7.4 us, 200 tokens (72 MB) 27.8 -> 14.3 us.
+// (Registers: what is in flight, the rows of A of two pieces and the B rows of eight pairs, is 110 of them at rank 8.
+// Held to 128 the kernel spills 83 and the 48 tokens take 13.7 us, so ranks 8 and 16 run one workgroup per CU.)
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kTokThreads = 512;
+
+// KB: pairs whose B rows are in flight together (K rounded up to 2, 4 or 8; more pairs than that follow in turn).
+template <int RP, int KB>
+__global__ __launch_bounds__(kTokThreads, RP >= 8 ? 2 : 4)
+void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_out)
+{
+    constexpr int NW = kTokThreads / 64;
+    constexpr int F = RP <= 8 ? 2 : 1;             // 16-byte units of d_in per lane and flight
+    constexpr int BW = (RP + 1) / 2;               // words of an output's B row
+    __shared__ float hs[KMAX * RP];
+    __shared__ float hp[NW * RP];
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = (int)blockIdx.x >> 3, g8 = q / parts, part = q - g8 * parts, t = g8 * 8 + ((int)blockIdx.x & 7);
+    if (t >= a.T) return;
+    const int K = a.K, U = a.d_in >> 3;
+    const int64_t p0 = (int64_t)t * K;
+    const int key_l = lane < K ? a.key_of[p0 + lane] : -1;
+    const float w_l = lane < K ? a.pair_w[p0 + lane] : 0.f;
+    const uint32_t valid = (uint32_t)__ballot(key_l >= 0);               // (K <= 16)
+    if (valid == 0) return;                                              // the plan left the token out
+    const int key_v = __builtin_amdgcn_readlane(key_l, __builtin_ctz(valid)), s = key_v / a.E;      // (a token's pairs share its slot)
+    // (a pair that the plan left out, or that the token has not, loads a valid one's rows: every load is issued)
+    auto key_at = [&](int k) __attribute__((always_inline)) { const int v = __builtin_amdgcn_readlane(key_l, k); return v < 0 ? key_v : v; };
+
+    // ---- shrink: wave w takes pair w % K and slice w / K of d_in (pairs w, w + 8, .. where K is above 8) ----
+    const int n_sl = K < NW ? NW / K : 1, slice = w / K;
+    const bool busy = w < (K < NW ? n_sl * K : NW);
+    const uint32_t row = (uint32_t)a.d_in * 2u, step = (uint32_t)n_sl * 1024u;
+    uint4 av[F][RP], xv[F];
+    float acc[RP];
+    auto load_ax = [&](int k, uint32_t u0) __attribute__((always_inline)) {
+        const char *A = (const char *)(a.a_tab + (int64_t)key_at(k) * RP * a.d_in), *x = (const char *)(a.x + (p0 + k) * a.ldx);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            const uint32_t u = min(u0 + f * step, row - 16u);
+#pragma unroll
+            for (int j = 0; j < RP; ++j) av[f][j] = *(const uint4 *)(A + (j * row + u));
+            xv[f] = *(const uint4 *)(x + u);
+        }
+    };
+    auto dot_ax = [&](uint32_t u0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            const uint4 xz = u0 + f * step < row ? xv[f] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < RP; ++j) acc[j] = dot8(xz, av[f][j], acc[j]);
+        }
+    };
+    const int o_lo = part * part_out, o_hi = min(a.d_out, o_lo + part_out);
+    uint32_t bv[KB][BW];
+    uint16_t yv;
+    auto load_b = [&](int o, int kb) __attribute__((always_inline)) {
+        const uint32_t ob = (uint32_t)min(o, a.d_out - 1) * (uint32_t)(RP * 2);
+#pragma unroll
+        for (int i = 0; i < KB; ++i) {
+            const char *src = (const char *)a.b_tab + (int64_t)key_at(min(kb + i, KMAX - 1)) * a.d_out * (RP * 2) + ob;
+            if constexpr (RP >= 8) {
+#pragma unroll
+                for (int u = 0; u < RP / 8; ++u) { const uint4 v = ((const uint4 *)src)[u]; bv[i][4 * u] = v.x; bv[i][4 * u + 1] = v.y; bv[i][4 * u + 2] = v.z; bv[i][4 * u + 3] = v.w; }
+            } else if constexpr (RP == 4) { const uint2 v = *(const uint2 *)src; bv[i][0] = v.x; bv[i][1] = v.y; }
+            else if constexpr (RP == 2) bv[i][0] = *(const uint32_t *)src;
+            else bv[i][0] = *(const uint16_t *)src;
+        }
+        if (kb == 0) yv = a.y[(int64_t)t * a.ldy + min(o, a.d_out - 1)];
+    };
+    const uint32_t u_first = (uint32_t)(slice * 64 + lane) * 16u;
+    load_ax(w % K, u_first);
+    if constexpr (RP <= 8) load_b(o_lo + tid, 0);
+    const int r_s = a.rank[s];
+    const float scale = a.scale[s];
+    for (int k = busy ? w % K : K; k < K; k += NW) {
+#pragma unroll
+        for (int j = 0; j < RP; ++j) acc[j] = 0.f;
+        uint32_t u = u_first;
+        if (k != w % K) load_ax(k, u);
+        dot_ax(u);
+        for (u += F * step; u - (uint32_t)lane * 16u < row; u += F * step) { load_ax(k, u); dot_ax(u); }
+        wave_sum_transpose<RP>(acc, lane);
+        const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_l), k));
+        if (lane < RP) {
+            const int j = bitrev<Log2<RP>::v>(lane);
+            if (n_sl == 1) hs[k * RP + j] = acc[0] * scale * wk;
+            else hp[w * RP + j] = acc[0];
+        }
+    }
+    if constexpr (RP > 8) load_b(o_lo + tid, 0);
+    if (r_s <= 0) return;                                                // the slot holds no adapter at this site
+    __syncthreads();
+    if (n_sl > 1) {
+        if (tid < K * RP) {
+            const int k = tid / RP, j = tid - k * RP;
+            float v = 0.f;
+            for (int i = 0; i < n_sl; ++i) v += hp[(i * K + k) * RP + j];
+            hs[tid] = v * scale * a.pair_w[p0 + k];
+        }
+        __syncthreads();
+    }
+    // ---- expand: a thread per output ----
+    for (int o = o_lo + tid; o - tid < o_hi; o += kTokThreads) {
+        float sum = 0.f;
+        const uint16_t y0 = yv;
+        for (int kb = 0; kb < K; kb += KB) {
+            if (kb > 0) load_b(o, kb);
+#pragma unroll
+            for (int i = 0; i < KB; ++i) {
+                if (!(valid >> (kb + i) & 1u)) continue;
+                const float *h = hs + (kb + i) * RP;
+#pragma unroll
+                for (int j = 0; j < RP; ++j) sum += h[j] * (j & 1 ? bf_hi(bv[i][j >> 1]) : bf_lo(bv[i][j >> 1]));
+            }
+        }
+        if (o - tid + kTokThreads < o_hi) load_b(o + kTokThreads, 0);
+        if (o < o_hi) a.y[(int64_t)t * a.ldy + o] = (uint16_t)f2bf(__uint_as_float((uint32_t)y0 << 16) + sum);
+    }
+}
+
+template <int RP, int KB>
+static hipError_t launch_moe_down_token_kb(const MoeDownArgs &a, int cus, hipStream_t st)
+{
+    // one workgroup per CU (48 tokens in 2, 4, 5 and 6 parts: 7.4, 7.5, 7.6 and 10.4 us), at least two waves of outputs each
+    int parts = std::max(1, std::min(cus / a.T, (a.d_out + 127) / 128));
+    const int part_out = ((a.d_out + parts - 1) / parts + 63) / 64 * 64;
+    parts = (a.d_out + part_out - 1) / part_out;
+    moe_down_token_kernel<RP, KB><<<dim3((unsigned)((a.T + 7) / 8 * 8 * parts)), dim3(kTokThreads), 0, st>>>(a, parts, part_out);
+    return hipGetLastError();
+}
+
+template <int RP>
+static hipError_t launch_moe_down_token_rp(const MoeDownArgs &a, int cus, hipStream_t st)
+{
+    if (a.K <= 2) return launch_moe_down_token_kb<RP, 2>(a, cus, st);
+    if (a.K <= 4 || RP == 16) return launch_moe_down_token_kb<RP, 4>(a, cus, st);
+    return launch_moe_down_token_kb<RP, (RP == 16 ? 4 : 8)>(a, cus, st);
+}
+
+// Whether a down call goes token by token.  What the two forms take, in us and MB, from a sweep of 50 calls (ranks 2 to 16,
+// 8 to 128 experts, top-1 to top-8, 100 to 1500 tokens): token by token, per round of one token per CU, 3 (4.5 at rank
+// 16, whose B rows come in two flights) and its adapters, fetched for every pair, at 6.5 TB/s; in two launches 9,
+// an eighth per expert up to 64, and the distinct adapters at 5.9 TB/s.  128 experts x 32 slots, top-8, rank 8, two
+// launches / token by token: 300 tokens 33.0 / 25.8 us, 500 40.8 / 31.5, 600 42.4 / 41.4, 800 46.4 / 54.4; rank 16, 300
+// tokens 41.3 / 44.9; 8 experts, top-4, rank 8, 200 tokens 11.3 / 9.4, 300 11.9 / 15.3.
+bool moe_down_takes_tokens(int T, int K, int E, int n_slots, int r_pad, int d_in, int d_out, int cus)
+{
+    const int form = tuning(kMoeDownForm);
+    if (r_pad > 16 || form < 0) return false;
+    if (form > 0) return true;
+    if (tuning(kTileMoeRows) > 0) return false;                          // (tiles asked for)
+    const double mb = 2e-6 * r_pad * ((double)d_in + d_out), pairs = (double)T * K, keys = (double)n_slots * E;
+    const double rounds = std::max(1.0, (double)T / cus + 0.2), distinct = keys * -std::expm1(-pairs / keys);
+    return rounds * ((r_pad == 16 ? 4.5 : 3.0) + mb * K * cus / 6.5) < 9.0 + std::min(E, 64) / 8.0 + 0.17 * mb * distinct;
+}
+
+hipError_t launch_moe_down_token(const MoeDownArgs &a, int cus, hipStream_t st)
+{
+    if (a.T <= 0) return hipSuccess;
+    if (a.K < 1 || a.K > KMAX) return hipErrorInvalidValue;
+    switch (a.r_pad) {
+        case 1:  return launch_moe_down_token_rp<1>(a, cus, st);
+        case 2:  return launch_moe_down_token_rp<2>(a, cus, st);
+        case 4:  return launch_moe_down_token_rp<4>(a, cus, st);
+        case 8:  return launch_moe_down_token_rp<8>(a, cus, st);
+        case 16: return launch_moe_down_token_rp<16>(a, cus, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 bool moe_down_shrinks_by_wave(int r_pad) { return r_pad <= 16; }

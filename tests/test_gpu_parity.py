@@ -1625,6 +1625,38 @@ def test_moe_down_shrink_in_tiles(M, oracle, r, d_in, q):
         M.set_tuning("tile_moe_rows", 0)
 
 
+@pytest.mark.parametrize("form", [1, -1])
+@pytest.mark.parametrize("T,K,E,S,r,d_in,d_out", [(1, 1, 1, 1, 8, 8, 8), (9, 3, 6, 4, 8, 520, 136), (37, 2, 4, 3, 8, 1032, 200), (300, 2, 5, 2, 8, 136, 200),
+                                                  (20, 7, 16, 3, 4, 72, 1096), (64, 8, 8, 2, 16, 2056, 72), (12, 5, 12, 2, 2, 264, 648),
+                                                  (50, 3, 6, 4, 1, 136, 520), (33, 16, 24, 2, 8, 136, 72), (17, 9, 16, 2, 16, 520, 1032), (260, 4, 40, 2, 16, 136, 200)])
+def test_moe_down_forms(M, oracle, form, T, K, E, S, r, d_in, d_out):
+    """The down projection token by token (1) and in two launches (-1), whatever the rule would take: d_in of one piece, of part of a
+    wave's pieces and of several flights, outputs that leave parts and passes ragged, fewer pairs than waves, an odd number of
+    them and more, tokens that the grid's rounding adds, every padded rank, an empty slot, rows without adapter."""
+    ranks = [r] * S
+    if S > 2:
+        ranks[1] = 0
+    c = W.moe_down_case(f"down_form_{T}_{K}_{r}", 5800 + T + K, T, K, E, d_in, d_out, S, r, 2.0 * r, ranks=ranks, std_a=0.05, std_b=0.05)
+    if T > 1:
+        c.token_slot[::7] = -1
+    site = moe_site(M, c)
+    M.set_tuning("moe_down_form", form)
+    try:
+        check_moe_down(M, oracle, c, site)
+    finally:
+        M.set_tuning("moe_down_form", 0)
+
+
+@pytest.mark.parametrize("form", [1, -1])
+def test_moe_down_forms_on_dropped_pairs(M, oracle, form):
+    """Pairs that the plan left out, in both forms."""
+    M.set_tuning("moe_down_form", form)
+    try:
+        test_moe_down_pairs_the_plan_left_out(M, oracle)
+    finally:
+        M.set_tuning("moe_down_form", 0)
+
+
 def test_moe_down_pairs_the_plan_left_out(M, oracle):
     """Pairs that the route plan drops must add nothing: expert ids outside [0, E) (masked or padded
     routing tables), and tokens whose slot was not ready at the site the plan was built against
