@@ -23,8 +23,7 @@
 //
 // A workgroup owns a tile of up to 96 tokens of one slot and 128 outputs; each of its 4 waves owns
 // 32 outputs and streams its rows of B straight from the tables in operand layout (lane = output,
-// 8 consecutive ranks: one 16-byte load), one chunk of 8 contraction steps ahead (two ahead measured
-// slower: more of B in flight than the memory system serves only queues in front of the rest).  H is never
+// 8 consecutive ranks: one 16-byte load), half a chunk of 8 contraction steps ahead (see the contraction).  H is never
 // written out densely.  The tile's h vectors are fetched once into LDS, split into bf16 head and
 // tail in operand layout (K vectors per token, plus one vector of zeros), beside a byte table
 // inv[token][expert] = which of the token's K pairs went to that expert (0xff: none).  A lane's
@@ -46,6 +45,7 @@ constexpr int NWD = 4;             // waves: 32 outputs each
 constexpr int NTD = NWD * 64;
 constexpr int CHK = 128;           // contraction values per chunk (8 steps of 16)
 constexpr int NST = CHK / 16;
+constexpr int HST = NST / 2;       // steps whose B rows are fetched together
 constexpr int KMAX = 16;           // largest top-k (a pair's index fits the table byte)
 constexpr int STG_LD = TN + 4;     // padded row stride of the output staging block, in floats
 constexpr int kStageBytes = 32 * STG_LD * 4;
@@ -97,8 +97,18 @@ __device__ __forceinline__ f32x16_t mfma32d(const uint4 &a, const uint4 &b, f32x
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
+// 16 bytes of B (or the ranks there are) at a byte offset; zeros, and nothing moved, at an offset behind the descriptor's range.
+template <int RP>
+__device__ __forceinline__ uint4 load_b_or_zero(__amdgpu_buffer_rsrc_t rsrc, uint32_t off)
+{
+    if constexpr (RP >= 8) return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0));
+    else if constexpr (RP == 4) { const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)off, 0, 0)); return make_uint4(v.x, v.y, 0u, 0u); }
+    else if constexpr (RP == 2) return make_uint4(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, 0), 0u, 0u, 0u);
+    else return make_uint4(__builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0), 0u, 0u, 0u);
+}
+
 template <int RP, int MB>
-__global__ __launch_bounds__(NTD, 2)
+__global__ __launch_bounds__(NTD, 3)
 void moe_down_kernel(const MoeDownArgs a)
 {
     constexpr int RPE = RP < 8 ? 8 : RP, TM = 32 * MB;
@@ -144,21 +154,21 @@ void moe_down_kernel(const MoeDownArgs a)
     const int am = lane & 31, kg = lane >> 5;
     const uint32_t o_b = (uint32_t)min(nt * TN + w * 32 + am, a.d_out - 1);   // this lane's output as B operand
 
+    // (B is read through a descriptor of the slot's tables: a dead step's offset lies behind them and gives zeros)
+    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)Bs, 0, (int)((uint32_t)E * (uint32_t)a.d_out * (RP * 2u)), 0x00020000);
     // B rows of one contraction step: ranks [j0, j0 + 8) of expert e (the real ranks when there are fewer)
     auto load_b = [&](int c, int st, bool live) __attribute__((always_inline)) -> uint4 {
-        const int kv0 = live ? c * CHK + st * 16 + kg * 8 : 0;           // (dead steps: the slot's first rows again, a cache hit)
-        const uint32_t e = (uint32_t)min(kv0 / RPE, E - 1), j0 = (uint32_t)(kv0 % RPE);
-        const char *src = Bs + ((e * (uint32_t)a.d_out + o_b) * (uint32_t)RP + (RP >= 8 ? j0 : 0u)) * 2u;
-        if constexpr (RP >= 8) return *(const uint4 *)src;
-        else if constexpr (RP == 4) { const uint2 v = *(const uint2 *)src; return make_uint4(v.x, v.y, 0u, 0u); }
-        else if constexpr (RP == 2) return make_uint4(*(const uint32_t *)src, 0u, 0u, 0u);
-        else return make_uint4(*(const uint16_t *)src, 0u, 0u, 0u);
+        const int kv0 = c * CHK + st * 16 + kg * 8;
+        const uint32_t e = (uint32_t)(kv0 / RPE), j0 = (uint32_t)(kv0 % RPE);
+        live = live && (int)e < E;
+        const uint32_t off = ((e * (uint32_t)a.d_out + o_b) * (uint32_t)RP + (RP >= 8 ? j0 : 0u)) * 2u;
+        return load_b_or_zero<RP>(b_rsrc, live ? off : 0xfffffff0u);
     };
-    uint4 bq[2][NST];
-    auto load_chunk_b = [&](int c, auto bufc, uint32_t mask) __attribute__((always_inline)) {
+    uint4 bq[2][HST];
+    auto load_steps_b = [&](int c, int st0, auto bufc, uint32_t mask) __attribute__((always_inline)) {
         constexpr int bi = decltype(bufc)::value;
 #pragma unroll
-        for (int st = 0; st < NST; ++st) bq[bi][st] = load_b(c, st, (mask >> st & 1u) != 0);   // (every load is issued: the waits count them)
+        for (int i = 0; i < HST; ++i) bq[bi][i] = load_b(c, st0 + i, (mask >> (st0 + i) & 1u) != 0);   // (every load is issued: the waits count them)
     };
     auto range_mask = [&](int c) { const int left = E * RPE - c * CHK; return left >= CHK ? 0xffu : (left <= 0 ? 0u : (1u << ((left + 15) >> 4)) - 1u); };
 
@@ -177,23 +187,10 @@ void moe_down_kernel(const MoeDownArgs a)
         const uint64_t bits = __ballot(live);
         if (st == 0 && c < n_chunks) live_l[c] = (uint8_t)(bits >> (lane & 56));
     }
-    load_chunk_b(0, IntC<0>{}, range_mask(0));     // on their way while the tile's tables are built
+    load_steps_b(0, 0, IntC<0>{}, range_mask(0));     // on their way while the tile's tables are built
     for (int i = tid; i < TM * L.inv_ld / 8; i += NTD) ((uint2 *)inv)[i] = make_uint2(0xffffffffu, 0xffffffffu);
     if (tid < RPE / 8) { ((uint4 *)(hch + zero_row * RPE))[tid] = make_uint4(0, 0, 0, 0); ((uint4 *)(hcl + zero_row * RPE))[tid] = make_uint4(0, 0, 0, 0); }
     __syncthreads();
-
-    // ---- this thread's pieces of the tile's y rows (16 bytes each): on their way until the epilogue ----
-    constexpr int YP = 32 * (TN / 8) / NTD;                          // pieces per thread and block of 32 rows
-    uint4 yv[MB][YP];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int i = 0; i < YP; ++i) {
-            const int q = tid + i * NTD, m = mb * 32 + q / (TN / 8), o = nt * TN + (q % (TN / 8)) * 8;
-            const int t = tokM[m];
-            yv[mb][i] = make_uint4(0, 0, 0, 0);
-            if (t >= 0 && o < a.d_out) yv[mb][i] = *(const uint4 *)(a.y + (int64_t)t * a.ldy + o);
-        }
 
     // ---- the tile's pairs: which expert (as the plan saw it) -> inv; the h vector -> head and tail.
     //      Several pairs per thread at a time, so that their loads travel together. ----
@@ -250,17 +247,10 @@ void moe_down_kernel(const MoeDownArgs a)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x16_t{0};
     const uint8_t *inv_lane = inv + am * L.inv_ld + (RPE == 8 ? kg * L.inv_half : 0);
-    auto chunk = [&](int c, auto bufc) __attribute__((always_inline)) {
-        constexpr int bi = decltype(bufc)::value;
-        {
-            const int c2 = c + 1;
-            const uint32_t m2 = __builtin_amdgcn_readfirstlane(c2 < n_chunks ? (uint32_t)live_l[c2] : 0u);
-            load_chunk_b(c2, IntC<(bi + 1) % 2>{}, m2);
-        }
-        const uint32_t mask = __builtin_amdgcn_readfirstlane((uint32_t)live_l[c]);
-        if (mask == 0u) return;
-        // which of the token's pairs each step's expert is, for this lane's token of every block
-        uint64_t sel[MB];
+    auto chunk_mask = [&](int c) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(c < n_chunks ? (uint32_t)live_l[c] : 0u); };
+    // which of the token's pairs each step's expert is, for this lane's token of every block
+    uint64_t sel[MB];
+    auto load_sel = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const uint8_t *p = inv_lane + mb * 32 * L.inv_ld;
@@ -268,27 +258,68 @@ void moe_down_kernel(const MoeDownArgs a)
             else if constexpr (RPE == 32) sel[mb] = *(const uint32_t *)(p + 4 * c);
             else sel[mb] = *(const uint16_t *)(p + 2 * c);
         }
+    };
+    auto operand = [&](int mb, int st, uint4 &ah, uint4 &al) __attribute__((always_inline)) {
+        constexpr int per = RPE <= 16 ? 1 : RPE / 16;                         // steps per expert
+        const int j0 = RPE == 8 ? 0 : (RPE == 16 ? kg * 8 : (st % per) * 16 + kg * 8);
+        const uint32_t kb = (uint32_t)(sel[mb] >> (8 * (st / per))) & 0xffu;
+        const int row = kb == 0xffu ? zero_row : (mb * 32 + am) * K + (int)kb;
+        ah = *(const uint4 *)(hch + row * RPE + j0);
+        al = *(const uint4 *)(hcl + row * RPE + j0);
+    };
+    // Half a chunk is straight code, the operands PD (block, step) pairs ahead of the matrix instructions.  With a branch per
+    // step and per block the LDS reads of each pair stayed behind it: a workgroup alone on its CU took 20 us for 5 us of
+    // matrix instructions.  Rows of B of a dead step are zeros, blocks without a token read the vector of zeros; tiles of up
+    // to 32 rows, where that would be two thirds of the work, have their own loop.  Fetching half a chunk and y only
+    // behind the loop leaves 147 registers at rank 8, three workgroups per CU (a whole chunk and y in front: 230, two; held
+    // to 128, four, it spills 14 and is 4 % slower).  The down call, us before / after, 128 experts, top-8, rank 8,
+    // 768 -> 2048: 32 slots 2048 tokens 48.9 / 46.2, 4000 76.3 / 69.8, 8000 101.5 / 96.7; 8 slots 1000 tokens 30.3 / 23.9;
+    // one slot 500 tokens 26.1 / 21.0; 16 slots, rank 16, 8000 tokens 164.8 / 147.2; 8 slots of 64 experts, top-4, rank 64,
+    // 100 tokens 43.0 / 35.1.
+    constexpr int PD = 2;
+    auto consume = [&](auto nbc, auto st0c, auto bufc, uint32_t mask) __attribute__((always_inline)) {
+        constexpr int NB = decltype(nbc)::value, st0 = decltype(st0c)::value, N = HST * NB, bi = decltype(bufc)::value;
+        if ((mask >> st0 & ((1u << HST) - 1u)) == 0u) return;
+        uint4 ah[PD], al[PD];
+        static_for<PD>([&](auto n) { operand(n.value % NB, st0 + n.value / NB, ah[n.value], al[n.value]); });
+        static_for<N>([&](auto n) {
+            constexpr int mb = n.value % NB, i = n.value / NB, d = n.value % PD;
+            acc[mb] = mfma32d(ah[d], bq[bi][i], acc[mb]);
+            acc[mb] = mfma32d(al[d], bq[bi][i], acc[mb]);
+            if constexpr (n.value + PD < N) operand((n.value + PD) % NB, st0 + (n.value + PD) / NB, ah[d], al[d]);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto contract = [&](auto nbc) __attribute__((always_inline)) {
+        uint32_t mask = chunk_mask(0);
+        // (the first steps' B were fetched before it was known which of them are dead)
 #pragma unroll
-        for (int st = 0; st < NST; ++st) {
-            if (!(mask >> st & 1u)) continue;
-            constexpr int per = RPE <= 16 ? 1 : RPE / 16;                     // steps per expert
-            const int j0 = RPE == 8 ? 0 : (RPE == 16 ? kg * 8 : (st % per) * 16 + kg * 8);
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                if (mb * 32 >= rows) continue;
-                const uint32_t kb = (uint32_t)(sel[mb] >> (8 * (st / per))) & 0xffu;
-                const int row = kb == 0xffu ? zero_row : (mb * 32 + am) * K + (int)kb;
-                const uint4 ah = *(const uint4 *)(hch + row * RPE + j0);
-                const uint4 al = *(const uint4 *)(hcl + row * RPE + j0);
-                acc[mb] = mfma32d(ah, bq[bi][st], acc[mb]);
-                acc[mb] = mfma32d(al, bq[bi][st], acc[mb]);
-            }
+        for (int i = 0; i < HST; ++i) if (!(mask >> i & 1u)) bq[0][i] = make_uint4(0, 0, 0, 0);
+        for (int c = 0; c < n_chunks; ++c) {
+            const uint32_t next = chunk_mask(c + 1);
+            load_sel(c);
+            load_steps_b(c, HST, IntC<1>{}, mask);
+            consume(nbc, IntC<0>{}, IntC<0>{}, mask);
+            load_steps_b(c + 1, 0, IntC<0>{}, next);
+            consume(nbc, IntC<HST>{}, IntC<1>{}, mask);
+            mask = next;
         }
     };
-    for (int c = 0; c < n_chunks; c += 2) {
-        chunk(c, IntC<0>{});
-        if (c + 1 < n_chunks) chunk(c + 1, IntC<1>{});
-    }
+    if (MB > 1 && rows <= 32) contract(IntC<1>{});
+    else contract(IntC<MB>{});
+
+    // ---- this thread's pieces of the tile's y rows (16 bytes each) ----
+    constexpr int YP = 32 * (TN / 8) / NTD;                          // pieces per thread and block of 32 rows
+    uint4 yv[MB][YP];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < YP; ++i) {
+            const int q = tid + i * NTD, m = mb * 32 + q / (TN / 8), o = nt * TN + (q % (TN / 8)) * 8;
+            const int t = tokM[m];
+            yv[mb][i] = make_uint4(0, 0, 0, 0);
+            if (t >= 0 && o < a.d_out) yv[mb][i] = *(const uint4 *)(a.y + (int64_t)t * a.ldy + o);
+        }
 
     // ---- accumulators -> staging block (the tables are dead) -> y, whole 16-byte row pieces ----
     float *stg = (float *)lds;

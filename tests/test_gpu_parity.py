@@ -1647,6 +1647,24 @@ def test_moe_down_forms(M, oracle, form, T, K, E, S, r, d_in, d_out):
         M.set_tuning("moe_down_form", 0)
 
 
+@pytest.mark.parametrize("T,S,K,E,r", [(1, 1, 1, 9, 8), (32, 1, 2, 14, 8), (33, 1, 4, 12, 8), (96, 1, 3, 21, 4), (97, 1, 8, 15, 16),
+                                       (129, 1, 2, 40, 8), (200, 2, 4, 13, 16), (100, 3, 2, 10, 32), (65, 1, 2, 9, 64)])
+def test_moe_down_contraction_steps(M, oracle, T, S, K, E, r):
+    """The contraction in two launches: tiles at the edges of their blocks of 32 rows, part of a half chunk at the end, and steps
+    without a pair at either end, whose experts hold infinities that must not reach a token."""
+    c = W.moe_down_case(f"down_steps_{T}_{K}_{r}", 5900 + T + E, T, K, E - 4, 72, 136, S, r, 2.0 * r, std_a=0.05, std_b=0.05)
+    full = W.moe_down_case(f"down_steps_{T}_{K}_{r}_all", 5901 + T + E, T, K, E, 72, 136, S, r, 2.0 * r, std_a=0.05, std_b=0.05)
+    full.topk[:] = c.topk + 2
+    for e in [0, 1, E - 1] + ([E - 2] if r >= 16 or E % 2 == 0 else []):
+        full.B[:, e] = 0x7F80
+    site = moe_site(M, full)
+    M.set_tuning("moe_down_form", -1)
+    try:
+        check_moe_down(M, oracle, full, site)
+    finally:
+        M.set_tuning("moe_down_form", 0)
+
+
 @pytest.mark.parametrize("form", [1, -1])
 def test_moe_down_forms_on_dropped_pairs(M, oracle, form):
     """Pairs that the plan left out, in both forms."""
