@@ -107,7 +107,8 @@ __device__ __forceinline__ uint4 load_b_or_zero(__amdgpu_buffer_rsrc_t rsrc, uin
     else return make_uint4(__builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0), 0u, 0u, 0u);
 }
 
-template <int RP, int MB>
+// SHORT: with a loop of its own for tiles of up to 32 rows (see launch_moe_down_rp).
+template <int RP, int MB, bool SHORT>
 __global__ __launch_bounds__(NTD, 3)
 void moe_down_kernel(const MoeDownArgs a)
 {
@@ -270,12 +271,12 @@ void moe_down_kernel(const MoeDownArgs a)
     // Half a chunk is straight code, the operands PD (block, step) pairs ahead of the matrix instructions.  With a branch per
     // step and per block the LDS reads of each pair stayed behind it: a workgroup alone on its CU took 20 us for 5 us of
     // matrix instructions.  Rows of B of a dead step are zeros, blocks without a token read the vector of zeros; tiles of up
-    // to 32 rows, where that would be two thirds of the work, have their own loop.  Fetching half a chunk and y only
-    // behind the loop leaves 147 registers at rank 8, three workgroups per CU (a whole chunk and y in front: 230, two; held
-    // to 128, four, it spills 14 and is 4 % slower).  The down call, us before / after, 128 experts, top-8, rank 8,
-    // 768 -> 2048: 32 slots 2048 tokens 48.9 / 46.2, 4000 76.3 / 69.8, 8000 101.5 / 96.7; 8 slots 1000 tokens 30.3 / 23.9;
-    // one slot 500 tokens 26.1 / 21.0; 16 slots, rank 16, 8000 tokens 164.8 / 147.2; 8 slots of 64 experts, top-4, rank 64,
-    // 100 tokens 43.0 / 35.1.
+    // to 32 rows, where that would be two thirds of the work, may have their own loop.  Fetching half a chunk and y only
+    // behind the loop leaves 147 registers at rank 8, three workgroups per CU, or 128 and four without that loop (a whole
+    // chunk and y in front: 230, two; the loop held to 128 spills 14 and is 4 % slower).  The down call, us before / after,
+    // 128 experts, top-8, rank 8, 768 -> 2048: 32 slots 2048 tokens 49.5 / 46.4, 4000 76.0 / 61.7, 8000 100.5 / 95.5; 8 slots
+    // 1000 tokens 30.2 / 23.3; one slot 500 tokens 26.1 / 20.9; 16 slots, rank 16, 8000 tokens 160.4 / 142.7; 8 slots of 64
+    // experts, top-4, rank 64, 100 tokens 44.1 / 36.5.
     constexpr int PD = 2;
     auto consume = [&](auto nbc, auto st0c, auto bufc, uint32_t mask) __attribute__((always_inline)) {
         constexpr int NB = decltype(nbc)::value, st0 = decltype(st0c)::value, N = HST * NB, bi = decltype(bufc)::value;
@@ -305,7 +306,7 @@ void moe_down_kernel(const MoeDownArgs a)
             mask = next;
         }
     };
-    if (MB > 1 && rows <= 32) contract(IntC<1>{});
+    if (SHORT && rows <= 32) contract(IntC<1>{});
     else contract(IntC<MB>{});
 
     // ---- this thread's pieces of the tile's y rows (16 bytes each) ----
@@ -734,7 +735,7 @@ int moe_down_tile_rows(int r_pad, int K, int E) { return 32 * down_blocks(r_pad,
 int moe_down_tile_cols() { return TN; }
 int moe_down_max_k() { return KMAX; }
 
-template <int RP, int MB>
+template <int RP, int MB, bool SHORT>
 static hipError_t launch_moe_down_mb(const MoeDownArgs &a, hipStream_t st)
 {
     const int dyn = down_dyn_bytes(RP < 8 ? 8 : RP, 32 * MB, a.K, a.E);
@@ -743,22 +744,27 @@ static hipError_t launch_moe_down_mb(const MoeDownArgs &a, hipStream_t st)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!(allowed.load(std::memory_order_acquire) >> dev & 1u)) {
-        if (hipFuncSetAttribute((const void *)moe_down_kernel<RP, MB>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOne) != hipSuccess)
+        if (hipFuncSetAttribute((const void *)moe_down_kernel<RP, MB, SHORT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOne) != hipSuccess)
             return hipErrorUnknown;
         allowed.fetch_or(1ull << dev, std::memory_order_release);
     }
     const dim3 grid((unsigned)((int64_t)a.n_mtiles * a.n_ntiles)), block(NTD);
-    moe_down_kernel<RP, MB><<<grid, block, (size_t)dyn, st>>>(a);
+    moe_down_kernel<RP, MB, SHORT><<<grid, block, (size_t)dyn, st>>>(a);
     return hipGetLastError();
 }
 
 template <int RP>
 static hipError_t launch_moe_down_rp(const MoeDownArgs &a, hipStream_t st)
 {
+    // The loop for short tiles costs 20 registers, a fourth workgroup per CU: it is left out from 64 tokens per slot on, where
+    // few tiles are short.  The down call with / without it, us: 16 slots x 128 experts, top-2, rank 32, 12 tokens per slot 26.6 /
+    // 34.5; 32 x 64, top-8, rank 2, 22 per slot 14.3 / 18.4; 32 x 128, top-8, rank 8, 64 per slot 46.4 / 46.4, 94 54.6 / 51.7,
+    // 125 71.4 / 61.7, 250 94.7 / 95.5; 13 x 16, top-2, rank 4, 598 per slot 41.5 / 38.2.
+    const bool shorts = a.T < 64 * (int64_t)a.n_slots;
     switch (down_blocks(RP, a.K, a.E)) {
-        case 3: return launch_moe_down_mb<RP, 3>(a, st);
-        case 2: return launch_moe_down_mb<RP, 2>(a, st);
-        case 1: return launch_moe_down_mb<RP, 1>(a, st);
+        case 3: return shorts ? launch_moe_down_mb<RP, 3, true>(a, st) : launch_moe_down_mb<RP, 3, false>(a, st);
+        case 2: return shorts ? launch_moe_down_mb<RP, 2, true>(a, st) : launch_moe_down_mb<RP, 2, false>(a, st);
+        case 1: return launch_moe_down_mb<RP, 1, false>(a, st);
     }
     return hipErrorInvalidValue;
 }
