@@ -252,11 +252,15 @@ TileArgs tile_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int
     a.n_tiles = (int32_t)max_tiles(T, n_slots, tile_rows);
     a.tiles = pv.tiles; a.sorted = pv.sorted;
     const int32_t n_blk = (s->d.d_out + 63) / 64, n_steps = (s->d.d_in + 63) / 64;
-    // Parts per tile: as many as leave a CU for every workgroup (the bound on the tiles is about a quarter
-    // above what a batch with Zipf(1.1) slots has, hence 17 / 20).  A part sums all of d_in again unless the adapter's A is long: then the
+    // Parts per tile: as many as leave a CU for every workgroup.  The bound on the tiles is about a quarter above what a batch
+    // with Zipf(1.1) slots has, hence 17 / 20; a batch of few slots has nearly all of them, half a tile per slot beyond its
+    // full ones, and a few workgroups above the CUs cost a second round (rank 16, 2560 -> 2560, 1001 rows of 8 slots in 4
+    // parts 10.2 us, in 3 8.0; rank 8, 4096 -> 4096, 500 rows of 16 slots 9.3 / 7.2; the other way, 256 rows of one slot,
+    // q, k, v, 5.8 / 6.0).  A part sums all of d_in again unless the adapter's A is long: then the
     // parts divide d_in and trade sums, about a microsecond, what a CU needs for 40 KB.
     const bool trade = xch && s->r_pad * s->d.d_in >= 65536;
-    const int32_t live = trade ? a.n_tiles : std::max(1, (int32_t)((int64_t)a.n_tiles * 17 / 20));
+    const int32_t likely = std::max((int32_t)((int64_t)a.n_tiles * 17 / 20), T / tile_rows + std::min(n_slots, T) / 2);
+    const int32_t live = trade ? a.n_tiles : std::max(1, std::min(a.n_tiles, likely));
     int32_t parts = tuning(kTileParts) > 0 ? tuning(kTileParts) : cu_count(s->d.device) / (live * n_sites);
     const int32_t words = (tile_rows + 7) / 8 * 8 * std::max(s->r_pad, 8);
     // A part waits for every other one's words, four at a time: beyond 8 parts that costs more than a shorter slice of A
