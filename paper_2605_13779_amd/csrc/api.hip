@@ -1305,8 +1305,13 @@ int32_t moe_lora_apply_down(mlora_site *s, const mlora_plan *plan, const void *x
         d.tiles = plan->pv.tiles; d.tile_rows = plan->tile_rows;
         d.n_tiles = (int32_t)max_tiles(plan->items, (int64_t)plan->n_slots * plan->n_experts, plan->tile_rows);
     }
+    // Token by token, a workgroup stores its outputs while others still read x and the weights: only where y shares no
+    // bytes with them (in two launches everything but y has been read before y is written).
+    const int64_t pairs = plan->items;
+    const bool apart = !areas_meet(x, ldx, s->d.d_in, pairs, y, ldy, s->d.d_out, T) &&
+                       !areas_meet(pair_w, 2 * pairs, 2 * pairs, 1, y, ldy, s->d.d_out, T);
     const int32_t cus = cu_count(s->d.device);
-    if (moe_down_takes_tokens(T, plan->top_k, s->E, plan->n_slots, s->r_pad, s->d.d_in, s->d.d_out, cus))
+    if (apart && moe_down_takes_tokens(T, plan->top_k, s->E, plan->n_slots, s->r_pad, s->d.d_in, s->d.d_out, cus))
         return ok(launch_moe_down_token(d, cus, st)) ? MLORA_OK : MLORA_E_HIP;
     // first launch: per chunk of a (slot, expert) group, h = w * (alpha / r) * A x for the chunk's pairs
     if (moe_down_shrinks_by_wave(s->r_pad)) {

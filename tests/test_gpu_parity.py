@@ -1675,6 +1675,33 @@ def test_moe_down_forms_on_dropped_pairs(M, oracle, form):
         M.set_tuning("moe_down_form", 0)
 
 
+@pytest.mark.parametrize("form", [0, 1, -1])
+@pytest.mark.parametrize("K,d,ldy,start", [(1, 1032, 1032, 0), (1, 520, 520, 520), (2, 520, 1040, 0), (3, 264, 800, 0), (2, 136, 272, 136)])
+def test_moe_down_in_place(M, oracle, form, K, d, ldy, start):
+    """y among the rows of x: x itself, the next rows, one of a token's K rows, rows of another stride.  Every pair's x is read
+    before y is written."""
+    T, E, S, r = 40, 6, 3, 8
+    c = W.moe_down_case(f"down_in_place_{K}_{d}", 6000 + K + d + start, T, K, E, d, d, S, r, 2.0 * r, std_a=0.05, std_b=0.05)
+    room = max(T * K * d, start + (T - 1) * ldy + d)
+    bits = W.normal_bf16(W.rng(6001 + K + d), (room,), 1.0)
+    x0 = bits[:T * K * d].reshape(T * K, d).copy()
+    y0 = np.stack([bits[start + t * ldy:start + t * ldy + d] for t in range(T)])
+    ref = oracle.apply_moe_down(x0, y0, c.A, c.B, c.rank, c.alpha, c.topk, c.w, c.token_slot)
+    site, ts, w = moe_site(M, c), torch.from_numpy(c.token_slot).cuda(), torch.from_numpy(c.w).cuda()
+    plan = M.Plan(T * K, S * E)
+    M.moe_plan_route(plan, torch.from_numpy(c.topk).cuda(), ts, S, E)
+    ws = torch.empty(M.moe_down_workspace_bytes(T, K, d), dtype=torch.uint8, device="cuda")
+    buf = P.dev_bf16(bits)
+    y = buf.as_strided((T, d), (ldy, 1), start)
+    M.set_tuning("moe_down_form", form)
+    try:
+        M.moe_lora_apply_down(site, plan, buf[:T * K * d].view(T * K, d), w, ts, ws, y)
+        torch.cuda.synchronize()
+    finally:
+        M.set_tuning("moe_down_form", 0)
+    P.check_close(P.host_bits(y), ref, "in place")
+
+
 def test_moe_down_pairs_the_plan_left_out(M, oracle):
     """Pairs that the route plan drops must add nothing: expert ids outside [0, E) (masked or padded
     routing tables), and tokens whose slot was not ready at the site the plan was built against
