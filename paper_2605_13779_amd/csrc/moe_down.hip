@@ -551,7 +551,7 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = (int)blockIdx.x >> 3, g8 = q / parts, part = q - g8 * parts, t = g8 * 8 + ((int)blockIdx.x & 7);
     if (t >= a.T) return;
-    const int K = a.K, U = a.d_in >> 3;
+    const int K = a.K;
     const int64_t p0 = (int64_t)t * K;
     const int key_l = lane < K ? a.key_of[p0 + lane] : -1;
     const float w_l = lane < K ? a.pair_w[p0 + lane] : 0.f;
@@ -587,9 +587,10 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
     };
     const int o_lo = part * part_out, o_hi = min(a.d_out, o_lo + part_out);
     uint32_t bv[KB][BW];
-    uint16_t yv;
+    uint16_t yv = 0;
+    // (threads past the part's end share its last row of B; y there is another workgroup's to write, and is left alone)
     auto load_b = [&](int o, int kb) __attribute__((always_inline)) {
-        const uint32_t ob = (uint32_t)min(o, a.d_out - 1) * (uint32_t)(RP * 2);
+        const uint32_t ob = (uint32_t)min(o, o_hi - 1) * (uint32_t)(RP * 2);
 #pragma unroll
         for (int i = 0; i < KB; ++i) {
             const char *src = (const char *)a.b_tab + (int64_t)key_at(min(kb + i, KMAX - 1)) * a.d_out * (RP * 2) + ob;
@@ -600,7 +601,7 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
             else if constexpr (RP == 2) bv[i][0] = *(const uint32_t *)src;
             else bv[i][0] = *(const uint16_t *)src;
         }
-        if (kb == 0) yv = a.y[(int64_t)t * a.ldy + min(o, a.d_out - 1)];
+        if (kb == 0 && o < o_hi) yv = a.y[(int64_t)t * a.ldy + o];
     };
     const uint32_t u_first = (uint32_t)(slice * 64 + lane) * 16u;
     load_ax(w % K, u_first);

@@ -1628,11 +1628,13 @@ def test_moe_down_shrink_in_tiles(M, oracle, r, d_in, q):
 @pytest.mark.parametrize("form", [1, -1])
 @pytest.mark.parametrize("T,K,E,S,r,d_in,d_out", [(1, 1, 1, 1, 8, 8, 8), (9, 3, 6, 4, 8, 520, 136), (37, 2, 4, 3, 8, 1032, 200), (300, 2, 5, 2, 8, 136, 200),
                                                   (20, 7, 16, 3, 4, 72, 1096), (64, 8, 8, 2, 16, 2056, 72), (12, 5, 12, 2, 2, 264, 648),
-                                                  (50, 3, 6, 4, 1, 136, 520), (33, 16, 24, 2, 8, 136, 72), (17, 9, 16, 2, 16, 520, 1032), (260, 4, 40, 2, 16, 136, 200)])
+                                                  (50, 3, 6, 4, 1, 136, 520), (33, 16, 24, 2, 8, 136, 72), (17, 9, 16, 2, 16, 520, 1032), (260, 4, 40, 2, 16, 136, 200),
+                                                  (3, 8, 8, 1, 8, 136, 2056), (30, 4, 8, 2, 4, 72, 1032)])
 def test_moe_down_forms(M, oracle, form, T, K, E, S, r, d_in, d_out):
     """The down projection token by token (1) and in two launches (-1), whatever the rule would take: d_in of one piece, of part of a
     wave's pieces and of several flights, outputs that leave parts and passes ragged, fewer pairs than waves, an odd number of
-    them and more, tokens that the grid's rounding adds, every padded rank, an empty slot, rows without adapter."""
+    them and more, parts of fewer outputs than threads, tokens that the grid's rounding adds, every padded rank, an empty slot, rows
+    without adapter."""
     ranks = [r] * S
     if S > 2:
         ranks[1] = 0
