@@ -527,7 +527,7 @@ static void launch_moe_down_shrink_tile(const MoeDownArgs &a, hipStream_t st)
 // Both halves in one launch, token by token, for batches with few pairs per adapter (decode steps; see
 // moe_down_takes_tokens).  A workgroup owns one token and a range of outputs: its waves take the token's pairs,
 // h = w * (alpha / r) * A x per pair (dot products, one transposing reduction over the wave) meets in LDS, and a
-// thread per output adds the K deltas in fp32, in order of k.  Of the plan it needs the pairs' keys only.  It is bound
+// thread per output adds the K deltas in fp32, in order of expert id.  Of the plan it needs the pairs' keys only.  It is bound
 // by one chain, launch -> keys -> rows of A, x and the first B -> sums -> outputs, where the two launches pay two
 // and a dense form whose tiles hold a token or two each.  Parts of a token sum its A again; they sit on one XCD and
 // find it in L2.  Expert layers of 128 experts x 32 slots, rank 8, 768 -> 2048, top-8, the down call: 48 tokens
@@ -546,7 +546,7 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
     constexpr int F = RP <= 8 ? 2 : 1;             // 16-byte units of d_in per lane and flight
     constexpr int BW = (RP + 1) / 2;               // words of an output's B row
     __shared__ float hs[KMAX * RP];
-    __shared__ float hp[NW * RP];
+    __shared__ float hp[NW * RP], hw[NW];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = (int)blockIdx.x >> 3, g8 = q / parts, part = q - g8 * parts, t = g8 * 8 + ((int)blockIdx.x & 7);
@@ -554,6 +554,7 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
     const int K = a.K;
     const int64_t p0 = (int64_t)t * K;
     const int key_l = lane < K ? a.key_of[p0 + lane] : -1;
+    const int key_i = lane >> 3 < K ? a.key_of[p0 + (lane >> 3)] : -1, key_j = (lane & 7) < K ? a.key_of[p0 + (lane & 7)] : -1;
     const float w_l = lane < K ? a.pair_w[p0 + lane] : 0.f;
     const uint32_t valid = (uint32_t)__ballot(key_l >= 0);               // (K <= 16)
     if (valid == 0) return;                                              // the plan left the token out
@@ -585,6 +586,7 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
             for (int j = 0; j < RP; ++j) acc[j] = dot8(xz, av[f][j], acc[j]);
         }
     };
+    int key_o;                                     // lane i: the key of the pair that is added i-th
     const int o_lo = part * part_out, o_hi = min(a.d_out, o_lo + part_out);
     uint32_t bv[KB][BW];
     uint16_t yv = 0;
@@ -593,7 +595,7 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
         const uint32_t ob = (uint32_t)min(o, o_hi - 1) * (uint32_t)(RP * 2);
 #pragma unroll
         for (int i = 0; i < KB; ++i) {
-            const char *src = (const char *)a.b_tab + (int64_t)key_at(min(kb + i, KMAX - 1)) * a.d_out * (RP * 2) + ob;
+            const char *src = (const char *)a.b_tab + (int64_t)__builtin_amdgcn_readlane(key_o, min(kb + i, KMAX - 1)) * a.d_out * (RP * 2) + ob;
             if constexpr (RP >= 8) {
 #pragma unroll
                 for (int u = 0; u < RP / 8; ++u) { const uint4 v = ((const uint4 *)src)[u]; bv[i][4 * u] = v.x; bv[i][4 * u + 1] = v.y; bv[i][4 * u + 2] = v.z; bv[i][4 * u + 3] = v.w; }
@@ -605,6 +607,30 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
     };
     const uint32_t u_first = (uint32_t)(slice * 64 + lane) * 16u;
     load_ax(w % K, u_first);
+    // The deltas are added in order of expert id, and of pairs of one expert the first alone, as in the two launches: lane i
+    // takes the pair whose key comes i-th (pairs left out last).  On the way of A's first rows, which take longer; up to
+    // eight pairs meet in one comparison, lane 8 * i + j with j-th against i-th key.
+    int at = lane, key_once = -1;
+    if (K <= 8) {
+        const int i = lane >> 3, j = lane & 7;
+        const bool twin = key_j == key_i && j < i;
+        const uint64_t less = __ballot((uint32_t)key_j < (uint32_t)key_i || twin), twins = __ballot(twin);
+        if (lane < 8) {
+            at = __popc((uint32_t)(less >> (8 * lane)) & 0xffu);
+            if (!((uint32_t)(twins >> (8 * lane)) & 0xffu)) key_once = key_l;
+        }
+    } else {
+        if (lane < K) { at = 0; key_once = key_l; }
+        for (int j = 0; j < K; ++j) {
+            const int kj = __builtin_amdgcn_readlane(key_l, j);
+            const bool twin = kj == key_l && j < lane;
+            if (lane < K && ((uint32_t)kj < (uint32_t)key_l || twin)) ++at;
+            if (twin) key_once = -1;
+        }
+    }
+    key_o = __builtin_amdgcn_ds_permute(at * 4, key_once);
+    const uint32_t added = (uint32_t)__ballot(key_o >= 0);
+    if (key_o < 0) key_o = key_v;
     if constexpr (RP <= 8) load_b(o_lo + tid, 0);
     const int r_s = a.rank[s];
     const float scale = a.scale[s];
@@ -619,8 +645,9 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
         const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_l), k));
         if (lane < RP) {
             const int j = bitrev<Log2<RP>::v>(lane);
-            if (n_sl == 1) hs[k * RP + j] = acc[0] * scale * wk;
-            else hp[w * RP + j] = acc[0];
+            const int pos = __builtin_amdgcn_readlane(at, k);
+            if (n_sl == 1) hs[pos * RP + j] = acc[0] * scale * wk;
+            else { hp[(slice * K + pos) * RP + j] = acc[0]; hw[pos] = wk; }
         }
     }
     if constexpr (RP > 8) load_b(o_lo + tid, 0);
@@ -631,7 +658,7 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
             const int k = tid / RP, j = tid - k * RP;
             float v = 0.f;
             for (int i = 0; i < n_sl; ++i) v += hp[(i * K + k) * RP + j];
-            hs[tid] = v * scale * a.pair_w[p0 + k];
+            hs[tid] = v * scale * hw[k];
         }
         __syncthreads();
     }
@@ -643,7 +670,7 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
             if (kb > 0) load_b(o, kb);
 #pragma unroll
             for (int i = 0; i < KB; ++i) {
-                if (!(valid >> (kb + i) & 1u)) continue;
+                if (!(added >> (kb + i) & 1u)) continue;
                 const float *h = hs + (kb + i) * RP;
 #pragma unroll
                 for (int j = 0; j < RP; ++j) sum += h[j] * (j & 1 ? bf_hi(bv[i][j >> 1]) : bf_lo(bv[i][j >> 1]));

@@ -1677,6 +1677,49 @@ def test_moe_down_forms_on_dropped_pairs(M, oracle, form):
         M.set_tuning("moe_down_form", 0)
 
 
+@pytest.mark.parametrize("form", [1, -1])
+@pytest.mark.parametrize("K,r", [(2, 8), (3, 2), (8, 8), (8, 16), (11, 4), (16, 8)])
+def test_moe_down_order_of_the_sum(M, oracle, form, K, r):
+    """A token's deltas are added in order of expert id: the same bits whatever the order of its top-k entries, some of which
+    the plan leaves out.  Of two entries on one expert one is added."""
+    T, E, S, d_in, d_out = 60, 20, 3, 264, 200
+    c = W.moe_down_case(f"down_order_{K}_{r}", 6050 + K + r, T, K, E, d_in, d_out, S, r, 2.0 * r, std_a=0.05, std_b=0.05)
+    site = moe_site(M, c)
+    topk = c.topk.copy()
+    topk[::5, K // 2] = -1
+    ts = torch.from_numpy(c.token_slot).cuda()
+
+    def run(topk, x, w):
+        plan = M.Plan(T * K, S * E)
+        M.moe_plan_route(plan, torch.from_numpy(topk).cuda(), ts, S, E)
+        ws, y = torch.empty(M.moe_down_workspace_bytes(T, K, d_out), dtype=torch.uint8, device="cuda"), P.dev_bf16(c.y0)
+        M.moe_lora_apply_down(site, plan, P.dev_bf16(x), torch.from_numpy(w).cuda(), ts, ws, y)
+        torch.cuda.synchronize()
+        return P.host_bits(y)
+    M.set_tuning("moe_down_form", form)
+    try:
+        as_given = run(topk, c.x, c.w)
+        perm = np.argsort(W.rng(6051).random((T, K)), axis=1)
+        x = c.x.reshape(T, K, d_in)
+        other = run(*(np.ascontiguousarray(np.take_along_axis(v, q, 1)).reshape(shape) for v, q, shape in
+                      ((topk, perm, (T, K)), (x, perm[:, :, None], (T * K, d_in)), (c.w, perm, (T, K)))))
+        assert np.array_equal(as_given, other)
+        twice = c.topk.copy()
+        twice[:, K - 1] = twice[:, 0]                  # entries 0 and K - 1 on one expert
+        got = P.widen(run(twice, c.x, c.w))
+    finally:
+        M.set_tuning("moe_down_form", 0)
+    refs = []
+    for drop in (0, K - 1):
+        w = c.w.copy()
+        w[:, drop] = 0.0
+        refs.append(oracle.apply_moe_down(c.x, c.y0, c.A, c.B, c.rank, c.alpha, twice, w, c.token_slot))
+    near = [np.abs(got - ref) <= P.ATOL + P.RTOL * np.abs(ref) for ref in refs]
+    assert (near[0] | near[1]).all()
+    both = oracle.apply_moe_down(c.x, c.y0, c.A, c.B, c.rank, c.alpha, twice, c.w, c.token_slot)
+    assert not (np.abs(both - refs[0]) <= P.ATOL + P.RTOL * np.abs(both)).all(), "a sum of both must show"
+
+
 @pytest.mark.parametrize("form", [0, 1, -1])
 @pytest.mark.parametrize("K,d,ldy,start", [(1, 1032, 1032, 0), (1, 520, 520, 520), (2, 520, 1040, 0), (3, 264, 800, 0), (2, 136, 272, 136)])
 def test_moe_down_in_place(M, oracle, form, K, d, ldy, start):
