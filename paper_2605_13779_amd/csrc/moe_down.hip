@@ -681,14 +681,21 @@ void moe_down_token_kernel(const MoeDownArgs a, const int parts, const int part_
     }
 }
 
+// Parts of a token and the outputs of each: one workgroup per CU (48 tokens in 2, 4, 5 and 6 parts: 7.4, 7.5, 7.6 and 10.4 us), at
+// least two waves of outputs each.
+struct TokenParts { int parts, outs; };
+static TokenParts token_parts(int T, int d_out, int cus)
+{
+    const int want = std::max(1, std::min(cus / T, (d_out + 127) / 128));
+    const int outs = ((d_out + want - 1) / want + 63) / 64 * 64;
+    return {(d_out + outs - 1) / outs, outs};
+}
+
 template <int RP, int KB>
 static hipError_t launch_moe_down_token_kb(const MoeDownArgs &a, int cus, hipStream_t st)
 {
-    // one workgroup per CU (48 tokens in 2, 4, 5 and 6 parts: 7.4, 7.5, 7.6 and 10.4 us), at least two waves of outputs each
-    int parts = std::max(1, std::min(cus / a.T, (a.d_out + 127) / 128));
-    const int part_out = ((a.d_out + parts - 1) / parts + 63) / 64 * 64;
-    parts = (a.d_out + part_out - 1) / part_out;
-    moe_down_token_kernel<RP, KB><<<dim3((unsigned)((a.T + 7) / 8 * 8 * parts)), dim3(kTokThreads), 0, st>>>(a, parts, part_out);
+    const TokenParts p = token_parts(a.T, a.d_out, cus);
+    moe_down_token_kernel<RP, KB><<<dim3((unsigned)((a.T + 7) / 8 * 8 * p.parts)), dim3(kTokThreads), 0, st>>>(a, p.parts, p.outs);
     return hipGetLastError();
 }
 
@@ -700,21 +707,31 @@ static hipError_t launch_moe_down_token_rp(const MoeDownArgs &a, int cus, hipStr
     return launch_moe_down_token_kb<RP, (RP == 16 ? 4 : 8)>(a, cus, st);
 }
 
-// Whether a down call goes token by token.  What the two forms take, in us and MB, from a sweep of 50 calls (ranks 2 to 16,
-// 8 to 128 experts, top-1 to top-8, 100 to 1500 tokens): token by token, per round of one token per CU, 3 (4.5 at rank
-// 16, whose B rows come in two flights) and its adapters, fetched for every pair, at 6.5 TB/s; in two launches 9,
-// an eighth per expert up to 64, and the distinct adapters at 5.9 TB/s.  128 experts x 32 slots, top-8, rank 8, two
-// launches / token by token: 300 tokens 33.0 / 25.8 us, 500 40.8 / 31.5, 600 42.4 / 41.4, 800 46.4 / 54.4; rank 16, 300
-// tokens 41.3 / 44.9; 8 experts, top-4, rank 8, 200 tokens 11.3 / 9.4, 300 11.9 / 15.3.
+// Whether a down call goes token by token: the estimated time of both forms, in us, fitted to 1960 pairs of calls on cold tables
+// (140 sites of ranks 1 to 16, 1 to 128 experts, top-1 to top-12, 1 to 32 slots, 1 to 1000 tokens).  Token by token: a round per workgroup
+// that a CU runs at a time (two up to rank 4), a flight of B per 512 outputs, the distinct adapters and, from the caches,
+// those of every pair; one chain, so little where tokens are few.  In two launches: two chains, a chunk of the contraction
+// after the other, distinct adapters and rows.  Beyond a token per CU the estimate of the rounds is coarser, and the new form
+// has to be 8 % ahead.  Over these calls the choice takes 0.6 % more than the better form each time (at most 5 % more
+// in 97 of 100; slower than two launches by more than 3 % in 18, at most 1.34 times, 1000 tokens on one expert).  Two launches / token by
+// token: 128 experts x 32 slots, top-8, 768 -> 2048, rank 8, 1 token 11.3 / 5.1, 48 17.6 / 7.0, 200 27.8 / 15.3, 300 33.0 / 27.0, 800
+// 46.0 / 54.0; rank 16, 100 tokens 23.9 / 13.4, 300 36.6 / 42.5; 16 experts, top-4, rank 8, 1024 -> 4096, 64 tokens 11.0 / 7.5,
+// 200 11.6 / 12.3.
 bool moe_down_takes_tokens(int T, int K, int E, int n_slots, int r_pad, int d_in, int d_out, int cus)
 {
     const int form = tuning(kMoeDownForm);
     if (r_pad > 16 || form < 0) return false;
     if (form > 0) return true;
     if (tuning(kTileMoeRows) > 0) return false;                          // (tiles asked for)
-    const double mb = 2e-6 * r_pad * ((double)d_in + d_out), pairs = (double)T * K, keys = (double)n_slots * E;
-    const double rounds = std::max(1.0, (double)T / cus + 0.2), distinct = keys * -std::expm1(-pairs / keys);
-    return rounds * ((r_pad == 16 ? 4.5 : 3.0) + mb * K * cus / 6.5) < 9.0 + std::min(E, 64) / 8.0 + 0.17 * mb * distinct;
+    const TokenParts p = token_parts(T, d_out, cus);
+    const int per_cu = r_pad <= 4 ? 2 : 1, chunks = (E * std::max(r_pad, 8) + CHK - 1) / CHK;
+    const double rounds = std::ceil((double)T * p.parts / (cus * per_cu)), flights = (p.outs + kTokThreads - 1) / kTokThreads;
+    const double pairs = (double)T * K, keys = (double)n_slots * E;
+    const double adapter_mb = 2e-6 * r_pad * ((double)d_in + d_out), distinct_mb = adapter_mb * keys * -std::expm1(-pairs / keys);
+    const double x_mb = 2e-6 * pairs * d_in, y_mb = 4e-6 * T * d_out;
+    const double token = 3.5 + rounds * (1.9 + 0.2 * flights) + 0.115 * distinct_mb + 0.062 * (pairs * adapter_mb + x_mb);
+    const double two = 7.3 + 0.8 * chunks + 0.1 * distinct_mb + 0.35 * (x_mb + y_mb) + 1.7e-4 * r_pad * d_in;
+    return token < (T <= cus ? 1.0 : 0.92) * two;
 }
 
 hipError_t launch_moe_down_token(const MoeDownArgs &a, int cus, hipStream_t st)

@@ -160,3 +160,25 @@ def test_one_thread_reads_the_launch_tag():
     sums = text["tile_body.h"]
     sums = sums[sums.index("auto sums_to_lds ="):]
     assert "__syncthreads();" in sums[:sums.index("};")]
+
+
+def test_down_form_for_few_tokens(lib):
+    """The down projection's choice of form (host code): a decode step of few tokens always goes token by token up to rank
+    16, and up to a token per CU the choice never flips back as tokens get fewer.  Large batches keep the two launches."""
+    takes = lib._ZN5mlora21moe_down_takes_tokensEiiiiiiii
+    takes.restype, takes.argtypes = C.c_bool, [C.c_int] * 8
+    rng = np.random.default_rng(5)
+    cus = 256
+    for _ in range(300):
+        E = int(rng.choice([1, 2, 4, 8, 16, 32, 64, 128, 200]))
+        K, S, r = int(rng.integers(1, min(E, 16) + 1)), int(rng.integers(1, 65)), int(rng.choice([1, 2, 4, 8, 16]))
+        d_in, d_out = 8 * int(rng.integers(1, 257)), 8 * int(rng.integers(1, 513))
+        by_token = [takes(T, K, E, S, r, d_in, d_out, cus) for T in range(1, cus + 1)]
+        assert all(by_token[:8]), (K, E, S, r, d_in, d_out)
+        assert by_token == sorted(by_token, reverse=True), (K, E, S, r, d_in, d_out)
+        assert not takes(100, K, E, S, 32, d_in, d_out, cus)
+    for r in (8, 16):
+        for T in (1, 2, 3, 4, 48, 100):
+            assert takes(T, 8, 128, 32, r, 768, 2048, cus) and takes(T, 8, 128, 16, r, 1536, 4096, cus)
+        assert not takes(2048, 8, 128, 32, r, 768, 2048, cus)
+    assert takes(64, 4, 16, 8, 8, 1024, 4096, cus) and not takes(256, 4, 16, 8, 8, 1024, 4096, cus)
