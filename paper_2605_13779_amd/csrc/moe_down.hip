@@ -801,11 +801,14 @@ static hipError_t launch_moe_down_mb(const MoeDownArgs &a, hipStream_t st)
 template <int RP>
 static hipError_t launch_moe_down_rp(const MoeDownArgs &a, hipStream_t st)
 {
-    // The loop for short tiles costs 20 registers, a fourth workgroup per CU: it is left out from 64 tokens per slot on, where
-    // few tiles are short.  The down call with / without it, us: 16 slots x 128 experts, top-2, rank 32, 12 tokens per slot 26.6 /
-    // 34.5; 32 x 64, top-8, rank 2, 22 per slot 14.3 / 18.4; 32 x 128, top-8, rank 8, 64 per slot 46.4 / 46.4, 94 54.6 / 51.7,
-    // 125 71.4 / 61.7, 250 94.7 / 95.5; 13 x 16, top-2, rank 4, 598 per slot 41.5 / 38.2.
-    const bool shorts = a.T < 64 * (int64_t)a.n_slots;
+    // The loop for short tiles is left out where slots average 112 tokens, so that few tiles are short: up to rank 8, where it costs
+    // the fourth workgroup per CU, that gives a few percent, above 8 it is even.  Below, popular slots leave many short
+    // tiles behind.  The down call on cold tables with / without it, us, 32 slots of Zipf(1.1) popularity and all alike, top-8, 768 -> 2048:
+    // 64 experts, rank 8, 64 tokens per slot 32.0 / 33.7 and 31.8 / 32.0, 94 39.3 / 37.8 and 37.5 / 37.4, 125 44.4 / 41.8 and
+    // 44.2 / 42.1, 250 66.7 / 64.7 and 63.1 / 63.3; 128 experts, rank 4, 94 44.3 / 50.2 and 43.7 / 44.1; rank 16, 64 78.1 / 89.9 and
+    // 88.7 / 88.9, 94 96.7 / 100.4 and 107.2 / 104.4, 188 145.5 / 143.1 and 138.3 / 135.2.  8 slots of 64 experts, top-4, rank 64, alike, 64
+    // 56.1 / 56.2, 125 96.7 / 92.3.
+    const bool shorts = a.T < 112 * (int64_t)a.n_slots;
     switch (down_blocks(RP, a.K, a.E)) {
         case 3: return shorts ? launch_moe_down_mb<RP, 3, true>(a, st) : launch_moe_down_mb<RP, 3, false>(a, st);
         case 2: return shorts ? launch_moe_down_mb<RP, 2, true>(a, st) : launch_moe_down_mb<RP, 2, false>(a, st);

@@ -1667,6 +1667,23 @@ def test_moe_down_contraction_steps(M, oracle, T, S, K, E, r):
         M.set_tuning("moe_down_form", 0)
 
 
+@pytest.mark.parametrize("T", [335, 336])
+@pytest.mark.parametrize("K,E,r", [(2, 10, 8), (2, 10, 4), (2, 10, 2), (2, 10, 1), (2, 10, 16), (2, 10, 32), (4, 6, 64), (12, 130, 8)])
+def test_moe_down_short_and_full_tiles(M, oracle, K, E, r, T):
+    """Slots with a few full tiles, tiles at the edges of 32 rows and a token or two, below and from the mean number of tokens
+    per slot at which the contraction does without its loop for short tiles; tiles of 96 and of 64 rows."""
+    c = W.moe_down_case(f"down_short_{K}_{r}_{T}", 5950 + K + r + T, T, K, E, 72, 136, 3, r, 2.0 * r, std_a=0.05, std_b=0.05)
+    c.token_slot[:] = 0
+    c.token_slot[5:38] = 1                             # 33 tokens, 2 tokens, the rest: three full tiles and one of 12 or 13
+    c.token_slot[100:102] = 2
+    site = moe_site(M, c)
+    M.set_tuning("moe_down_form", -1)
+    try:
+        check_moe_down(M, oracle, c, site)
+    finally:
+        M.set_tuning("moe_down_form", 0)
+
+
 @pytest.mark.parametrize("form", [1, -1])
 def test_moe_down_forms_on_dropped_pairs(M, oracle, form):
     """Pairs that the plan left out, in both forms."""
