@@ -578,6 +578,33 @@ def test_decode_tiles(M, oracle, r, d_in, d_out, q):
     site.check()
 
 
+@pytest.mark.parametrize("T,S,r", [(64, 1, 8), (64, 4, 16), (101, 6, 8), (256, 1, 16), (250, 3, 32), (530, 2, 4), (700, 12, 8)])
+@pytest.mark.parametrize("planned", [False, True])
+def test_parts_of_sites_of_unequal_widths(M, oracle, T, S, r, planned):
+    """Sites of 18, 9, 2 and 1 blocks of 64 outputs in one launch, each cut into the parts that the launch has room for: the bits of
+    one part per tile."""
+    cs = [W.dense_case(f"parts{i}_{T}_{r}", 7300 + T + r + i, T, 136, o, S, r, 2.0 * r, std_a=0.05, std_b=0.05) for i, o in enumerate((1096, 520, 136, 48))]
+    sites, ts = [dense_site(M, c) for c in cs], torch.from_numpy(cs[0].token_slot).cuda()
+    x, plan = P.dev_bf16(cs[0].x), M.Plan(T, S)
+    outs = []
+    for parts in (0, 1, 3):
+        M.set_tuning("tile_parts", parts)
+        try:
+            ys = [P.dev_bf16(c.y0) for c in cs]
+            if planned:
+                M.lora_plan_decode(plan, ts, S)
+                M.lora_apply_decode_multi(sites, plan, [x] * 4, ys)
+            else:
+                M.lora_plan_apply_decode_multi(sites, plan, ts, S, [x] * 4, ys)
+            torch.cuda.synchronize()
+            outs.append([P.host_bits(y) for y in ys])
+        finally:
+            M.set_tuning("tile_parts", 0)
+    for i, c in enumerate(cs):
+        P.check_close(outs[0][i], oracle.apply_decode(cs[0].x, c.y0, c.A, c.B, c.rank, c.alpha, cs[0].token_slot), f"site {i}")
+        assert np.array_equal(outs[0][i], outs[1][i]) and np.array_equal(outs[0][i], outs[2][i])
+
+
 def _plan_tiles(plan, max_items, n_keys):
     """The tile records of a plan buffer (behind everything else, 16-byte aligned)."""
     chunks = (max_items + 3 * min(n_keys, max_items)) // 4
