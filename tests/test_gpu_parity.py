@@ -1598,6 +1598,14 @@ def run_moe_down(M, site, c, y0_bits):
     return P.host_bits(y)
 
 
+@pytest.fixture(params=[1, -1], ids=["token by token", "two launches"])
+def down_form(M, request):
+    """Every test that takes this runs in both forms of the down projection (ranks above 16 have the second one only)."""
+    M.set_tuning("moe_down_form", request.param)
+    yield request.param
+    M.set_tuning("moe_down_form", 0)
+
+
 def check_moe_down(M, oracle, c, site, tokens=None, report=None):
     sel = np.arange(c.T) if tokens is None else np.asarray(tokens)
     pairs = (sel[:, None] * c.K + np.arange(c.K)[None, :]).reshape(-1)
@@ -1621,7 +1629,7 @@ def check_moe_down(M, oracle, c, site, tokens=None, report=None):
 @pytest.mark.parametrize("T,K,E,S,r", [(37, 2, 4, 3, 8), (200, 4, 16, 5, 4), (64, 8, 8, 2, 16), (9, 1, 1, 2, 2), (50, 3, 6, 4, 1),
                                        (300, 2, 5, 2, 8), (70, 2, 4, 2, 32), (40, 2, 3, 2, 64), (260, 4, 40, 2, 16),
                                        (300, 2, 4, 70, 8), (64, 4, 300, 2, 8), (33, 16, 520, 1, 4)])
-def test_moe_down_small(M, oracle, T, K, E, S, r):
+def test_moe_down_small(M, oracle, down_form, T, K, E, S, r):
     """Down projection with the routing-weight combine: ragged widths, tokens without adapter, an
     empty slot, K from 1 to 16, every padded rank, odd expert counts (a half-filled last contraction
     step), slots with more tokens than one tile holds, several chunks of the contraction axis, more
@@ -1690,6 +1698,20 @@ def test_moe_down_contraction_steps(M, oracle, T, S, K, E, r):
     M.set_tuning("moe_down_form", -1)
     try:
         check_moe_down(M, oracle, full, site)
+    finally:
+        M.set_tuning("moe_down_form", 0)
+
+
+@pytest.mark.parametrize("T,S,K,E,r", [(230, 2, 16, 200, 16), (150, 2, 16, 40, 16), (230, 2, 8, 40, 32), (150, 2, 8, 40, 32), (230, 2, 8, 900, 8), (100, 1, 16, 520, 2),
+                                       (230, 2, 16, 40, 32), (150, 2, 16, 24, 32), (100, 2, 16, 520, 16), (200, 2, 8, 1500, 4), (500, 130, 3, 12, 8), (700, 65, 2, 5, 1)])
+def test_moe_down_heights_of_tiles(M, oracle, T, S, K, E, r):
+    """The contraction in two launches with tiles of 64 rows (the first six) and of 32 (the next four) at ranks up to 32, and
+    the search for a tile beyond 64 and 128 slots."""
+    c = W.moe_down_case(f"down_heights_{T}_{K}_{E}_{r}", 5980 + T + K + r, T, K, E, 72, 136, S, r, 2.0 * r, std_a=0.05, std_b=0.05)
+    site = moe_site(M, c)
+    M.set_tuning("moe_down_form", -1)
+    try:
+        check_moe_down(M, oracle, c, site)
     finally:
         M.set_tuning("moe_down_form", 0)
 
@@ -1837,7 +1859,7 @@ def test_moe_down_pairs_the_plan_left_out(M, oracle):
 
 
 @pytest.mark.parametrize("seed", [1, 2])
-def test_moe_down_random_routing(M, oracle, seed):
+def test_moe_down_random_routing(M, oracle, down_form, seed):
     """Down projection over seeded draws of token count, expert count (up to 200), top-k (up to 16), slot
     count (up to 40, so that many slots hold no or one token), rank, widths; tokens without a slot,
     empty slots, and masked routing entries (ids of -1 and ids past the last expert), which must add
@@ -1881,7 +1903,7 @@ def test_moe_down_random_routing(M, oracle, seed):
         site.close()
 
 
-def test_moe_step_graph_replay_with_changing_routing(M, oracle):
+def test_moe_step_graph_replay_with_changing_routing(M, oracle, down_form):
     """Route plan, gate projection in place on the pair rows and down projection with the combine,
     captured once and replayed: the planner's counters must be back at zero for every replay and
     nothing may survive from the routing of the replay before.  The routing, the slots and the
@@ -1925,7 +1947,7 @@ def test_moe_step_graph_replay_with_changing_routing(M, oracle):
         P.check_close(P.host_bits(yd), ref_d, f"down, replay {rep}")
 
 
-def test_moe_down_limits(M, oracle):
+def test_moe_down_limits(M, oracle, down_form):
     """Sixteen experts per token is the most the down projection takes; more is refused before any launch."""
     c = W.moe_down_case("down_k16", 5395, 40, 16, 32, 72, 136, 3, 4, 8.0, std_a=0.05, std_b=0.05)
     check_moe_down(M, oracle, c, moe_site(M, c))
