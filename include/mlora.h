@@ -214,15 +214,21 @@ int32_t moe_lora_apply_multi(mlora_site *const *sites, int32_t n_sites, const ml
  *   pair_w: DEVICE fp32 [T, K];  token_slot: DEVICE int32[T], the array given to moe_plan_route
  *   (the plan already holds the grouping of the tokens by slot; the argument is checked, not read);
  *   workspace: DEVICE, moe_down_workspace_bytes(T, K, d_out) bytes (T * K * MLORA_MAX_RANK 32-bit
- *   words), 16-byte aligned, overwritten.
- * Two launches.  The first leaves in the workspace, for every pair of the plan, the rank-r vector
- * h[p] = pair_w[p] * (alpha / r) * A x[p] as bf16 head and tail (one wave per chunk of up to four
- * pairs of a (slot, expert) group, or per tile of up to 16 where the plan holds tiles; those of a group
- * run side by side, so an adapter's A rows leave memory once).  The second is, per slot, the dense contraction
- * Y_s += H_s * Bcat_s on the matrix cores: H_s holds h[(t, k)] in the r columns of expert e(t, k)
- * of row t, Bcat_s is the slot's per-expert B tensors stacked along the contraction axis, as the
- * packed tables store them.  Pairs that the plan left out (expert ids outside [0, n_experts), slots
- * not ready when the plan was built) add nothing, whatever the workspace holds.
+ *   words), 16-byte aligned; it may be overwritten, and nothing in it matters before or after the call.
+ * Two forms; the call's sizes choose (tokens, K, experts, slots, rank, widths), so a token's sum may round differently in
+ * batches of different size.  Both leave the same result up to the order of the fp32 partial sums inside a pair's
+ * delta and, in two launches, the rounding of h to bf16 head and tail.
+ *   Few pairs per adapter, rank up to 16, y apart from x and pair_w in memory: one launch, a workgroup per
+ *   token (or per range of its outputs) shrinks and expands the token's K pairs.
+ *   Else two launches.  The first leaves in the workspace, for every pair of the plan, the rank-r vector
+ *   h[p] = pair_w[p] * (alpha / r) * A x[p] as bf16 head and tail (one wave per chunk of up to four
+ *   pairs of a (slot, expert) group, or per tile of up to 16 where the plan holds tiles; those of a group
+ *   run side by side, so an adapter's A rows leave memory once).  The second is, per slot, the dense contraction
+ *   Y_s += H_s * Bcat_s on the matrix cores: H_s holds h[(t, k)] in the r columns of expert e(t, k)
+ *   of row t, Bcat_s is the slot's per-expert B tensors stacked along the contraction axis, as the
+ *   packed tables store them.
+ * Pairs that the plan left out (expert ids outside [0, n_experts), slots not ready when the plan was built) add nothing,
+ * whatever the workspace holds.  y may lie among the rows of x: x is read as it was before the call.
  * A token's K expert ids must be distinct (as a top-k routing gives them): of two pairs of one token
  * on the same expert only one would be added.
  * Limits: K <= 16, and 32 * (n_experts + 4 * K * max(r_pad, 8)) bytes of tables must fit the LDS

@@ -17,9 +17,9 @@
 // tokens per (slot, expert) group nearly every expert's block is touched), so it runs on
 // v_mfma_f32_32x32x16_bf16, and it has what the row-by-row form lacks: every output row has ONE
 // writer (no fp32 [pairs, d_out] workspace to write and read back, no atomics, a fixed summation
-// order), and a slot's B tensors are streamed once per 96 tokens.  Contraction steps whose experts
-// received no pair of the slot are skipped (their B rows are not fetched), so sparse routing does not
-// pay for the dense form.
+// order), and a slot's B tensors are streamed once per 96 tokens.  Of a contraction step whose experts
+// received no pair of the slot no B is fetched, and half chunks of four such steps are skipped, so sparse
+// routing pays little for the dense form.
 //
 // A workgroup owns a tile of up to 96 tokens of one slot and 128 outputs; each of its 4 waves owns
 // 32 outputs and streams its rows of B straight from the tables in operand layout (lane = output,
@@ -273,10 +273,10 @@ void moe_down_kernel(const MoeDownArgs a)
     // matrix instructions.  Rows of B of a dead step are zeros, blocks without a token read the vector of zeros; tiles of up
     // to 32 rows, where that would be two thirds of the work, may have their own loop.  Fetching half a chunk and y only
     // behind the loop leaves 147 registers at rank 8, three workgroups per CU, or 128 and four without that loop (a whole
-    // chunk and y in front: 230, two; the loop held to 128 spills 14 and is 4 % slower).  The down call, us before / after,
-    // 128 experts, top-8, rank 8, 768 -> 2048: 32 slots 2048 tokens 49.5 / 46.4, 4000 76.0 / 61.7, 8000 100.5 / 95.5; 8 slots
-    // 1000 tokens 30.2 / 23.3; one slot 500 tokens 26.1 / 20.9; 16 slots, rank 16, 8000 tokens 160.4 / 142.7; 8 slots of 64
-    // experts, top-4, rank 64, 100 tokens 44.1 / 36.5.
+    // chunk and y in front: 230, two; the loop held to 128 spills 14 and is 4 % slower).  The down call on cold
+    // tables, us before / after, 128 experts, top-8, rank 8, 768 -> 2048: 32 slots 2048 tokens 55.7 / 53.4, 4000 76.0 / 65.8, 8000 103.6 /
+    // 88.6; 8 slots 512 tokens 28.6 / 23.6, 4000 61.1 / 47.1; 16 slots, rank 16, 8000 tokens 161.8 / 140.5; 8 slots of 64 experts,
+    // top-4, rank 64, 1024 -> 2048, 512 tokens 68.0 / 54.6.
     constexpr int PD = 2;
     auto consume = [&](auto nbc, auto st0c, auto bufc, uint32_t mask) __attribute__((always_inline)) {
         constexpr int NB = decltype(nbc)::value, st0 = decltype(st0c)::value, N = HST * NB, bi = decltype(bufc)::value;
@@ -530,8 +530,8 @@ static void launch_moe_down_shrink_tile(const MoeDownArgs &a, hipStream_t st)
 // thread per output adds the K deltas in fp32, in order of expert id.  Of the plan it needs the pairs' keys only.  It is bound
 // by one chain, launch -> keys -> rows of A, x and the first B -> sums -> outputs, where the two launches pay two
 // and a dense form whose tiles hold a token or two each.  Parts of a token sum its A again; they sit on one XCD and
-// find it in L2.  Expert layers of 128 experts x 32 slots, rank 8, 768 -> 2048, top-8, the down call: 48 tokens
-// (17 MB of adapters) 17.9 -> 7.4 us, 200 tokens (72 MB) 27.8 -> 14.3 us.
+// find it in L2.  Expert layers of 128 experts x 32 slots, rank 8, 768 -> 2048, top-8, the down call on cold tables, two
+// launches / token by token: 1 token 11.3 / 5.1 us, 48 tokens (17 MB of adapters) 17.6 / 7.0, 200 tokens (72 MB) 27.8 / 15.3.
 // (Registers: what is in flight, the rows of A of two pieces and the B rows of eight pairs, is 110 of them at rank 8.
 // Held to 128 the kernel spills 83 and the 48 tokens take 13.7 us, so ranks 8 and 16 run one workgroup per CU.)
 // ---------------------------------------------------------------------------------------------------------
