@@ -243,18 +243,47 @@ bool takes_tiles(const mlora_site *s, int32_t tile_rows)
 // Whether the parts of a site's tiles divide d_in and trade sums (see tile_args).
 bool parts_trade(const mlora_site *s, const uint64_t *xch) { return xch && s->r_pad * s->d.d_in >= 65536; }
 
-// Parts of a site's tiles where nothing is traded and `want` are wanted: at least eight blocks of 64 outputs each.
-int32_t whole_parts(const mlora_site *s, int32_t want)
+// The most parts that a site's tiles are cut in where nothing is traded: at least eight blocks of 64 outputs each.
+int32_t most_whole_parts(const mlora_site *s) { return std::max(1, (s->d.d_out + 63) / 64 / 8); }
+
+// The tiles a dense batch is likely to have: the bound is about a quarter above what Zipf(1.1) slots give, hence 17 / 20; a
+// batch of few slots has nearly all of them, half a tile per slot beyond its full ones.
+int32_t likely_tiles(int32_t T, int32_t n_slots, int32_t tile_rows)
 {
-    const int32_t n_blk = (s->d.d_out + 63) / 64, parts = std::max(1, std::min(want, n_blk / 8));
-    return (n_blk + (n_blk + parts - 1) / parts - 1) / ((n_blk + parts - 1) / parts);
+    const int32_t bound = (int32_t)max_tiles(T, n_slots, tile_rows);
+    const int32_t likely = std::max((int32_t)((int64_t)bound * 17 / 20), T / tile_rows + std::min(n_slots, T) / 2);
+    return std::max(1, std::min(bound, likely));
 }
 
-// Launch arguments of sites[k], one of n_sites that share a launch.
-TileArgs tile_args(const mlora_site *const *sites, int32_t n_sites, int32_t k, const void *x, int64_t ldx, void *y, int64_t ldy,
-                   const PlanView &pv, uint64_t *xch, uint32_t *ctrl, int32_t T, int32_t n_slots, int32_t tile_rows)
+// Parts per tile of sites that share a launch and trade nothing: as many as leave a CU for every workgroup.  (0: some of them
+// trade, and each counts for itself.)
+// A tile's parts, of all sites, sit on one of the eight XCDs: it is the CUs of the one with most tiles that they must not
+// outnumber.  By the likely tiles every site counts in full, which leaves some room for a batch that has more; by the
+// bound on them only what a site of few outputs can take.  (Counted as tiles x sites over all CUs, rank 16, 2560 -> 9728 twice, 64
+// rows of 4 slots, 10 tiles, went in 12 parts and took 8.8 us, 8 parts 7.1; 2560 -> 2560 and 1024 twice, 256 rows of one slot, in 2, 2 and
+// 2 parts 6.9, in 4, 2 and 2 6.6.  A few workgroups too many: 2560 -> 2560, 1001 rows of 8 slots, in 4 parts 10.6 us, in 3 8.3;
+// rank 8, 4096 -> 4096, 500 rows of 16 slots 9.6 / 7.4.)
+int32_t parts_of_launch(const mlora_site *const *sites, int32_t n_sites, const uint64_t *xch, int32_t T, int32_t n_slots, int32_t tile_rows)
 {
-    const mlora_site *s = sites[k];
+    int32_t most = 1;
+    for (int32_t i = 0; i < n_sites; ++i) {
+        if (parts_trade(sites[i], xch)) return 0;
+        most = std::max(most, most_whole_parts(sites[i]));
+    }
+    const uint32_t cus = (uint32_t)cu_count(sites[0]->d.device) / 8;
+    auto room = [&](int32_t tiles) { return (int32_t)(cus / (((uint32_t)tiles + 7) / 8)); };
+    int32_t parts = std::max(1, room(likely_tiles(T, n_slots, tile_rows)) / n_sites);
+    if (n_sites == 1) return parts;
+    const int32_t sure = room((int32_t)max_tiles(T, n_slots, tile_rows));
+    auto taken = [&](int32_t want) { int32_t n = 0; for (int32_t i = 0; i < n_sites; ++i) n += std::min(want, most_whole_parts(sites[i])); return n; };
+    while (parts < most && taken(parts + 1) <= sure) ++parts;
+    return parts;
+}
+
+// Launch arguments of one of n_sites sites that share a launch; launch_parts: parts_of_launch.
+TileArgs tile_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy, const PlanView &pv,
+                   uint64_t *xch, uint32_t *ctrl, int32_t T, int32_t n_slots, int32_t tile_rows, int32_t n_sites, int32_t launch_parts)
+{
     TileArgs a{};
     a.x = (const uint16_t *)x; a.ldx = ldx; a.y = (uint16_t *)y; a.ldy = ldy;
     a.a_tab = s->a_tab; a.b_tab = s->b_tab; a.rank = s->rank; a.scale = s->scale;
@@ -262,31 +291,12 @@ TileArgs tile_args(const mlora_site *const *sites, int32_t n_sites, int32_t k, c
     a.tile_rows = tile_rows;
     a.n_tiles = (int32_t)max_tiles(T, n_slots, tile_rows);
     a.tiles = pv.tiles; a.sorted = pv.sorted;
-    const int32_t n_blk = (s->d.d_out + 63) / 64, n_steps = (s->d.d_in + 63) / 64, cus = cu_count(s->d.device);
-    // Parts per tile: as many as leave a CU for every workgroup.  A part sums all of d_in again unless the adapter's A is
-    // long: then the parts divide d_in and trade sums, about a microsecond, what a CU needs for 40 KB.
+    const int32_t n_blk = (s->d.d_out + 63) / 64, n_steps = (s->d.d_in + 63) / 64;
+    // A part sums all of d_in again unless the adapter's A is long: then the parts divide d_in and trade sums, about a
+    // microsecond, what a CU needs for 40 KB.
     const bool trade = parts_trade(s, xch);
-    int32_t parts = tuning(kTileParts);
-    if (parts <= 0) {
-        // The tiles a batch is likely to have: the bound is about a quarter above what Zipf(1.1) slots give, hence 17 / 20; a batch
-        // of few slots has nearly all of them, half a tile per slot beyond its full ones.
-        const int32_t likely = std::max((int32_t)((int64_t)a.n_tiles * 17 / 20), T / tile_rows + std::min(n_slots, T) / 2);
-        const int32_t live = trade ? a.n_tiles : std::max(1, std::min(a.n_tiles, likely));
-        parts = cus / (live * n_sites);
-        bool whole = true;
-        for (int32_t i = 0; i < n_sites; ++i) whole = whole && !parts_trade(sites[i], xch);
-        if (whole) {
-            // A tile's parts, of all sites, sit on one of the eight XCDs: it is the CUs of the one with most tiles that they must
-            // not outnumber.  By the likely tiles every site counts in full, which leaves some room for a batch that has more;
-            // by the bound on them only what a site of few outputs can take.  (Counted as tiles x sites over all CUs, rank 16,
-            // 2560 -> 9728 twice, 64 rows of 4 slots, 10 tiles, went in 12 parts and took 8.8 us, 8 parts 7.1; 2560 -> 2560 and 1024 twice, 256
-            // rows of one slot, in 2, 2 and 2 parts 6.9, in 4, 2 and 2 6.6.  A few workgroups too many: 2560 -> 2560, 1001 rows of
-            // 8 slots, in 4 parts 10.6 us, in 3 8.3; rank 8, 4096 -> 4096, 500 rows of 16 slots 9.6 / 7.4.)
-            auto room = [&](int32_t tiles) { return cus / 8 / ((tiles + 7) / 8); };
-            auto taken = [&](int32_t want) { int32_t n = 0; for (int32_t i = 0; i < n_sites; ++i) n += whole_parts(sites[i], want); return n; };
-            for (parts = 1; parts < n_blk && ((parts + 1) * n_sites <= room(live) || taken(parts + 1) <= room(a.n_tiles)); ) ++parts;
-        }
-    }
+    int32_t parts = tuning(kTileParts) > 0 ? tuning(kTileParts) : launch_parts;
+    if (parts <= 0) parts = cu_count(s->d.device) / ((trade ? a.n_tiles : likely_tiles(T, n_slots, tile_rows)) * n_sites);
     const int32_t words = (tile_rows + 7) / 8 * 8 * std::max(s->r_pad, 8);
     // A part waits for every other one's words, four at a time: beyond 8 parts that costs more than a shorter slice of A
     // saves, unless the slices are still 56 KB long.  One row, 8 / 16 parts: rank 8, 9728 -> 2560 8.8 / 9.9 us, rank 16,
@@ -294,7 +304,7 @@ TileArgs tile_args(const mlora_site *const *sites, int32_t n_sites, int32_t k, c
     const int32_t most = std::max(8, std::min(16, s->r_pad * s->d.d_in / 28672));
     if (tuning(kTileParts) <= 0 && trade) parts = std::min(parts, most);
     if (trade) parts = std::min({parts, 16, n_steps, (int32_t)(kXchBytes / 8 / ((int64_t)a.n_tiles * words))});
-    else parts = whole_parts(s, parts);
+    else parts = std::min(parts, most_whole_parts(s));
     parts = std::max(1, std::min(parts, n_blk));
     a.part_blocks = (n_blk + parts - 1) / parts;
     a.parts = (n_blk + a.part_blocks - 1) / a.part_blocks;
@@ -394,7 +404,8 @@ int32_t apply_planned_impl(mlora_site *s, const mlora_plan *plan, const void *x,
 {
     if (plan->items == 0) return MLORA_OK;
     if (!plan->moe && takes_tiles(s, plan->tile_rows)) {
-        const TileArgs t = tile_args(&s, 1, 0, x, ldx, y, ldy, plan->pv, s->xch, s->ctrl, plan->items, plan->n_slots, plan->tile_rows);
+        const TileArgs t = tile_args(s, x, ldx, y, ldy, plan->pv, s->xch, s->ctrl, plan->items, plan->n_slots, plan->tile_rows, 1,
+                                     parts_of_launch(&s, 1, s->xch, plan->items, plan->n_slots, plan->tile_rows));
         return ok(launch_tile_multi(&t, 1, st)) ? MLORA_OK : MLORA_E_HIP;
     }
     if (takes_moe_tiles(s, plan, false)) {
@@ -1133,8 +1144,9 @@ static int32_t apply_multi_impl(mlora_site *const *sites, int32_t n_sites, const
         const MultiCall rest = call.from(k);
         if (const int32_t n = tile_group(rest, n_sites - k, plan->moe ? 0 : plan->tile_rows)) {
             TileArgs grp[kMaxMulti];
+            const int32_t parts = parts_of_launch(sites + k, n, sites[k]->xch, plan->items, plan->n_slots, plan->tile_rows);
             for (int32_t i = 0; i < n; ++i)
-                grp[i] = tile_args(sites + k, n, i, xs[k + i], ldxs[k + i], ys[k + i], ldys[k + i], plan->pv, sites[k + i]->xch, sites[k + i]->ctrl, plan->items, plan->n_slots, plan->tile_rows);
+                grp[i] = tile_args(sites[k + i], xs[k + i], ldxs[k + i], ys[k + i], ldys[k + i], plan->pv, sites[k + i]->xch, sites[k + i]->ctrl, plan->items, plan->n_slots, plan->tile_rows, n, parts);
             if (!ok(launch_tile_multi(grp, n, st))) return MLORA_E_HIP;
             k += n;
             continue;
@@ -1221,7 +1233,8 @@ int32_t lora_plan_apply_decode_multi(mlora_site *const *sites, int32_t n_sites, 
         const int32_t q = dense_tile_rows(plan->pv, T, n_slots);
         if (const int32_t nt = tile_group(call, n_sites, q)) {
             TileArgs tg[kMaxMulti];
-            for (int32_t i = 0; i < nt; ++i) tg[i] = tile_args(sites, nt, i, xs[i], ldxs[i], ys[i], ldys[i], plan->pv, sites[i]->xch, sites[i]->ctrl, T, n_slots, q);
+            const int32_t parts = parts_of_launch(sites, nt, sites[0]->xch, T, n_slots, q);
+            for (int32_t i = 0; i < nt; ++i) tg[i] = tile_args(sites[i], xs[i], ldxs[i], ys[i], ldys[i], plan->pv, sites[i]->xch, sites[i]->ctrl, T, n_slots, q, nt, parts);
             plan_is_dense(plan, T, n_slots);
             if (!ok(launch_tile_multi_plan(tg, nt, plan->pv, token_slot, T, n_slots, ready_rank, st))) return MLORA_E_HIP;
             if (nt == n_sites) return MLORA_OK;
@@ -1386,7 +1399,7 @@ static int32_t apply_decode_impl(mlora_site *s, const void *x, int64_t ldx, void
             max_chunks(n, s->d.n_slots) <= rows_local_plan_rows() && !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
             const int32_t q = dense_tile_rows(plan->pv, n, s->d.n_slots);
             if (takes_tiles(s, q)) {
-                const TileArgs t = tile_args(&s, 1, 0, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, q);
+                const TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, q, 1, parts_of_launch(&s, 1, sc.xch, n, s->d.n_slots, q));
                 plan_is_dense(plan, n, s->d.n_slots);
                 if (!ok(launch_tile_multi_plan(&t, 1, plan->pv, token_slot + t0, n, s->d.n_slots, s->rank, st))) return MLORA_E_HIP;
                 continue;
@@ -1402,7 +1415,8 @@ static int32_t apply_decode_impl(mlora_site *s, const void *x, int64_t ldx, void
         int32_t rc = plan_decode_impl(plan, token_slot + t0, n, s->d.n_slots, s->rank, st);
         if (rc) return rc;
         if (takes_tiles(s, plan->tile_rows)) {
-            const TileArgs t = tile_args(&s, 1, 0, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, plan->tile_rows);
+            const TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, plan->tile_rows, 1,
+                                         parts_of_launch(&s, 1, sc.xch, n, s->d.n_slots, plan->tile_rows));
             if (!ok(launch_tile_multi(&t, 1, st))) return MLORA_E_HIP;
             continue;
         }
