@@ -161,10 +161,10 @@ int32_t lora_apply_decode_multi(mlora_site *const *sites, int32_t n_sites, const
 /* lora_plan_decode followed by lora_apply_decode_multi, for the first sites of a decode step (q/k/v
  * of the first layer): the batch is grouped by slot (Section 4: the requests of one decoding step
  * name at most 64 distinct resident adapters) and the plan is left in `plan` for every later
- * planned apply of the step.  For batches of up to 256 rows the leading sites that can share a
- * launch build the plan inside that launch (every workgroup sorts the batch's keys itself instead
- * of waiting for a planner launch; workgroup 0 writes the plan out), which saves the planner
- * launch; otherwise this is exactly the two calls.  Plan and results are those of the two calls,
+ * planned apply of the step.  The leading sites that can share a launch are applied by workgroups that find
+ * their rows in the batch by themselves (batches of up to 1024 rows over up to 1024 slots; 256 rows where the
+ * sites' rank is 1 or 2), which saves the planner launch; one more workgroup of that launch writes the plan.
+ * Otherwise this is exactly the two calls.  Plan and results are those of the two calls,
  * bit for bit.  Arguments and errors as for those two calls. */
 int32_t lora_plan_apply_decode_multi(mlora_site *const *sites, int32_t n_sites, mlora_plan *plan,
                                      const int32_t *token_slot, int32_t T, int32_t n_slots,
@@ -242,9 +242,8 @@ int32_t moe_lora_apply_down(mlora_site *site, const mlora_plan *plan, const void
 /* ---- the four calls of the problem statement ------------------------------------------------ */
 
 /* Decode: one token per row, gather-by-index.  Equivalent to lora_plan_decode on the site's
- * private scratch followed by lora_apply_decode_planned (for batches of up to 256 rows over up to
- * 1024 slots, at ranks above 2, the plan is built inside the apply launch: same
- * plan, same bits, one launch).  Sites of rank 1 and 2 (compact catalogs of tiny adapters, Section 4)
+ * private scratch followed by lora_apply_decode_planned (batches of up to 1024 rows over up to 1024 slots, at ranks
+ * above 2, are grouped inside the apply launch: same bits, one launch).  Sites of rank 1 and 2 (compact catalogs of tiny adapters, Section 4)
  * are applied row by row without any plan: grouping rows by slot would save at most two adapter
  * rows per row, less than a planner launch costs; the result equals the planned one up to the order
  * in which the fp32 partial sums of the shrink are added.  T = 0 is MLORA_OK and launches nothing.

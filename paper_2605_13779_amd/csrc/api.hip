@@ -1227,19 +1227,20 @@ int32_t lora_plan_apply_decode_multi(mlora_site *const *sites, int32_t n_sites, 
     const int32_t *ready_rank = ready_from ? ready_from->rank : nullptr;
     // the leading sites that can share a launch plan inside it; everything else as two calls would do
     const MultiCall call{sites, xs, ldxs, ys, ldys, T, T};
-    if (T <= rows_local_plan_rows() && n_slots <= rows_local_plan_slots() && max_chunks(T, n_slots) <= rows_local_plan_rows() &&
-        !tuning(kPlanGeneral) &&
-        !tuning(kPlanSeparate)) {
+    if (T <= tile_plan_rows() && n_slots <= tile_plan_slots() && !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
         const int32_t q = dense_tile_rows(plan->pv, T, n_slots);
         if (const int32_t nt = tile_group(call, n_sites, q)) {
             TileArgs tg[kMaxMulti];
             const int32_t parts = parts_of_launch(sites, nt, sites[0]->xch, T, n_slots, q);
             for (int32_t i = 0; i < nt; ++i) tg[i] = tile_args(sites[i], xs[i], ldxs[i], ys[i], ldys[i], plan->pv, sites[i]->xch, sites[i]->ctrl, T, n_slots, q, nt, parts);
             plan_is_dense(plan, T, n_slots);
-            if (!ok(launch_tile_multi_plan(tg, nt, plan->pv, token_slot, T, n_slots, ready_rank, st))) return MLORA_E_HIP;
+            if (!ok(launch_tile_multi_plan(tg, nt, plan->pv, token_slot, T, n_slots, ready_rank, true, st))) return MLORA_E_HIP;
             if (nt == n_sites) return MLORA_OK;
             return apply_multi_impl(sites + nt, n_sites - nt, plan, xs + nt, ldxs + nt, ys + nt, ldys + nt, st);
         }
+    }
+    if (T <= rows_local_plan_rows() && n_slots <= rows_local_plan_slots() && max_chunks(T, n_slots) <= rows_local_plan_rows() &&
+        !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
         RowsArgs a = rows_args(sites[0], xs[0], ldxs[0], ys[0], ldys[0]);
         if (rows_plans_alone(a)) {
             a.chunks = plan->pv.chunks; a.top_k = 1; a.grid_chunks = (int32_t)max_chunks(T, n_slots);
@@ -1395,15 +1396,18 @@ static int32_t apply_decode_impl(mlora_site *s, const void *x, int64_t ldx, void
         uint16_t *ys = (uint16_t *)y + (int64_t)t0 * ldy;
         // a small batch on a site whose launch can plan for itself needs no planner launch (same plan,
         // same bits; see lora_plan_apply_decode_multi)
-        if (n <= rows_local_plan_rows() && s->d.n_slots <= rows_local_plan_slots() &&
-            max_chunks(n, s->d.n_slots) <= rows_local_plan_rows() && !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
+        if (n <= tile_plan_rows() && s->d.n_slots <= tile_plan_slots() && !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
             const int32_t q = dense_tile_rows(plan->pv, n, s->d.n_slots);
             if (takes_tiles(s, q)) {
                 const TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, q, 1, parts_of_launch(&s, 1, sc.xch, n, s->d.n_slots, q));
                 plan_is_dense(plan, n, s->d.n_slots);
-                if (!ok(launch_tile_multi_plan(&t, 1, plan->pv, token_slot + t0, n, s->d.n_slots, s->rank, st))) return MLORA_E_HIP;
+                // (nobody reads the private plan after the call: it is not written)
+                if (!ok(launch_tile_multi_plan(&t, 1, plan->pv, token_slot + t0, n, s->d.n_slots, s->rank, false, st))) return MLORA_E_HIP;
                 continue;
             }
+        }
+        if (n <= rows_local_plan_rows() && s->d.n_slots <= rows_local_plan_slots() &&
+            max_chunks(n, s->d.n_slots) <= rows_local_plan_rows() && !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
             RowsArgs a = args(xs, ys);
             a.chunks = plan->pv.chunks; a.top_k = 1; a.grid_chunks = (int32_t)max_chunks(n, s->d.n_slots);
             if (rows_plans_alone(a)) {

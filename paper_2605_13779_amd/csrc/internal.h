@@ -148,7 +148,9 @@ hipError_t launch_tile_seg(const TileArgs &a, const uint32_t *inl, hipStream_t s
 hipError_t launch_tile_moe(const TileArgs *sites, int n, hipStream_t st);
 hipError_t launch_tile_multi(const TileArgs *sites, int n, hipStream_t st);
 hipError_t launch_tile_multi_plan(const TileArgs *sites, int n, const PlanView &pv, const int32_t *token_slot, int T,
-                                  int n_slots, const int32_t *ready_rank, hipStream_t st);
+                                  int n_slots, const int32_t *ready_rank, bool write_plan, hipStream_t st);
+int tile_plan_rows();
+int tile_plan_slots();
 
 // moe_down.hip: second launch of the MoE down projection (expand + routing-weight combine on the matrix cores)
 struct MoeDownArgs {

@@ -77,76 +77,17 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Small dense batches (up to kSortMax rows) over up to kSmallSlots slots: one workgroup, one row per thread.
-// A row's place is (rows of smaller slots) + (earlier rows of its slot); the second term comes from comparing
-// with the wave's 64 slots (four at a time, all lanes one LDS address) and from the waves adding their
-// counts to an LDS table in turn, the first from a scan over the slots.  All of it is barriers and LDS
-// latency, and there are about as many of the former as the batch has waves.  (The sorting network below,
-// which larger slot tables take, has fifty exchange steps: 8.9 against 7.9 us for 1001 rows over 64 slots.)
+// Small dense batches (up to kSortMax rows) over up to kSmallSlots slots: one workgroup, one row per thread (see
+// plan_dense_count).  (The sorting network below, which larger slot tables take, has fifty exchange steps: 8.9
+// against 7.9 us for 1001 rows over 64 slots.)
 // ---------------------------------------------------------------------------------------------
 constexpr int kSmallSlots = 4096;
 __global__ __launch_bounds__(kSortMax)
 void plan_dense_count_kernel(PlanView pv, const int32_t *__restrict__ token_slot, int T, int n_slots,
                              const int32_t *__restrict__ ready_rank, int rec_bound, int tile_rows, int tile_bound)
 {
-    __shared__ int32_t cnt[kSmallSlots];           // rows of the slot
-    __shared__ int32_t off[kSmallSlots];           // rows of smaller slots
-    __shared__ int32_t base2[kSmallSlots];         // chunks | tiles << 16 of smaller slots
-    __shared__ __attribute__((aligned(16))) int32_t lkey[kSortMax];
-    __shared__ __attribute__((aligned(16))) int32_t wave_tot[16];
-    __shared__ int32_t s_tot[2];
-    const int i = (int)threadIdx.x, N = (int)blockDim.x, lane = i & 63, w = i >> 6;
-    int s = -1;
-    if (i < T) {
-        const int v = token_slot[i];
-        if (v >= 0 && v < n_slots && !(ready_rank && ready_rank[v] <= 0)) s = v;
-    }
-    for (int k = i; k < n_slots; k += N) cnt[k] = 0;
-    lkey[i] = s;                                   // (read back by the same wave only: LDS serves a wave in order)
-    int rank = 0, same = 0;
-    const int32_t *mine = lkey + 64 * w;
-#pragma unroll 4
-    for (int j = 0; j < 64; j += 4) {
-        const int4 v = *(const int4 *)(mine + j);
-        same += (v.x == s) + (v.y == s) + (v.z == s) + (v.w == s);
-        rank += (v.x == s && j < lane) + (v.y == s && j + 1 < lane) + (v.z == s && j + 2 < lane) + (v.w == s && j + 3 < lane);
-    }
-    __syncthreads();
-    const bool first = rank == 0;
-    for (int v = 0; v < (N >> 6); ++v) {
-        if (v == w && s >= 0) {
-            const int before = cnt[s];
-            rank += before;
-            if (first) cnt[s] = before + same;
-        }
-        __syncthreads();
-    }
-    const int per = (n_slots + N - 1) / N, k_lo = min(n_slots, i * per), k_hi = min(n_slots, k_lo + per);
-    int size = 0, recs = 0;
-    auto recs_of = [&](int c) { return (c + kChunk - 1) / kChunk + (tile_rows > 0 ? (c + tile_rows - 1) / tile_rows << 16 : 0); };
-    for (int k = k_lo; k < k_hi; ++k) { size += cnt[k]; recs += recs_of(cnt[k]); }
-    const int inc_s = block_scan<false>(size, i, N >> 6, wave_tot), inc_r = block_scan<false>(recs, i, N >> 6, wave_tot);
-    int run_s = inc_s - size, run_r = inc_r - recs;
-    for (int k = k_lo; k < k_hi; ++k) {
-        off[k] = run_s; base2[k] = run_r;
-        run_s += cnt[k]; run_r += recs_of(cnt[k]);
-    }
-    if (i == N - 1) { s_tot[0] = inc_s; s_tot[1] = inc_r; }
-    __syncthreads();
-    const int n_rows = s_tot[0], n_chunks = s_tot[1] & 0xffff, n_tiles = s_tot[1] >> 16;
-    if (s >= 0) {
-        const int pos = off[s] + rank, n = cnt[s], b = base2[s];
-        pv.sorted[pos] = i;
-        int32_t *rec = pv.chunks + (int64_t)((b & 0xffff) + rank / kChunk) * kRec;
-        rec[4 + (rank % kChunk)] = i;
-        if (rank % kChunk == 0) { rec[0] = s; rec[1] = min(kChunk, n - rank); rec[2] = pos; rec[3] = 0; }
-        if (tile_rows > 0 && rank % tile_rows == 0)
-            ((int4 *)pv.tiles)[(b >> 16) + rank / tile_rows] = make_int4(s, min(tile_rows, n - rank), pos, 0);
-    }
-    if (i == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
-    // records past the live ones are marked empty (count 0): the apply kernels read only records
-    for (int d = n_chunks + i; d < rec_bound; d += N) pv.chunks[(int64_t)d * kRec + 1] = 0;
-    for (int d = n_tiles + i; d < tile_bound; d += N) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
+    __shared__ PlanCountLds<kSmallSlots> lds;
+    plan_dense_count<1, kSmallSlots>(pv, token_slot, T, n_slots, ready_rank, rec_bound, tile_rows, tile_bound, (int)threadIdx.x, (int)blockDim.x, lds);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -104,6 +104,95 @@ __device__ __forceinline__ int block_scan(int v, int tid, int nw, int32_t *wave_
     return IS_MAX ? max(v, base) : v + base;
 }
 
+// The dense planner of up to RPT * N rows (N threads, whole waves) over up to SLOTS slots, by counting; one workgroup
+// writes the plan.  A row's place is (rows of smaller slots) + (earlier rows of its slot); the second term comes from
+// comparing with the 64 slots of its group of rows (four at a time, all lanes one LDS address) and from the
+// groups adding their counts to an LDS table in turn, the first from a scan over the slots.  All of it is
+// barriers and LDS latency, and there are about as many of the former as the batch has groups of 64 rows.
+template <int SLOTS>
+struct PlanCountLds {
+    int32_t cnt[SLOTS];                    // rows of the slot
+    int32_t off[SLOTS];                    // rows of smaller slots
+    int32_t base2[SLOTS];                  // chunks | tiles << 16 of smaller slots
+    __attribute__((aligned(16))) int32_t lkey[kSortMax];
+    __attribute__((aligned(16))) int32_t wave_tot[16];
+    int32_t tot[2];
+};
+
+template <int RPT, int SLOTS>
+__device__ __forceinline__ void plan_dense_count(const PlanView &pv, const int32_t *__restrict__ token_slot, int T, int n_slots,
+                                                 const int32_t *__restrict__ ready_rank, int rec_bound, int tile_rows, int tile_bound,
+                                                 const int i, const int N, PlanCountLds<SLOTS> &L)
+{
+    const int lane = i & 63, w = i >> 6, nw = N >> 6;
+    int s[RPT], rank[RPT], same[RPT];
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        s[r] = -1;
+        if (i + r * N < T) {
+            const int v = token_slot[i + r * N];
+            if (v >= 0 && v < n_slots && !(ready_rank && ready_rank[v] <= 0)) s[r] = v;
+        }
+    }
+    for (int k = i; k < n_slots; k += N) L.cnt[k] = 0;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        int32_t *mine = L.lkey + 64 * (w + r * nw);
+        mine[lane] = s[r];                         // (read back by the same wave only: LDS serves a wave in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        int rk = 0, sm = 0;
+#pragma unroll 4
+        for (int j = 0; j < 64; j += 4) {
+            const int4 v = *(const int4 *)(mine + j);
+            sm += (v.x == s[r]) + (v.y == s[r]) + (v.z == s[r]) + (v.w == s[r]);
+            rk += (v.x == s[r] && j < lane) + (v.y == s[r] && j + 1 < lane) + (v.z == s[r] && j + 2 < lane) + (v.w == s[r] && j + 3 < lane);
+        }
+        rank[r] = rk; same[r] = sm;
+    }
+    __syncthreads();
+    const int n_groups = (T + 63) >> 6;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        const bool first = rank[r] == 0;
+        for (int v = r * nw; v < min(n_groups, (r + 1) * nw); ++v) {
+            if (v == w + r * nw && s[r] >= 0) {
+                const int before = L.cnt[s[r]];
+                rank[r] += before;
+                if (first) L.cnt[s[r]] = before + same[r];
+            }
+            __syncthreads();
+        }
+    }
+    const int per = (n_slots + N - 1) / N, k_lo = min(n_slots, i * per), k_hi = min(n_slots, k_lo + per);
+    int size = 0, recs = 0;
+    auto recs_of = [&](int c) { return (c + kChunk - 1) / kChunk + (tile_rows > 0 ? (c + tile_rows - 1) / tile_rows << 16 : 0); };
+    for (int k = k_lo; k < k_hi; ++k) { size += L.cnt[k]; recs += recs_of(L.cnt[k]); }
+    const int inc_s = block_scan<false>(size, i, nw, L.wave_tot), inc_r = block_scan<false>(recs, i, nw, L.wave_tot);
+    int run_s = inc_s - size, run_r = inc_r - recs;
+    for (int k = k_lo; k < k_hi; ++k) {
+        L.off[k] = run_s; L.base2[k] = run_r;
+        run_s += L.cnt[k]; run_r += recs_of(L.cnt[k]);
+    }
+    if (i == N - 1) { L.tot[0] = inc_s; L.tot[1] = inc_r; }
+    __syncthreads();
+    const int n_rows = L.tot[0], n_chunks = L.tot[1] & 0xffff, n_tiles = L.tot[1] >> 16;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        if (s[r] < 0) continue;
+        const int row = i + r * N, pos = L.off[s[r]] + rank[r], n = L.cnt[s[r]], b = L.base2[s[r]];
+        pv.sorted[pos] = row;
+        int32_t *rec = pv.chunks + (int64_t)((b & 0xffff) + rank[r] / kChunk) * kRec;
+        rec[4 + (rank[r] % kChunk)] = row;
+        if (rank[r] % kChunk == 0) { rec[0] = s[r]; rec[1] = min(kChunk, n - rank[r]); rec[2] = pos; rec[3] = 0; }
+        if (tile_rows > 0 && rank[r] % tile_rows == 0)
+            ((int4 *)pv.tiles)[(b >> 16) + rank[r] / tile_rows] = make_int4(s[r], min(tile_rows, n - rank[r]), pos, 0);
+    }
+    if (i == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
+    // records past the live ones are marked empty (count 0): the apply kernels read only records
+    for (int d = n_chunks + i; d < rec_bound; d += N) pv.chunks[(int64_t)d * kRec + 1] = 0;
+    for (int d = n_tiles + i; d < tile_bound; d += N) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
+}
+
 // The planner inside a workgroup of an apply kernel: every thread calls it (i = thread index,
 // nthreads a multiple of 64, 256..512, T <= 256 rows (waves 0..3), n_slots <= kLocalPlanSlots).  token_slot[0..T) ->
 // the batch's chunk records in LDS (lrec, kRec ints per chunk, rec_bound of them, the ones past the
@@ -130,7 +219,7 @@ __device__ __forceinline__ void plan_dense_local(const int32_t *__restrict__ tok
                                                  const int32_t *__restrict__ ready_rank, int rec_bound,
                                                  int i, int nthreads, PlanLocalLds &L,
                                                  int32_t *lrec, bool write_pv, const PlanView &pv,
-                                                 int tile_rows, int tile_bound, int4 *ltile = nullptr, int32_t *lsorted = nullptr)
+                                                 int tile_rows, int tile_bound)
 {
     const int lane = i & 63, w = i >> 6, nw = nthreads >> 6;
     constexpr int kRowWaves = 4;
@@ -210,15 +299,10 @@ __device__ __forceinline__ void plan_dense_local(const int32_t *__restrict__ tok
             rec[4 + (rank % kChunk)] = i;
             if (rank % kChunk == 0) { rec[0] = s; rec[1] = min(kChunk, n - rank); rec[2] = pos; rec[3] = 0; }
         }
-        if (lsorted) lsorted[pos] = i;
-        if (tile_rows > 0) {
+        if (write_pv && tile_rows > 0) {
             int t = 0, r0 = 0;                     // this row's tile of the slot, and the tile's first row
             while (r0 + tile_rows <= rank) { r0 += tile_rows; ++t; }
-            if (r0 == rank) {
-                const int4 v = make_int4(s, min(tile_rows, n - rank), pos, 0);
-                if (ltile) ltile[L.tbase[s] + t] = v;
-                if (write_pv) ((int4 *)pv.tiles)[L.tbase[s] + t] = v;
-            }
+            if (r0 == rank) ((int4 *)pv.tiles)[L.tbase[s] + t] = make_int4(s, min(tile_rows, n - rank), pos, 0);
         }
         if (write_pv) {
             pv.sorted[pos] = i;
@@ -232,10 +316,8 @@ __device__ __forceinline__ void plan_dense_local(const int32_t *__restrict__ tok
         if (lrec) lrec[d * kRec + 1] = 0;
         if (write_pv) pv.chunks[(int64_t)d * kRec + 1] = 0;
     }
-    for (int d = n_tiles + i; d < tile_bound; d += nthreads) {
-        if (ltile) ltile[d] = make_int4(0, 0, 0, 0);
-        if (write_pv) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
-    }
+    if (write_pv)
+        for (int d = n_tiles + i; d < tile_bound; d += nthreads) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
     __syncthreads();
 }
 

@@ -652,6 +652,40 @@ def test_plan_tile_records(M, T, S, q):
         M.set_tuning("tile_rows", 0)
 
 
+@pytest.mark.parametrize("T,S,q", [(1, 1024, 8), (63, 65, 5), (257, 64, 16), (300, 7, 8), (512, 256, 16), (513, 257, 7), (1000, 1, 16),
+                                   (1001, 64, 16), (1024, 1024, 4), (1024, 513, 16)])
+def test_launch_that_finds_its_tiles_in_the_batch(M, oracle, T, S, q):
+    """Batches of up to 1024 rows and slots are grouped inside the apply launch: the bits of a planner launch and a planned
+    apply, and the same plan left behind.  Slots that are not ready, indices outside the table, a crowded slot, empty tiles."""
+    r = W.rng(77 * T + S)
+    slots = r.integers(-2, S + 2, size=T).astype(np.int32)
+    slots[T // 3:T // 3 + min(T // 4, 70)] = S // 2
+    c = W.dense_case(f"find{T}", 3400 + T, T, 264, 136, S, 16, 32.0, token_slot=np.where((slots < 0) | (slots >= S), -1, slots).astype(np.int32),
+                     ranks=[0 if k % 7 == 3 else 16 for k in range(S)], std_a=0.05, std_b=0.05)
+    site, ts, x = dense_site(M, c), torch.from_numpy(slots).cuda(), P.dev_bf16(c.x)
+    pa, pb = M.Plan(T, S), M.Plan(T, S)
+    pa.buf.fill_(0x5A); pb.buf.fill_(0x5A)
+    pa.buf[:4 * (8 + 3 * (S + 1))].zero_(); pb.buf[:4 * (8 + 3 * (S + 1))].zero_()
+    ya, yb, yc = (P.dev_bf16(c.y0) for _ in range(3))
+    M.set_tuning("tile_rows", q)
+    try:
+        M.lora_plan_decode(pa, ts, S, ready_from=site)
+        M.lora_apply_decode_planned(site, pa, x, ya)
+        M.lora_plan_apply_decode_multi([site], pb, ts, S, [x], [yb], ready_from=site)
+        M.lora_apply_decode(site, x, yc, ts)
+        torch.cuda.synchronize()
+    finally:
+        M.set_tuning("tile_rows", 0)
+    assert torch.equal(ya, yb) and torch.equal(ya, yc)
+    ref = oracle.apply_decode(c.x, c.y0, c.A, c.B, c.rank, c.alpha, c.token_slot)
+    P.check_close(P.host_bits(yb), ref, c.name)
+    P.check_untouched(P.host_bits(yb), c.y0, c.token_slot < 0, c.name)
+    (ha, sa, _), (hb, sb, _) = _plan_words(pa, T, S), _plan_words(pb, T, S)
+    assert np.array_equal(ha, hb) and np.array_equal(sa[:ha[1]], sb[:ha[1]])
+    bound = (T + (q - 1) * min(S, T)) // q
+    assert np.array_equal(_plan_tiles(pa, T, S)[:bound], _plan_tiles(pb, T, S)[:bound])
+
+
 def test_graph_replay_keeps_results_right(M, oracle):
     """A captured graph replays the same kernel arguments; the launches that exchange partial
     results between workgroups must still tell one replay from the next.  Inputs change between
