@@ -241,48 +241,16 @@ bool takes_tiles(const mlora_site *s, int32_t tile_rows)
 }
 
 // Whether the parts of a site's tiles divide d_in and trade sums (see tile_args).
+// (Rank 16, 2560 -> 2560, 64 and 256 rows over 64 slots, whole / traded: 5.8 / 6.2 and 7.1 / 6.9 us; rank 32, 1024 -> 1024 5.3 / 6.0 and 5.5 / 6.0;
+// 9728 -> 2560, 155,648, 14.7 / 7.4 and 16.5 / 11.0.)
 bool parts_trade(const mlora_site *s, const uint64_t *xch) { return xch && s->r_pad * s->d.d_in >= 65536; }
 
 // The most parts that a site's tiles are cut in where nothing is traded: at least eight blocks of 64 outputs each.
-int32_t most_whole_parts(const mlora_site *s) { return std::max(1, (s->d.d_out + 63) / 64 / 8); }
+int32_t most_whole_parts(int32_t d_out) { return std::max(1, std::min((d_out + 63) / 64 / 8, 255)); }
 
-// The tiles a dense batch is likely to have: the bound is about a quarter above what Zipf(1.1) slots give, hence 17 / 20; a
-// batch of few slots has nearly all of them, half a tile per slot beyond its full ones.
-int32_t likely_tiles(int32_t T, int32_t n_slots, int32_t tile_rows)
-{
-    const int32_t bound = (int32_t)max_tiles(T, n_slots, tile_rows);
-    const int32_t likely = std::max((int32_t)((int64_t)bound * 17 / 20), T / tile_rows + std::min(n_slots, T) / 2);
-    return std::max(1, std::min(bound, likely));
-}
-
-// Parts per tile of sites that share a launch and trade nothing: as many as leave a CU for every workgroup.  (0: some of them
-// trade, and each counts for itself.)
-// A tile's parts, of all sites, sit on one of the eight XCDs: it is the CUs of the one with most tiles that they must not
-// outnumber.  By the likely tiles every site counts in full, which leaves some room for a batch that has more; by the
-// bound on them only what a site of few outputs can take.  (Counted as tiles x sites over all CUs, rank 16, 2560 -> 9728 twice, 64
-// rows of 4 slots, 10 tiles, went in 12 parts and took 8.8 us, 8 parts 7.1; 2560 -> 2560 and 1024 twice, 256 rows of one slot, in 2, 2 and
-// 2 parts 6.9, in 4, 2 and 2 6.6.  A few workgroups too many: 2560 -> 2560, 1001 rows of 8 slots, in 4 parts 10.6 us, in 3 8.3;
-// rank 8, 4096 -> 4096, 500 rows of 16 slots 9.6 / 7.4.)
-int32_t parts_of_launch(const mlora_site *const *sites, int32_t n_sites, const uint64_t *xch, int32_t T, int32_t n_slots, int32_t tile_rows)
-{
-    int32_t most = 1;
-    for (int32_t i = 0; i < n_sites; ++i) {
-        if (parts_trade(sites[i], xch)) return 0;
-        most = std::max(most, most_whole_parts(sites[i]));
-    }
-    const uint32_t cus = (uint32_t)cu_count(sites[0]->d.device) / 8;
-    auto room = [&](int32_t tiles) { return (int32_t)(cus / (((uint32_t)tiles + 7) / 8)); };
-    int32_t parts = std::max(1, room(likely_tiles(T, n_slots, tile_rows)) / n_sites);
-    if (n_sites == 1) return parts;
-    const int32_t sure = room((int32_t)max_tiles(T, n_slots, tile_rows));
-    auto taken = [&](int32_t want) { int32_t n = 0; for (int32_t i = 0; i < n_sites; ++i) n += std::min(want, most_whole_parts(sites[i])); return n; };
-    while (parts < most && taken(parts + 1) <= sure) ++parts;
-    return parts;
-}
-
-// Launch arguments of one of n_sites sites that share a launch; launch_parts: parts_of_launch.
+// Launch arguments of a dense site; parts: the most its tiles are cut in.
 TileArgs tile_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy, const PlanView &pv,
-                   uint64_t *xch, uint32_t *ctrl, int32_t T, int32_t n_slots, int32_t tile_rows, int32_t n_sites, int32_t launch_parts)
+                   uint64_t *xch, uint32_t *ctrl, int32_t T, int32_t n_slots, int32_t tile_rows)
 {
     TileArgs a{};
     a.x = (const uint16_t *)x; a.ldx = ldx; a.y = (uint16_t *)y; a.ldy = ldy;
@@ -294,26 +262,84 @@ TileArgs tile_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int
     const int32_t n_blk = (s->d.d_out + 63) / 64, n_steps = (s->d.d_in + 63) / 64;
     // A part sums all of d_in again unless the adapter's A is long: then the parts divide d_in and trade sums, about a
     // microsecond, what a CU needs for 40 KB.
-    const bool trade = parts_trade(s, xch);
-    int32_t parts = tuning(kTileParts) > 0 ? tuning(kTileParts) : launch_parts;
-    if (parts <= 0) parts = cu_count(s->d.device) / ((trade ? a.n_tiles : likely_tiles(T, n_slots, tile_rows)) * n_sites);
-    const int32_t words = (tile_rows + 7) / 8 * 8 * std::max(s->r_pad, 8);
-    // A part waits for every other one's words, four at a time: beyond 8 parts that costs more than a shorter slice of A
-    // saves, unless the slices are still 56 KB long.  One row, 8 / 16 parts: rank 8, 9728 -> 2560 8.8 / 9.9 us, rank 16,
-    // 7168 -> 7168 8.7 / 9.6, rank 64 12.6 / 11.0.
-    const int32_t most = std::max(8, std::min(16, s->r_pad * s->d.d_in / 28672));
-    if (tuning(kTileParts) <= 0 && trade) parts = std::min(parts, most);
-    if (trade) parts = std::min({parts, 16, n_steps, (int32_t)(kXchBytes / 8 / ((int64_t)a.n_tiles * words))});
-    else parts = std::min(parts, most_whole_parts(s));
-    parts = std::max(1, std::min(parts, n_blk));
-    a.part_blocks = (n_blk + parts - 1) / parts;
-    a.parts = (n_blk + a.part_blocks - 1) / a.part_blocks;
-    if (trade && a.parts > 1) {
+    if (parts_trade(s, xch)) {
+        // A part waits for every other one's words, four at a time: beyond 8 parts that costs more than a shorter slice of A
+        // saves, unless the slices are still 56 KB long.  One row, 8 / 16 parts: rank 8, 9728 -> 2560 8.8 / 9.9 us, rank 16,
+        // 7168 -> 7168 8.7 / 9.6, rank 64 12.6 / 11.0.
+        const int32_t most = tuning(kTileParts) > 0 ? 16 : std::max(8, std::min(16, s->r_pad * s->d.d_in / 28672));
+        a.parts = std::min({most, n_steps, n_blk});
         a.xch = xch; a.ctrl = ctrl;
         const int pl = tuning(kRowsPollLimit);
         a.poll_limit = pl < 0 ? 0 : (pl > 0 ? pl : kPollLimit);
+    } else {
+        a.parts = most_whole_parts(s->d.d_out);
     }
     return a;
+}
+
+// Parts per tile of sites that share a launch, by the number of live tiles (see TileSplit).  A tile's parts, of all sites, sit on
+// one of the eight XCDs: as many as leave a CU for every workgroup of the one with most tiles.  What the host can say
+// of the tiles, a bound, is twice what a small batch of Zipf slots has, and 17 / 20 of it, which launches were cut by, still a quarter
+// too many; by the live ones, which the plan records, rank 16, 2560 -> 9728 twice, 64 rows over 64 slots went from 14.3 to 10.9
+// us, 9728 -> 2560, 256 rows 12.4 to 11.0.
+// Two workgroups per CU where they move little more than one would, up to 1.3 times (the wide sites; a second one hides the
+// first one's round trips), and fill three quarters of the places: 2560 -> 9728 twice, 256 rows in 1 / 3 parts 24.6 / 21.2, 128
+// rows of uniform slots in 2 / 4 23.9 / 18.4; rank 32, 1024 -> 4096 twice, 1001 rows 20.3 / 18.2.  Beyond that the adapter's A
+// costs more: 2560 -> 2560, 256 rows, in 3 / 6 parts 6.8 / 8.2, rank 4, 3000 -> 9000 7.0 / 7.8.  Never where sums are traded (9728 -> 2560, 256
+// rows, in 3 / 6 parts 11.0 / 12.0).
+TileSplit split_tiles(TileArgs *sites, int32_t n, int32_t cus)
+{
+    TileSplit sp{};
+    int32_t top = 1, trades = 1 << 20;
+    bool trade = false;
+    for (int32_t i = 0; i < n; ++i) {
+        top = std::max(top, sites[i].parts);
+        if (!sites[i].xch) continue;
+        trade = true;
+        const int32_t words = (sites[i].tile_rows + 7) / 8 * 8 * std::max(sites[i].r_pad, 8);
+        trades = std::min(trades, (int32_t)(kXchBytes / 8 / ((int64_t)8 * words)));      // eight tiles' words once
+    }
+    const int32_t forced = tuning(kTileParts), room = cus / 8, h = (sites[0].tile_rows + 7) / 8 * 8;
+    auto taken = [&](int32_t p) { int32_t k = 0; for (int32_t i = 0; i < n; ++i) k += std::min(p, sites[i].parts); return k; };
+    // bytes that the largest part of p moves: all of A and x, its share of B and y
+    auto bytes = [&](int32_t p) {
+        float most = 0.f;
+        for (int32_t i = 0; i < n; ++i) {
+            const TileArgs &s = sites[i];
+            const int32_t q = std::min(p, s.parts);
+            most = std::max(most, (float)s.d_in * (float)(std::max(s.r_pad, 8) + h) + (float)s.d_out * (float)(s.r_pad + 2 * h) / (float)q);
+        }
+        return most;
+    };
+    const int32_t eighths = (sites[0].n_tiles + 7) / 8;
+    if (trade && forced <= 0 && std::min(room, trades) < 2 * (eighths * 9 / 10)) {
+        // So many tiles that the words for more than one part are missing, or CUs: parts sum for themselves (rank 64, 7168 -> 7168, 1001
+        // rows over 16 slots, one part / three 66 / 46 us).
+        for (int32_t i = 0; i < n; ++i) {
+            if (!sites[i].xch) continue;
+            sites[i].xch = nullptr;
+            sites[i].parts = most_whole_parts(sites[i].d_out);
+        }
+        return split_tiles(sites, n, cus);
+    }
+    int32_t one = top, two = top;                      // parts for one workgroup per CU, and for two
+    for (int32_t t = 1; t <= std::min(eighths, kSplitEighths); ++t) {
+        auto fit = [&](int32_t p, int32_t wgs) {
+            p = std::max(1, std::min({p, wgs / t, trades / t}));
+            while (p > 1 && taken(p) * t > wgs) --p;
+            return p;
+        };
+        int32_t p = one = fit(one, room);
+        if (forced > 0) p = std::max(1, std::min({forced, top, trades / t}));
+        else if (!trade && one < top) {
+            two = fit(two, 2 * room);
+            if (two > one && 4 * taken(two) * t >= 6 * room && 2.f * bytes(two) <= 1.3f * bytes(one) * (taken(one) * t > room ? 2.f : 1.f)) p = two;
+        }
+        sp.table[(t - 1) / 8] |= (uint64_t)p << ((t - 1) % 8 * 8);
+        sp.wgs = std::max(sp.wgs, 8 * t * taken(p));
+    }
+    if (eighths > kSplitEighths) sp.wgs = std::max(sp.wgs, 8 * eighths * n);
+    return sp;
 }
 
 // The same for a route plan: from 1.5 pairs per (slot, expert) on, and where the tiles (up to one group each, four waves)
@@ -404,9 +430,8 @@ int32_t apply_planned_impl(mlora_site *s, const mlora_plan *plan, const void *x,
 {
     if (plan->items == 0) return MLORA_OK;
     if (!plan->moe && takes_tiles(s, plan->tile_rows)) {
-        const TileArgs t = tile_args(s, x, ldx, y, ldy, plan->pv, s->xch, s->ctrl, plan->items, plan->n_slots, plan->tile_rows, 1,
-                                     parts_of_launch(&s, 1, s->xch, plan->items, plan->n_slots, plan->tile_rows));
-        return ok(launch_tile_multi(&t, 1, st)) ? MLORA_OK : MLORA_E_HIP;
+        TileArgs t = tile_args(s, x, ldx, y, ldy, plan->pv, s->xch, s->ctrl, plan->items, plan->n_slots, plan->tile_rows);
+        return ok(launch_tile_multi(&t, 1, split_tiles(&t, 1, cu_count(s->d.device)), st)) ? MLORA_OK : MLORA_E_HIP;
     }
     if (takes_moe_tiles(s, plan, false)) {
         const TileArgs t = moe_tile_args(s, plan, x, ldx, y, ldy);
@@ -1144,10 +1169,9 @@ static int32_t apply_multi_impl(mlora_site *const *sites, int32_t n_sites, const
         const MultiCall rest = call.from(k);
         if (const int32_t n = tile_group(rest, n_sites - k, plan->moe ? 0 : plan->tile_rows)) {
             TileArgs grp[kMaxMulti];
-            const int32_t parts = parts_of_launch(sites + k, n, sites[k]->xch, plan->items, plan->n_slots, plan->tile_rows);
             for (int32_t i = 0; i < n; ++i)
-                grp[i] = tile_args(sites[k + i], xs[k + i], ldxs[k + i], ys[k + i], ldys[k + i], plan->pv, sites[k + i]->xch, sites[k + i]->ctrl, plan->items, plan->n_slots, plan->tile_rows, n, parts);
-            if (!ok(launch_tile_multi(grp, n, st))) return MLORA_E_HIP;
+                grp[i] = tile_args(sites[k + i], xs[k + i], ldxs[k + i], ys[k + i], ldys[k + i], plan->pv, sites[k + i]->xch, sites[k + i]->ctrl, plan->items, plan->n_slots, plan->tile_rows);
+            if (!ok(launch_tile_multi(grp, n, split_tiles(grp, n, cu_count(plan->device)), st))) return MLORA_E_HIP;
             k += n;
             continue;
         }
@@ -1231,10 +1255,9 @@ int32_t lora_plan_apply_decode_multi(mlora_site *const *sites, int32_t n_sites, 
         const int32_t q = dense_tile_rows(plan->pv, T, n_slots);
         if (const int32_t nt = tile_group(call, n_sites, q)) {
             TileArgs tg[kMaxMulti];
-            const int32_t parts = parts_of_launch(sites, nt, sites[0]->xch, T, n_slots, q);
-            for (int32_t i = 0; i < nt; ++i) tg[i] = tile_args(sites[i], xs[i], ldxs[i], ys[i], ldys[i], plan->pv, sites[i]->xch, sites[i]->ctrl, T, n_slots, q, nt, parts);
+            for (int32_t i = 0; i < nt; ++i) tg[i] = tile_args(sites[i], xs[i], ldxs[i], ys[i], ldys[i], plan->pv, sites[i]->xch, sites[i]->ctrl, T, n_slots, q);
             plan_is_dense(plan, T, n_slots);
-            if (!ok(launch_tile_multi_plan(tg, nt, plan->pv, token_slot, T, n_slots, ready_rank, true, st))) return MLORA_E_HIP;
+            if (!ok(launch_tile_multi_plan(tg, nt, split_tiles(tg, nt, cu_count(plan->device)), plan->pv, token_slot, T, n_slots, ready_rank, true, st))) return MLORA_E_HIP;
             if (nt == n_sites) return MLORA_OK;
             return apply_multi_impl(sites + nt, n_sites - nt, plan, xs + nt, ldxs + nt, ys + nt, ldys + nt, st);
         }
@@ -1399,10 +1422,10 @@ static int32_t apply_decode_impl(mlora_site *s, const void *x, int64_t ldx, void
         if (n <= tile_plan_rows() && s->d.n_slots <= tile_plan_slots() && !tuning(kPlanGeneral) && !tuning(kPlanSeparate)) {
             const int32_t q = dense_tile_rows(plan->pv, n, s->d.n_slots);
             if (takes_tiles(s, q)) {
-                const TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, q, 1, parts_of_launch(&s, 1, sc.xch, n, s->d.n_slots, q));
+                TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, q);
                 plan_is_dense(plan, n, s->d.n_slots);
                 // (nobody reads the private plan after the call: it is not written)
-                if (!ok(launch_tile_multi_plan(&t, 1, plan->pv, token_slot + t0, n, s->d.n_slots, s->rank, false, st))) return MLORA_E_HIP;
+                if (!ok(launch_tile_multi_plan(&t, 1, split_tiles(&t, 1, cu_count(s->d.device)), plan->pv, token_slot + t0, n, s->d.n_slots, s->rank, false, st))) return MLORA_E_HIP;
                 continue;
             }
         }
@@ -1419,9 +1442,8 @@ static int32_t apply_decode_impl(mlora_site *s, const void *x, int64_t ldx, void
         int32_t rc = plan_decode_impl(plan, token_slot + t0, n, s->d.n_slots, s->rank, st);
         if (rc) return rc;
         if (takes_tiles(s, plan->tile_rows)) {
-            const TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, plan->tile_rows, 1,
-                                         parts_of_launch(&s, 1, sc.xch, n, s->d.n_slots, plan->tile_rows));
-            if (!ok(launch_tile_multi(&t, 1, st))) return MLORA_E_HIP;
+            TileArgs t = tile_args(s, xs, ldx, ys, ldy, plan->pv, sc.xch, sc.ctrl, n, s->d.n_slots, plan->tile_rows);
+            if (!ok(launch_tile_multi(&t, 1, split_tiles(&t, 1, cu_count(s->d.device)), st))) return MLORA_E_HIP;
             continue;
         }
         RowsArgs a = args(xs, ys);

@@ -31,7 +31,7 @@ struct PlanView {
     int32_t *sorted;      // [max_items]
     int32_t *chunks;      // [kRec * max_chunks]
     // Dense plans also cut every group into tiles of up to the plan's tile height (>= kChunk rows): 4 ints per tile
-    // {key, count, first position in `sorted`, 0}; records past the live tiles have count 0.
+    // {key, count, first position in `sorted`, live tiles}; records past the live tiles have count 0.
     int32_t *tiles;       // [4 * max_chunks]
     // Route plans also group the batch's TOKENS by slot (the MoE down projection sums a token's pairs
     // into one output row and works per slot): tok_hdr[1] = usable tokens, tok_off = exclusive prefix
@@ -135,8 +135,8 @@ struct TileArgs {
     int32_t top_k;           // x row = item / top_k
     int32_t one_tile;        // most groups are one tile
     int32_t rank_bound;      // 1: read the slot's rank first and fetch only that many rows of A (packed MoE)
-    int32_t parts;           // workgroups per tile: part p expands blocks [p * part_blocks, ...) of 64 outputs
-    int32_t part_blocks;
+    int32_t parts;           // workgroups per tile; plans: at most (see TileSplit)
+    int32_t part_blocks;     // segments: part p expands blocks [p * part_blocks, ...) of 64 outputs
     // parts that also divide d_in trade their partial sums (see the exchange below); null: every part sums alone
     uint64_t *xch;           // [n_tiles][parts][tile height rounded up to 8][padded rank] words
     uint32_t *ctrl;          // [0] launch tag, [1] error flag, [8..72) sign-ins
@@ -146,8 +146,16 @@ constexpr int kMaxTileRows = 16;  // of a plan's tiles (those of segments: tile_
 int tile_max_rows();
 hipError_t launch_tile_seg(const TileArgs &a, const uint32_t *inl, hipStream_t st);
 hipError_t launch_tile_moe(const TileArgs *sites, int n, hipStream_t st);
-hipError_t launch_tile_multi(const TileArgs *sites, int n, hipStream_t st);
-hipError_t launch_tile_multi_plan(const TileArgs *sites, int n, const PlanView &pv, const int32_t *token_slot, int T,
+// Into how many parts a launch over a plan's tiles cuts each, by the number of live tiles, which the device knows: byte
+// t - 1 of the table for up to 8 * t of them, one part beyond 8 * kSplitEighths (a site takes no more than its
+// TileArgs::parts); wgs: workgroups that any number of live tiles takes.
+constexpr int kSplitEighths = 16;
+struct TileSplit {
+    uint64_t table[kSplitEighths / 8];
+    int32_t wgs;
+};
+hipError_t launch_tile_multi(const TileArgs *sites, int n, const TileSplit &split, hipStream_t st);
+hipError_t launch_tile_multi_plan(const TileArgs *sites, int n, const TileSplit &split, const PlanView &pv, const int32_t *token_slot, int T,
                                   int n_slots, const int32_t *ready_rank, bool write_plan, hipStream_t st);
 int tile_plan_rows();
 int tile_plan_slots();

@@ -137,9 +137,9 @@ void plan_dense_small_kernel(PlanView pv, const int32_t *__restrict__ token_slot
     if (tstart) tls[tl] = i;
     if (i == 0) { cs[n_chunks] = n_rows; tls[n_tiles] = n_rows; }
     __syncthreads();
-    if (tstart) ((int4 *)pv.tiles)[tl] = make_int4((int)ks, tls[tl + 1] - i, i, 0);
+    if (tstart) ((int4 *)pv.tiles)[tl] = make_int4((int)ks, tls[tl + 1] - i, i, n_tiles);
     if (tile_rows > 0)
-        for (int d = n_tiles + i; d < tile_bound; d += N) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
+        for (int d = n_tiles + i; d < tile_bound; d += N) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, n_tiles);
     if (live) {
         pv.sorted[i] = (int32_t)kt;
         int32_t *rec = pv.chunks + (int64_t)c * kRec;
@@ -427,7 +427,7 @@ void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, c
         const int j = p0 + tid;                  // this range also owns positions / records [p0, p0 + kOneRange)
         if (j < P) {
             if (records && j >= n_chunks && j < rec_bound) pv.chunks[(int64_t)j * kRec + 1] = 0;   // empty record past the live chunks
-            if (tiled && j >= n_tiles && j < tile_bound) ((int4 *)pv.tiles)[j] = make_int4(0, 0, 0, 0);
+            if (tiled && j >= n_tiles && j < tile_bound) ((int4 *)pv.tiles)[j] = make_int4(0, 0, 0, n_tiles);
             if (j >= n_rows) {
                 pv.sorted[j] = -1;
                 if (out_sorted) out_sorted[j] = -1;
@@ -444,7 +444,7 @@ void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, c
                     rec[4 + (r % kChunk)] = j;
                     if (r % kChunk == 0) { rec[0] = key; rec[1] = min(kChunk, n - r); rec[2] = off + r; rec[3] = 0; }
                 }
-                if (tiled && r % tile_rows == 0) ((int4 *)pv.tiles)[tbase[key] + r / tile_rows] = make_int4(key, min(tile_rows, n - r), off + r, 0);
+                if (tiled && r % tile_rows == 0) ((int4 *)pv.tiles)[tbase[key] + r / tile_rows] = make_int4(key, min(tile_rows, n - r), off + r, n_tiles);
             }
         }
     }
@@ -630,7 +630,7 @@ void plan_big_place_kernel(const BigSide pairs, const BigSide toks, int32_t *__r
     if (block == 0 && tid == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
     if (j >= d.P) return;
     if (records && j >= n_chunks && j < rec_bound) pv.chunks[(int64_t)j * kRec + 1] = 0;      // empty record past the live chunks
-    if (TILED && records && j >= n_tiles && j < tile_bound) ((int4 *)pv.tiles)[j] = make_int4(0, 0, 0, 0);
+    if (TILED && records && j >= n_tiles && j < tile_bound) ((int4 *)pv.tiles)[j] = make_int4(0, 0, 0, n_tiles);
     if (j >= n_rows) {
         pv.sorted[j] = -1;
         if (records && out_sorted) out_sorted[j] = -1;
@@ -643,7 +643,7 @@ void plan_big_place_kernel(const BigSide pairs, const BigSide toks, int32_t *__r
     int32_t *rec = pv.chunks + (int64_t)(cbase[key] + r / kChunk) * kRec;
     rec[4 + (r % kChunk)] = j;
     if (r % kChunk == 0) { rec[0] = key; rec[1] = min(kChunk, n - r); rec[2] = off + r; rec[3] = 0; }
-    if (TILED && r % tile_rows == 0) ((int4 *)pv.tiles)[tbase[key] + r / tile_rows] = make_int4(key, min(tile_rows, n - r), off + r, 0);
+    if (TILED && r % tile_rows == 0) ((int4 *)pv.tiles)[tbase[key] + r / tile_rows] = make_int4(key, min(tile_rows, n - r), off + r, n_tiles);
 }
 
 bool plan_route_in_one_launch(int64_t P, int64_t NK)

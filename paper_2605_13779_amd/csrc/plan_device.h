@@ -185,12 +185,12 @@ __device__ __forceinline__ void plan_dense_count(const PlanView &pv, const int32
         rec[4 + (rank[r] % kChunk)] = row;
         if (rank[r] % kChunk == 0) { rec[0] = s[r]; rec[1] = min(kChunk, n - rank[r]); rec[2] = pos; rec[3] = 0; }
         if (tile_rows > 0 && rank[r] % tile_rows == 0)
-            ((int4 *)pv.tiles)[(b >> 16) + rank[r] / tile_rows] = make_int4(s[r], min(tile_rows, n - rank[r]), pos, 0);
+            ((int4 *)pv.tiles)[(b >> 16) + rank[r] / tile_rows] = make_int4(s[r], min(tile_rows, n - rank[r]), pos, n_tiles);
     }
     if (i == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
     // records past the live ones are marked empty (count 0): the apply kernels read only records
     for (int d = n_chunks + i; d < rec_bound; d += N) pv.chunks[(int64_t)d * kRec + 1] = 0;
-    for (int d = n_tiles + i; d < tile_bound; d += N) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
+    for (int d = n_tiles + i; d < tile_bound; d += N) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, n_tiles);
 }
 
 // The planner inside a workgroup of an apply kernel: every thread calls it (i = thread index,
@@ -302,7 +302,7 @@ __device__ __forceinline__ void plan_dense_local(const int32_t *__restrict__ tok
         if (write_pv && tile_rows > 0) {
             int t = 0, r0 = 0;                     // this row's tile of the slot, and the tile's first row
             while (r0 + tile_rows <= rank) { r0 += tile_rows; ++t; }
-            if (r0 == rank) ((int4 *)pv.tiles)[L.tbase[s] + t] = make_int4(s, min(tile_rows, n - rank), pos, 0);
+            if (r0 == rank) ((int4 *)pv.tiles)[L.tbase[s] + t] = make_int4(s, min(tile_rows, n - rank), pos, n_tiles);
         }
         if (write_pv) {
             pv.sorted[pos] = i;
@@ -317,7 +317,7 @@ __device__ __forceinline__ void plan_dense_local(const int32_t *__restrict__ tok
         if (write_pv) pv.chunks[(int64_t)d * kRec + 1] = 0;
     }
     if (write_pv)
-        for (int d = n_tiles + i; d < tile_bound; d += nthreads) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, 0);
+        for (int d = n_tiles + i; d < tile_bound; d += nthreads) ((int4 *)pv.tiles)[d] = make_int4(0, 0, 0, n_tiles);
     __syncthreads();
 }
 

@@ -62,11 +62,10 @@ struct TileRows {
     int yrow[TM / 8];              // row 8 * g + lane / 8
 };
 
-// Tile `tile` of a plan: its record and rows (in global memory, or in LDS where the launch planned for itself).
+// A tile of a plan from its record, which every lane holds.
 template <int TM>
-__device__ __forceinline__ bool tile_from_plan(const int4 *tiles, const int32_t *sorted, int top_k, int tile, int lane, TileRows<TM> &t)
+__device__ __forceinline__ bool tile_from_record(const int4 &r, const int32_t *sorted, int top_k, int lane, TileRows<TM> &t)
 {
-    const int4 r = tiles[tile];
     t.key = __builtin_amdgcn_readfirstlane(r.x);
     t.cnt = __builtin_amdgcn_readfirstlane(r.y);
     if (t.cnt <= 0) return false;
@@ -83,14 +82,21 @@ __device__ __forceinline__ bool tile_from_plan(const int4 *tiles, const int32_t 
     return true;
 }
 
+template <int TM>
+__device__ __forceinline__ bool tile_from_plan(const int4 *tiles, const int32_t *sorted, int top_k, int tile, int lane, TileRows<TM> &t)
+{
+    return tile_from_record<TM>(tiles[tile], sorted, top_k, lane, t);
+}
+
 // A launch whose parts trade partial sums, as a workgroup sees it.
 struct TileTrade {
     bool on;                       // this site trades
     int wg;                        // the workgroup's number among the site's
+    int parts;                     // workgroups of a tile
     uint32_t tag;                  // the launch tag (thread 0 only)
 };
 
-// blk0, n_blk: the blocks of 64 outputs to expand.  XCH: the tile's a.parts workgroups also divide d_in; each
+// blk0, n_blk: the blocks of 64 outputs to expand.  XCH: the tile's trade.parts workgroups also divide d_in; each
 // publishes the sums of its slice as words (value, launch tag) and adds everybody's in slice order.  A wait
 // for a partner's words is bounded: on giving up the workgroup sums all of d_in itself.  A launch tag that says
 // so (kTagPoison) makes every part do that without waiting.
@@ -104,7 +110,7 @@ template <bool NT> __device__ __forceinline__ uint4 ld16(const void *p) { if con
 
 template <int RP, int NW, int TM, bool XCH = false, int NS = 1, int CP = 0, bool RB = false>
 __device__ __forceinline__ void tile_body(const TileArgs &a, const TileArgs &b2, const TileRows<TM> &t, unsigned char *lds, const int blk0,
-                                          const int n_blk, const int tile = 0, const int part_i = 0, const TileTrade &trade = TileTrade{false, 0, 0u})
+                                          const int n_blk, const int tile = 0, const int part_i = 0, const TileTrade &trade = TileTrade{false, 0, 1, 0u})
 {
     static_assert(NS == 1 || (!XCH && RP <= 16), "two sites: small ranks, nothing traded");
     using C = TileCfg<RP, NW, TM, NS>;
@@ -140,7 +146,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, const TileArgs &b2,
     __shared__ int s_missing;
     __shared__ uint32_t s_tag;
     // steps [st0, st1) of d_in; this wave's i-th is st0 + ksw + i * KSW
-    const int st0 = solo ? 0 : part_i * n_steps / a.parts, st1 = solo ? n_steps : (part_i + 1) * n_steps / a.parts;
+    const int st0 = solo ? 0 : part_i * n_steps / trade.parts, st1 = solo ? n_steps : (part_i + 1) * n_steps / trade.parts;
     const int n = (st1 - st0 - ksw + C::KSW - 1) / C::KSW;
     auto unit_of = [&](int i) { return (st0 + i * C::KSW + ksw) * 8 + lu; };
     uint4 av[C::DP][C::RGN], xv[C::DP][C::TG];
@@ -308,7 +314,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, const TileArgs &b2,
         for (int e = tid; e < TM * C::RT; e += C::NT) put_h(e, own_sum(e));
     } else {
         const int n_e = t.cnt * C::RPE;                          // rows past the count are nobody's
-        uint64_t *const xw = a.xch + (int64_t)tile * a.parts * (TM * C::RPE);
+        uint64_t *const xw = a.xch + (int64_t)tile * trade.parts * (TM * C::RPE);
         const uint32_t tag = __builtin_amdgcn_readfirstlane(s_tag);
         bool gave_up = tag == kTagPoison;
         if (!gave_up)
@@ -316,13 +322,16 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, const TileArgs &b2,
         int spins = 0;                                           // (one allowance for all of the thread's words)
         for (int e = tid; e < n_e && !gave_up; e += C::NT) {
             float s = 0.f;
-            for (int p0 = 0; p0 < a.parts; p0 += 4) {            // four words in flight, added in slice order
-                uint64_t wv[4];
+            // Words in flight, added in slice order.  (All asked for, past the last part its own again: behind a condition
+            // each waited for the one before it, 2 us of 16 parts.)
+            constexpr int W = 4;
+            for (int p0 = 0; p0 < trade.parts; p0 += W) {
+                uint64_t wv[W];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) if (p0 + k < a.parts) wv[k] = xch_get(xw + (int64_t)(p0 + k) * (TM * C::RPE) + e);
+                for (int k = 0; k < W; ++k) wv[k] = xch_get(xw + (int64_t)min(p0 + k, trade.parts - 1) * (TM * C::RPE) + e);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if (p0 + k >= a.parts) break;
+                for (int k = 0; k < W; ++k) {
+                    if (p0 + k >= trade.parts) break;
                     if (p0 + k == part_i) { s += own_sum(e); continue; }
                     while ((uint32_t)(wv[k] >> 32) != tag) {
                         if (++spins > a.poll_limit) { gave_up = true; break; }

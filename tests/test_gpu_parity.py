@@ -686,6 +686,38 @@ def test_launch_that_finds_its_tiles_in_the_batch(M, oracle, T, S, q):
     assert np.array_equal(_plan_tiles(pa, T, S)[:bound], _plan_tiles(pb, T, S)[:bound])
 
 
+@pytest.mark.parametrize("live", [1, 8, 9, 63, 64, 65, 127, 128, 129, 150])
+def test_parts_by_live_tiles(M, oracle, live):
+    """The device cuts tiles in parts by the number of live ones: one tile per slot, on the edges of eight and of the
+    128 beyond which a tile is whole; three sites of different widths in a launch, one of which trades sums where the
+    launch does; rows without an adapter between them, so that the bound lies above.  Three calls in a row: the launch tag
+    goes on, nobody gave up a wait."""
+    T = 2 * live + 5
+    slots = np.full(T, -1, np.int32)
+    slots[W.rng(510 + live).permutation(T)[:live]] = W.rng(511 + live).permutation(live)
+    shapes = [(264, 1032), (264, 4104), (264, 72)] if live % 2 else [(4160, 1032), (264, 136)]
+    cases = [W.dense_case(f"live{live}_{k}", 5200 + 7 * live + k, T, i, o, live, 16, 32.0, token_slot=slots, std_a=0.05, std_b=0.05) for k, (i, o) in enumerate(shapes)]
+    sites = [dense_site(M, c) for c in cases]
+    ts, xs, plan = torch.from_numpy(slots).cuda(), [P.dev_bf16(c.x) for c in cases], M.Plan(T, live)
+    refs = [oracle.apply_decode(c.x, c.y0, c.A, c.B, c.rank, c.alpha, c.token_slot) for c in cases]
+    M.set_tuning("tile_rows", 8)
+    try:
+        for k in range(3):
+            ys = [P.dev_bf16(c.y0) for c in cases]
+            if k == 1:
+                M.lora_plan_decode(plan, ts, live)
+                M.lora_apply_decode_multi(sites, plan, xs, ys)
+            else:
+                M.lora_plan_apply_decode_multi(sites, plan, ts, live, xs, ys)
+            torch.cuda.synchronize()
+            for c, y, ref, site in zip(cases, ys, refs, sites):
+                P.check_close(P.host_bits(y), ref, c.name)
+                P.check_untouched(P.host_bits(y), c.y0, slots < 0, c.name)
+                site.check()
+    finally:
+        M.set_tuning("tile_rows", 0)
+
+
 def test_graph_replay_keeps_results_right(M, oracle):
     """A captured graph replays the same kernel arguments; the launches that exchange partial
     results between workgroups must still tell one replay from the next.  Inputs change between
