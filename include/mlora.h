@@ -271,7 +271,8 @@ int32_t lora_apply_decode_noalloc(mlora_site *site, const void *x, int64_t ldx, 
  * they are validated here (MLORA_E_SEGMENTS / MLORA_E_SLOT) and travel in the kernel arguments (long
  * tables are copied to the device).  Everything runs on the matrix cores: wide rank-64 sites with d_in a
  * multiple of 16 as a shrink and an expand half with d_in and d_out cut over workgroups, others in tiles
- * of up to 48 rows. */
+ * of up to 48 rows, which batches of few rows divide over d_in and d_out too (up to the order of the fp32 partial sums
+ * the same result). */
 int32_t lora_apply_segmented(mlora_site *site, const void *x, int64_t ldx, void *y, int64_t ldy,
                              const int32_t *seg_off, const int32_t *seg_slot, int32_t S,
                              int32_t T, void *stream);
@@ -326,7 +327,7 @@ int32_t mlora_resident_stats(mlora_resident *r, int64_t *out /* [MLORA_RESIDENT_
  * rows_mode, rows_waves, rows_chunk_run (launches over chunks), tile_rows, tile_moe_rows (height of
  * the tiles of a decode and of a route plan: 4..16, negative: none), tile_parts (launches over tiles); plan_general, plan_separate, plan_pipeline (planners);
  * seg_expand_groups, seg_table_copy, seg_shrink_wgs, seg_tiles (1 / -1: rank-64 prefill always / never in
- * tiles; seg_no_mfma, 0 or 1, is an earlier name of it), seg_overlap (batches of the rank-64
+ * tiles; seg_no_mfma, 0 or 1, is an earlier name of it), seg_parts (prompts in tiles: parts that trade sums, -1: none), seg_overlap (batches of the rank-64
  * prefill in flight on a second stream), seg_fused (-1: that prefill as two launches instead of one);
  * upload_piece_kb; moe_down_form (down projection: 1 token by token up to rank 16, -1 in two launches).
  * MLORA_E_INVALID for any other name and for a tile height outside its range. */

@@ -3,6 +3,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <atomic>
 #include <mutex>
@@ -30,6 +31,7 @@ struct mlora_site {
     mlora_plan priv;            // private plan living in the caller-provided scratch
     uint32_t *ctrl;             // dense sites: launch tag / sign-in counters of launches whose workgroups trade partial sums
     uint64_t *xch;              // dense sites: partial shrink results in flight between workgroups
+    uint64_t *prompt_xch;       // the same of prompts
     int32_t *seg_dev;           // device area for segment tiles / chunks
     int32_t seg_cap;            // in entries of 3 ints
     int32_t *stage[2];          // pinned host staging for the segment tables (lazy)
@@ -52,6 +54,10 @@ constexpr int32_t kMoePrivItems = 131072;      // pairs per private MoE plan
 constexpr int32_t kSegCap = 65536;             // segment tiles / chunks per call
 constexpr size_t kCtrlBytes = 1024;
 constexpr size_t kXchBytes = (size_t)1 << 20;          // words that the parts of a launch's tiles trade their partial sums through
+constexpr int32_t kTradeCus = 256;                     // workgroups of a launch of prompts whose tiles are divided, at most
+// The words of such prompts (see divided_parts): one per workgroup, row of a tile and rank, for tiles of up to 48
+// rows.  In front of the control block, in an area of their own: nothing else may ever stand there.
+size_t prompt_xch_bytes(int32_t r_pad) { return r_pad >= 8 ? (size_t)kTradeCus * 48 * 8 * (size_t)r_pad : 0; }
 constexpr size_t kSegXchBytes = (size_t)24 << 20;   // rank-64 sites: exchange words, then the prefill's partial shrink results
 // behind the exchange words: tile counters (16 KB), then per tile 16 KB of h (bf16 head + tail), then the
 // fp32 partials of the k-slices
@@ -63,7 +69,7 @@ std::atomic<int32_t> g_knob[kKnobCount];
 const char *const kKnobName[kKnobCount] = {
     "rows_poll_limit", "rows_rank_bound", "rows_items_target", "rows_mode", "rows_waves", "plan_general",
     "plan_separate", "plan_pipeline", "seg_expand_groups", "seg_table_copy", "seg_shrink_wgs", "seg_tiles", "seg_overlap",
-    "upload_piece_kb", "seg_fused", "rows_chunk_run", "tile_rows", "tile_parts", "tile_moe_rows", "moe_down_form"};
+    "upload_piece_kb", "seg_fused", "rows_chunk_run", "tile_rows", "tile_parts", "tile_moe_rows", "moe_down_form", "seg_parts"};
 
 // Host-side record of a slot's rank (the kernels read the device table; this only tells the launch
 // code whether any slot is padded, i.e. whether rank-bounded reads of A can save traffic).
@@ -661,9 +667,66 @@ int32_t segmented_mfma(mlora_site *s, const void *x, int64_t ldx, void *y, int64
     return MLORA_OK;
 }
 
+// Into how many parts that trade sums the tiles of a batch of prompts are divided (0: not at all), `pair`: in place of the
+// rank-64 pair.  A batch of few rows leaves a CU with a low tile and all of an adapter: 1024 rows of 6 prompts, rank 32, 9728 ->
+// 1024, in 256 tiles of four rows 19.9 us.  Divided over d_in and d_out the tiles are p times as high and the CU moves
+// a p-th of the adapter (3 parts of 13 rows 13.5 us), for the words that a tile's parts wait for.  Each way's time, in us, from the
+// bytes that one CU moves (adapter, rows, words) and those of the batch, fitted to 466 random batches of 64 to 8000 rows of 1 to 64
+// prompts, ranks 8 to 64, 512 to 9728 -> 512 to 18432, over which the choice takes 3.4 % more than the better way each time, 8 %
+// less than without it (a quarter of them at least 5 %, at most half the time); slower by more than 2 % in 3, at most 1.18
+// times.  Before / after: rank 8, 7168 -> 7168, 1024 rows 19.7 / 15.8; rank 16, 1024 -> 9728, 1024 rows 22.7 / 16.7; rank 32, 7168 ->
+// 7168, 64 rows 14.2 / 8.4, 2048 rows 38.9 / 31.4; rank 64, 2560 -> 2560, 64 rows 13.9 / 7.7, 512 rows 16.7 / 10.8.
+int32_t divided_parts(const mlora_site *s, const int32_t *seg_off, const int32_t *seg_slot, int32_t S, bool pair)
+{
+    const int32_t asked = tuning(kSegParts);
+    if (!s->prompt_xch || asked < 0 || tuning(kTileParts) > 0) return 0;
+    if (asked > 1) return asked;
+    int32_t live = 0, longest = 0, tiles64 = 0;
+    int64_t n_rows = 0;
+    for (int32_t k = 0; k < S; ++k) {
+        const int32_t len = seg_off[k + 1] - seg_off[k];
+        if (seg_slot[k] < 0 || len == 0) continue;
+        ++live;
+        longest = std::max(longest, len);
+        tiles64 += (len + 63) / 64;
+        n_rows += len;
+    }
+    const float cus = (float)std::min(cu_count(s->d.device), kTradeCus), rows = (float)n_rows, half = 0.5f * (float)live;
+    if (live == 0 || rows + half > 48.f * 0.5f * cus) return 0;          // (two parts of the highest tiles would not fit)
+    const int32_t r = s->r_pad, n_blk = (s->d.d_out + 63) / 64;
+    const float d_in = (float)s->d.d_in, d_out = (float)s->d.d_out, adapter = 2e-3f * (float)r * (d_in + d_out), row = 1e-3f * (2.f * d_in + 4.f * d_out), batch = 1e-3f * rows * row;
+    auto height = [&](float q) { return (float)(((int32_t)std::ceil(q) + 7) / 8 * 8); };          // rows that a tile loads
+    auto fits = [&](float tiles) { return std::min((float)longest, std::max(1.f, rows / std::max(1.f, tiles - half))); };
+    float other;
+    if (pair) other = 8.6f + 1.6e-3f * d_in + 9e-5f * d_out + 0.2f * batch + 0.136f * 128e-6f * (float)tiles64 * (d_in + d_out);
+    else {
+        const float rounds = std::ceil((rows / 48.f + half) / cus);
+        float parts = std::floor(std::min(cus / (rows / (float)std::min(8, longest) + half), (float)(n_blk / 8))), q = 8.f;
+        if (parts < 2.f) { parts = 1.f; q = std::min(48.f, fits(rounds * cus)); }
+        other = 3.7f + rounds * ((r == 64 ? 0.0222f : 0.0172f) * 2e-3f * (float)r * (d_in + d_out / parts) + 0.0082f * 1e-3f * height(q) * (2.f * d_in + 4.f * d_out / parts)) + 0.143f * batch;
+    }
+    float least = 0.9f * other;
+    int32_t best = 0;
+    for (const int32_t p : {2, 3, 4, 6, 8, 12, 16}) {
+        const float tiles = cus / (float)p, q = fits(tiles);
+        if (p > n_blk || tiles <= half || tiles < (float)live || q > (r == 64 ? 32.f : 48.f)) break;
+        const float t = 4.5f + 0.143f * (float)p + (0.02f * adapter + 0.0161f * height(q) * row) / (float)p + 0.0637f * 8e-3f * (float)p * std::ceil(q) * (float)r + 0.127f * batch;
+        if (t < least) { least = t; best = p; }
+    }
+    // (the estimate of the tiles may be a few short)
+    auto tiles_at_most = [&](int32_t q) {
+        int64_t n = 0;
+        for (int32_t k = 0; k < S; ++k) if (seg_slot[k] >= 0) n += (seg_off[k + 1] - seg_off[k] + q - 1) / q;
+        return n;
+    };
+    while (best >= 2 && tiles_at_most(r == 64 ? 32 : tile_max_rows()) * best > (int64_t)cus) --best;
+    return best >= 2 ? best : 0;
+}
+
 // Prefill through the tile kernel: one launch, a table of the segments (in the kernel arguments when it fits).
+// divide: into parts that trade sums (see divided_parts).
 int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy,
-                        const int32_t *seg_off, const int32_t *seg_slot, int32_t S, hipStream_t st)
+                        const int32_t *seg_off, const int32_t *seg_slot, int32_t S, int32_t divide, hipStream_t st)
 {
     TileArgs a{};
     a.x = (const uint16_t *)x; a.ldx = ldx; a.y = (uint16_t *)y; a.ldy = ldy;
@@ -687,7 +750,7 @@ int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int6
             if (seg_slot[k] >= 0) n += (seg_off[k + 1] - seg_off[k] + q - 1) / q;
         return n;
     };
-    const int32_t cus = cu_count(s->d.device), q_max = tile_max_rows();
+    const int32_t cus = cu_count(s->d.device), q_max = tile_max_rows(), trade_cus = std::min(cus, kTradeCus);
     const int64_t rounds = (count(q_max) + cus - 1) / cus;
     const int32_t n_blk = (s->d.d_out + 63) / 64, low = std::min(8, longest);
     int32_t lo = 1, hi = std::min(q_max, longest);
@@ -705,6 +768,21 @@ int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int6
         if (count(q) <= rounds * cus) hi = q; else lo = q + 1;
     }
     a.tile_rows = lo;
+    if (divide >= 2) {
+        const int32_t p = std::min(divide, n_blk);
+        lo = 1; hi = std::min(q_max, longest);
+        while (lo < hi) { const int32_t q = (lo + hi) / 2; if (count(q) * p <= trade_cus) hi = q; else lo = q + 1; }
+        if (count(lo) * p <= trade_cus) {
+            a.tile_rows = lo;
+            a.part_blocks = (n_blk + p - 1) / p;
+            a.parts = (n_blk + a.part_blocks - 1) / a.part_blocks;
+            if (a.parts > 1) {
+                a.xch = s->prompt_xch; a.ctrl = s->ctrl;
+                const int pl = tuning(kRowsPollLimit);
+                a.poll_limit = pl < 0 ? 0 : (pl > 0 ? pl : kPollLimit);
+            }
+        }
+    }
     // A table that the site's device area does not hold goes there in pieces, one copy + one launch each (the
     // stream orders a piece's copy behind the launch that read the piece before it).
     const size_t piece = (size_t)s->seg_cap * 3 / 4 * 4;
@@ -796,7 +874,7 @@ int32_t mlora_site_bytes(const mlora_site_desc *d, size_t *a_tab, size_t *b_tab,
     *b_tab = align256((size_t)d->n_slots * E * d->d_out * rp * 2);
     *meta = align256((size_t)d->n_slots * 16);
     *scratch = align256(plan_words(priv_items(d), (int64_t)d->n_slots * E) * 4) + align256((size_t)kSegCap * 3 * 4)
-             + (d->n_experts > 0 ? 0 : kCtrlBytes + (round_pow2(d->r_max) == 64 ? kSegXchBytes : kXchBytes));
+             + (d->n_experts > 0 ? 0 : prompt_xch_bytes(round_pow2(d->r_max)) + kCtrlBytes + (round_pow2(d->r_max) == 64 ? kSegXchBytes : kXchBytes));
     return MLORA_OK;
 }
 
@@ -820,9 +898,10 @@ int32_t mlora_site_create(const mlora_site_desc *d, void *a_tab, void *b_tab, vo
     init_plan(&s->priv, priv_items(d), (int32_t)NK, d->device, scratch);
     s->seg_dev = (int32_t *)((char *)scratch + align256(plan_words(priv_items(d), NK) * 4));
     s->seg_cap = kSegCap;
-    s->ctrl = nullptr; s->xch = nullptr;
+    s->ctrl = nullptr; s->xch = nullptr; s->prompt_xch = nullptr;
     if (d->n_experts == 0) {
-        s->ctrl = (uint32_t *)((char *)s->seg_dev + align256((size_t)kSegCap * 3 * 4));
+        s->prompt_xch = (uint64_t *)((char *)s->seg_dev + align256((size_t)kSegCap * 3 * 4));
+        s->ctrl = (uint32_t *)((char *)s->prompt_xch + prompt_xch_bytes(s->r_pad));
         s->xch = (uint64_t *)((char *)s->ctrl + kCtrlBytes);
     }
     s->stage[0] = s->stage[1] = nullptr;
@@ -835,7 +914,7 @@ int32_t mlora_site_create(const mlora_site_desc *d, void *a_tab, void *b_tab, vo
     hipError_t e = launch_fill_i32(s->priv.pv.hdr, 0, 8 + 3 * (NK + 1), 0);
     if (ok(e)) e = launch_fill_i32(s->priv.pv.tok_hdr, 0, 8 + 2 * (NK + 1), 0);
     if (ok(e) && s->ctrl) {
-        e = launch_fill_i32((int32_t *)s->ctrl, 0, (int64_t)((kCtrlBytes + (s->r_pad == 64 ? kSegXchBytes : kXchBytes)) / 4), 0);   // tag 0 = never written
+        e = launch_fill_i32((int32_t *)s->prompt_xch, 0, (int64_t)((prompt_xch_bytes(s->r_pad) + kCtrlBytes + (s->r_pad == 64 ? kSegXchBytes : kXchBytes)) / 4), 0);   // tag 0 = never written
         if (ok(e)) e = launch_fill_i32((int32_t *)s->ctrl, 1, 1, 0);                               // first launch tag
         if (ok(e) && s->r_pad == 64) e = launch_fill_i32((int32_t *)seg_ctrl_of(s), 1, 1, 0);      // ... and the prefill's first epoch
     }
@@ -1565,8 +1644,9 @@ int32_t lora_apply_segmented(mlora_site *s, const void *x, int64_t ldx, void *y,
     const int tiles = tuning(kSegTiles);
     const bool small = s->d.d_in + s->d.d_out <= 4096 && (s->d.d_in <= 2048 || T >= 128);
     const bool pair = s->r_pad == 64 && (s->d.d_in & 15) == 0 && s->xch && tiles <= 0 && (tiles < 0 || !small);
-    return pair ? segmented_mfma(s, x, ldx, y, ldy, seg_off, seg_slot, S, st)
-                : segmented_tiles(s, x, ldx, y, ldy, seg_off, seg_slot, S, st);
+    const int32_t divide = tiles < 0 && s->r_pad == 64 ? 0 : divided_parts(s, seg_off, seg_slot, S, pair);
+    return pair && divide == 0 ? segmented_mfma(s, x, ldx, y, ldy, seg_off, seg_slot, S, st)
+                               : segmented_tiles(s, x, ldx, y, ldy, seg_off, seg_slot, S, divide, st);
 }
 
 int32_t moe_lora_apply_packed(mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy,

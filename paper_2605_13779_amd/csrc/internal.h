@@ -239,7 +239,7 @@ int seg_expand_capacity();
 enum Knob {
     kRowsPollLimit, kRowsRankBound, kRowsItemsTarget, kRowsMode, kRowsWaves, kPlanGeneral, kPlanSeparate,
     kPlanPipeline, kSegExpandGroups, kSegTableCopy, kSegShrinkWgs, kSegTiles, kSegOverlap, kUploadPieceKb, kSegFused,
-    kRowsChunkRun, kTileRows, kTileParts, kTileMoeRows, kMoeDownForm, kKnobCount
+    kRowsChunkRun, kTileRows, kTileParts, kTileMoeRows, kMoeDownForm, kSegParts, kKnobCount
 };
 int tuning(Knob k);             // api.hip
 #ifdef MLORA_PROF

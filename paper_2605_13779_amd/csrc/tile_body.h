@@ -320,28 +320,36 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, const TileArgs &b2,
         if (!gave_up)
             for (int e = tid; e < n_e; e += C::NT) xch_put(xw + (int64_t)part_i * (TM * C::RPE) + e, own_sum(e), tag);
         int spins = 0;                                           // (one allowance for all of the thread's words)
-        for (int e = tid; e < n_e && !gave_up; e += C::NT) {
-            float s = 0.f;
-            // Words in flight, added in slice order.  (All asked for, past the last part its own again: behind a condition
-            // each waited for the one before it, 2 us of 16 parts.)
-            constexpr int W = 4;
+        // EB elements at once, W words of each in flight, added in slice order.  (All asked for, past the last part or element its
+        // own again: behind a condition each waited for the one before it, 2 us of 16 parts.)
+        constexpr int W = 4, EB = TM <= 16 ? 1 : 4;
+        for (int e0 = tid; e0 < n_e && !gave_up; e0 += EB * C::NT) {
+            float s[EB];
+#pragma unroll
+            for (int u = 0; u < EB; ++u) s[u] = 0.f;
             for (int p0 = 0; p0 < trade.parts; p0 += W) {
-                uint64_t wv[W];
+                uint64_t wv[EB][W];
+                auto word = [&](int u, int k) __attribute__((always_inline)) { return xw + (int64_t)min(p0 + k, trade.parts - 1) * (TM * C::RPE) + min(e0 + u * C::NT, n_e - 1); };
 #pragma unroll
-                for (int k = 0; k < W; ++k) wv[k] = xch_get(xw + (int64_t)min(p0 + k, trade.parts - 1) * (TM * C::RPE) + e);
+                for (int u = 0; u < EB; ++u)
 #pragma unroll
-                for (int k = 0; k < W; ++k) {
-                    if (p0 + k >= trade.parts) break;
-                    if (p0 + k == part_i) { s += own_sum(e); continue; }
-                    while ((uint32_t)(wv[k] >> 32) != tag) {
-                        if (++spins > a.poll_limit) { gave_up = true; break; }
-                        __builtin_amdgcn_s_sleep(1);
-                        wv[k] = xch_get(xw + (int64_t)(p0 + k) * (TM * C::RPE) + e);
+                    for (int k = 0; k < W; ++k) wv[u][k] = xch_get(word(u, k));
+#pragma unroll
+                for (int u = 0; u < EB; ++u)
+#pragma unroll
+                    for (int k = 0; k < W; ++k) {
+                        if (p0 + k >= trade.parts || gave_up) break;
+                        if (p0 + k == part_i) { s[u] += own_sum(min(e0 + u * C::NT, n_e - 1)); continue; }
+                        while ((uint32_t)(wv[u][k] >> 32) != tag) {
+                            if (++spins > a.poll_limit) { gave_up = true; break; }
+                            __builtin_amdgcn_s_sleep(1);
+                            wv[u][k] = xch_get(word(u, k));
+                        }
+                        s[u] += __uint_as_float((uint32_t)wv[u][k]);
                     }
-                    s += __uint_as_float((uint32_t)wv[k]);
-                }
             }
-            put_h(e, s);
+#pragma unroll
+            for (int u = 0; u < EB; ++u) if (EB == 1 || e0 + u * C::NT < n_e) put_h(e0 + u * C::NT, s[u]);
         }
         if (gave_up) atomicOr(&s_missing, 1);
         __syncthreads();

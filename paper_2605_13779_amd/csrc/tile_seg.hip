@@ -39,18 +39,53 @@ __device__ __forceinline__ bool tile_from_segments(const TileArgs &a, const uint
 
 struct TileSegInline { uint32_t w[kTileInline]; };
 
-template <int RP, int NW, int TM, int CP = 0>
+// TRADE: a tile's parts also divide d_in and trade partial sums; they run at the same time, one workgroup per CU.
+template <int RP, int NW, int TM, int CP = 0, bool TRADE = false>
 __global__ __launch_bounds__(NW * 64, 2)
 void tile_seg_kernel(const TileArgs a, const TileSegInline inl)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[TileCfg<RP, NW, TM>::LDS];
     // an XCD gets a contiguous range of tiles (workgroups are dealt round-robin): neighbours share an adapter, in its L2
     const int n8 = (int)gridDim.x >> 3, item = ((int)blockIdx.x & 7) * n8 + ((int)blockIdx.x >> 3);
-    const int tile = a.parts > 1 ? item / a.parts : item, blk0 = (item - tile * a.parts) * a.part_blocks;
-    if (tile >= a.n_tiles) return;
-    TileRows<TM> t;
-    if (!tile_from_segments<TM>(a, a.segs ? (const uint32_t *)a.segs : inl.w, tile, (int)threadIdx.x & 63, t)) return;
-    tile_body<RP, NW, TM, false, 1, CP>(a, a, t, lds, blk0, min(a.part_blocks, ((a.d_out + 63) >> 6) - blk0));
+    const int tile = a.parts > 1 ? item / a.parts : item, part = item - tile * a.parts, blk0 = part * a.part_blocks;
+    if constexpr (!TRADE) {
+        if (tile >= a.n_tiles) return;
+        TileRows<TM> t;
+        if (!tile_from_segments<TM>(a, a.segs ? (const uint32_t *)a.segs : inl.w, tile, (int)threadIdx.x & 63, t)) return;
+        tile_body<RP, NW, TM, false, 1, CP>(a, a, t, lds, blk0, min(a.part_blocks, ((a.d_out + 63) >> 6) - blk0));
+    } else {
+        // (see tile_multi_body: the last workgroup advances the launch tag when those with a tile have signed in)
+        const bool last = item == (int)gridDim.x - 1;
+        if (tile >= a.n_tiles && !last) return;
+        TileTrade trade{true, item, a.parts, 0u};
+        if (threadIdx.x == 0) trade.tag = tag_read(a.ctrl);
+        if (tile < a.n_tiles) {
+            TileRows<TM> t;
+            if (tile_from_segments<TM>(a, a.segs ? (const uint32_t *)a.segs : inl.w, tile, (int)threadIdx.x & 63, t))
+                tile_body<RP, NW, TM, true, 1, CP>(a, a, t, lds, blk0, min(a.part_blocks, ((a.d_out + 63) >> 6) - blk0), tile, part, trade);
+            else if (threadIdx.x == 0) tag_sign_in(a.ctrl, item, trade.tag);
+        }
+        if (last && threadIdx.x < 64) {
+            const uint32_t tag = __builtin_amdgcn_readfirstlane(trade.tag);
+            if (tag != kTagPoison) tag_advance(a.ctrl, a.n_tiles * a.parts, tag, (int)threadIdx.x);
+        }
+    }
+}
+
+template <int RP>
+static hipError_t launch_tile_seg_trade(const TileArgs &a, const TileSegInline &table, const dim3 &grid, hipStream_t st)
+{
+    const dim3 block(512);
+    switch ((a.tile_rows + 7) / 8) {
+        case 1: tile_seg_kernel<RP, 8, 8, 0, true><<<grid, block, 0, st>>>(a, table); break;
+        case 2: tile_seg_kernel<RP, 8, 16, 0, true><<<grid, block, 0, st>>>(a, table); break;
+        case 3: tile_seg_kernel<RP, 8, 24, 0, true><<<grid, block, 0, st>>>(a, table); break;
+        case 4: tile_seg_kernel<RP, 8, 32, 0, true><<<grid, block, 0, st>>>(a, table); break;
+        case 5: tile_seg_kernel<RP, 8, 40, 0, true><<<grid, block, 0, st>>>(a, table); break;
+        case 6: tile_seg_kernel<RP, 8, 48, 0, true><<<grid, block, 0, st>>>(a, table); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 template <int RP>
@@ -59,6 +94,7 @@ static hipError_t launch_tile_seg_rp(const TileArgs &a, const uint32_t *inl, hip
     TileSegInline table;
     if (!a.segs) for (int i = 0; i < 4 * a.n_segs; ++i) table.w[i] = inl[i];
     const dim3 grid((unsigned)(((int64_t)a.n_tiles * a.parts + 7) / 8 * 8)), block(512);
+    if constexpr (RP >= 8) if (a.xch) return launch_tile_seg_trade<RP>(a, table, grid, st);
     // (8192 rows, 2560 -> 9728 at rank 16: 81.1 -> 73.7 us with y streamed; 2560 -> 2560: 25.7 -> 26.6)
     const bool stream = (int64_t)a.n_tiles * a.tile_rows * a.d_out * 2 >= (96 << 20);
     if constexpr (RP >= 8) if (stream) switch ((a.tile_rows + 7) / 8) {

@@ -718,6 +718,66 @@ def test_parts_by_live_tiles(M, oracle, live):
         M.set_tuning("tile_rows", 0)
 
 
+@pytest.mark.parametrize("r,parts", [(8, 2), (8, 16), (12, 3), (16, 5), (24, 4), (32, 2), (48, 3), (64, 2), (64, 8)])
+def test_prompts_in_divided_tiles(M, oracle, r, parts):
+    """Prompts whose tiles are divided into parts that trade sums: tile heights of all kinds (one row to the highest), runs
+    of one row, runs without an adapter and on an empty slot, widths that leave parts of different size, d_in that
+    leaves a part of a step.  Twice in a row and once where every wait is given up at once (parts sum for themselves)."""
+    for k, (T, S, d_in, d_out) in enumerate([(1, 1, 264, 1096), (9, 2, 520, 136), (100, 5, 1032, 1288), (47 * (256 // parts) - 450, 9, 72, 264)]):
+        g = W.rng(4400 + 10 * r + k)
+        cuts = np.sort(g.choice(np.arange(1, T), size=S - 1, replace=False)) if S > 1 else np.zeros(0, int)
+        off = np.concatenate([[0], cuts, [T]]).astype(np.int32)
+        slot = g.integers(0, 4, size=S).astype(np.int32)
+        if S > 4:
+            slot[1], slot[3], off[3] = -1, 3, off[2]          # no adapter; a run of no rows
+        ranks = [r, max(1, r - 3), r, 0] if S > 1 else [r] * 4
+        c = W.seg_case(f"div{r}_{parts}_{k}", 4500 + 10 * r + k, T, S, d_in, d_out, 4, r, 2.0 * r, ranks=ranks, seg_off=off.tolist(), seg_slot=slot.tolist(), std_a=0.05, std_b=0.05)
+        site, x = dense_site(M, c), P.dev_bf16(c.x)
+        ref = oracle.apply_segmented(c.x, c.y0, c.A, c.B, c.rank, c.alpha, c.seg_off, c.seg_slot)
+        M.set_tuning("seg_parts", parts)
+        try:
+            for limit in (0, 0, -1):
+                M.set_tuning("rows_poll_limit", limit)
+                y = P.dev_bf16(c.y0)
+                M.lora_apply_segmented(site, x, y, c.seg_off, c.seg_slot)
+                torch.cuda.synchronize()
+                P.check_close(P.host_bits(y), ref, c.name)
+                for j in range(S):
+                    if slot[j] < 0 or ranks[slot[j]] == 0:
+                        assert np.array_equal(P.host_bits(y)[off[j]:off[j + 1]], c.y0[off[j]:off[j + 1]])
+        finally:
+            M.set_tuning("seg_parts", 0)
+            M.set_tuning("rows_poll_limit", 0)
+        site.check()
+
+
+def test_divided_prompts_in_a_graph(M, oracle):
+    """The launch tag of divided prompts lives in device memory: replays of one launch do not take each other's sums."""
+    c = W.seg_case("divgraph", 4700, 200, 3, 1032, 520, 3, 16, 32.0, seg_off=[0, 70, 71, 200], seg_slot=[1, 0, 2], std_a=0.05, std_b=0.05)
+    site = dense_site(M, c)
+    x, y = P.dev_bf16(c.x), P.dev_bf16(c.y0)
+    M.set_tuning("seg_parts", 4)
+    try:
+        M.lora_apply_segmented(site, x, y, c.seg_off, c.seg_slot)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            M.lora_apply_segmented(site, x, y, c.seg_off, c.seg_slot)
+        for k in range(4):
+            xk = P.dev_bf16(W.normal_bf16(W.rng(4710 + k), (200, c.d_in), 1.0))
+            x.copy_(xk)
+            y.copy_(P.dev_bf16(c.y0))
+            g.replay()
+            torch.cuda.synchronize()
+            ref = oracle.apply_segmented(P.host_bits(x), c.y0, c.A, c.B, c.rank, c.alpha, c.seg_off, c.seg_slot)
+            P.check_close(P.host_bits(y), ref, f"replay {k}")
+            M.lora_apply_segmented(site, x, y, c.seg_off, c.seg_slot)      # the program's own work between replays
+            torch.cuda.synchronize()
+    finally:
+        M.set_tuning("seg_parts", 0)
+    site.check()
+
+
 def test_graph_replay_keeps_results_right(M, oracle):
     """A captured graph replays the same kernel arguments; the launches that exchange partial
     results between workgroups must still tell one replay from the next.  Inputs change between
