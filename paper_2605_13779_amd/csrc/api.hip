@@ -612,6 +612,7 @@ int32_t segmented_mfma(mlora_site *s, const void *x, int64_t ldx, void *y, int64
         a.hfin += (size_t)half * (kSegMaxTiles / halves) * 8192;
         a.hpart += (size_t)half * hp_blocks * 4096;
         a.upt = upt; a.n_slices = n_slices;
+        a.stream = streams_y(y, ldy, seg_off[S], d_out);
         int64_t swg = (int64_t)nt * upt / 3;               // every workgroup keeps three units in flight
         const int tuned = tuning(kSegShrinkWgs);
         // As many workgroups as the GPU holds at once; a whole number per tile instead, where that
@@ -732,6 +733,7 @@ int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int6
     a.x = (const uint16_t *)x; a.ldx = ldx; a.y = (uint16_t *)y; a.ldy = ldy;
     a.a_tab = s->a_tab; a.b_tab = s->b_tab; a.rank = s->rank; a.scale = s->scale;
     a.d_in = s->d.d_in; a.d_out = s->d.d_out; a.r_pad = s->r_pad; a.n_experts = 1;
+    a.stream = streams_y(y, ldy, seg_off[S], s->d.d_out);
     // Rows per tile: the fewest that cut the batch into one round of tiles (one per CU), or two, three, ...
     // rounds when a round's tiles would be too large.  A round takes as long as its tiles, so a few
     // tiles more than CUs cost a whole second one: 8192 rows in 16 runs, 2560 -> 2560 at rank 16, take 33.2

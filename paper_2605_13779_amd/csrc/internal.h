@@ -135,6 +135,7 @@ struct TileArgs {
     int32_t top_k;           // x row = item / top_k
     int32_t one_tile;        // most groups are one tile
     int32_t rank_bound;      // 1: read the slot's rank first and fetch only that many rows of A (packed MoE)
+    int32_t stream;          // segments, 1: y does not stay in the caches (see streams_y)
     int32_t parts;           // workgroups per tile; plans: at most (see TileSplit)
     int32_t part_blocks;     // segments: part p expands blocks [p * part_blocks, ...) of 64 outputs
     // parts that also divide d_in trade their partial sums (see the exchange below); null: every part sums alone
@@ -142,9 +143,20 @@ struct TileArgs {
     uint32_t *ctrl;          // [0] launch tag, [1] error flag, [8..72) sign-ins
     int32_t poll_limit;
 };
+// Whether y, [rows, d_out] of bf16, goes past the caches (non-temporal loads and stores; both count, either alone changes
+// nothing).  Where it is larger than what the caches still hold of it from the launch that wrote it, and only where every block of
+// 64 outputs is a whole line: of a line that two waves touch, the second would come back to memory.  Prompts of
+// 8192 rows, 7168 -> 7168 (117 MB), kept / streamed: rank 16 81.0 / 68.8 us, rank 64 94.5 / 86.2; 14,999 rows, 7168 -> 18,432, rank 64 286.8 / 266.4;
+// 3206 rows, rank 8, 2680 -> 15,784 (31,568 bytes a row, 101 MB) 62.1 / 87.0.  Smaller ones: on cold buffers up to 25 % faster streamed, on warm ones as
+// much slower (1001 rows of a dense decode layer 86.0 / 81.0 cold, 70.6 / 78.3 warm; rank 16, 8192 rows, 2560 -> 2560 25.3 / 28.4 warm).
+inline bool streams_y(const void *y, int64_t ldy, int64_t rows, int64_t d_out)
+{
+    return (((uintptr_t)y | (uintptr_t)(2 * ldy)) & 127) == 0 && 2 * rows * d_out >= (96 << 20);
+}
 constexpr int kMaxTileRows = 16;  // of a plan's tiles (those of segments: tile_max_rows())
 int tile_max_rows();
 hipError_t launch_tile_seg(const TileArgs &a, const uint32_t *inl, hipStream_t st);
+hipError_t launch_tile_seg_trade(const TileArgs &a, const uint32_t *inl, hipStream_t st);
 hipError_t launch_tile_moe(const TileArgs *sites, int n, hipStream_t st);
 // Into how many parts a launch over a plan's tiles cuts each, by the number of live tiles, which the device knows: byte
 // t - 1 of the table for up to 8 * t of them, one part beyond 8 * kSplitEighths (a site takes no more than its
@@ -199,6 +211,7 @@ constexpr int kSegInline = 832;   // words of tables inside the kernel arguments
 struct SegArgs {
     const uint16_t *x; int64_t ldx;
     uint16_t *y;       int64_t ldy;
+    int32_t stream;          // 1: y does not stay in the caches (see streams_y)
     const uint16_t *a_tab; const uint16_t *b_tab;
     MetaView meta;
     const int32_t *tiles;    // [4 * n_tiles]: slot, first row, rows (<= 64), 0 -- consecutive pieces of the segments

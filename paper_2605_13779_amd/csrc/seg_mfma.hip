@@ -331,7 +331,7 @@ void seg_shrink_kernel(const SegArgs a)
 // FUSED: the shrink runs in the same launch; a piece's rows are worked on once the flags of the tiles
 // they lie in show the launch's epoch (B_s and the first y pieces are requested before the wait), and h
 // is read with device-scope loads.
-template <bool FUSED>
+template <bool FUSED, bool STREAM>
 __device__ __forceinline__ void seg_expand_body(const SegArgs &a, const int id, unsigned char *lds, const uint32_t epoch)
 {
     uint16_t *const hh0 = (uint16_t *)lds, *const hl0 = hh0 + 2 * 32 * H_LD;
@@ -391,7 +391,8 @@ __device__ __forceinline__ void seg_expand_body(const SegArgs &a, const int id, 
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int tok = min(blk * 32 + half * 16 + tr + 8 * q, nrows - 1);
-            yv[half][q] = *(const uint4 *)(a.y + (int64_t)(row0 + tok) * a.ldy + oc);
+            const char *src = (const char *)(a.y + (int64_t)(row0 + tok) * a.ldy + oc);
+            yv[half][q] = STREAM ? ld_stream(src) : *(const uint4 *)src;
         }
     };
 
@@ -435,7 +436,10 @@ __device__ __forceinline__ void seg_expand_body(const SegArgs &a, const int id, 
                 o.y = pack_bf2(bf_lo(yo.y) + d0.z, bf_hi(yo.y) + d0.w);
                 o.z = pack_bf2(bf_lo(yo.z) + d1.x, bf_hi(yo.z) + d1.y);
                 o.w = pack_bf2(bf_lo(yo.w) + d1.z, bf_hi(yo.w) + d1.w);
-                if (tok < nrows && col_ok) st_quiet(a.y + (int64_t)(row0 + tok) * a.ldy + oc, o);
+                if (tok < nrows && col_ok) {
+                    if constexpr (STREAM) st_quiet_stream(a.y + (int64_t)(row0 + tok) * a.ldy + oc, o);
+                    else st_quiet(a.y + (int64_t)(row0 + tok) * a.ldy + oc, o);
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // reads of the tile precede its reuse
             if constexpr (MORE) y_fetch(blk + 1, half_c);              // into the registers just used
@@ -484,11 +488,12 @@ __device__ __forceinline__ void seg_expand_body(const SegArgs &a, const int id, 
     }
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(NT, 4)
 void seg_expand_kernel(const SegArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[EXPAND_LDS];
-    seg_expand_body<false>(a, xcd_contiguous_id((int)blockIdx.x, (int)gridDim.x), lds, 0u);
+    seg_expand_body<false, STREAM>(a, xcd_contiguous_id((int)blockIdx.x, (int)gridDim.x), lds, 0u);
 }
 
 // Both halves in one launch: the first n_sblocks workgroups shrink, the others expand.  All shrink
@@ -498,6 +503,7 @@ void seg_expand_kernel(const SegArgs a)
 // word and goes on).  The epoch that the flags carry lives in device memory and is advanced by the
 // launch's last workgroup (as the exchange tag of the decode launches is), so that a replayed graph,
 // which repeats the kernel arguments, still gets a fresh one.
+template <bool STREAM>
 __global__ __launch_bounds__(NT, 4)
 void seg_fused_kernel(const SegArgs a, const int n_sblocks)
 {
@@ -512,7 +518,7 @@ void seg_fused_kernel(const SegArgs a, const int n_sblocks)
     __syncthreads();
     const uint32_t epoch = s_epoch;
     if (blk < n_sblocks) seg_shrink_body<true>(a, xcd_contiguous_id(blk, n_sblocks), lds, epoch);
-    else seg_expand_body<true>(a, xcd_contiguous_id(blk - n_sblocks, n_blk - n_sblocks), lds, epoch);
+    else seg_expand_body<true, STREAM>(a, xcd_contiguous_id(blk - n_sblocks, n_blk - n_sblocks), lds, epoch);
     if (blk == n_blk - 1 && threadIdx.x < 64) {
         // every workgroup has signed in (all are past their first instructions or done): next epoch
         const int lane = (int)threadIdx.x;
@@ -554,7 +560,7 @@ int seg_expand_capacity()
     if (cap == 0) {
         int per_cu = 0, cus = 0, dev = 0;
         if (hipGetDevice(&dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, seg_expand_kernel, NT, 0) != hipSuccess) return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, seg_expand_kernel<true>, NT, 0) != hipSuccess) return 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
         cap = per_cu * cus;
     }
@@ -567,7 +573,7 @@ int seg_fused_capacity()
     if (cap == 0) {
         int per_cu = 0, cus = 0, dev = 0;
         if (hipGetDevice(&dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, seg_fused_kernel, NT, 0) != hipSuccess) return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, seg_fused_kernel<true>, NT, 0) != hipSuccess) return 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
         cap = per_cu * cus;
     }
@@ -582,7 +588,8 @@ hipError_t launch_seg_fused(const SegArgs &a, hipStream_t st)
     const int gs = (a.n_swg + 7) / 8 * 8;
     if (gs > seg_fused_capacity()) return hipErrorInvalidValue;
     const int ge = (int)(((int64_t)a.n_groups * a.n_slices + 7) / 8 * 8);
-    seg_fused_kernel<<<dim3((unsigned)(gs + ge)), dim3(NT), 0, st>>>(a, gs);
+    if (a.stream) seg_fused_kernel<true><<<dim3((unsigned)(gs + ge)), dim3(NT), 0, st>>>(a, gs);
+    else seg_fused_kernel<false><<<dim3((unsigned)(gs + ge)), dim3(NT), 0, st>>>(a, gs);
     return hipGetLastError();
 }
 
@@ -599,7 +606,8 @@ hipError_t launch_seg_expand(const SegArgs &a, hipStream_t st)
 {
     if (a.n_tiles <= 0 || a.n_ranges <= 0 || a.n_groups <= 0) return hipSuccess;
     const unsigned ge = (unsigned)(((int64_t)a.n_groups * a.n_slices + 7) / 8 * 8);
-    seg_expand_kernel<<<dim3(ge), dim3(NT), 0, st>>>(a);
+    if (a.stream) seg_expand_kernel<true><<<dim3(ge), dim3(NT), 0, st>>>(a);
+    else seg_expand_kernel<false><<<dim3(ge), dim3(NT), 0, st>>>(a);
     return hipGetLastError();
 }
 

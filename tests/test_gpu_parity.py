@@ -778,6 +778,36 @@ def test_divided_prompts_in_a_graph(M, oracle):
     site.check()
 
 
+@pytest.mark.parametrize("form", ["tiles", "pair", "pair_two"])
+def test_streamed_y_is_the_same(M, oracle, form):
+    """Rows of y that are whole 128-byte lines go past the caches from 96 MB on: the bits of rows that lie across lines (a
+    wider buffer, shifted by 16 bytes), whose columns around the slice stay as they are.  Some rows against the oracle."""
+    T, d_in, d_out, r = 2740, 272, 18432, 64 if form.startswith("pair") else 8
+    c = W.seg_case("stream_" + form, 4812, T, 5, d_in, d_out, 4, r, 16.0, std_a=0.05, std_b=0.05)
+    site, x, y0 = dense_site(M, c), P.dev_bf16(c.x), P.dev_bf16(c.y0)
+    knobs = {"tiles": (("seg_parts", -1),), "pair": (("seg_tiles", -1),), "pair_two": (("seg_tiles", -1), ("seg_fused", -1))}[form]
+    for k in knobs:
+        M.set_tuning(*k)
+    try:
+        ya, wide = y0.clone(), torch.full((T, d_out + 24), 3.0, dtype=torch.bfloat16, device="cuda")
+        yb = wide[:, 8:8 + d_out]
+        yb.copy_(y0)
+        assert ya.data_ptr() % 128 == 0 and 2 * ya.numel() >= 96 << 20 and yb.data_ptr() % 128
+        M.lora_apply_segmented(site, x, ya, c.seg_off, c.seg_slot)
+        M.lora_apply_segmented(site, x, yb, c.seg_off, c.seg_slot)
+        torch.cuda.synchronize()
+    finally:
+        for k, _ in knobs:
+            M.set_tuning(k, 0)
+    assert torch.equal(ya, yb)
+    assert bool((wide[:, :8] == 3).all()) and bool((wide[:, 8 + d_out:] == 3).all())
+    got = P.host_bits(ya)
+    for k in range(5):
+        t = int(c.seg_off[k])
+        ref = oracle.apply_segmented(c.x[t:t + 1], c.y0[t:t + 1], c.A, c.B, c.rank, c.alpha, [0, 1], c.seg_slot[k:k + 1])
+        P.check_close(got[t:t + 1], ref, f"{form} row {t}")
+
+
 def test_graph_replay_keeps_results_right(M, oracle):
     """A captured graph replays the same kernel arguments; the launches that exchange partial
     results between workgroups must still tell one replay from the next.  Inputs change between
