@@ -11,6 +11,10 @@ constexpr int kOneRange = 256;     // one-launch route index build: pairs owned 
 constexpr int kOneKeys = 4096;     // ... largest key space (LDS: three int32 tables of this size, four with tile records)
 constexpr int kOnePairs = 32768;   // ... largest batch (each workgroup walks all of it)
 constexpr int kOneThreads = 1024;
+// ... up to so many pairs a thread takes single ones, beyond whole tokens: 384 pairs, 48 threads of eight LDS adds each before,
+// 7.1 -> 6.4 us, 2048 pairs 7.2 -> 6.6; with eight per thread 8000 pairs 8.9 -> 9.3.  (Half of the gain is that all workgroups write the
+// group offsets, which the first did alone.)
+constexpr int kFewPairs = 2048;
 constexpr int kBigRange = 1024;    // three-launch form: items owned by a workgroup
 constexpr int kBigKeys = 16384;    // ... largest key space (LDS: two int32 tables of this size)
 
@@ -286,7 +290,7 @@ __device__ __forceinline__
 void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, const int32_t *__restrict__ token_slot,
                          int P, int K, uint32_t k_magic, int E, int n_slots, const int32_t *__restrict__ ready_rank,
                          int32_t *__restrict__ out_sorted, int32_t *__restrict__ out_group_off, int rec_bound, const int block,
-                         const int tile_rows, const int tile_bound)
+                         const int n_blocks, const int tile_rows, const int tile_bound)
 {
     __shared__ int32_t tbase[TILED ? kOneKeys + 1 : 1];      // first tile of each group
     __shared__ int32_t goff[kOneKeys + 1];       // exclusive group starts
@@ -308,7 +312,7 @@ void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, c
         if (key >= 0) atomicAdd(&cnt2[key], q < p0 ? 0x10001u : 1u);
         if (q >= p0 && q < p0 + kOneRange) lkey[q - p0] = key;
     };
-    if (topk && K > 1) {
+    if (topk && K > 1 && P > kFewPairs) {
         // a thread takes whole tokens: the slot (and whether it is ready) once, the token's K experts
         // as 16-byte pieces where K allows -- an eighth of the loads of a pair-by-pair walk at K = 8
         const int T = P / K;
@@ -350,7 +354,16 @@ void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, c
         }
     } else {
         constexpr int kU = 16;                                  // keys per thread in flight
-        for (int q0 = 0; q0 < P; q0 += kU * kOneThreads) {
+        if (P <= kFewPairs) {
+            int key[kFewPairs / kOneThreads];
+#pragma unroll
+            for (int u = 0; u < kFewPairs / kOneThreads; ++u) {
+                const int q = u * kOneThreads + tid;
+                key[u] = q < P ? route_key(topk, token_slot, ready_rank, q, k_magic, E, n_slots) : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < kFewPairs / kOneThreads; ++u) visit(u * kOneThreads + tid, key[u]);
+        } else for (int q0 = 0; q0 < P; q0 += kU * kOneThreads) {
             int key[kU];
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
@@ -415,14 +428,13 @@ void plan_route_one_body(const PlanView &pv, const int32_t *__restrict__ topk, c
     }
     __syncthreads();
     const int n_rows = goff[NK], n_chunks = cbase[NK], n_tiles = tiled ? tbase[NK] : 0;
-    if (block == 0) {
-        for (int k = tid; k <= NK; k += kOneThreads) {
-            pv.group_off[k] = goff[k];
-            if (out_group_off) out_group_off[k] = goff[k];
-            if (records) pv.chunk_base[k] = cbase[k];
-        }
-        if (tid == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
+    // group offsets: each workgroup writes a share
+    for (int k = block * kOneThreads + tid; k <= NK; k += n_blocks * kOneThreads) {
+        pv.group_off[k] = goff[k];
+        if (out_group_off) out_group_off[k] = goff[k];
+        if (records) pv.chunk_base[k] = cbase[k];
     }
+    if (block == 0 && tid == 0) { pv.hdr[0] = n_chunks; pv.hdr[1] = n_rows; }
     if (tid < kOneRange) {
         const int j = p0 + tid;                  // this range also owns positions / records [p0, p0 + kOneRange)
         if (j < P) {
@@ -461,10 +473,10 @@ void plan_route_one_kernel(PlanView pv, const int32_t *__restrict__ topk, const 
 {
     const int b = (int)blockIdx.x;
     if (b < pair_blocks) {
-        plan_route_one_body<TILED>(pv, topk, token_slot, P, K, k_magic, E, n_slots, ready_rank, out_sorted, out_group_off, rec_bound, b, tile_rows, tile_bound);
+        plan_route_one_body<TILED>(pv, topk, token_slot, P, K, k_magic, E, n_slots, ready_rank, out_sorted, out_group_off, rec_bound, b, pair_blocks, tile_rows, tile_bound);
     } else {
         const PlanView tv = plan_token_view(pv);
-        plan_route_one_body<TILED>(tv, nullptr, token_slot, T, 1, 0u, 1, n_slots, ready_rank, nullptr, nullptr, 0, b - pair_blocks, 0, 0);
+        plan_route_one_body<TILED>(tv, nullptr, token_slot, T, 1, 0u, 1, n_slots, ready_rank, nullptr, nullptr, 0, b - pair_blocks, (int)gridDim.x - pair_blocks, 0, 0);
     }
 }
 

@@ -808,6 +808,30 @@ def test_streamed_y_is_the_same(M, oracle, form):
         P.check_close(got[t:t + 1], ref, f"{form} row {t}")
 
 
+@pytest.mark.parametrize("T,K,S,E", [(1, 8, 32, 128), (1, 1, 1, 2), (2047, 1, 20, 16), (682, 3, 7, 64), (683, 3, 7, 64), (256, 8, 32, 128), (257, 8, 32, 128), (1024, 2, 5, 8)])
+def test_route_build_of_few_pairs(M, T, K, S, E):
+    """Up to 2048 pairs a thread takes single pairs, beyond whole tokens: group offsets, sorted pairs and the
+    pairs' keys on both sides of the line, rows without a slot and expert ids outside the table among them."""
+    from oracle import ref
+    r = W.rng(6100 + T + K)
+    topk = np.argsort(r.random((T, E)), axis=1)[:, :K].astype(np.int32)
+    slots = r.integers(-1, S, size=T).astype(np.int32)
+    site = M.Site(16, 16, 2, S, n_experts=E)
+    for s in range(S):
+        if s != 1:
+            M.lora_slots_upload(site, s, s, np.zeros((E, 2, 16), np.uint16), np.zeros((E, 16, 2), np.uint16), 2, 2.0)
+    rank = np.array([0 if s == 1 else 2 for s in range(S)], np.int32)
+    plan, sp, go = M.Plan(T * K, S * E), torch.empty(T * K, dtype=torch.int32, device="cuda"), torch.empty(S * E + 1, dtype=torch.int32, device="cuda")
+    M.moe_plan_route(plan, torch.from_numpy(topk).cuda(), torch.from_numpy(slots).cuda(), S, E, ready_from=site, out_sorted_pair=sp, out_group_off=go)
+    torch.cuda.synchronize()
+    want_sp, want_go = ref.route_sort(topk, slots, rank, E)
+    assert np.array_equal(sp.cpu().numpy(), want_sp) and np.array_equal(go.cpu().numpy(), want_go)
+    words = plan.buf.view(torch.int32).cpu().numpy()
+    n = S * E + 1
+    key = np.where((slots[:, None] >= 0) & (rank[np.maximum(slots, 0)] > 0)[:, None], slots[:, None] * E + topk, -1).reshape(-1)
+    assert np.array_equal(words[8 + n:8 + 2 * n], want_go) and np.array_equal(words[8 + 3 * n:8 + 3 * n + T * K], key)
+
+
 def test_graph_replay_keeps_results_right(M, oracle):
     """A captured graph replays the same kernel arguments; the launches that exchange partial
     results between workgroups must still tell one replay from the next.  Inputs change between
