@@ -668,10 +668,10 @@ int32_t segmented_mfma(mlora_site *s, const void *x, int64_t ldx, void *y, int64
     return MLORA_OK;
 }
 
-// Into how many parts that trade sums the tiles of a batch of prompts are divided (0: not at all), `pair`: in place of the
-// rank-64 pair.  A batch of few rows leaves a CU with a low tile and all of an adapter: 1024 rows of 6 prompts, rank 32, 9728 ->
-// 1024, in 256 tiles of four rows 19.9 us.  Divided over d_in and d_out the tiles are p times as high and the CU moves
-// a p-th of the adapter (3 parts of 13 rows 13.5 us), for the words that a tile's parts wait for.  Each way's time, in us, from the
+// Into how many parts that trade sums the tiles of a batch of prompts are divided (0: not at all); `pair`: in place of the
+// rank-64 pair (1: whole tiles are).  A batch of few rows leaves a CU with a low tile and all of an adapter: 1024 rows of 6
+// prompts, rank 32, 9728 -> 1024, in 256 tiles of four rows 19.9 us.  Divided over d_in and d_out the tiles are p times as high
+// and the CU moves a p-th of the adapter (3 parts of 13 rows 13.5 us), for the words that a tile's parts wait for.  Each way's time, in us, from the
 // bytes that one CU moves (adapter, rows, words) and those of the batch, fitted to 466 random batches of 64 to 8000 rows of 1 to 64
 // prompts, ranks 8 to 64, 512 to 9728 -> 512 to 18432, over which the choice takes 3.4 % more than the better way each time, 8 %
 // less than without it (a quarter of them at least 5 %, at most half the time); slower by more than 2 % in 3, at most 1.18
@@ -698,16 +698,20 @@ int32_t divided_parts(const mlora_site *s, const int32_t *seg_off, const int32_t
     const float d_in = (float)s->d.d_in, d_out = (float)s->d.d_out, adapter = 2e-3f * (float)r * (d_in + d_out), row = 1e-3f * (2.f * d_in + 4.f * d_out), batch = 1e-3f * rows * row;
     auto height = [&](float q) { return (float)(((int32_t)std::ceil(q) + 7) / 8 * 8); };          // rows that a tile loads
     auto fits = [&](float tiles) { return std::min((float)longest, std::max(1.f, rows / std::max(1.f, tiles - half))); };
-    float other;
-    if (pair) other = 8.6f + 1.6e-3f * d_in + 9e-5f * d_out + 0.2f * batch + 0.136f * 128e-6f * (float)tiles64 * (d_in + d_out);
-    else {
-        const float rounds = std::ceil((rows / 48.f + half) / cus);
-        float parts = std::floor(std::min(cus / (rows / (float)std::min(8, longest) + half), (float)(n_blk / 8))), q = 8.f;
-        if (parts < 2.f) { parts = 1.f; q = std::min(48.f, fits(rounds * cus)); }
-        other = 3.7f + rounds * ((r == 64 ? 0.0222f : 0.0172f) * 2e-3f * (float)r * (d_in + d_out / parts) + 0.0082f * 1e-3f * height(q) * (2.f * d_in + 4.f * d_out / parts)) + 0.143f * batch;
+    const float rounds = std::ceil((rows / 48.f + half) / cus);
+    float parts = std::floor(std::min(cus / (rows / (float)std::min(8, longest) + half), (float)(n_blk / 8))), q_whole = 8.f;
+    if (parts < 2.f) { parts = 1.f; q_whole = std::min(48.f, fits(rounds * cus)); }
+    const float whole = 3.7f + rounds * ((r == 64 ? 0.0222f : 0.0172f) * 2e-3f * (float)r * (d_in + d_out / parts) + 0.0082f * 1e-3f * height(q_whole) * (2.f * d_in + 4.f * d_out / parts)) + 0.143f * batch;
+    float other = whole;
+    int32_t best = 0;
+    if (pair) {
+        // (few rows on a short d_in: whole tiles, 1 in place of a number of parts.  544 -> 14,832, 161 rows 17.2 / 11.1 us,
+        // 608 -> 5752, 76 rows 9.8 / 7.5; of 62 random batches on wide rank-64 sites one got slower by more than 2 %.)
+        const float two = 8.6f + 1.6e-3f * d_in + 9e-5f * d_out + 0.2f * batch + 0.136f * 128e-6f * (float)tiles64 * (d_in + d_out);
+        if (rows <= 1024.f && whole < 0.85f * two) best = 1;
+        else other = two;
     }
     float least = 0.9f * other;
-    int32_t best = 0;
     for (const int32_t p : {2, 3, 4, 6, 8, 12, 16}) {
         const float tiles = cus / (float)p, q = fits(tiles);
         if (p > n_blk || tiles <= half || tiles < (float)live || q > (r == 64 ? 32.f : 48.f)) break;
@@ -720,8 +724,8 @@ int32_t divided_parts(const mlora_site *s, const int32_t *seg_off, const int32_t
         for (int32_t k = 0; k < S; ++k) if (seg_slot[k] >= 0) n += (seg_off[k + 1] - seg_off[k] + q - 1) / q;
         return n;
     };
-    while (best >= 2 && tiles_at_most(r == 64 ? 32 : tile_max_rows()) * best > (int64_t)cus) --best;
-    return best >= 2 ? best : 0;
+    while (best >= 2 && tiles_at_most(r == 64 ? 32 : tile_max_rows()) * best > (int64_t)cus) best = best == 2 ? 0 : best - 1;
+    return best;
 }
 
 // Prefill through the tile kernel: one launch, a table of the segments (in the kernel arguments when it fits).

@@ -751,6 +751,31 @@ def test_prompts_in_divided_tiles(M, oracle, r, parts):
         site.check()
 
 
+@pytest.mark.parametrize("d_in,d_out,T,S", [(72, 4104, 1, 1), (544, 14832, 161, 7), (608, 5752, 76, 4), (264, 8200, 1024, 3), (264, 8200, 1025, 3), (2056, 4096, 40, 2)])
+def test_wide_rank64_prompts_of_few_rows(M, oracle, d_in, d_out, T, S):
+    """Rank 64 on wide sites at few rows: whole tiles, divided ones or the pair of kernels, as the rule takes it, against
+    the pair by request and the oracle; both sides of the rule's last row and of its d_in."""
+    g = W.rng(4800 + T)
+    off = np.concatenate([[0], np.sort(g.choice(np.arange(1, T), size=S - 1, replace=False)) if S > 1 else np.zeros(0, int), [T]]).astype(np.int32)
+    slot = (np.arange(S) % 3).astype(np.int32)
+    slot[1:2] = -1
+    c = W.seg_case(f"few64_{d_in}_{T}", 4810 + T, T, S, d_in, d_out, 3, 64, 64.0, ranks=[64, 61, 64], seg_off=off.tolist(), seg_slot=slot.tolist(), std_a=0.05, std_b=0.05)
+    site, x = dense_site(M, c), P.dev_bf16(c.x)
+    ref = oracle.apply_segmented(c.x, c.y0, c.A, c.B, c.rank, c.alpha, c.seg_off, c.seg_slot)
+    try:
+        for pair in (0, -1):
+            M.set_tuning("seg_tiles", pair)
+            y = P.dev_bf16(c.y0)
+            M.lora_apply_segmented(site, x, y, c.seg_off, c.seg_slot)
+            torch.cuda.synchronize()
+            P.check_close(P.host_bits(y), ref, c.name)
+            if S > 1:
+                assert np.array_equal(P.host_bits(y)[off[1]:off[2]], c.y0[off[1]:off[2]])
+    finally:
+        M.set_tuning("seg_tiles", 0)
+    site.check()
+
+
 def test_divided_prompts_in_a_graph(M, oracle):
     """The launch tag of divided prompts lives in device memory: replays of one launch do not take each other's sums."""
     c = W.seg_case("divgraph", 4700, 200, 3, 1032, 520, 3, 16, 32.0, seg_off=[0, 70, 71, 200], seg_slot=[1, 0, 2], std_a=0.05, std_b=0.05)
