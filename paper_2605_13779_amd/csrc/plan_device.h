@@ -201,9 +201,9 @@ __device__ __forceinline__ void plan_dense_count(const PlanView &pv, const int32
 // the workgroup also leaves the plan in global memory for the launches that follow.
 //
 // No sort here: a row's place is (rows of smaller slots) + (earlier rows of its own slot).  Inside a
-// wave the second term comes from ballots, one per distinct slot of the wave; across waves from a
-// small table of per-wave counts; the first term from one scan over the slots.  Five barriers,
-// against fifteen of the sorting network, which is what a 512-thread workgroup feels.
+// wave the second term comes from comparing with the wave's 64 slots, read from LDS four at a time;
+// across waves from a small table of per-wave counts; the first term from one scan over the slots.
+// A third of the barriers of the sorting network, which is what a 512-thread workgroup feels.
 constexpr int kLocalPlanSlots = 1024;
 struct PlanLocalLds {
     int32_t cntw[4][kLocalPlanSlots];      // rows of slot s in wave w (the rows sit in the first 4 waves)

@@ -545,11 +545,10 @@ void rows_multi_kernel(const MultiArgs m)
     rows_body<RP, NW, false, RUN>(m.site[s], b - m.first[s], m.first[s + 1] - m.first[s]);
 }
 
-// The first launch of a decode step can plan for itself: every workgroup sorts the batch's
-// (slot, row) keys in LDS (what the one-workgroup planner kernel does, a microsecond of work) instead
-// of waiting for a planner launch and then fetching its chunk record; workgroup 0 also leaves the
-// plan in global memory for the launches that follow.  Batches of up to kLocalPlanRows rows over up
-// to kLocalPlanSlots slots.
+// The first launch of a decode step in chunks (ranks 1 and 2; from rank 4 on tile_multi.hip) can plan for itself: every
+// workgroup groups the batch in LDS instead of waiting for a planner launch and then fetching its chunk
+// record; workgroup 0 also leaves the plan in global memory for the launches that follow.  Batches of
+// up to kLocalPlanRows rows over up to kLocalPlanSlots slots.
 constexpr int kLocalPlanRows = 256;   // more rows mean more distinct slots per wave, and every workgroup pays for them
 struct PlanLocalArgs {
     const int32_t *token_slot;

@@ -1,8 +1,8 @@
 // Dense decode in tiles (see tile_body.h): one or several sites that share a batch plan.
 // Bound by the chain launch -> plan -> first loads -> (trade) -> expand, one or two tiles per CU.  Measured
-// against the chunk launches of rows.hip: 93 rows at rank 64, 7168 -> 7168, 40.9 -> 14.5 us (33 MB); the seven
-// projections of a 2560-wide layer at rank 16, 256 rows 58.5 -> 54.7 us (123 MB), 1001 rows 131.5 -> 92.8 us
-// (261 MB).
+// against the chunk launches of rows.hip: 93 rows at rank 64, 7168 -> 7168, 40.9 -> 12.5 us (33 MB); the seven
+// projections of a 2560-wide layer at rank 16, 256 rows 58.5 -> 47 us (123 MB), 1001 rows 131.5 -> 86 us
+// (261 MB).  Before every workgroup found its own tile and tiles were cut by the live ones: 14.5, 54.7, 92.8.
 #include "tile_body.h"
 
 namespace mlora {
