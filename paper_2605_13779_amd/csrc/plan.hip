@@ -485,8 +485,10 @@ void plan_route_one_kernel(PlanView pv, const int32_t *__restrict__ topk, const 
 // no global atomics, every step parallel over the batch.
 //   count   a workgroup owns kBigRange consecutive items: each one's rank among the range's earlier items
 //           of its key (-> ticket), and the range's count of every key (-> a row of the count table).
-//           Inside a wave the rank comes from comparing with the wave's 64 keys; the sixteen waves then
-//           take turns adding their counts to the LDS table, which keeps the order stable.
+//           Inside a wave the rank comes from the lanes of equal key, found by one ballot per bit of the keys;
+//           the sixteen waves then take turns adding their counts to the LDS table, which keeps the order stable.
+//           (Comparing with the wave's 64 keys through LDS, whose broadcast reads of sixteen waves bound the launch: 64000 pairs on 4096
+//           keys, all three launches, 18.1 us, now 16.7; 60000 rows on 32 slots 14.3, now 12.4.)
 //   scan    per key, an exclusive prefix over the ranges, in place; the totals go to the last row.
 //   place   every workgroup scans the totals of all keys (group starts, chunk numbers) and puts its items
 //           at  group start + items of the key in earlier ranges + ticket.
@@ -507,7 +509,6 @@ void plan_big_count_kernel(const BigSide pairs, const BigSide toks, const int32_
                            const int32_t *__restrict__ ready_rank)
 {
     __shared__ uint16_t cnt[kBigKeys];
-    __shared__ __attribute__((aligned(16))) int32_t lkey[kBigRange];
     const bool is_tok = (int)blockIdx.x >= pairs.blocks;
     const BigSide &d = is_tok ? toks : pairs;
     const int block = (int)blockIdx.x - (is_tok ? pairs.blocks : 0);
@@ -515,15 +516,13 @@ void plan_big_count_kernel(const BigSide pairs, const BigSide toks, const int32_
     const int p = block * kBigRange + tid;
     const int key = p < d.P ? route_key(d.topk, token_slot, ready_rank, p, d.k_magic, d.E, n_slots) : -1;
     for (int k = tid; k < d.NK; k += kBigRange) cnt[k] = 0;
-    lkey[tid] = key;                             // (read back by the same wave only: LDS serves a wave in order)
-    int rank = 0, same = 0;
-    const int32_t *mine = lkey + 64 * w;
-#pragma unroll 4
-    for (int j = 0; j < 64; j += 4) {
-        const int4 v = *(const int4 *)(mine + j);
-        same += (v.x == key) + (v.y == key) + (v.z == key) + (v.w == key);
-        rank += (v.x == key && j < lane) + (v.y == key && j + 1 < lane) + (v.z == key && j + 2 < lane) + (v.w == key && j + 3 < lane);
+    uint64_t equal = __ballot(key >= 0);
+    for (int bit = 0; d.NK - 1 >> bit; ++bit) {
+        const bool one = key >> bit & 1;
+        const uint64_t ones = __ballot(one);
+        equal &= one ? ones : ~ones;
     }
+    const int rank = __popcll(equal & (((uint64_t)1 << lane) - 1)), same = __popcll(equal);
     __syncthreads();
     int base = 0;
     for (int v = 0; v < kBigRange / 64; ++v) {

@@ -1769,6 +1769,13 @@ def test_route_index_build_of_large_batches(M, oracle, T, K, E, S):
     test_route_index_build_paths_agree(M, oracle, T, K, E, S)
 
 
+@pytest.mark.parametrize("S", [3, 4, 64, 65])
+def test_large_route_build_on_few_keys(M, oracle, S):
+    """The equal keys of a wave come from one ballot per bit of the largest key: powers of two (whose largest key is
+    all ones, as an item without a key is), one below and one above, whole waves on one key."""
+    test_route_index_build_paths_agree(M, oracle, 33000, 1, 1, S)
+
+
 def test_route_plan_with_many_experts_per_token(M):
     """257 tokens on all of 4096 experts: pairs times experts per token pass 2^32, where the planner falls back to
     its pipeline, which writes no tile records -- so the apply must not look for any.  Against float64."""
