@@ -196,6 +196,16 @@ int32_t check_xy(const mlora_site *s, const void *x, int64_t ldx, const void *y,
     return MLORA_OK;
 }
 
+// The exchange at its start: counters and flag cleared, launch tag 1, and all words (of prompts, in front of the control block; `bytes` of
+// them behind it) under tag 0, which no launch has.  The words too: those of the site's first launches carry the tags that come again now.
+hipError_t start_exchange(mlora_site *s, size_t bytes, hipStream_t st)
+{
+    const size_t front = prompt_xch_bytes(s->r_pad);
+    hipError_t e = launch_fill_i32((int32_t *)((char *)s->ctrl - front), 0, (int64_t)((front + kCtrlBytes + bytes) / 4), st);
+    if (ok(e)) e = launch_fill_i32((int32_t *)s->ctrl, 1, 1, st);
+    return e;
+}
+
 RowsArgs rows_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy)
 {
     RowsArgs a{};
@@ -920,8 +930,7 @@ int32_t mlora_site_create(const mlora_site_desc *d, void *a_tab, void *b_tab, vo
     hipError_t e = launch_fill_i32(s->priv.pv.hdr, 0, 8 + 3 * (NK + 1), 0);
     if (ok(e)) e = launch_fill_i32(s->priv.pv.tok_hdr, 0, 8 + 2 * (NK + 1), 0);
     if (ok(e) && s->ctrl) {
-        e = launch_fill_i32((int32_t *)s->prompt_xch, 0, (int64_t)((prompt_xch_bytes(s->r_pad) + kCtrlBytes + (s->r_pad == 64 ? kSegXchBytes : kXchBytes)) / 4), 0);   // tag 0 = never written
-        if (ok(e)) e = launch_fill_i32((int32_t *)s->ctrl, 1, 1, 0);                               // first launch tag
+        e = start_exchange(s, s->r_pad == 64 ? kSegXchBytes : kXchBytes, 0);
         if (ok(e) && s->r_pad == 64) e = launch_fill_i32((int32_t *)seg_ctrl_of(s), 1, 1, 0);      // ... and the prefill's first epoch
     }
     if (!ok(e) || !ok(hipGetLastError()) || !ok(hipStreamSynchronize(0))) { delete s; return MLORA_E_HIP; }
@@ -1097,9 +1106,9 @@ int32_t mlora_site_check(mlora_site *s, void *stream)
     uint32_t flag = 0;
     if (!ok(hipMemcpy(&flag, s->ctrl + 1, sizeof flag, hipMemcpyDeviceToHost))) return MLORA_E_HIP;
     if (flag) {
-        // back to a working exchange: counters and flag cleared, a fresh tag
-        (void)launch_fill_i32((int32_t *)s->ctrl, 0, (int64_t)(kCtrlBytes / 4), (hipStream_t)stream);
-        (void)launch_fill_i32((int32_t *)s->ctrl, 1, 1, (hipStream_t)stream);
+        // (waited for: the launches behind it may come on another stream)
+        (void)start_exchange(s, kXchBytes, (hipStream_t)stream);
+        (void)hipStreamSynchronize((hipStream_t)stream);
         return MLORA_E_HIP;
     }
     if (s->r_pad == 64 && s->xch) {

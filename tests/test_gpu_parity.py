@@ -287,8 +287,8 @@ def test_grouped_call_with_a_repeated_site_and_shared_rows(M, oracle, r, d_in, p
 
 
 def _ctrl(site):
-    """The control block of a dense site below rank 64: in front of the 1 MiB of exchange words that end its scratch."""
-    return site.bufs[3][site.bytes[3] - (1 << 20) - 1024:][:1024].view(torch.int32)
+    """The control block of a dense site: in front of the exchange words that end its scratch (1 MiB of them, 24 at rank 64)."""
+    return site.bufs[3][site.bytes[3] - ((24 if site.r_max > 32 else 1) << 20) - 1024:][:1024].view(torch.int32)
 
 
 def test_decode_parts_when_partners_never_answer(M, oracle):
@@ -399,6 +399,44 @@ def test_decode_after_an_exchange_wait_gave_up(M, oracle):
     assert int(ctrl[0]) == 1 and int(ctrl[1]) == 0
     assert np.array_equal(run(), before)
     assert int(ctrl[0]) == 2
+
+
+@pytest.mark.parametrize("r", [16, 64])
+def test_no_old_word_is_current_after_the_exchange_starts_again(M, oracle, r):
+    """mlora_site_check takes a site whose exchange was switched off back to its first launch tag.  Words that the site's
+    first launches left under that tag and the next ones must not count then: the host plants such words, of
+    wrong sums, everywhere in both areas (decode and prompts), and every launch behind the check meets the oracle."""
+    T, S, d_in, d_out = 77, 6, 4608, 520
+    c = W.seg_case(f"stale{r}", 3370 + r, T, S, d_in, d_out, S, r, 2.0 * r, seg_off=[0, 9, 30, 31, 50, 60, T], seg_slot=[0, 3, 1, 5, 2, 4], std_a=0.05, std_b=0.05)
+    slots = np.repeat(c.seg_slot, np.diff(c.seg_off)).astype(np.int32)
+    site, plan, ts, x = dense_site(M, c), M.Plan(T, S), torch.from_numpy(slots).cuda(), P.dev_bf16(c.x)
+    ref = oracle.apply_segmented(c.x, c.y0, c.A, c.B, c.rank, c.alpha, c.seg_off, c.seg_slot)
+    M.lora_plan_decode(plan, ts, S)
+    ctrl, at = _ctrl(site), site.bytes[3] - ((24 if r == 64 else 1) << 20) - 1024
+    for area in (site.bufs[3][at + 1024:at + 1024 + (1 << 20)], site.bufs[3][at - 98304 * r:at]):
+        w = area.view(torch.int32).view(-1, 2)                  # (value, tag)
+        w[:, 0] = 0x45000000                                    # 2048.0
+        w[:, 1] = torch.arange(len(w), device="cuda", dtype=torch.int32) % 6 + 1
+    ctrl[0] = -1                                                # the switched-off value
+    ctrl[1] = 2
+    torch.cuda.synchronize()
+    with pytest.raises(M.MLoraError):
+        site.check()
+    assert int(ctrl[0]) == 1
+    M.set_tuning("seg_parts", 4)
+    try:
+        for k in range(6):
+            y = P.dev_bf16(c.y0)
+            if k % 2:
+                M.lora_apply_segmented(site, x, y, c.seg_off, c.seg_slot)
+            else:
+                M.lora_apply_decode_planned(site, plan, x, y)
+            torch.cuda.synchronize()
+            P.check_close(P.host_bits(y), ref, f"launch {k}")
+            assert int(ctrl[0]) == 2 + k                        # (it did trade)
+    finally:
+        M.set_tuning("seg_parts", 0)
+    site.check()
 
 
 @pytest.mark.parametrize("mode", [1, 3])
