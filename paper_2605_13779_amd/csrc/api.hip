@@ -31,7 +31,7 @@ struct mlora_site {
     mlora_plan priv;            // private plan living in the caller-provided scratch
     uint32_t *ctrl;             // dense sites: launch tag / sign-in counters of launches whose workgroups trade partial sums
     uint64_t *xch;              // dense sites: partial shrink results in flight between workgroups
-    uint64_t *prompt_xch;       // the same of prompts
+    uint64_t *prompt_xch;       // the same of prompts (null below padded rank 8: their kernels trade nothing)
     int32_t *seg_dev;           // device area for segment tiles / chunks
     int32_t seg_cap;            // in entries of 3 ints
     int32_t *stage[2];          // pinned host staging for the segment tables (lazy)
@@ -916,8 +916,9 @@ int32_t mlora_site_create(const mlora_site_desc *d, void *a_tab, void *b_tab, vo
     s->seg_cap = kSegCap;
     s->ctrl = nullptr; s->xch = nullptr; s->prompt_xch = nullptr;
     if (d->n_experts == 0) {
-        s->prompt_xch = (uint64_t *)((char *)s->seg_dev + align256((size_t)kSegCap * 3 * 4));
-        s->ctrl = (uint32_t *)((char *)s->prompt_xch + prompt_xch_bytes(s->r_pad));
+        char *const words = (char *)s->seg_dev + align256((size_t)kSegCap * 3 * 4);
+        if (prompt_xch_bytes(s->r_pad)) s->prompt_xch = (uint64_t *)words;      // (null: the site's prompts stay in whole tiles)
+        s->ctrl = (uint32_t *)(words + prompt_xch_bytes(s->r_pad));
         s->xch = (uint64_t *)((char *)s->ctrl + kCtrlBytes);
     }
     s->stage[0] = s->stage[1] = nullptr;

@@ -789,6 +789,32 @@ def test_prompts_in_divided_tiles(M, oracle, r, parts):
         site.check()
 
 
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
+@pytest.mark.parametrize("d_in,d_out", [(14336, 4096), (28672, 8192)])
+def test_narrow_ranks_on_wide_sites_in_prompts(M, oracle, r, d_in, d_out):
+    """Sites of padded ranks below 8 have no words to trade sums through: their prompts stay in whole tiles, also where the
+    rule for other ranks divides them and where parts are asked for (the same bits)."""
+    for T, S in ((1, 1), (64, 3), (300, 5)):
+        g = W.rng(4900 + T + r)
+        off = np.concatenate([[0], np.sort(g.choice(np.arange(1, T), size=S - 1, replace=False)) if S > 1 else np.zeros(0, int), [T]]).astype(np.int32)
+        slot = (np.arange(S) % 3 - (np.arange(S) == 3)).astype(np.int32)
+        c = W.seg_case(f"narrow{r}_{d_in}_{T}", 4910 + T + r, T, S, d_in, d_out, 3, r, 2.0 * r, ranks=[r, max(1, r - 1), r], seg_off=off.tolist(), seg_slot=slot.tolist(), std_a=0.02, std_b=0.05)
+        site, x = dense_site(M, c), P.dev_bf16(c.x)
+        ref, outs = oracle.apply_segmented(c.x, c.y0, c.A, c.B, c.rank, c.alpha, c.seg_off, c.seg_slot), []
+        try:
+            for parts in (0, 4, -1):
+                M.set_tuning("seg_parts", parts)
+                y = P.dev_bf16(c.y0)
+                M.lora_apply_segmented(site, x, y, c.seg_off, c.seg_slot)
+                torch.cuda.synchronize()
+                outs.append(P.host_bits(y))
+        finally:
+            M.set_tuning("seg_parts", 0)
+        P.check_close(outs[0], ref, c.name)
+        assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+        site.check()
+
+
 @pytest.mark.parametrize("d_in,d_out,T,S", [(72, 4104, 1, 1), (544, 14832, 161, 7), (608, 5752, 76, 4), (264, 8200, 1024, 3), (264, 8200, 1025, 3), (2056, 4096, 40, 2)])
 def test_wide_rank64_prompts_of_few_rows(M, oracle, d_in, d_out, T, S):
     """Rank 64 on wide sites at few rows: whole tiles, divided ones or the pair of kernels, as the rule takes it, against
