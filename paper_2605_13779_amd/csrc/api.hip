@@ -256,6 +256,18 @@ bool takes_tiles(const mlora_site *s, int32_t tile_rows)
     return !(tuning(kRowsMode) || tuning(kRowsWaves) || tuning(kRowsItemsTarget));   // shapes of the chunk launches asked for
 }
 
+// Whether two areas of rows of bf16 (row strides ldp, ldq and widths wp, wq in elements) have bytes in common.
+// Column slices of one buffer (equal strides: q|k|v side by side) have not, though their address ranges overlap.
+bool areas_meet(const void *p, int64_t ldp, int64_t wp, int64_t np, const void *q, int64_t ldq, int64_t wq, int64_t nq)
+{
+    if (np <= 0 || nq <= 0) return false;
+    const uintptr_t p0 = (uintptr_t)p, q0 = (uintptr_t)q;
+    if (q0 >= p0 + 2 * (uintptr_t)((np - 1) * ldp + wp) || p0 >= q0 + 2 * (uintptr_t)((nq - 1) * ldq + wq)) return false;
+    if (ldp != ldq) return true;
+    const int64_t ld = 2 * ldp, d = (((int64_t)q0 - (int64_t)p0) % ld + ld) % ld;      // where q's rows start in p's
+    return d < 2 * wp || d + 2 * wq > ld;
+}
+
 // Whether the parts of a site's tiles divide d_in and trade sums (see tile_args).
 // (Rank 16, 2560 -> 2560, 64 and 256 rows over 64 slots, whole / traded: 5.8 / 6.2 and 7.1 / 6.9 us; rank 32, 1024 -> 1024 5.3 / 6.0 and 5.5 / 6.0;
 // 9728 -> 2560, 155,648, 14.7 / 7.4 and 16.5 / 11.0.)
@@ -276,6 +288,11 @@ TileArgs tile_args(const mlora_site *s, const void *x, int64_t ldx, void *y, int
     a.n_tiles = (int32_t)max_tiles(T, n_slots, tile_rows);
     a.tiles = pv.tiles; a.sorted = pv.sorted;
     const int32_t n_blk = (s->d.d_out + 63) / 64, n_steps = (s->d.d_in + 63) / 64;
+    // y in the place of x: a part would store its outputs while others still read these rows.
+    if (areas_meet(x, ldx, s->d.d_in, T, y, ldy, s->d.d_out, T)) {
+        a.parts = 1;
+        return a;
+    }
     // A part sums all of d_in again unless the adapter's A is long: then the parts divide d_in and trade sums, about a
     // microsecond, what a CU needs for 40 KB.
     if (parts_trade(s, xch)) {
@@ -739,9 +756,10 @@ int32_t divided_parts(const mlora_site *s, const int32_t *seg_off, const int32_t
 }
 
 // Prefill through the tile kernel: one launch, a table of the segments (in the kernel arguments when it fits).
-// divide: into parts that trade sums (see divided_parts).
+// divide: into parts that trade sums (see divided_parts); apart: y shares no bytes with x, else one workgroup takes a whole
+// tile, which has read its rows of x before it stores y.
 int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy,
-                        const int32_t *seg_off, const int32_t *seg_slot, int32_t S, int32_t divide, hipStream_t st)
+                        const int32_t *seg_off, const int32_t *seg_slot, int32_t S, int32_t divide, bool apart, hipStream_t st)
 {
     TileArgs a{};
     a.x = (const uint16_t *)x; a.ldx = ldx; a.y = (uint16_t *)y; a.ldy = ldy;
@@ -773,9 +791,9 @@ int32_t segmented_tiles(mlora_site *s, const void *x, int64_t ldx, void *y, int6
     // A tile of one row costs what a tile of eight costs: where tiles of eight leave half of the CUs idle, the outputs are
     // divided instead of the rows (every part sums all of d_in again).  64 rows in one run, 7168 -> 18432, in 64 tiles of one
     // row / 8 tiles of 32 parts: rank 16 21.9 / 8.8 us, rank 32 30.8 / 14.2; 512 rows, 512 -> 9728, rank 8 13.5 / 7.5.
-    int32_t parts = (int32_t)std::min<int64_t>(cus / count(low), n_blk / 8);
+    int32_t parts = apart ? (int32_t)std::min<int64_t>(cus / count(low), n_blk / 8) : 1;
     if (parts >= 2) lo = hi = low;
-    if (tuning(kTileParts) > 0) parts = tuning(kTileParts);
+    if (apart && tuning(kTileParts) > 0) parts = tuning(kTileParts);
     parts = std::max(1, std::min(parts, n_blk));
     a.part_blocks = (n_blk + parts - 1) / parts;
     a.parts = (n_blk + a.part_blocks - 1) / a.part_blocks;
@@ -1207,18 +1225,6 @@ struct MultiCall {
     int64_t x_rows, y_rows;
     MultiCall from(int32_t k) const { return {sites + k, xs + k, ldxs + k, ys + k, ldys + k, x_rows, y_rows}; }
 };
-
-// Whether two areas of rows of bf16 (row strides ldp, ldq and widths wp, wq in elements) have bytes in common.
-// Column slices of one buffer (equal strides: q|k|v side by side) have not, though their address ranges overlap.
-static bool areas_meet(const void *p, int64_t ldp, int64_t wp, int64_t np, const void *q, int64_t ldq, int64_t wq, int64_t nq)
-{
-    if (np <= 0 || nq <= 0) return false;
-    const uintptr_t p0 = (uintptr_t)p, q0 = (uintptr_t)q;
-    if (q0 >= p0 + 2 * (uintptr_t)((np - 1) * ldp + wp) || p0 >= q0 + 2 * (uintptr_t)((nq - 1) * ldq + wq)) return false;
-    if (ldp != ldq) return true;
-    const int64_t ld = 2 * ldp, d = (((int64_t)q0 - (int64_t)p0) % ld + ld) % ld;      // where q's rows start in p's
-    return d < 2 * wp || d + 2 * wq > ld;
-}
 
 // Whether entry n may run in one launch with the entries [0, n) in front of it: not with one of the same site, whose
 // exchange words it would share, and not with one whose y it reads or writes or whose x it writes (the call's
@@ -1660,9 +1666,11 @@ int32_t lora_apply_segmented(mlora_site *s, const void *x, int64_t ldx, void *y,
     const int tiles = tuning(kSegTiles);
     const bool small = s->d.d_in + s->d.d_out <= 4096 && (s->d.d_in <= 2048 || T >= 128);
     const bool pair = s->r_pad == 64 && (s->d.d_in & 15) == 0 && s->xch && tiles <= 0 && (tiles < 0 || !small);
-    const int32_t divide = tiles < 0 && s->r_pad == 64 ? 0 : divided_parts(s, seg_off, seg_slot, S, pair);
+    // (in place a tile is neither divided nor cut in parts; the pair has read all of a row of x before it stores that row of y)
+    const bool apart = !areas_meet(x, ldx, s->d.d_in, T, y, ldy, s->d.d_out, T);
+    const int32_t divide = !apart || (tiles < 0 && s->r_pad == 64) ? 0 : divided_parts(s, seg_off, seg_slot, S, pair);
     return pair && divide == 0 ? segmented_mfma(s, x, ldx, y, ldy, seg_off, seg_slot, S, st)
-                               : segmented_tiles(s, x, ldx, y, ldy, seg_off, seg_slot, S, divide, st);
+                               : segmented_tiles(s, x, ldx, y, ldy, seg_off, seg_slot, S, divide, apart, st);
 }
 
 int32_t moe_lora_apply_packed(mlora_site *s, const void *x, int64_t ldx, void *y, int64_t ldy,

@@ -756,6 +756,50 @@ def test_parts_by_live_tiles(M, oracle, live):
         M.set_tuning("tile_rows", 0)
 
 
+@pytest.mark.parametrize("r,d,T,S", [(4, 3072, 40, 3), (16, 2056, 300, 4), (16, 4160, 77, 5), (64, 1032, 200, 3), (64, 2176, 161, 7), (64, 2176, 1100, 4)])
+def test_dense_calls_in_place(M, oracle, r, d, T, S):
+    """y is x: the rows that a call of one workgroup per tile leaves in a y of its own, in prompts and decode, with and without
+    the waits for partners; widths whose tiles are cut in parts otherwise, with traded sums and without."""
+    g = W.rng(5600 + r + d + T)
+    off = np.concatenate([[0], np.sort(g.choice(np.arange(1, T), size=S - 1, replace=False)), [T]]).astype(np.int32)
+    slot = (np.arange(S) % 3).astype(np.int32)
+    slot[1] = -1
+    c = W.seg_case(f"inplace{r}_{d}_{T}", 5610 + r + T, T, S, d, d, 3, r, 2.0 * r, ranks=[r, max(1, r - 3), r], seg_off=off.tolist(), seg_slot=slot.tolist(), std_a=0.05, std_b=0.05)
+    site, x = dense_site(M, c), P.dev_bf16(c.x)
+    ts = torch.from_numpy(np.repeat(slot, np.diff(off)).astype(np.int32)).cuda()
+    ref = oracle.apply_segmented(c.x, c.x, c.A, c.B, c.rank, c.alpha, c.seg_off, c.seg_slot)
+    calls = {"prompts": lambda xx, yy: M.lora_apply_segmented(site, xx, yy, c.seg_off, c.seg_slot), "decode": lambda xx, yy: M.lora_apply_decode(site, xx, yy, ts)}
+    knobs = ("tile_parts", "seg_parts", "rows_poll_limit", "seg_tiles")
+    for name, call in calls.items():
+        try:
+            want = x.clone()
+            M.set_tuning("tile_parts", 1)
+            if r == 64 and d > 2048 and name == "prompts":
+                M.set_tuning("seg_tiles", -1)                  # in place such sites stay with the pair of kernels
+            call(x, want)
+            torch.cuda.synchronize()
+            for k in knobs:
+                M.set_tuning(k, 0)
+            for limit in (0, 0, -1):
+                M.set_tuning("rows_poll_limit", limit)
+                got = x.clone()
+                call(got, got)
+                torch.cuda.synchronize()
+                P.check_close(P.host_bits(got), ref, f"{c.name} {name}")
+                assert torch.equal(got, want), (name, limit)
+        finally:
+            for k in knobs:
+                M.set_tuning(k, 0)
+        # columns of one buffer lie apart
+        wide = torch.zeros((T, 2 * d), dtype=torch.bfloat16, device="cuda")
+        wide[:, :d] = x
+        wide[:, d:] = x
+        call(wide[:, :d], wide[:, d:])
+        torch.cuda.synchronize()
+        P.check_close(P.host_bits(wide[:, d:]), ref, f"{c.name} {name}, columns")
+        assert torch.equal(wide[:, :d], x)
+
+
 @pytest.mark.parametrize("r,parts", [(8, 2), (8, 16), (12, 3), (16, 5), (24, 4), (32, 2), (48, 3), (64, 2), (64, 8)])
 def test_prompts_in_divided_tiles(M, oracle, r, parts):
     """Prompts whose tiles are divided into parts that trade sums: tile heights of all kinds (one row to the highest), runs
