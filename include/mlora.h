@@ -80,9 +80,11 @@ int32_t mlora_site_bytes(const mlora_site_desc *desc, size_t *a_tab, size_t *b_t
 int32_t mlora_site_create(const mlora_site_desc *desc, void *a_tab_dev, void *b_tab_dev,
                           void *meta_dev, void *scratch_dev, mlora_site **out);
 void    mlora_site_destroy(mlora_site *site);   /* frees host state only */
-/* Synchronises `stream`, then returns MLORA_E_HIP if a launch on this site gave up waiting for
- * an intermediate result of its own launch (bounded wait; not expected to happen) and clears
- * that flag; MLORA_OK otherwise. */
+/* Synchronises `stream`, then returns MLORA_E_HIP if a launch on this site could not account for all of its
+ * workgroups (the wait for them is bounded; not expected to happen), after which launches run without
+ * handing sums over, and puts the site back to work; MLORA_OK otherwise.  The same where the halves of a rank-64
+ * prefill wait for each other in vain.  A workgroup that gives up waiting for another one's sums adds them up
+ * itself: slower, as right, and no error. */
 int32_t mlora_site_check(mlora_site *site, void *stream);
 
 /* Copies one adapter into slot `slot` (the last hop of an adapter load, Sections 3.4 and 4:

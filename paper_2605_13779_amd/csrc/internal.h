@@ -291,7 +291,8 @@ typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 // arguments, so it lives in device memory (ctrl[0]): one thread of every workgroup reads it for all of them
 // (the sign-in vouches for that read only), then signs in with a fire-and-forget add on one of 64 counters (ctrl[8..72)); the last workgroup of the grid, once its
 // own work is done, sees all sign-ins, clears the counters and advances the tag.  ctrl[1] is an
-// error flag raised when a bounded wait gives up.
+// error flag, raised when that wait gives up; ctrl[2] counts the workgroups that gave up waiting for a partner's
+// words and computed the values themselves, which is no error.
 constexpr int kSpinLimit = 1 << 18;
 constexpr uint32_t kTagPoison = 0xffffffffu;   // exchange switched off after a bounded wait gave up (see tag_advance)
 // Polls that a reader spends on its partners' exchange words, all of them together, before its workgroup computes
@@ -318,6 +319,10 @@ __device__ __forceinline__ void tag_sign_in(uint32_t *ctrl, int wg, uint32_t tag
 {
     if (tag != kTagPoison)
         (void)__hip_atomic_fetch_add(ctrl + 8 + (wg & 63), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void gave_up_count(uint32_t *ctrl)
+{
+    (void)__hip_atomic_fetch_add(ctrl + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Called by one full wave of the last workgroup of the grid when its work is done.
 __device__ __forceinline__ void tag_advance(uint32_t *ctrl, int n_wg, uint32_t tag, int lane)

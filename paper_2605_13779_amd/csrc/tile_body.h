@@ -354,7 +354,8 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, const TileArgs &b2,
         if (gave_up) atomicOr(&s_missing, 1);
         __syncthreads();
         if (s_missing) {
-            // Never expected: every element as a plain dot product (slow, but it needs nothing of what is in flight).
+            // Not expected: every element as a plain dot product (slow, but it needs nothing of what is in flight).
+            if (tid == 0 && tag != kTagPoison) gave_up_count(a.ctrl);
 #pragma unroll
             for (int g = 0; g < C::TG; ++g) {
                 for (int e0 = 0; e0 < 8 * C::RPE; e0 += C::NT) {

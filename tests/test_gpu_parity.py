@@ -291,6 +291,12 @@ def _ctrl(site):
     return site.bufs[3][site.bytes[3] - ((24 if site.r_max > 32 else 1) << 20) - 1024:][:1024].view(torch.int32)
 
 
+def _gave_up(*sites):
+    """Workgroups of the sites' launches so far that gave up waiting for a partner's words."""
+    torch.cuda.synchronize()
+    return sum(int(_ctrl(site)[2]) for site in sites)
+
+
 def test_decode_parts_when_partners_never_answer(M, oracle):
     """A tile of a dense site with a long A is cut into parts that trade partial sums.  With the wait for a
     partner's words cut to nothing, every part that has not been answered yet sums all of d_in on its
@@ -328,11 +334,14 @@ def test_decode_parts_when_partners_never_answer(M, oracle):
         advanced(at, [3, 1, 3, 3])
         return [P.host_bits(y) for y in out + ys + zs]
     traded = run_all()
+    assert _gave_up(*sites) == 0
     M.set_tuning("rows_poll_limit", -1)
     try:
         alone = run_all()
     finally:
         M.set_tuning("rows_poll_limit", 0)
+    alone_wgs = _gave_up(*sites)
+    assert alone_wgs > 0 and _gave_up(sites[3]) == 0
     for k, (c, a, b) in enumerate(zip(cases + 2 * [cases[k] for k in grp], traded, alone)):
         ref = oracle.apply_decode(c.x, c.y0, c.A, c.B, c.rank, c.alpha, c.token_slot)
         P.check_close(a, ref, c.name + (" (grouped)" if k >= len(cases) else ""))
@@ -359,6 +368,7 @@ def test_decode_parts_when_partners_never_answer(M, oracle):
         for y, want in zip(ys, traded[len(cases):]):
             assert np.array_equal(P.host_bits(y), want), rep
         M.lora_apply_decode_planned(sites[0], plan, xs[0], P.dev_bf16(cases[0].y0))
+    assert _gave_up(*sites) == alone_wgs
     for site in sites:
         site.check()
 
@@ -725,15 +735,15 @@ def test_launch_that_finds_its_tiles_in_the_batch(M, oracle, T, S, q):
 
 
 @pytest.mark.parametrize("live", [1, 8, 9, 63, 64, 65, 127, 128, 129, 150])
-def test_parts_by_live_tiles(M, oracle, live):
+@pytest.mark.parametrize("shapes", [((264, 1032), (264, 4104), (264, 72)), ((4160, 1032), (264, 136))], ids=["whole", "traded"])
+def test_parts_by_live_tiles(M, oracle, live, shapes):
     """The device cuts tiles in parts by the number of live ones: one tile per slot, on the edges of eight and of the
-    128 beyond which a tile is whole; three sites of different widths in a launch, one of which trades sums where the
-    launch does; rows without an adapter between them, so that the bound lies above.  Three calls in a row: the launch tag
-    goes on, nobody gave up a wait."""
+    128 beyond which a tile is whole; sites of different widths in a launch, one of which trades sums up to 80 tiles (beyond, no
+    CU is left for a second part); rows without an adapter between them, so that the bound lies above, and the last workgroup
+    often has no tile.  Three calls in a row: the launch tag goes on where sums are traded, nobody gives up a wait."""
     T = 2 * live + 5
     slots = np.full(T, -1, np.int32)
     slots[W.rng(510 + live).permutation(T)[:live]] = W.rng(511 + live).permutation(live)
-    shapes = [(264, 1032), (264, 4104), (264, 72)] if live % 2 else [(4160, 1032), (264, 136)]
     cases = [W.dense_case(f"live{live}_{k}", 5200 + 7 * live + k, T, i, o, live, 16, 32.0, token_slot=slots, std_a=0.05, std_b=0.05) for k, (i, o) in enumerate(shapes)]
     sites = [dense_site(M, c) for c in cases]
     ts, xs, plan = torch.from_numpy(slots).cuda(), [P.dev_bf16(c.x) for c in cases], M.Plan(T, live)
@@ -742,18 +752,21 @@ def test_parts_by_live_tiles(M, oracle, live):
     try:
         for k in range(3):
             ys = [P.dev_bf16(c.y0) for c in cases]
+            tags = [int(_ctrl(site)[0]) for site in sites]
             if k == 1:
                 M.lora_plan_decode(plan, ts, live)
                 M.lora_apply_decode_multi(sites, plan, xs, ys)
             else:
                 M.lora_plan_apply_decode_multi(sites, plan, ts, live, xs, ys)
             torch.cuda.synchronize()
-            for c, y, ref, site in zip(cases, ys, refs, sites):
+            for c, y, ref, site, tag in zip(cases, ys, refs, sites, tags):
                 P.check_close(P.host_bits(y), ref, c.name)
                 P.check_untouched(P.host_bits(y), c.y0, slots < 0, c.name)
+                assert int(_ctrl(site)[0]) - tag == (1 if c.d_in == 4160 and live <= 80 else 0)
                 site.check()
     finally:
         M.set_tuning("tile_rows", 0)
+    assert _gave_up(*sites) == 0
 
 
 @pytest.mark.parametrize("r,d,T,S", [(4, 3072, 40, 3), (16, 2056, 300, 4), (16, 4160, 77, 5), (64, 1032, 200, 3), (64, 2176, 161, 7), (64, 2176, 1100, 4)])
@@ -805,6 +818,7 @@ def test_prompts_in_divided_tiles(M, oracle, r, parts):
     """Prompts whose tiles are divided into parts that trade sums: tile heights of all kinds (one row to the highest), runs
     of one row, runs without an adapter and on an empty slot, widths that leave parts of different size, d_in that
     leaves a part of a step.  Twice in a row and once where every wait is given up at once (parts sum for themselves)."""
+    alone = 0
     for k, (T, S, d_in, d_out) in enumerate([(1, 1, 264, 1096), (9, 2, 520, 136), (100, 5, 1032, 1288), (47 * (256 // parts) - 450, 9, 72, 264)]):
         g = W.rng(4400 + 10 * r + k)
         cuts = np.sort(g.choice(np.arange(1, T), size=S - 1, replace=False)) if S > 1 else np.zeros(0, int)
@@ -821,8 +835,10 @@ def test_prompts_in_divided_tiles(M, oracle, r, parts):
             for limit in (0, 0, -1):
                 M.set_tuning("rows_poll_limit", limit)
                 y = P.dev_bf16(c.y0)
+                tag = int(_ctrl(site)[0])
                 M.lora_apply_segmented(site, x, y, c.seg_off, c.seg_slot)
                 torch.cuda.synchronize()
+                assert int(_ctrl(site)[0]) == tag + 1 and (limit < 0 or _gave_up(site) == 0)
                 P.check_close(P.host_bits(y), ref, c.name)
                 for j in range(S):
                     if slot[j] < 0 or ranks[slot[j]] == 0:
@@ -830,7 +846,9 @@ def test_prompts_in_divided_tiles(M, oracle, r, parts):
         finally:
             M.set_tuning("seg_parts", 0)
             M.set_tuning("rows_poll_limit", 0)
+        alone += _gave_up(site)
         site.check()
+    assert alone > 0
 
 
 @pytest.mark.parametrize("r", [1, 2, 3, 4])
@@ -908,6 +926,7 @@ def test_divided_prompts_in_a_graph(M, oracle):
             torch.cuda.synchronize()
     finally:
         M.set_tuning("seg_parts", 0)
+    assert _gave_up(site) == 0
     site.check()
 
 
@@ -997,6 +1016,7 @@ def test_graph_replay_keeps_results_right(M, oracle):
         assert np.array_equal(got, P.host_bits(y2)), f"replay {rep} differs from the eager launch"
         ref = oracle.apply_decode(xr, c.y0, c.A, c.B, c.rank, c.alpha, c.token_slot)
         P.check_close(got, ref, f"replay {rep}")
+    assert _gave_up(site) == 0
     site.check()
 
 
@@ -1043,6 +1063,7 @@ def test_decode_layer_graph_replay_with_changing_slots(M, oracle):
             ref = oracle.apply_decode(v, c.y0, c.A, c.B, c.rank, c.alpha, sl)
             P.check_close(P.host_bits(y), ref, f"{c.name}, replay {rep}")
             P.check_untouched(P.host_bits(y), c.y0, sl < 0, c.name)
+    assert _gave_up(*sites) == 0
     for site in sites:
         site.check()
 
