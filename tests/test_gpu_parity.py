@@ -490,12 +490,11 @@ def _plan_words(plan, max_items, n_keys):
     return w[:2].copy(), w[off_sorted:off_sorted + max_items].copy(), w[off_sorted + max_items:].copy()
 
 
-@pytest.mark.parametrize("T,S", [(61, 5), (256, 64), (1, 3), (200, 64), (300, 7), (256, 65), (250, 300), (256, 1000)])
+@pytest.mark.parametrize("T,S", [(61, 5), (256, 64), (1, 3), (200, 64), (300, 7), (256, 65), (250, 300), (256, 1000), (1024, 9), (1030, 9), (61, 1030)])
 def test_decode_step_that_plans_inside_its_first_launch(M, oracle, T, S):
     """lora_plan_apply_decode_multi = lora_plan_decode + lora_apply_decode_multi, bit for bit, in the
-    results and in the plan it leaves behind (which a later planned apply uses); 300 rows are more
-    than a launch plans for itself and take the two-call path, as does a first site that cannot
-    share a launch."""
+    results and in the plan it leaves behind (which a later planned apply uses); more than 1024 rows or slots
+    are more than a launch groups for itself and take the two calls."""
     shapes = [(2304, 264, 16), (2304, 1032, 16), (2304, 520, 16), (128, 72, 16)]
     slots = W.rng(90 + T).integers(-1, S, size=T).astype(np.int32)
     cases = [W.dense_case(f"pl{i}", 3200 + i, T, di, do, S, r, 32.0, token_slot=slots, ranks=[16 if k % 5 else 0 for k in range(S)] if S > 3 else None,
@@ -545,12 +544,13 @@ def test_decode_step_that_plans_inside_its_first_launch(M, oracle, T, S):
 
 def test_single_site_plans_inside_its_launch(M, oracle):
     """A rank-1 catalog site (every row its own slot, 1024 slots) and sites of the other ranks on their own:
-    the launch plans for itself up to 256 rows and 1024 slots (more rows take the two calls); same
-    bits as plan + planned apply."""
+    the launch plans for itself up to 1024 slots and 256 rows at ranks 1 and 2, 1024 at the others (more rows or slots take the
+    two calls); same bits as plan + planned apply."""
     for name, T, S, d_in, d_out, r in (("cat", 256, 1024, 4096, 264, 1), ("cat_ragged", 199, 700, 4096, 136, 1),
                                        ("cat_two_calls", 333, 700, 4096, 136, 1), ("one16", 200, 40, 2304, 264, 16),
                                        ("one2", 100, 9, 4096, 72, 2), ("one4", 130, 20, 4096, 136, 4),
-                                       ("one32", 90, 12, 1024, 200, 32), ("one64", 70, 6, 520, 136, 64)):
+                                       ("one32", 90, 12, 1024, 200, 32), ("one64", 70, 6, 520, 136, 64),
+                                       ("one8_rows", 1025, 40, 264, 136, 8), ("one8_slots", 333, 1025, 264, 136, 8)):
         slots = W.rng(95 + T).permutation(S)[:T].astype(np.int32) if r == 1 else W.rng(95 + T).integers(-1, S, size=T).astype(np.int32)
         slots[::11] = -1
         c = W.dense_case(name, 3300 + T, T, d_in, d_out, S, r, 2.0 * r, token_slot=slots, std_a=0.05, std_b=0.05)
@@ -661,11 +661,12 @@ def _plan_tiles(plan, max_items, n_keys):
     return plan.buf.view(torch.int32)[-(-off // 4) * 4:][:4 * chunks].cpu().numpy().reshape(-1, 4)
 
 
-@pytest.mark.parametrize("T,S,q", [(1, 1, 8), (64, 3, 8), (65, 64, 8), (256, 64, 8), (257, 64, 16), (1000, 7, 8), (1024, 4096, 8), (1024, 4097, 16),
+@pytest.mark.parametrize("T,S,q", [(1, 1, 8), (64, 3, 8), (65, 64, 8), (256, 64, 8), (257, 64, 16), (1000, 7, 8), (1024, 1024, 4), (1024, 4096, 8), (1024, 4097, 16),
                                    (1025, 64, 16), (4000, 300, 8), (33000, 20, 16), (2000, 5000, 8)])
 def test_plan_tile_records(M, T, S, q):
     """The planners (inside a launch, counting, sorting, one launch for large batches, three launches) leave the
-    same grouping and tiles: {slot, rows, first position} for every run of up to q rows of a slot, then zeros."""
+    same grouping and tiles: {slot, rows, first position, live tiles} for every run of up to q rows of a slot, then records
+    of no rows that hold the number of live tiles too."""
     slots = W.rng(7 * T + S).integers(-1, S, size=T).astype(np.int32)
     if T > 60:
         slots[10:40] = min(2, S - 1)                   # a crowded slot
@@ -676,6 +677,7 @@ def test_plan_tile_records(M, T, S, q):
         n = int((slots == s).sum())
         want += [(s, min(q, n - r), pos + r) for r in range(0, n, q)]
         pos += n
+    want = np.array([w + (len(want),) for w in want], dtype=np.int32).reshape(-1, 4)
     bound = (T + (q - 1) * min(S, T)) // q
     assert len(want) <= bound
     plan = M.Plan(T, S)
@@ -683,7 +685,7 @@ def test_plan_tile_records(M, T, S, q):
     x, y = (torch.zeros((T, 64), dtype=torch.bfloat16, device="cuda") for _ in range(2))
     M.set_tuning("tile_rows", q)
     try:
-        for fused in ((False, True) if T <= 256 and S <= 1024 else (False,)):
+        for fused in ((False, True) if T <= 1024 and S <= 1024 else (False,)):
             plan.buf.fill_(0x5A)
             plan.buf[:4 * (8 + 3 * (S + 1))].zero_()
             if fused:
@@ -694,8 +696,8 @@ def test_plan_tile_records(M, T, S, q):
             hdr, srt, _ = _plan_words(plan, T, S)
             assert int(hdr[1]) == len(order) and np.array_equal(srt[:len(order)], order)
             rec = _plan_tiles(plan, T, S)[:bound]
-            assert np.array_equal(rec[:len(want), :3], np.array(want, dtype=np.int32).reshape(-1, 3))
-            assert np.all(rec[len(want):, 1] == 0)
+            assert np.array_equal(rec[:len(want)], want)
+            assert np.all(rec[len(want):, 1] == 0) and np.all(rec[len(want):, 3] == len(want))
     finally:
         M.set_tuning("tile_rows", 0)
 
@@ -973,15 +975,26 @@ def test_route_build_of_few_pairs(M, T, K, S, E):
         if s != 1:
             M.lora_slots_upload(site, s, s, np.zeros((E, 2, 16), np.uint16), np.zeros((E, 16, 2), np.uint16), 2, 2.0)
     rank = np.array([0 if s == 1 else 2 for s in range(S)], np.int32)
-    plan, sp, go = M.Plan(T * K, S * E), torch.empty(T * K, dtype=torch.int32, device="cuda"), torch.empty(S * E + 1, dtype=torch.int32, device="cuda")
-    M.moe_plan_route(plan, torch.from_numpy(topk).cuda(), torch.from_numpy(slots).cuda(), S, E, ready_from=site, out_sorted_pair=sp, out_group_off=go)
-    torch.cuda.synchronize()
-    want_sp, want_go = ref.route_sort(topk, slots, rank, E)
-    assert np.array_equal(sp.cpu().numpy(), want_sp) and np.array_equal(go.cpu().numpy(), want_go)
-    words = plan.buf.view(torch.int32).cpu().numpy()
-    n = S * E + 1
-    key = np.where((slots[:, None] >= 0) & (rank[np.maximum(slots, 0)] > 0)[:, None], slots[:, None] * E + topk, -1).reshape(-1)
-    assert np.array_equal(words[8 + n:8 + 2 * n], want_go) and np.array_equal(words[8 + 3 * n:8 + 3 * n + T * K], key)
+    ts, n = torch.from_numpy(slots).cuda(), S * E + 1
+    for outside in (False, True):
+        if outside:
+            at = r.choice(T * K, size=T * K // 9 + 1, replace=False)
+            topk.reshape(-1)[at] = np.array([-1, E, 2 ** 31 - 1, -2 ** 31, E + 1], np.int32)[np.arange(len(at)) % 5]
+        plan, sp, go = M.Plan(T * K, S * E), torch.empty(T * K, dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+        M.moe_plan_route(plan, torch.from_numpy(topk).cuda(), ts, S, E, ready_from=site, out_sorted_pair=sp, out_group_off=go)
+        torch.cuda.synchronize()
+        usable = ((slots >= 0) & (rank[np.maximum(slots, 0)] > 0))[:, None] & (topk >= 0) & (topk < E)
+        key = np.where(usable, slots[:, None].astype(np.int64) * E + topk, -1).reshape(-1)
+        order = np.argsort(key, kind="stable")
+        live = order[np.count_nonzero(key < 0):]
+        want_sp = np.concatenate([live, np.full(T * K - len(live), -1)])
+        want_go = np.searchsorted(key[live], np.arange(n))
+        if not outside:
+            ref_sp, ref_go = ref.route_sort(topk, slots, rank, E)
+            assert np.array_equal(ref_sp, want_sp) and np.array_equal(ref_go, want_go)
+        assert np.array_equal(sp.cpu().numpy(), want_sp) and np.array_equal(go.cpu().numpy(), want_go)
+        words = plan.buf.view(torch.int32).cpu().numpy()
+        assert np.array_equal(words[8 + n:8 + 2 * n], want_go) and np.array_equal(words[8 + 3 * n:8 + 3 * n + T * K], key)
 
 
 def test_graph_replay_keeps_results_right(M, oracle):
