@@ -68,7 +68,9 @@ const char *mlora_status_str(int32_t status);
  *   a_tab: [n_slots, max(n_experts,1), r_pad, d_in]  bf16   (r_pad = r_max rounded to 2^k)
  *   b_tab: [n_slots, max(n_experts,1), d_out, r_pad] bf16
  *   meta : rank int32[n_slots] | scale fp32[n_slots] | catalog_id int64[n_slots]
- *   scratch: private grouping buffers for the entry points that take no explicit plan.
+ *   scratch: private grouping buffers for the entry points that take no explicit plan, and what a
+ *        launch's workgroups hand each other: for dense sites 1 MB (24 MB at rank 64) and, from r_pad 8 on,
+ *        98,304 bytes per rank of r_pad for prompts.
  * Errors: MLORA_E_INVALID (null, non-positive sizes), MLORA_E_SHAPE (d_in/d_out not a
  * multiple of 8, r_max outside 1..64). */
 int32_t mlora_site_bytes(const mlora_site_desc *desc, size_t *a_tab, size_t *b_tab,
@@ -273,8 +275,9 @@ int32_t lora_apply_decode_noalloc(mlora_site *site, const void *x, int64_t ldx, 
  * they are validated here (MLORA_E_SEGMENTS / MLORA_E_SLOT) and travel in the kernel arguments (long
  * tables are copied to the device).  Everything runs on the matrix cores: wide rank-64 sites with d_in a
  * multiple of 16 as a shrink and an expand half with d_in and d_out cut over workgroups, others in tiles
- * of up to 48 rows, which batches of few rows divide over d_in and d_out too (up to the order of the fp32 partial sums
- * the same result). */
+ * of up to 48 rows, which batches of few rows at ranks above 4 divide over d_in and d_out too (up to the order of the fp32
+ * partial sums the same result).  Workgroups that share a tile wait for each other's sums; where another stream's work keeps
+ * one of them from starting for half a millisecond, the others do without it, right but slower. */
 int32_t lora_apply_segmented(mlora_site *site, const void *x, int64_t ldx, void *y, int64_t ldy,
                              const int32_t *seg_off, const int32_t *seg_slot, int32_t S,
                              int32_t T, void *stream);

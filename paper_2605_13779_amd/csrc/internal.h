@@ -144,10 +144,11 @@ struct TileArgs {
     int32_t poll_limit;
 };
 // Whether y, [rows, d_out] of bf16, goes past the caches (non-temporal loads and stores; both count, either alone changes
-// nothing).  Where it is larger than what the caches still hold of it from the launch that wrote it, and only where every block of
-// 64 outputs is a whole line: of a line that two waves touch, the second would come back to memory.  Prompts of
-// 8192 rows, 7168 -> 7168 (117 MB), kept / streamed: rank 16 81.0 / 68.8 us, rank 64 94.5 / 86.2; 14,999 rows, 7168 -> 18,432, rank 64 286.8 / 266.4;
-// 3206 rows, rank 8, 2680 -> 15,784 (31,568 bytes a row, 101 MB) 62.1 / 87.0.  Smaller ones: on cold buffers up to 25 % faster streamed, on warm ones as
+// nothing): from 96 MB on, and only where every block of 64 outputs is a whole line -- of a line that two waves touch, the second
+// would come back to memory.  It pays where the memory-side cache no longer holds y, and costs where it does.  In us, kept / streamed, on the same
+// buffers again, on four sets in turn, and behind the product that writes y: 8192 rows, 7168 -> 7168 (117 MB), rank 64 80.6 / 88.8, 90.9 / 87.0,
+// 86.9 / 85.7, rank 16 56.7 / 66.2, 78.7 / 71.5, 65.1 / 66.5; 14,999 rows, 7168 -> 18,432 (553 MB), rank 64 293.0 / 272.3, 290.0 / 268.6, 251.0 / 273.0;
+// 3206 rows, rank 8, 2680 -> 15,784 (31,568 bytes a row, 101 MB) 39.1 / 83.7, 60.3 / 86.2, 69.7 / 80.7.  Smaller ones: on cold buffers up to 25 % faster streamed, on warm ones as
 // much slower (1001 rows of a dense decode layer 86.0 / 81.0 cold, 70.6 / 78.3 warm; rank 16, 8192 rows, 2560 -> 2560 25.3 / 28.4 warm).
 inline bool streams_y(const void *y, int64_t ldy, int64_t rows, int64_t d_out)
 {
@@ -297,7 +298,7 @@ constexpr int kSpinLimit = 1 << 18;
 constexpr uint32_t kTagPoison = 0xffffffffu;   // exchange switched off after a bounded wait gave up (see tag_advance)
 // Polls that a reader spends on its partners' exchange words, all of them together, before its workgroup computes
 // the values itself (a partner can start late): 0.55 ms (133 ns per poll on an idle GPU), longer than any launch
-// here lasts.  The two ways of getting the value add the same terms in a
+// that trades lasts.  The two ways of getting the value add the same terms in a
 // different order, so an output can differ by one rounding step between them; both are within the
 // tolerance of the result.
 constexpr int kPollLimit = 4096;

@@ -1,8 +1,8 @@
 // Dense decode in tiles (see tile_body.h): one or several sites that share a batch plan.
 // Bound by the chain launch -> plan -> first loads -> (trade) -> expand, one or two tiles per CU.  Measured
-// against the chunk launches of rows.hip: 93 rows at rank 64, 7168 -> 7168, 40.9 -> 12.5 us (33 MB); the seven
-// projections of a 2560-wide layer at rank 16, 256 rows 58.5 -> 47 us (123 MB), 1001 rows 131.5 -> 86 us
-// (261 MB).  Before every workgroup found its own tile and tiles were cut by the live ones: 14.5, 54.7, 92.8.
+// against the chunk launches of rows.hip: 93 rows at rank 64, 7168 -> 7168, 40.9 -> 12.9 us (33 MB); the seven
+// projections of a 2560-wide layer at rank 16, 256 rows 58.5 -> 46.5 us (123 MB), 1001 rows 131.5 -> 86 us
+// (261 MB).  Before every workgroup found its own tile and tiles were cut by the live ones: 14.7, 54.7, 92.6.
 #include "tile_body.h"
 
 namespace mlora {
@@ -87,7 +87,7 @@ struct TileBatchLds {
 // for all slots, two barriers around their count, then every wave by itself: a scan over the slots' tiles, and the rows
 // of the one slot by ballots.  The places of other tiles' rows, chunk records and their scans, which took two thirds of
 // the time of a launch in which everybody built the whole plan, are not needed for that.  One token, 2560 -> 2560, rank 16
-// 6.8 -> 6.2 us (the host's call takes as long), 93 rows, 7168 -> 7168, rank 64 14.5 -> 12.7; the 1001-row layer, whose plan had a
+// 6.8 -> 6.2 us (the host's call takes as long), 93 rows, 7168 -> 7168, rank 64 14.5 -> 12.7 by this alone; the 1001-row layer, whose plan had a
 // launch of its own (7.8 us), 93.5 -> 87.9.
 struct TileBatch {
     int per, n, inc;               // slots per lane, tiles of the lane's slots, tiles up to and with them
